@@ -63,7 +63,7 @@ void release(stem_ctx* c) {
   (void)hipSetDevice(c->device);
   (void)hipDeviceSynchronize();
   (void)hipFree(c->H_ws); (void)hipFree(c->dG_ws); (void)hipFree(c->dH_ws);
-  (void)hipFree(c->splitk_ws); (void)hipFree(c->dw_ws);
+  (void)hipFree(c->splitk_ws);
   (void)hipFree(c->Up_ws);
   for (int i = 0; i < 2; ++i) { (void)hipFree(c->sort_keys[i]); (void)hipFree(c->sort_vals[i]); }
   (void)hipFree(c->sort_counts); (void)hipFree(c->seg_of); (void)hipFree(c->seg_part);
@@ -166,14 +166,9 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipMalloc(&c->dG_ws, std::max<size_t>(TF * es, 16)));
   if (desc->dtype == STEM_F32) ok(hipMalloc(&c->dH_ws, std::max<size_t>(TF * 4, 16)));
   if (desc->dtype == STEM_BF16) {
-    ok(hipMalloc(reinterpret_cast<void**>(&c->splitk_ws), STEM_SPLITK_WS_BYTES));
-    // Weight gradients are [d,F] outputs with K = T: a narrow layer has fewer 256x256 tiles than the
-    // chip has compute units, so its K range is cut into slices (at most 8, at most ~256 workgroups).
-    const int dw_tiles = ((desc->d_model + 255) / 256) * ((desc->d_ff + 255) / 256);
-    c->dw_ksplit = 1;
-    while (c->dw_ksplit < 8 && dw_tiles * c->dw_ksplit * 2 <= 256) c->dw_ksplit *= 2;
-    if (c->dw_ksplit > 1)
-      ok(hipMalloc(reinterpret_cast<void**>(&c->dw_ws), (size_t)c->dw_ksplit * desc->d_model * desc->d_ff * 4));
+    // partial products of up to 8 K slices of a [T,d] or [d,F] output
+    c->splitk_bytes = std::min<size_t>(STEM_SPLITK_WS_MAX, (size_t)8 * 4 * desc->d_model * std::max<int64_t>({max_tokens, desc->d_ff, 1}));
+    ok(hipMalloc(reinterpret_cast<void**>(&c->splitk_ws), c->splitk_bytes));
   }
   for (int i = 0; i < 2; ++i) {
     ok(dmalloc(&c->sort_keys[i], (size_t)max_tokens));
@@ -280,6 +275,7 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     b.B = static_cast<const bf16_t*>(W_down); b.ldb = F;
     b.M = (int)T; b.N = d; b.K = F; b.C = y; b.flag = c->flag;
     b.residual = static_cast<const bf16_t*>(residual);
+    b.ws = c->splitk_ws; b.ws_bytes = c->splitk_bytes;
     const int down_epi = residual ? EPI_BF16_RES : EPI_BF16;
     if (!wait_event) {
       a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);
@@ -312,8 +308,7 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     }
     if (few) {
       b.ksplit = stem_gemm_skinny_ksplit(b.M, b.N, b.K);
-      b.ws = c->splitk_ws;
-      if ((size_t)b.ksplit * b.M * b.N * 4 > STEM_SPLITK_WS_BYTES) b.ksplit = 1;
+      if ((size_t)b.ksplit * b.M * b.N * 4 > c->splitk_bytes) b.ksplit = 1;
       HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_DOWN, b.ksplit > 1 ? EPI_SPLITK : EPI_BF16, b, s));
     } else {
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DOWN, OP_KC, OP_KC, down_epi, b, s));
@@ -379,8 +374,6 @@ stem_status stem_ffn_backward(stem_ctx* c, const void* dy, const void* x, const 
     const bf16_t* dyb = static_cast<const bf16_t*>(dy);
     const bf16_t* Hb = static_cast<const bf16_t*>(H);
     bf16_t* dGb = static_cast<bf16_t*>(c->dG_ws);
-    int dw_split = c->dw_ksplit;   // K slices of the weight-gradient GEMMs: at least 8 K tiles each
-    while (dw_split > 1 && (T + 63) / 64 / dw_split < 8) dw_split /= 2;
     // Every operand is read as it is stored.  The weights of the two activation-gradient products
     // ([K, N] with N contiguous) and both operands of the weight-gradient products ([T, rows]) are
     // rows-contiguous: their tiles go to LDS unchanged and the fragment reads transpose them.
@@ -396,20 +389,20 @@ stem_status stem_ffn_backward(stem_ctx* c, const void* dy, const void* x, const 
       GemmArgs a = {};
       a.A = dyb; a.lda = d; a.B = Hb; a.ldb = F;
       a.M = d; a.N = F; a.K = (int)T; a.C = dW_down; a.accumulate = accumulate; a.flag = c->flag;
-      a.ksplit = dw_split; a.ws = c->dw_ws;
+      a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, a, s));
     }
     if (dx) {  // dx = dG W_gate
       GemmArgs a = {};
       a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;
-      a.M = (int)T; a.N = d; a.K = F; a.C = dx; a.flag = c->flag;
+      a.M = (int)T; a.N = d; a.K = F; a.C = dx; a.flag = c->flag; a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DX, OP_KC, OP_MC, EPI_BF16, a, s));
     }
     {  // dW_gate[F,d] = dG^T x
       GemmArgs a = {};
       a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(x); a.ldb = d;
       a.M = F; a.N = d; a.K = (int)T; a.C = dW_gate; a.accumulate = accumulate; a.flag = c->flag;
-      a.ksplit = dw_split; a.ws = c->dw_ws;
+      a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, a, s));
     }
   } else {
@@ -514,8 +507,6 @@ stem_status stem_ffn_up_backward(stem_ctx* c, const void* dy, const void* x, con
   const bf16_t* dyb = static_cast<const bf16_t*>(dy);
   bf16_t* dGb = static_cast<bf16_t*>(c->dG_ws);
   bf16_t* dVb = static_cast<bf16_t*>(dV);
-  int dw_split = c->dw_ksplit;
-  while (dw_split > 1 && (T + 63) / 64 / dw_split < 8) dw_split /= 2;
   {  // dH = dy W_down, fused into dV = dH * SiLU(G) and dG = dH * (Up [+ E[ids]]) * SiLU'(G)
     GemmArgs a = {};
     a.A = dyb; a.lda = d; a.B = static_cast<const bf16_t*>(W_down); a.ldb = F;
@@ -529,21 +520,21 @@ stem_status stem_ffn_up_backward(stem_ctx* c, const void* dy, const void* x, con
     GemmArgs a = {};
     a.A = dyb; a.lda = d; a.B = static_cast<const bf16_t*>(saved_H); a.ldb = F;
     a.M = d; a.N = F; a.K = (int)T; a.C = dW_down; a.accumulate = accumulate; a.flag = c->flag;
-    a.ksplit = dw_split; a.ws = c->dw_ws;
+      a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
     HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, a, s));
   }
   if (dx) {  // dx = dG W_gate + dV W_up: one product over the concatenated K range
     GemmArgs a = {};
     a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;
     a.A2 = dVb; a.B2 = static_cast<const bf16_t*>(W_up); a.K2 = F;
-    a.M = (int)T; a.N = d; a.K = F; a.C = dx; a.flag = c->flag;
+    a.M = (int)T; a.N = d; a.K = F; a.C = dx; a.flag = c->flag; a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
     HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DX, OP_KC, OP_MC, EPI_BF16, a, s));
   }
   {  // dW_gate[F,d] = dG^T x and dW_up[F,d] = dV^T x
     GemmArgs a = {};
     a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(x); a.ldb = d;
     a.M = F; a.N = d; a.K = (int)T; a.C = dW_gate; a.accumulate = accumulate; a.flag = c->flag;
-    a.ksplit = dw_split; a.ws = c->dw_ws;
+      a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
     HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, a, s));
     a.A = dVb; a.C = dW_up;
     HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWUP, OP_MC, OP_MC, EPI_F32, a, s));

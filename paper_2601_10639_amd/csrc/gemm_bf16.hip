@@ -1,11 +1,12 @@
 // bf16 MFMA GEMMs of the STEM layer (gate, down, and the four backward products)
 // for gfx950, with the layer's element-wise work fused into the epilogues.
 //
-// One kernel template computes  C[m,n] = sum_k Aop[m,k] * Bop[n,k]  on a 256x256
-// output tile per workgroup: 4 wavefronts, each a 128x128 quadrant held as 4x4
-// accumulators of v_mfma_f32_32x32x16_bf16, K stepped by 64 through a ring of five 32 KB
-// LDS slots (one operand tile each), so that every global request is made more than a
-// whole K tile before its data is needed.
+// One kernel template computes  C[m,n] = sum_k Aop[m,k] * Bop[n,k]  on one output tile per
+// workgroup: 256x256 for products with enough of them to fill the chip, else 256x128 or 128x128
+// (see Tiling; choose_plan decides, and may also cut K into slices).  The 256x256 tile: 4 wavefronts,
+// each a 128x128 quadrant held as 4x4 accumulators of v_mfma_f32_32x32x16_bf16, K stepped by 64
+// through a ring of five 32 KB LDS slots (one operand tile each), so that every global request is made
+// more than a whole K tile before its data is needed.
 //
 // Operands.  "KC" = stored [rows,K] with K contiguous, "MC" = stored [K,rows] with rows
 // contiguous.  Tiles of both kinds go global -> LDS directly (buffer_load ... lds, 16 bytes per
@@ -26,7 +27,7 @@
 // banks once (measured per instruction with four wavefronts issuing: 16 clocks, conflict-free).
 // The layout of an MC tile is described at its loader.
 //
-// Schedule.  One iteration = one K tile = 4 k-steps of 16 MFMAs.  Fragments are double
+// Schedule of the 256x256 tile.  One iteration = one K tile = 4 k-steps of 16 MFMAs.  Fragments are double
 // buffered in registers: while the MFMAs of k-step s run, the 8 fragment reads of step
 // s+1 are issued between them.  The loads of later tiles are spread over the k-steps
 // (a vector-memory instruction blocks the issuing wavefront for tens of cycles, during
@@ -52,8 +53,7 @@ typedef __amdgpu_buffer_rsrc_t rsrc_t;
 
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int TILE_BYTES = 256 * BK * 2;  // one operand tile in LDS
+constexpr int BK = 64;
 constexpr uint32_t OOB = 0x80000000u;  // a buffer offset beyond any operand: reads as zero
 
 __device__ __forceinline__ uint32_t lds_addr(const char* p) {   // p points into LDS
@@ -98,29 +98,35 @@ __device__ __forceinline__ void lds_dma_16(u32x4_t rs, uint32_t lds_dst, uint32_
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_dst), "v"(off), "s"(rs) : "memory");
 }
 
+// the same load through the compiler (a function of its own: inside a template the host pass drops the builtin's caller)
+__device__ __forceinline__ void lds_dma_16_known(rsrc_t rs, char* lds_dst, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)lds_dst, 16, off, 0, 0, 0);
+}
+
 // ---- KC operand: global -> LDS direct -----------------------------------------------
 // Wavefront w loads row groups g = w*8 + i (8 rows each); lane -> row g*8 + (lane >> 3),
 // chunk slot lane & 7; the lane fetches the chunk that belongs in its slot.
+template <int EDGE, int WAVES>
 struct LoaderKC {
-  uint32_t off[8];
+  static constexpr int LOADS = EDGE / 8 / WAVES;   // per wavefront and tile
+  uint32_t off[LOADS];
   Window win;
   // `skip`: elements by which p already points past the operand's first element (a K slice)
   __device__ __forceinline__ void init(const bf16_t* p, int ld, int rows, int row0, int wave, int lane, int skip) {
     win.set(p, ((int64_t)rows * ld - skip) * 2);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = (wave * 8 + i) * 8 + (lane >> 3);
+    for (int i = 0; i < LOADS; ++i) {
+      const int row = (wave * LOADS + i) * 8 + (lane >> 3);
       const int c = (lane & 7) ^ lds_swz(row);
       off[i] = (row0 + row) < rows ? (uint32_t)(((int64_t)(row0 + row) * ld + c * 8) * 2) : OOB;
     }
   }
-  // load i (0..7) of the tile the window points at, into `tile` (LDS, wave-uniform)
+  // load i of the tile the window points at, into `tile` (LDS, wave-uniform)
   __device__ __forceinline__ void issue(int i, char* tile, int wave) const {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(win.rsrc(), (lds_ptr_t)(tile + (wave * 8 + i) * 1024), 16, off[i], 0, 0,
-                                             0);
+    lds_dma_16_known(win.rsrc(), tile + (wave * LOADS + i) * 1024, off[i]);
   }
   __device__ __forceinline__ void issue_opaque(int i, char* tile, int wave) const {
-    lds_dma_16(win.words(), lds_addr(tile + (wave * 8 + i) * 1024), off[i]);
+    lds_dma_16(win.words(), lds_addr(tile + (wave * LOADS + i) * 1024), off[i]);
   }
   __device__ __forceinline__ void next_tile() { win.advance(BK * 2); }
 };
@@ -135,40 +141,45 @@ struct LoaderKC {
 // With a = k and b = 4-column piece, lane j ends up with 4 consecutive k of column j: half a
 // fragment.  The slot swizzle puts the four K rows that 16 lanes read in different 64-byte bank
 // groups, so 32 lanes (one LDS pass of a 64-bit read) touch all 64 banks once.
+template <int EDGE, int WAVES>
 struct LoaderMC {
-  uint32_t off[8];
+  static constexpr int LOADS = EDGE / 8 / WAVES;
+  static constexpr int CHUNKS = EDGE / 8;          // 16-byte chunks of a K row
+  static constexpr int ROW_BYTES = CHUNKS * 16;
+  uint32_t off[LOADS];
   uint32_t tile_bytes;   // one K tile further along the operand
   Window win;
   __device__ __forceinline__ void init(const bf16_t* p, int ld, int rows, int K, int row0, int wave, int lane) {
     win.set(p, (int64_t)K * ld * 2);
     tile_bytes = (uint32_t)ld * (BK * 2);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int k = (wave * 8 + i) * 2 + (lane >> 5);
-      const int c = (lane & 31) ^ ((k & 3) << 2);
+    for (int i = 0; i < LOADS; ++i) {
+      const int k = (wave * LOADS + i) * (64 / CHUNKS) + lane / CHUNKS;
+      const int c = (lane & (CHUNKS - 1)) ^ ((k & 3) << 2);
       off[i] = (row0 + c * 8) < rows ? (uint32_t)(((int64_t)k * ld + row0 + c * 8) * 2) : OOB;
     }
   }
   __device__ __forceinline__ void issue(int i, char* tile, int wave) const {
-    lds_dma_16(win.words(), lds_addr(tile + (wave * 8 + i) * 1024), off[i]);
+    lds_dma_16(win.words(), lds_addr(tile + (wave * LOADS + i) * 1024), off[i]);
   }
   __device__ __forceinline__ void next_tile() { win.advance((int)tile_bytes); }
   // Byte offset within a tile of this lane's address for the first half (k + 0..3) of fragment i
-  // (rows w*128 + i*32 .. +31 of the product) of k-step 0; the second half is 2048 bytes on, k-step
-  // s another s * 8192.  Lane = 16 g + 4 a + b: K row 8 (g >> 1) + a, rows 16 (g & 1) + 4 b .. + 3.
-  static __device__ __forceinline__ uint32_t frag_off(int w, int i, int lane) {
+  // (rows base + i*32 .. +31 of the product tile) of k-step 0; the second half is 4 K rows on, k-step
+  // s another 16 s.  Lane = 16 g + 4 a + b: K row 8 (g >> 1) + a, rows 16 (g & 1) + 4 b .. + 3.
+  static __device__ __forceinline__ uint32_t frag_off(int base, int i, int lane) {
     const int g = lane >> 4, a = (lane >> 2) & 3, b = lane & 3;
-    const int c = w * 16 + i * 4 + 2 * (g & 1) + (b >> 1);
-    return (uint32_t)((8 * (g >> 1) + a) * 512 + ((c ^ (a << 2)) << 4) + 8 * (b & 1));
+    const int c = base / 8 + i * 4 + 2 * (g & 1) + (b >> 1);
+    return (uint32_t)((8 * (g >> 1) + a) * ROW_BYTES + ((c ^ (a << 2)) << 4) + 8 * (b & 1));
   }
 };
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(8))) short s16x8_t;
 // one MFMA fragment (8 consecutive k of this lane's row) from a tile in the layout above
+template <int ROW_BYTES>
 __device__ __forceinline__ bf16x8_t lds_read_frag_tr(const char* p) {
   typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr;
   const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_ptr_t) const_cast<char*>(p));
-  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_ptr_t) const_cast<char*>(p + 2048));
+  const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds_ptr_t) const_cast<char*>(p + 4 * ROW_BYTES));
   return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
@@ -215,26 +226,67 @@ __device__ __forceinline__ void tile_of_block(int b, int nb, int ntm, int ntn, i
   tn = in / gsize;
 }
 
-template <int LA, int LB, int EPI>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
-  __shared__ __attribute__((aligned(16))) char smem[5 * TILE_BYTES];
+// A tiling: a wavefront holds MI x NJ accumulators of 32 x 32, WM x WN wavefronts multiply, and the operand
+// tiles pass through the five-slot ring (STAGES = 0) or through STAGES whole K tiles of LDS that LW further
+// wavefronts do nothing but fill.
+//
+// Tile256 (160 KB of LDS, 256 accumulator registers) moves the fewest operand bytes per FLOP, 32 per clock and CU
+// at full MFMA rate, and is the one for products that fill the chip with 256 x 256 tiles.  Below that a smaller
+// tile keeps all CUs busy.  The smaller ones need 48 and 64 bytes per clock and CU and are bound by operand loads
+// (with MFMAs and fragment reads taken out they take as long), so what counts for them is the bytes in flight: a
+// loads-only walk of 128 x 128 tiles reaches 63 GB/s per CU with one K tile in flight and 105 with two; three stages
+// keep two in flight, and five bring nothing more.  The separate load wavefronts keep the multiplying ones from
+// stalling on load issue (2048 x 8192 down product, 256 tokens: 47.5 us without, 43.3 with; 256 x 128 tiles, 4096
+// tokens: 116.6 and 113.9).  Tile256 has no registers left for them.  Two workgroups of 128 x 128 tiles per CU on
+// an 80 KB ring were 1.3 x slower where one per CU is enough (57 us against 43) and equal elsewhere.
+template <int MI_, int NJ_, int WM_, int WN_, int STAGES_, int LW_>
+struct Tiling {
+  static constexpr int MI = MI_, NJ = NJ_, WM = WM_, WN = WN_, STAGES = STAGES_, LW = LW_;
+  static constexpr int TM = 32 * MI * WM, TN = 32 * NJ * WN, WAVES = WM * WN;
+  static constexpr int A_BYTES = TM * BK * 2, B_BYTES = TN * BK * 2;   // one operand tile in LDS
+  static constexpr int LDS_BYTES = STAGES == 0 ? 5 * A_BYTES : STAGES * (A_BYTES + B_BYTES);
+};
+typedef Tiling<4, 4, 2, 2, 0, 0> Tile256;
+typedef Tiling<4, 2, 2, 2, 3, 4> Tile256x128;
+typedef Tiling<2, 2, 2, 2, 3, 4> Tile128;
+
+template <class C, int LA, int LB, int EPI>
+__global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(GemmArgs p) {
+  constexpr int MI = C::MI, NJ = C::NJ;
+  constexpr int WSM = 32 * MI, WSN = 32 * NJ;  // a wavefront's piece of the tile
+  constexpr int TILE_BYTES = C::A_BYTES;       // ring: one slot (both operands alike)
+  constexpr int LOADERS = C::LW ? C::LW : C::WAVES;   // wavefronts that issue loads
+  typedef LoaderKC<C::TM, LOADERS> LoadAKC;
+  typedef LoaderMC<C::TM, LOADERS> LoadAMC;
+  typedef LoaderKC<C::TN, LOADERS> LoadBKC;
+  typedef LoaderMC<C::TN, LOADERS> LoadBMC;
+  constexpr int LOADS_A = LoadAKC::LOADS, LOADS_B = LoadBKC::LOADS;   // loads per wavefront and tile
+  __shared__ __attribute__((aligned(16))) char smem[C::LDS_BYTES];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-  const int ntm = (p.M + BM - 1) / BM, ntn = (p.N + BN - 1) / BN;
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool load_wave = C::LW && wave_id >= C::WAVES;
+  const int wave = load_wave ? wave_id - C::WAVES : wave_id;
+  const int wm = wave / C::WN, wn = wave % C::WN;
+  const int ntm = (p.M + C::TM - 1) / C::TM, ntn = (p.N + C::TN - 1) / C::TN;
   constexpr int BAND = (EPI == EPI_DH || EPI == EPI_DH_UP || EPI == EPI_DH_UPE) ? 7 : 4;   // see tile_of_block
   int tm, tn;
   if (EPI == EPI_F32 && p.ksplit > 1) {
-    // Split along K (weight gradients of narrow layers: few output tiles, long K): slice z of the
-    // K tiles, its product stored plainly to slice z of the partial buffer; a second kernel sums
-    // the slices in order.  The slice is expressed by moving the operands and shrinking K.
+    // Split along K (few output tiles, long K): slice z of the K tiles, its product stored plainly to
+    // slice z of the partial buffer; a second kernel sums the slices in order.  The slice is
+    // expressed by moving the operands and shrinking K.
     const int ntiles = ntm * ntn;
     const int z = blockIdx.x / ntiles;
     tile_of_block<BAND>(blockIdx.x - z * ntiles, ntiles, ntm, ntn, tm, tn);
+    int zk = z, slices = p.ksplit;
+    if (LA == OP_KC && p.A2) {   // two operand pairs of the same K: half of the slices each
+      slices >>= 1;
+      if (zk >= slices) { zk -= slices; p.A = p.A2; p.B = p.B2; }
+      p.A2 = nullptr;
+    }
     const int nk_all = (p.K + BK - 1) / BK;
-    const int per = (nk_all + p.ksplit - 1) / p.ksplit;
-    const int k0 = z * per * BK;
+    const int per = (nk_all + slices - 1) / slices;
+    const int k0 = zk * per * BK;
     int klen = p.K - k0;
     if (klen > per * BK) klen = per * BK;
     if (klen < 0) klen = 0;
@@ -247,7 +299,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   } else {
     tile_of_block<BAND>(blockIdx.x, gridDim.x, ntm, ntn, tm, tn);
   }
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * C::TM, n0 = tn * C::TN;
   // K rotation.  Workgroups on XCD x start their K loop x eighths of the way in and wrap around, so
   // the eight XCDs stream eight different stretches of the operands' rows at any moment instead of
   // the same one (measured: the down product, whose two operands have the same 16 KB row pitch, ran
@@ -264,32 +316,23 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
     p.A += rot; p.B += rot; p.K -= rot; p.kc_skip += rot;
   }
 
-  f32x16_t acc[4][4];
+  f32x16_t acc[MI][NJ];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  LoaderKC ka, kb_;
-  LoaderMC da, db;
+  LoadAKC ka;
+  LoadBKC kb_;
+  LoadAMC da;
+  LoadBMC db;
   if (LA == OP_KC) ka.init(p.A, p.lda, p.M, m0, wave, lane, p.kc_skip); else da.init(p.A, p.lda, p.M, p.K, m0, wave, lane);
   if (LB == OP_KC) kb_.init(p.B, p.ldb, p.N, n0, wave, lane, p.kc_skip); else db.init(p.B, p.ldb, p.N, p.K, n0, wave, lane);
 
-  // fragments: lane -> row (lane & 31) of a 32-row block, k half (lane >> 5) of a k-step; within a k-step
-  // they are read in the order a0,b0,b1,a1,b2,b3,a2,a3
+  // fragments: lane -> row (lane & 31) of a 32-row block, k half (lane >> 5) of a k-step
   const int frow = lane & 31, fk = lane >> 5;
-  // MFMA pair q (0..7), in an order that consumes fragments in the order they were read
-  auto mma2 = [&](int q, bf16x8_t(&fa)[4], bf16x8_t(&fb)[4]) {
-    constexpr int ii[16] = {0, 0, 1, 1, 0, 1, 0, 1, 2, 2, 2, 2, 3, 3, 3, 3};
-    constexpr int jj[16] = {0, 1, 0, 1, 2, 2, 3, 3, 0, 1, 2, 3, 0, 1, 2, 3};
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = ii[2 * q + u], j = jj[2 * q + u];
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
-    }
-  };
 
   // A second operand pair (A2, B2, K2; same layouts and leading dimensions as the first; A
   // K-contiguous) continues the sum: after the K tiles of the first pair the windows move to the second.
@@ -304,17 +347,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   // The touching loads return asynchronously into their destination registers, so these stay
   // reserved (never reused by the compiler) until the wait that follows the main loop.
   constexpr bool TOUCH = (EPI == EPI_GATE);
-  // Token ids of this wavefront's 128 output rows, lane l holding rows l and 64 + l, fetched here so
+  // Token ids of this wavefront's output rows (128 or 64), lane l holding rows l and 64 + l, fetched here so
   // that their latency passes under the main loop.  The epilogue takes each row's id from these
   // registers by a lane permute: loading ids there would put a wait for the newest loads in front of
   // every block of table-row requests, and with it a wait for all the stores issued before them
   // (loads and stores return through one in-order counter), 3 to 4 us per block.
   constexpr bool NEED_IDS = (EPI == EPI_GATE || EPI == EPI_DH || EPI == EPI_GATE_UPE || EPI == EPI_DH_UPE);
-  int row_id[2] = {0, 0};
-  if (NEED_IDS) {
+  int row_id[MI / 2] = {};
+  if (NEED_IDS && !load_wave) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int m = m0 + wm * 128 + h * 64 + lane;
+    for (int h = 0; h < MI / 2; ++h) {
+      const int m = m0 + wm * WSM + h * 64 + lane;
       int id = p.ids[m < p.M ? m : p.M - 1];
       if ((unsigned)id >= (unsigned)p.E_rows) {   // reported to the host, clamped so no access leaves the table
         *p.flag = 1;
@@ -323,62 +366,28 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
       row_id[h] = id;
     }
   }
-  uint32_t touched[4] = {0, 0, 0, 0};
+  uint32_t touched[MI] = {};
   auto touch_epilogue_inputs = [&]() {
     if (!TOUCH) return;
-    const int ncol = n0 + wn * 128;
+    const int ncol = n0 + wn * WSN;
     const int col = ncol < p.N ? ncol : 0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < MI / 2; ++h) {
       const int id = row_id[h];
       const bf16_t* e = p.E + (size_t)id * p.N + col;
+      if (NJ == 2) {   // 64 columns: one line
+        asm volatile("global_load_dword %0, %1, off" : "=&v"(touched[h]) : "v"(e) : "memory");
+        continue;
+      }
       // the second line of the row's 128 columns exists only if the matrix is that wide (d_ff may be
       // 64 modulo 128): otherwise touch the first line twice rather than the next row's memory
       const bf16_t* e2 = col + 64 < p.N ? e + 64 : e;
       asm volatile("global_load_dword %0, %2, off\n\tglobal_load_dword %1, %3, off"
-                   : "=&v"(touched[2 * h]), "=&v"(touched[2 * h + 1]) : "v"(e), "v"(e2) : "memory");
+                   : "=&v"(touched[(2 * h) % MI]), "=&v"(touched[(2 * h + 1) % MI]) : "v"(e), "v"(e2) : "memory");
     }
   };
   const int touch_at = nk > 8 ? ((nk - 6) & ~1) : -1;   // an even K tile index a few tiles before the end
-  bf16x8_t xa[4], xb[4], ya[4], yb[4];
-  // ---- main loop: ring of five 32 KB slots -----------------------------------------------------
-  // Operand tiles alternate through the slots: A of K tile t in slot 2t mod 5, B in slot 2t+1 mod 5.
-  // While K tile t is multiplied, A(t+1), B(t+1) are landing or landed and A(t+2) is requested
-  // during the first two k-steps into the slot B(t-1) left; after the barrier that ends the reads
-  // of K tile t, B(t+2) is requested into A(t)'s slot.  Every request thus has a whole K tile's
-  // time (B) or more (A) before it is waited for, a request is always in flight across the
-  // barrier, and the wait before the barrier leaves the youngest 8 loads pending.  With two 64 KB
-  // stages the loads of a K tile were requested and drained within that tile's own time, and the
-  // direct-load stream alone (no MFMA, no fragment reads) took as long as the whole kernel.
-  // [slot pair][x]; the odd slot of a pair is an immediate away.  x = k-step for a K-contiguous operand
-  // (whose swizzle depends on it; the fragment index is an immediate), x = fragment for a
-  // rows-contiguous one (the other way round).
-  uint32_t ra_addr[3][4], rb_addr[3][4];
-#pragma unroll
-  for (int pr = 0; pr < 3; ++pr)
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const uint32_t sw = (uint32_t)((((x * 2 + fk) ^ lds_swz(frow)) & 7) << 4);
-      ra_addr[pr][x] = (uint32_t)(pr * 2 * TILE_BYTES) +
-                       (LA == OP_KC ? (uint32_t)((wm * 128 + frow) * 128) + sw : LoaderMC::frag_off(wm, x, lane));
-      rb_addr[pr][x] = (uint32_t)(pr * 2 * TILE_BYTES) +
-                       (LB == OP_KC ? (uint32_t)((wn * 128 + frow) * 128) + sw : LoaderMC::frag_off(wn, x, lane));
-    }
-  auto rfrag_ring = [&](int sa, int sb, int ks, int q, bf16x8_t(&fa)[4], bf16x8_t(&fb)[4]) {
-    constexpr int isA[8] = {1, 0, 0, 1, 0, 0, 1, 1};
-    constexpr int idx[8] = {0, 0, 1, 1, 2, 3, 2, 3};
-    if (isA[q]) {
-      if (LA == OP_KC)
-        fa[idx[q]] = *reinterpret_cast<const bf16x8_t*>(smem + ra_addr[sa >> 1][ks] + (sa & 1) * TILE_BYTES + idx[q] * 4096);
-      else
-        fa[idx[q]] = lds_read_frag_tr(smem + ra_addr[sa >> 1][idx[q]] + (sa & 1) * TILE_BYTES + ks * 8192);
-    } else {
-      if (LB == OP_KC)
-        fb[idx[q]] = *reinterpret_cast<const bf16x8_t*>(smem + rb_addr[sb >> 1][ks] + (sb & 1) * TILE_BYTES + idx[q] * 4096);
-      else
-        fb[idx[q]] = lds_read_frag_tr(smem + rb_addr[sb >> 1][idx[q]] + (sb & 1) * TILE_BYTES + ks * 8192);
-    }
-  };
+  bf16x8_t xa[MI], xb[NJ], ya[MI], yb[NJ];
   int a_to_switch = p.A2 ? nk1 : -1, b_to_switch = a_to_switch;
   auto next_A = [&]() {
     if constexpr (LA == OP_KC) {
@@ -405,6 +414,61 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
     else if constexpr (OPAQUE) kb_.issue_opaque(q, tile, wave);
     else kb_.issue(q, tile, wave);
   };
+  constexpr int MCA_ROW = LoadAMC::ROW_BYTES, MCB_ROW = LoadBMC::ROW_BYTES;
+  // This lane's fragment address within a tile.  x = k-step for a K-contiguous operand (whose swizzle depends on
+  // it; the fragment index is an immediate), x = fragment for a rows-contiguous one (the other way round).
+  auto frag_addr_A = [&](int x) -> uint32_t {
+    if (LA == OP_MC) return LoadAMC::frag_off(wm * WSM, x % MI, lane);
+    return (uint32_t)((wm * WSM + frow) * 128) + (uint32_t)((((x * 2 + fk) ^ lds_swz(frow)) & 7) << 4);
+  };
+  auto frag_addr_B = [&](int x) -> uint32_t {
+    if (LB == OP_MC) return LoadBMC::frag_off(wn * WSN, x % NJ, lane);
+    return (uint32_t)((wn * WSN + frow) * 128) + (uint32_t)((((x * 2 + fk) ^ lds_swz(frow)) & 7) << 4);
+  };
+  // fragment i of k-step ks; addr[] = frag_addr of the operand's tile
+  auto frag_A = [&](const char* tile, const uint32_t(&addr)[4], int ks, int i) -> bf16x8_t {
+    if constexpr (LA == OP_KC) return *reinterpret_cast<const bf16x8_t*>(tile + addr[ks] + i * 4096);
+    else return lds_read_frag_tr<MCA_ROW>(tile + addr[i] + ks * 16 * MCA_ROW);
+  };
+  auto frag_B = [&](const char* tile, const uint32_t(&addr)[4], int ks, int i) -> bf16x8_t {
+    if constexpr (LB == OP_KC) return *reinterpret_cast<const bf16x8_t*>(tile + addr[ks] + i * 4096);
+    else return lds_read_frag_tr<MCB_ROW>(tile + addr[i] + ks * 16 * MCB_ROW);
+  };
+  auto mma = [&](int i, int j, bf16x8_t(&fa)[MI], bf16x8_t(&fb)[NJ]) {
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+  };
+  if constexpr (C::STAGES == 0) {
+  // ---- main loop: ring of five 32 KB slots -----------------------------------------------------
+  // Operand tiles alternate through the slots: A of K tile t in slot 2t mod 5, B in slot 2t+1 mod 5.
+  // While K tile t is multiplied, A(t+1), B(t+1) are landing or landed and A(t+2) is requested
+  // during the first two k-steps into the slot B(t-1) left; after the barrier that ends the reads
+  // of K tile t, B(t+2) is requested into A(t)'s slot.  Every request thus has a whole K tile's
+  // time (B) or more (A) before it is waited for, a request is always in flight across the
+  // barrier, and the wait before the barrier leaves the youngest 8 loads pending.  With two 64 KB
+  // stages the loads of a K tile were requested and drained within that tile's own time, and the
+  // direct-load stream alone (no MFMA, no fragment reads) took as long as the whole kernel.
+  uint32_t ra_addr[3][4], rb_addr[3][4];   // [slot pair][x]; the odd slot of a pair is an immediate away
+#pragma unroll
+  for (int pr = 0; pr < 3; ++pr)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      ra_addr[pr][x] = (uint32_t)(pr * 2 * TILE_BYTES) + frag_addr_A(x);
+      rb_addr[pr][x] = (uint32_t)(pr * 2 * TILE_BYTES) + frag_addr_B(x);
+    }
+  // within a k-step fragments are read in the order a0,b0,b1,a1,b2,b3,a2,a3, and the MFMA pairs q = 0..7 consume
+  // them in that order
+  auto mma2 = [&](int q, bf16x8_t(&fa)[MI], bf16x8_t(&fb)[NJ]) {
+    constexpr int ii[16] = {0, 0, 1, 1, 0, 1, 0, 1, 2, 2, 2, 2, 3, 3, 3, 3};
+    constexpr int jj[16] = {0, 1, 0, 1, 2, 2, 3, 3, 0, 1, 2, 3, 0, 1, 2, 3};
+    mma(ii[2 * q], jj[2 * q], fa, fb);
+    mma(ii[2 * q + 1], jj[2 * q + 1], fa, fb);
+  };
+  auto rfrag_ring = [&](int sa, int sb, int ks, int q, bf16x8_t(&fa)[MI], bf16x8_t(&fb)[NJ]) {
+    constexpr int isA[8] = {1, 0, 0, 1, 0, 0, 1, 1};
+    constexpr int idx[8] = {0, 0, 1, 1, 2, 3, 2, 3};
+    if (isA[q]) fa[idx[q]] = frag_A(smem + (sa & 1) * TILE_BYTES, ra_addr[sa >> 1], ks, idx[q]);
+    else fb[idx[q]] = frag_B(smem + (sb & 1) * TILE_BYTES, rb_addr[sb >> 1], ks, idx[q]);
+  };
   // prologue: A0, B0, A1, B1 into slots 0..3
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
@@ -417,7 +481,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   // A0 and B0 have landed; A1 and B1 stay in flight across the barrier.  (A plain __syncthreads() here
   // makes the compiler wait for every direct-to-LDS load it knows of, i.e. for all four tiles: stamps
   // inside the kernel, 8-9 K clocks to the first MFMA against 5-6 K.)
-  asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(16) : "memory");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -448,9 +512,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
       mma2(q, xa, xb);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // A(t+1) and B(t+1) have landed (only the 8 loads of A(t+2) may be pending) and nobody reads
+    // A(t+1) and B(t+1) have landed (only the loads of A(t+2) may be pending) and nobody reads
     // this tile's slots any more
-    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(8) : "memory");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -476,17 +540,108 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   if (kt + 1 < nk) ring_iteration(1);
   if (kt + 2 < nk) ring_iteration(2);
   if (kt + 3 < nk) ring_iteration(3);
+  } else {
+  // ---- main loop: STAGES whole K tiles in LDS ---------------------------------------------------
+  // K tile t sits in stage t mod STAGES.  One barrier per K tile, before its last k-step: in front of it the load
+  // wavefronts have seen tile t + 1 land (the tiles after it stay in flight) and the others have read the last of
+  // tile t, so behind it tile t + STAGES is requested into tile t's stage.
+  constexpr int S = C::STAGES, STAGE_BYTES = C::A_BYTES + C::B_BYTES, LOADS = LOADS_A + LOADS_B;
+  if (load_wave) {
+    auto request = [&](const int st) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < LOADS_A; ++q) issue_A(q, smem + st * STAGE_BYTES);
+      next_A();
+#pragma unroll
+      for (int q = 0; q < LOADS_B; ++q) issue_B(q, smem + st * STAGE_BYTES + C::A_BYTES);
+      next_B();
+    };
+#pragma unroll
+    for (int st = 0; st < S; ++st) request(st);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * LOADS) : "memory");
+    __builtin_amdgcn_s_barrier();
+    auto load_iteration = [&](const int st) __attribute__((always_inline)) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * LOADS) : "memory");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      request(st);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    int kt = 0;
+    for (; kt + S <= nk; kt += S) {
+#pragma unroll
+      for (int st = 0; st < S; ++st) load_iteration(st);
+    }
+#pragma unroll
+    for (int st = 0; st < S - 1; ++st)
+      if (kt + st < nk) load_iteration(st);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing lands in LDS once the epilogue stages through it
+    __syncthreads();
+    return;
+  }
+  constexpr int NMMA = MI * NJ, NFRAG = MI + NJ;
+  uint32_t sa_addr[S][4], sb_addr[S][4];
+#pragma unroll
+  for (int st = 0; st < S; ++st)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      sa_addr[st][x] = (uint32_t)(st * STAGE_BYTES) + frag_addr_A(x);
+      sb_addr[st][x] = (uint32_t)(st * STAGE_BYTES + C::A_BYTES) + frag_addr_B(x);
+    }
+  auto rfrag = [&](int st, int ks, int q, bf16x8_t(&fa)[MI], bf16x8_t(&fb)[NJ]) {   // order a0, b0, b1, .., a1, a2, ..
+    if (q == 0) fa[0] = frag_A(smem, sa_addr[st], ks, 0);
+    else if (q <= NJ) fb[q - 1] = frag_B(smem, sb_addr[st], ks, q - 1);
+    else fa[q - NJ] = frag_A(smem, sa_addr[st], ks, q - NJ);
+  };
+  // one k-step: its MFMAs, with the fragment reads of the next k-step between them
+  auto kstep = [&](int st, int ks_next, bf16x8_t(&fa)[MI], bf16x8_t(&fb)[NJ], bf16x8_t(&na)[MI],
+                   bf16x8_t(&nb)[NJ]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NMMA; ++u) {
+#pragma unroll
+      for (int q = u * NFRAG / NMMA; q < (u + 1) * NFRAG / NMMA; ++q) rfrag(st, ks_next, q, na, nb);
+      mma(u / NJ, u % NJ, fa, fb);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < NFRAG; ++q) rfrag(0, 0, q, xa, xb);
+  auto stage_iteration = [&](const int st) __attribute__((always_inline)) {
+    kstep(st, 1, xa, xb, ya, yb);
+    kstep(st, 2, ya, yb, xa, xb);
+    kstep(st, 3, xa, xb, ya, yb);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    kstep((st + 1) % S, 0, ya, yb, xa, xb);
+  };
+  int kt = 0;
+  for (; kt + S <= nk; kt += S) {
+    if (TOUCH && kt <= touch_at && touch_at < kt + S) touch_epilogue_inputs();
+#pragma unroll
+    for (int st = 0; st < S; ++st) stage_iteration(st);
+  }
+  if (TOUCH && kt <= touch_at) touch_epilogue_inputs();
+#pragma unroll
+  for (int st = 0; st < S - 1; ++st)
+    if (kt + st < nk) stage_iteration(st);
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (TOUCH)   // end of the touched registers' reservation
-    asm volatile("" ::"v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
+#pragma unroll
+    for (int x = 0; x < MI; ++x) asm volatile("" ::"v"(touched[x]));
   __syncthreads();
 
   // ---- epilogue: per wavefront, 32 rows at a time through LDS ----------------------------
-  constexpr int SROW = 528;                   // staged row: 128 fp32 + 16 bytes of padding
-  char* stg = smem + wave * 32768;            // 32 x 528 = 16896 bytes used
-  const int srow = lane >> 4;                 // row within a group of 4
-  const int scol = (lane & 15) * 8;           // first of this lane's 8 consecutive columns
-  const int n = n0 + wn * 128 + scol;
+  constexpr int SROW = WSN * 4 + 16;           // staged row: fp32 values + 16 bytes of padding
+  constexpr int LPR = WSN / 8;                // lanes per row, 8 columns each
+  constexpr int RPP = 64 / LPR;               // rows per pass of the wavefront
+  constexpr int PASSES = 32 / RPP;
+  char* stg = smem + wave * (32 * SROW);
+  const int srow = lane / LPR;                // row within a pass
+  const int scol = (lane & (LPR - 1)) * 8;    // first of this lane's 8 consecutive columns
+  const int n = n0 + wn * WSN + scol;
   const bool n_ok = n < p.N;
   const int n_ld = n_ok ? n : 0;              // in-bounds column for the prefetching loads
   constexpr bool GATE_LIKE = (EPI == EPI_GATE || EPI == EPI_GATE_UP || EPI == EPI_GATE_UPE);
@@ -496,18 +651,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   constexpr bool FUSED = GATE_LIKE || DH_LIKE;
 
   // Everything the element-wise part needs from memory is requested one 32-row block ahead
-  // (8 rows per lane and block), so the gathered table rows arrive while the previous block
+  // (PASSES rows per lane and block), so the gathered table rows arrive while the previous block
   // is being staged and stored.
   // ev: gathered table row, uv: up-projection row (dense and additive variants), gv: saved G row
-  uint4 ev[2][8], gv[2][8], uv[2][8];
+  uint4 ev[2][PASSES], gv[2][PASSES], uv[2][PASSES];
   auto prefetch = [&](int i, int buf) __attribute__((always_inline)) {
     if (!FUSED) return;
 #pragma unroll
-    for (int pass = 0; pass < 8; ++pass) {
-      const int m = m0 + wm * 128 + i * 32 + pass * 4 + srow;
+    for (int pass = 0; pass < PASSES; ++pass) {
+      const int m = m0 + wm * WSM + i * 32 + pass * RPP + srow;
       const int mc = m < p.M ? m : p.M - 1;
       if (USE_E) {
-        const int r = i * 32 + pass * 4 + srow;   // row within the wavefront's 128: held by lane r & 63
+        const int r = i * 32 + pass * RPP + srow;   // row within the wavefront's quadrant: held by lane r & 63
         const int id = __builtin_amdgcn_ds_bpermute((r & 63) * 4, row_id[i >> 1]);
         ev[buf][pass] = *reinterpret_cast<const uint4*>(p.E + (size_t)id * p.N + n_ld);
       }
@@ -517,7 +672,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   };
   // Outputs leave through buffer stores: a lane outside the matrix (ragged last tile) is given an
   // offset beyond the buffer and the hardware drops its store, so the element-wise part below is
-  // straight-line code that the compiler schedules as a whole (the staged values of all eight
+  // straight-line code that the compiler schedules as a whole (the staged values of all
   // passes are read from LDS up front and the arithmetic of one pass covers the latency of the
   // next; with a branch around every store each pass waited for its own LDS reads: stamps inside
   // the kernel, 5.7 K clocks per 32-row block against 3.6 K of arithmetic).
@@ -535,11 +690,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
   };
   prefetch(0, 0);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (i + 1 < 4) prefetch(i + 1, (i + 1) & 1);
+  for (int i = 0; i < MI; ++i) {
+    if (i + 1 < MI) prefetch(i + 1, (i + 1) & 1);
     // accumulators -> LDS: lane holds row frow, columns j*32 + g*8 + fk*4 .. +3
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       const f32x16_t v = acc[i][j];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -550,17 +705,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs p) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    f32x4_t cv[8][2];
+    f32x4_t cv[PASSES][2];
 #pragma unroll
-    for (int pass = 0; pass < 8; ++pass) {
-      const int r = pass * 4 + srow;
+    for (int pass = 0; pass < PASSES; ++pass) {
+      const int r = pass * RPP + srow;
       cv[pass][0] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + scol * 4);
       cv[pass][1] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + scol * 4 + 16);
     }
 #pragma unroll
-    for (int pass = 0; pass < 8; ++pass) {
-      const int r = pass * 4 + srow;
-      const int m = m0 + wm * 128 + i * 32 + r;
+    for (int pass = 0; pass < PASSES; ++pass) {
+      const int r = pass * RPP + srow;
+      const int m = m0 + wm * WSM + i * 32 + r;
       const f32x4_t c0 = cv[pass][0], c1 = cv[pass][1];
       const float c[8] = {c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
       const bool ok = n_ok && m < p.M;
@@ -633,26 +788,75 @@ __global__ __launch_bounds__(256) void splitk_sum_f32_kernel(const float* __rest
   *reinterpret_cast<f32x4_t*>(C + i) = s;
 }
 
-template <int LA, int LB, int EPI>
-hipError_t launch(stem_ctx* ctx, int kid, const GemmArgs& a, hipStream_t s) {
-  const int ntm = (a.M + BM - 1) / BM, ntn = (a.N + BN - 1) / BN;
-  if (EPI == EPI_F32 && a.ksplit > 1) {
-    if (!a.ws || (a.M * (int64_t)a.N) % 4 != 0) return hipErrorInvalidValue;
-    {
-      ProfScope ps(ctx, kid, s);
-      hipLaunchKernelGGL((gemm_bf16_kernel<LA, LB, EPI>), dim3(ntm * ntn * a.ksplit), dim3(256), 0, s, a);
+// ---- choice of the tiling and of the K split ----------------------------------------------------
+// A launch is priced as rounds of 256 workgroups: a round takes (K tiles per workgroup) x (time per K tile) plus a
+// fixed part (prologue, epilogue).  The time per K tile grows with the share of the chip that is busy (operand
+// loads, clock), from `idle` with a few workgroups to `full` with 256.  The constants (us) are fits to measured
+// launches of d_model 1024 and 2048, d_ff 4096 and 8192, 128 to 16384 tokens; the model is within 8 % of nearly all.
+// Examples, us (Tile256 / Tile256x128 / Tile128): down product 2048 x 8192, 1999 tokens 146 / 92 / 70, 4096 tokens
+// 165 / 114 / 129, 16384 tokens 408 / 460 / 538; gate product 700 tokens 51 / 34 / 39, 1999 tokens 69 / 73 / 85.
+struct TilingCost { int tm, tn; double idle, full, fixed_plain, fixed_fused, fixed_f32; };
+constexpr TilingCost kTilings[3] = {{256, 256, 0.95, 1.50, 8, 18, 18}, {256, 128, 0.52, 0.86, 7, 10, 12}, {128, 128, 0.33, 0.54, 5, 6, 5}};
+
+struct Plan { int tiling, ksplit; };
+
+// fused: the epilogue carries the layer's element-wise work and cannot be split.  ops: operand pairs of the K range
+// (a split into an even number of slices gives each pair half of them).
+Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_bytes) {
+  Plan best = {0, 1};
+  double best_us = 1e30;
+  const int nk = ops * ((K + BK - 1) / BK);
+  for (int t = 0; t < 3; ++t) {
+    const TilingCost& c = kTilings[t];
+    const double tiles = (double)((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn);
+    for (int ks = 1; ks <= 8; ks *= 2) {
+      if (ks > 1 && (fused || (double)M * N * 4 * ks > (double)ws_bytes || nk / ks < 4 || tiles * ks > 512)) break;
+      const double wgs = tiles * ks, fixed = fused ? c.fixed_fused : f32 || ks > 1 ? c.fixed_f32 : c.fixed_plain;
+      const int kt = (nk + ks - 1) / ks, rounds = (int)(wgs / 256);
+      const double rest = wgs - rounds * 256.0;
+      double us = rounds * (kt * c.full + fixed);
+      if (rest > 0) us += kt * (rounds ? c.full : c.idle + (c.full - c.idle) * rest / 256) + fixed;
+      if (ks > 1) us += 3.5 + (ks + 1.0) * M * N * 4 / 5e6;   // the kernel that sums the slices: launch, and 5 TB/s
+      if (us < best_us) { best_us = us; best = {t, ks}; }
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t total = (int64_t)a.M * a.N;
-    ProfScope ps(ctx, K_SPLITK_REDUCE, s);
-    hipLaunchKernelGGL(splitk_sum_f32_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, s, a.ws, a.ksplit,
-                       total, static_cast<float*>(a.C), a.accumulate);
-    return hipGetLastError();
   }
+  return best;
+}
+
+template <class C, int LA, int LB, int EPI>
+hipError_t launch_tiles(stem_ctx* ctx, int kid, const GemmArgs& a, hipStream_t s) {
+  const int ntm = (a.M + C::TM - 1) / C::TM, ntn = (a.N + C::TN - 1) / C::TN;
   ProfScope ps(ctx, kid, s);
-  hipLaunchKernelGGL((gemm_bf16_kernel<LA, LB, EPI>), dim3(ntm * ntn), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((gemm_bf16_kernel<C, LA, LB, EPI>), dim3(ntm * ntn * a.ksplit), dim3((C::WAVES + C::LW) * 64), 0, s, a);
   return hipGetLastError();
+}
+
+template <int LA, int LB, int EPI>
+hipError_t launch_tiling(int tiling, stem_ctx* ctx, int kid, const GemmArgs& a, hipStream_t s) {
+  if (tiling == 2) return launch_tiles<Tile128, LA, LB, EPI>(ctx, kid, a, s);
+  if (tiling == 1) return launch_tiles<Tile256x128, LA, LB, EPI>(ctx, kid, a, s);
+  return launch_tiles<Tile256, LA, LB, EPI>(ctx, kid, a, s);
+}
+
+template <int LA, int LB, int EPI>
+hipError_t launch(stem_ctx* ctx, int kid, GemmArgs a, hipStream_t s) {
+  constexpr bool PLAIN = (EPI == EPI_BF16 || EPI == EPI_BF16_RES), F32 = (EPI == EPI_F32);
+  const size_t ws_bytes = a.ws && (int64_t)a.M * a.N % 4 == 0 && (!a.A2 || a.K2 == a.K) ? a.ws_bytes : 0;
+  const Plan plan = choose_plan(a.M, a.N, a.K, a.A2 ? 2 : 1, !PLAIN && !F32, F32, ws_bytes);
+  a.ksplit = plan.ksplit;
+  if constexpr (PLAIN || F32) {
+    if (plan.ksplit > 1) {   // fp32 partial products, one per K slice, and a kernel that sums them in slice order
+      hipError_t e = launch_tiling<LA, LB, EPI_F32>(plan.tiling, ctx, kid, a, s);
+      if (e != hipSuccess) return e;
+      const int64_t total = (int64_t)a.M * a.N;
+      if (PLAIN) return stem_splitk_reduce(ctx, a.ws, plan.ksplit, total, EPI == EPI_BF16_RES ? a.residual : nullptr, a.C, s);
+      ProfScope ps(ctx, K_SPLITK_REDUCE, s);
+      hipLaunchKernelGGL(splitk_sum_f32_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, s, a.ws,
+                         plan.ksplit, total, static_cast<float*>(a.C), a.accumulate);
+      return hipGetLastError();
+    }
+  }
+  return launch_tiling<LA, LB, EPI>(plan.tiling, ctx, kid, a, s);
 }
 
 }  // namespace

@@ -286,6 +286,14 @@ int stem_gemm_skinny_ksplit(int M, int N, int K) {
   return ks;
 }
 
+hipError_t stem_splitk_reduce(stem_ctx* ctx, const float* ws, int ksplit, int64_t total, const bf16_t* residual, void* out,
+                              hipStream_t s) {
+  ProfScope ps(ctx, K_SPLITK_REDUCE, s);
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, s, ws, ksplit,
+                     total, residual, static_cast<bf16_t*>(out));
+  return hipGetLastError();
+}
+
 hipError_t stem_gemm_skinny_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipSuccess;
   const int64_t lim = 0x7fffffff;
@@ -306,11 +314,7 @@ hipError_t stem_gemm_skinny_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t total = (int64_t)a.M * a.N;
-    ProfScope ps(ctx, K_SPLITK_REDUCE, s);
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, s, p.ws,
-                       p.ksplit, total, p.residual, static_cast<bf16_t*>(p.C));
-    return hipGetLastError();
+    return stem_splitk_reduce(ctx, p.ws, p.ksplit, (int64_t)a.M * a.N, p.residual, p.C, s);
   }
   p.ksplit = 1;
   ProfScope ps(ctx, kid, s);

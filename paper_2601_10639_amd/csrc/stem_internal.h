@@ -49,9 +49,8 @@ struct stem_ctx {
   void* dG_ws;           // [max_tokens, F] context dtype
   void* dH_ws;           // [max_tokens, F] fp32, STEM_F32 only
   void* Up_ws;           // [max_tokens, F] bf16, allocated by the first stem_ffn_up_* call
-  float* splitk_ws;      // STEM_SPLITK_WS_BYTES: fp32 partial products of the few-row GEMMs
-  float* dw_ws;          // [dw_ksplit][d*F] fp32 partial weight gradients, when the layer is narrow
-  int dw_ksplit;         // K slices of the weight-gradient GEMMs (1 = no split)
+  float* splitk_ws;      // fp32 partial products of GEMMs whose K range is cut into slices
+  size_t splitk_bytes;   // its size; no launch splits beyond it
   int32_t* sort_keys[2]; // [max_tokens]
   int32_t* sort_vals[2]; // [max_tokens]
   int32_t* sort_counts;  // [64 * waves]
@@ -154,8 +153,9 @@ struct GemmArgs {
   bf16_t* outdU;   // EPI_DH
   bf16_t* outdG;   // EPI_DH
   int32_t* flag;
-  float* ws;       // split-K launches: [ksplit][M][N] fp32 partial products
-  int ksplit;      // number of k slices (few-row kernel: EPI_SPLITK; large kernel: EPI_F32 with ksplit > 1)
+  float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
+  size_t ws_bytes; // capacity of ws
+  int ksplit;      // number of k slices (few-row kernel: EPI_SPLITK; large kernel: chosen by its launcher)
   int kc_skip;     // set by the large kernel itself: elements a K slice starts after the operand's start
   int mt, nt;      // few-row kernel: tile counts and exact float reciprocals, filled in by the launcher
   float inv_mt, inv_per_z;
@@ -165,8 +165,13 @@ hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const
 
 // ---- few-row bf16 GEMM (gemm_skinny_bf16.hip): both operands K-contiguous, K % 64 == 0 --------
 // 128x64 tiles; used when M is small enough that 256x256 tiles would leave most of the chip idle.
-#define STEM_SKINNY_MAX_M 512
-#define STEM_SPLITK_WS_BYTES ((size_t)8 << 20)   // >= ksplit * M * N * 4 whenever ksplit > 1
+// Up to 256 rows: at d_model 2048, d_ff 8192 the gate / down products take 17 / 17 us at 128 rows against 23 / 35 on
+// 128x128 tiles, 19 / 21 against 20 / 24 at 256 and 35 / 33 against 26 / 33 at 512.
+#define STEM_SKINNY_MAX_M 256
+#define STEM_SPLITK_WS_MAX ((size_t)64 << 20)   // more is never worth it: beyond it the tiles fill the chip
+// out = bf16(sum of the ksplit fp32 partial products in ws, in slice order (+ residual)); total elements each
+hipError_t stem_splitk_reduce(stem_ctx* ctx, const float* ws, int ksplit, int64_t total, const bf16_t* residual, void* out,
+                              hipStream_t s);
 // k slices that bring the launch to about one workgroup per compute unit (1 = no split)
 int stem_gemm_skinny_ksplit(int M, int N, int K);
 // epi: EPI_BF16, EPI_GATE, or EPI_SPLITK (a.ksplit slices through a.ws, then summed into a.C)

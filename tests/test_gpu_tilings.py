@@ -1,0 +1,51 @@
+"""GPU parity at the edges of the tile shapes the bf16 products choose from."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import stem_oracle as O
+from paper_2601_10639_amd import inputs, stemlib as L
+from tests import harness as Hn
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("T,d,F", [
+    (1000, 512, 4160),    # gate, dH: 256x128 tiles with ragged last ones; down, dx: 128x128 in 8 K slices, the last one short
+    (1300, 1152, 6016),   # gate, dH: 256x256; down, dx: 128x128 in 2 slices; weight gradients: 256x128, a ragged last K tile
+    (520, 64, 8192),      # gate, dH on 256x128 tiles with one K tile, fewer than the stages in LDS
+    (385, 128, 128),      # 128x128 with two K tiles, one row in the last tile
+])
+@pytest.mark.parametrize("up", [False, True])
+def test_bf16_products_on_every_tiling(T, d, F, up):
+    """Forward and backward of the layer, and (up) of the additive variant, whose dx product sums two operand
+    pairs and cuts them into K slices."""
+    V = 300
+    s = inputs.StemShape("tilings", d, F, V, 1, T, "bf16")
+    inp = inputs.layer_inputs(s, seed=61, device=DEV, tokens=T)
+    ctx = Hn.make_ctx(s, T, reserve=L.STEM_RESERVE_UP if up else 0)
+    f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
+    ids = inp["ids"].cpu().numpy()
+    if not up:
+        out = Hn.hip_forward_backward(ctx, inp)
+        y, _ = O.ffn_forward(f64["x"], ids, f64["W_gate"], f64["W_down"], f64["E"])
+        bw = O.ffn_backward(f64["dy"], f64["x"], ids, f64["W_gate"], f64["W_down"], f64["E"])
+        ref = {"y": y, "dx": bw["dx"], "dU": bw["dU"], "dW_gate": bw["dW_gate"], "dW_down": bw["dW_down"]}
+    else:
+        Wu = inputs.normal((F, d), 0.02, 62, torch.bfloat16, DEV)
+        e = lambda *sh, dt=torch.bfloat16: torch.empty(*sh, dtype=dt, device=DEV)  # noqa: E731
+        out = {"y": e(T, d), "dx": e(T, d), "dU": e(T, F), "dW_gate": e(F, d, dt=torch.float32),
+               "dW_up": e(F, d, dt=torch.float32), "dW_down": e(d, F, dt=torch.float32)}
+        G, Up, H = e(T, F), e(T, F), e(T, F)
+        L.stem_ffn_up_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], Wu, inp["W_down"], inp["E"], out["y"], G, Up, H)
+        L.stem_ffn_up_backward(ctx, inp["dy"], inp["x"], inp["ids"], inp["W_gate"], Wu, inp["W_down"], inp["E"], G, Up, H,
+                               out["dx"], out["dW_gate"], out["dW_up"], out["dW_down"], out["dU"])
+        wu = inputs.to_f64(Wu)
+        y, _ = O.up_forward(f64["x"], ids, f64["W_gate"], wu, f64["W_down"], f64["E"])
+        bw = O.up_backward(f64["dy"], f64["x"], ids, f64["W_gate"], wu, f64["W_down"], f64["E"])
+        ref = {"y": y, "dx": bw["dx"], "dU": bw["dV"], "dW_gate": bw["dW_gate"], "dW_up": bw["dW_up"], "dW_down": bw["dW_down"]}
+    L.stem_sync_status(ctx)
+    errs = {k: Hn.max_rel(out[k].float().cpu(), v) for k, v in ref.items()}
+    assert all(v <= Hn.TOL["bf16"] for v in errs.values()), errs
+    ctx.close()
