@@ -18,7 +18,7 @@ char g_create_err[512] = "";
 
 const char* const kKernelNames[K_COUNT_] = {
     "gemm_gate_fused", "gemm_gate_plain", "gemm_down",    "gemm_dh_fused", "gemm_dx",      "gemm_dw_down",
-    "gemm_dw_gate",    "silu_gather",     "dh_epilogue",  "sort_count",    "sort_scan",    "sort_scatter",
+    "gemm_dw_gate",    "silu_gather",      "sort_count",    "sort_scan",    "sort_scatter",
     "sort_fused",      "unique",          "seg_reduce",   "seg_combine",   "sparse_adamw", "row_copy",
     "splitk_reduce",   "gemm_up",      "gemm_dw_up"};
 
@@ -62,7 +62,7 @@ void release(stem_ctx* c) {
   if (!c) return;
   (void)hipSetDevice(c->device);
   (void)hipDeviceSynchronize();
-  (void)hipFree(c->H_ws); (void)hipFree(c->dG_ws); (void)hipFree(c->dH_ws);
+  (void)hipFree(c->H_ws); (void)hipFree(c->dG_ws);
   (void)hipFree(c->splitk_ws);
   (void)hipFree(c->Up_ws);
   for (int i = 0; i < 2; ++i) { (void)hipFree(c->sort_keys[i]); (void)hipFree(c->sort_vals[i]); }
@@ -164,7 +164,6 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   auto ok = [&](hipError_t r) { if (e == hipSuccess) e = r; };
   ok(hipMalloc(&c->H_ws, std::max<size_t>(TF * es, 16)));
   ok(hipMalloc(&c->dG_ws, std::max<size_t>(TF * es, 16)));
-  if (desc->dtype == STEM_F32) ok(hipMalloc(&c->dH_ws, std::max<size_t>(TF * 4, 16)));
   if (desc->dtype == STEM_BF16) {
     // partial products of up to 8 K slices of a [T,d] or [d,F] output
     c->splitk_bytes = std::min<size_t>(STEM_SPLITK_WS_MAX, (size_t)8 * 4 * desc->d_model * std::max<int64_t>({max_tokens, desc->d_ff, 1}));
@@ -314,16 +313,25 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DOWN, OP_KC, OP_KC, down_epi, b, s));
     }
   } else {
-    float* G = static_cast<float*>(save_G ? save_G : c->dG_ws);
-    HIP_TRY(c, stem_sgemm(c, wait_event ? K_GEMM_GATE_PLAIN : K_GEMM_GATE, static_cast<const float*>(x), d, 1,
-                          static_cast<const float*>(W_gate), d, 1, G, (int)T, F, d, 0, s));
-    if (wait_event) HIP_TRY(c, hipStreamWaitEvent(s, static_cast<hipEvent_t>(wait_event), 0));
-    HIP_TRY(c, stem_silu_gather(c, 0, G, ids, E, (int)E_rows, H, T, F, s));
-    // with a residual the product is added to it: y starts as a copy of the residual unless it is the same buffer
-    if (residual && residual != y)
-      HIP_TRY(c, hipMemcpyAsync(y, residual, (size_t)T * d * 4, hipMemcpyDeviceToDevice, s));
-    HIP_TRY(c, stem_sgemm(c, K_GEMM_DOWN, static_cast<const float*>(H), F, 1, static_cast<const float*>(W_down), F,
-                          1, static_cast<float*>(y), (int)T, d, F, residual ? 1 : 0, s));
+    GemmF32Args a = {};
+    a.A = static_cast<const float*>(x); a.lda = d;
+    a.B = static_cast<const float*>(W_gate); a.ldb = d;
+    a.M = (int)T; a.N = F; a.K = d; a.C = static_cast<float*>(save_G);
+    if (!wait_event) {
+      a.ids = ids; a.E = static_cast<const float*>(E); a.E_rows = (int)E_rows; a.flag = c->flag;
+      a.out0 = static_cast<float*>(H);
+      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_GATE, OP_KC, OP_KC, EPI_GATE, a, s));
+    } else {
+      if (!a.C) a.C = static_cast<float*>(c->dG_ws);
+      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_GATE_PLAIN, OP_KC, OP_KC, EPI_F32, a, s));
+      HIP_TRY(c, hipStreamWaitEvent(s, static_cast<hipEvent_t>(wait_event), 0));
+      HIP_TRY(c, stem_silu_gather(c, 0, a.C, ids, E, (int)E_rows, H, T, F, s));
+    }
+    GemmF32Args b = {};
+    b.A = static_cast<const float*>(H); b.lda = F;
+    b.B = static_cast<const float*>(W_down); b.ldb = F;
+    b.M = (int)T; b.N = d; b.K = F; b.C = static_cast<float*>(y); b.add = static_cast<const float*>(residual);
+    HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DOWN, OP_KC, OP_KC, EPI_F32, b, s));
   }
   return STEM_OK;
 }
@@ -407,18 +415,33 @@ stem_status stem_ffn_backward(stem_ctx* c, const void* dy, const void* x, const 
     }
   } else {
     const float* dyf = static_cast<const float*>(dy);
-    const float* Hf = static_cast<const float*>(H);
-    const float* Wg = static_cast<const float*>(W_gate);
-    const float* Wd = static_cast<const float*>(W_down);
-    float* dH = static_cast<float*>(c->dH_ws);
     float* dG = static_cast<float*>(c->dG_ws);
-    HIP_TRY(c, stem_sgemm(c, K_GEMM_DH, dyf, d, 1, Wd, 1, F, dH, (int)T, F, d, 0, s));
-    HIP_TRY(c, stem_dh_epilogue_f32(c, dH, static_cast<const float*>(saved_G), ids, static_cast<const float*>(E),
-                                    (int)E_rows, static_cast<float*>(dU), dG, T, F, s));
-    HIP_TRY(c, stem_sgemm(c, K_GEMM_DWDOWN, dyf, 1, d, Hf, 1, F, dW_down, d, F, (int)T, accumulate, s));
-    if (dx) HIP_TRY(c, stem_sgemm(c, K_GEMM_DX, dG, F, 1, Wg, 1, d, static_cast<float*>(dx), (int)T, d, F, 0, s));
-    HIP_TRY(c, stem_sgemm(c, K_GEMM_DWGATE, dG, 1, F, static_cast<const float*>(x), 1, d, dW_gate, F, d, (int)T,
-                          accumulate, s));
+    {  // dH = dy W_down, fused into dU and dG
+      GemmF32Args a = {};
+      a.A = dyf; a.lda = d; a.B = static_cast<const float*>(W_down); a.ldb = F;
+      a.M = (int)T; a.N = F; a.K = d;
+      a.ids = ids; a.E = static_cast<const float*>(E); a.E_rows = (int)E_rows; a.flag = c->flag;
+      a.inG = static_cast<const float*>(saved_G); a.out0 = static_cast<float*>(dU); a.out1 = dG;
+      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DH, OP_KC, OP_MC, EPI_DH, a, s));
+    }
+    {  // dW_down[d,F] = dy^T H
+      GemmF32Args a = {};
+      a.A = dyf; a.lda = d; a.B = static_cast<const float*>(H); a.ldb = F;
+      a.M = d; a.N = F; a.K = (int)T; a.C = dW_down; a.add = accumulate ? dW_down : nullptr;
+      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, a, s));
+    }
+    if (dx) {  // dx = dG W_gate
+      GemmF32Args a = {};
+      a.A = dG; a.lda = F; a.B = static_cast<const float*>(W_gate); a.ldb = d;
+      a.M = (int)T; a.N = d; a.K = F; a.C = static_cast<float*>(dx);
+      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DX, OP_KC, OP_MC, EPI_F32, a, s));
+    }
+    {  // dW_gate[F,d] = dG^T x
+      GemmF32Args a = {};
+      a.A = dG; a.lda = F; a.B = static_cast<const float*>(x); a.ldb = d;
+      a.M = F; a.N = d; a.K = (int)T; a.C = dW_gate; a.add = accumulate ? dW_gate : nullptr;
+      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, a, s));
+    }
   }
   return STEM_OK;
 }

@@ -1,61 +1,8 @@
 // fp32 path of the STEM layer (small exactness-oriented runs) and the stand-alone
-// element-wise kernels: H = SiLU(G) * E[ids] and the dU / dG products of backward.
+// element-wise kernel H = SiLU(G) * E[ids].
 #include "stem_internal.h"
 
 namespace {
-
-// C[m,n] (+)= sum_k A[m*sam + k*sak] * B[n*sbn + k*sbk]; 64x64 tile, 16-wide K step,
-// 256 threads each owning a 4x4 block.  Arbitrary strides cover all six products.
-__global__ __launch_bounds__(256) void sgemm_kernel(const float* __restrict__ A, int64_t sam, int64_t sak,
-                                                    const float* __restrict__ B, int64_t sbn, int64_t sbk,
-                                                    float* __restrict__ C, int M, int N, int K, int accumulate) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int e = tid; e < 64 * 16; e += 256) {
-      // index so that the contiguous direction of each operand is the fast one
-      int r, k;
-      if (sak == 1) { k = e & 15; r = e >> 4; } else { r = e & 63; k = e >> 6; }
-      float a = 0.f;
-      if (m0 + r < M && k0 + k < K) a = A[(int64_t)(m0 + r) * sam + (int64_t)(k0 + k) * sak];
-      As[k][r] = a;
-      if (sbk == 1) { k = e & 15; r = e >> 4; } else { r = e & 63; k = e >> 6; }
-      float b = 0.f;
-      if (n0 + r < N && k0 + k < K) b = B[(int64_t)(n0 + r) * sbn + (int64_t)(k0 + k) * sbk];
-      Bs[k][r] = b;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float* c = C + (int64_t)m * N + n;
-      *c = accumulate ? (*c + acc[i][j]) : acc[i][j];
-    }
-  }
-}
 
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.0f / (1.0f + expf(-z)); }
 __device__ __forceinline__ int checked_id(const int32_t* ids, int64_t t, int E_rows, int32_t* flag) {
@@ -65,6 +12,184 @@ __device__ __forceinline__ int checked_id(const int32_t* ids, int64_t t, int E_r
     id = id < 0 ? 0 : E_rows - 1;
   }
   return id;
+}
+
+// ---- fp32 products on the matrix cores -------------------------------------------------------------
+// C[m,n] = sum_k Aop[m,k] * Bop[n,k] with v_mfma_f32_32x32x2_f32 (full fp32 products and sums).  Operands are
+// K-contiguous ([rows,K], OP_KC) or rows-contiguous ([K,rows], OP_MC); dimensions are multiples of 4 except the
+// token count, so every 16-byte piece is whole or absent.
+//
+// Workgroup = 4 wavefronts and a TS x TS tile.  TS = 64: each wavefront a 32x32 quadrant, K in tiles of 32.
+// TS = 32: all four share the 32x32 tile and take a quarter of each 64-wide K tile, summed through LDS in a fixed
+// order; four times the workgroups, and a quarter of the serial chain of MFMAs (64 cycles each), which is what a
+// small product waits for.  Tiles travel global -> registers -> LDS, four K tiles in flight in registers (a short K
+// range is requested whole before anything waits), two stages in LDS, one barrier per K tile.
+// MFMA j of a group of 8 k takes k = 4 h + j from lane half h, for both operands alike, so a lane's four values of a
+// K-contiguous operand are one 16-byte LDS read; those of a rows-contiguous operand are four 4-byte reads.
+// The element-wise part of the layer runs in the epilogue, on rows read back from LDS.
+//
+// Against a 64x64 tile of scalar FMAs on 4-byte loads with nothing in flight across barriers, plus separate
+// element-wise kernels: d_model 64, d_ff 256, 128 tokens 13-47 us -> 4-5 us per product; d_model 256, d_ff 1024, 1000 tokens
+// 55-215 us -> 12-15 us.
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+
+template <int TS, int LOP>
+struct TileF32 {
+  static constexpr int KT = TS == 64 ? 32 : 64;     // K tile: 8 KB of one operand either way
+  static constexpr int ITEMS = 2;                   // 16-byte pieces per thread and K tile
+  const float* p;                                   // the piece's address at K tile 0
+  int64_t step;                                     // elements from one K tile to the next
+  int64_t dist;                                     // from piece 0 to piece 1
+  uint32_t lds0, lds1;
+  int k_of[ITEMS];
+  bool in[ITEMS];
+  __device__ __forceinline__ void init(const float* base, int64_t ld, int rows, int row0, int tid) {
+    if (LOP == OP_KC) {
+      constexpr int CH = KT / 4;
+      const int c = tid % CH, r = tid / CH;
+      constexpr int RSTEP = 256 / CH;
+      p = base + (int64_t)(row0 + r) * ld + c * 4;
+      step = KT;
+      dist = (int64_t)RSTEP * ld;
+      k_of[0] = k_of[1] = c * 4;
+      in[0] = row0 + r < rows;
+      in[1] = row0 + r + RSTEP < rows;
+      lds0 = slot(r, c);
+      lds1 = slot(r + RSTEP, c);
+    } else {
+      constexpr int CH = TS / 4;
+      const int c = tid % CH, k = tid / CH;
+      constexpr int KSTEP = 256 / CH;
+      p = base + (int64_t)k * ld + row0 + c * 4;
+      step = (int64_t)KT * ld;
+      dist = (int64_t)KSTEP * ld;
+      k_of[0] = k;
+      k_of[1] = k + KSTEP;
+      in[0] = in[1] = row0 + c * 4 < rows;
+      lds0 = (uint32_t)(k * TS + c * 4) * 4;
+      lds1 = (uint32_t)((k + KSTEP) * TS + c * 4) * 4;
+    }
+  }
+  // K-contiguous: 16-byte piece c of row r; the swizzle spreads a fragment read's 16 rows over all banks
+  static __device__ __forceinline__ uint32_t slot(int r, int c) {
+    return (uint32_t)(r * KT * 4 + ((c ^ (TS == 64 ? (r >> 1) & 7 : r & 15)) << 4));
+  }
+  __device__ __forceinline__ void load(int t, int K, f32x4_t (&v)[ITEMS]) const {
+    const float* q = p + t * step;
+    v[0] = v[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (in[0] && t * KT + k_of[0] < K) v[0] = *reinterpret_cast<const f32x4_t*>(q);
+    if (in[1] && t * KT + k_of[1] < K) v[1] = *reinterpret_cast<const f32x4_t*>(q + dist);
+  }
+  __device__ __forceinline__ void store(char* lds, const f32x4_t (&v)[ITEMS]) const {
+    *reinterpret_cast<f32x4_t*>(lds + lds0) = v[0];
+    *reinterpret_cast<f32x4_t*>(lds + lds1) = v[1];
+  }
+  // the lane's four k of group g (8 k of the tile), row `row`
+  static __device__ __forceinline__ f32x4_t frag(const char* lds, int row, int half, int g) {
+    if (LOP == OP_KC) return *reinterpret_cast<const f32x4_t*>(lds + slot(row, g * 2 + half));
+    f32x4_t v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float*>(lds + ((g * 8 + half * 4 + j) * TS + row) * 4);
+    return v;
+  }
+};
+
+template <int TS, int LA, int LB, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args p) {
+  typedef TileF32<TS, LA> TA;
+  typedef TileF32<TS, LB> TB;
+  constexpr int KT = TA::KT, STAGE = 2 * TS * KT * 4;        // A and B of one K tile: 16 KB
+  constexpr int DEPTH = 4;
+  constexpr int PITCH = TS + 4;                              // epilogue row in LDS (floats)
+  constexpr int PARTS = TS == 64 ? 1 : 4;                    // K quarters to sum
+  constexpr int EPI_BYTES = PARTS * TS * PITCH * 4;
+  __shared__ __attribute__((aligned(16))) char smem[EPI_BYTES > 2 * STAGE ? EPI_BYTES : 2 * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ntn = (p.N + TS - 1) / TS;
+  const int tm = blockIdx.x / ntn, tn = blockIdx.x - tm * ntn;
+  const int m0 = tm * TS, n0 = tn * TS;
+  const int wm = TS == 64 ? (wave >> 1) * 32 : 0, wn = TS == 64 ? (wave & 1) * 32 : 0;
+  const int r = lane & 31, half = lane >> 5;
+  TA ta;
+  TB tb;
+  ta.init(p.A, p.lda, p.M, m0, tid);
+  tb.init(p.B, p.ldb, p.N, n0, tid);
+  f32x16_t acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  f32x4_t ra[DEPTH][2], rb[DEPTH][2];
+  const int nk = (p.K + KT - 1) / KT;
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) {
+    ta.load(d, p.K, ra[d]);
+    tb.load(d, p.K, rb[d]);
+  }
+  for (int t0 = 0; t0 < nk; t0 += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      if (t0 + d < nk) {
+        char* st = smem + (d & 1) * STAGE;
+        ta.store(st, ra[d]);
+        tb.store(st + TS * KT * 4, rb[d]);
+        ta.load(t0 + d + DEPTH, p.K, ra[d]);
+        tb.load(t0 + d + DEPTH, p.K, rb[d]);
+        __syncthreads();
+        const int g0 = TS == 64 ? 0 : wave * 2, gn = TS == 64 ? 4 : 2;
+#pragma unroll
+        for (int g = 0; g < gn; ++g) {
+          const f32x4_t fa = TA::frag(st, wm + r, half, g0 + g);
+          const f32x4_t fb = TB::frag(st + TS * KT * 4, wn + r, half, g0 + g);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j], fa[j], acc, 0, 0, 0);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  // lane holds, for row r of its 32x32 piece, columns 8 g + 4 half .. + 3
+  {
+    float* o = reinterpret_cast<float*>(smem) + (TS == 64 ? 0 : wave * TS * PITCH) + (wm + r) * PITCH + wn + half * 4;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) *reinterpret_cast<f32x4_t*>(o + g * 8) = f32x4_t{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < TS * TS / 1024; ++it) {
+    constexpr int LPR = TS / 4;
+    const int row = it * (256 / LPR) + tid / LPR, col = (tid % LPR) * 4;
+    const int m = m0 + row, n = n0 + col;
+    if (m >= p.M || n >= p.N) continue;
+    const float* src = reinterpret_cast<const float*>(smem) + row * PITCH + col;
+    f32x4_t c = *reinterpret_cast<const f32x4_t*>(src);
+#pragma unroll
+    for (int q = 1; q < PARTS; ++q) c += *reinterpret_cast<const f32x4_t*>(src + q * TS * PITCH);
+    const int64_t o = (int64_t)m * p.N + n;
+    if (EPI == EPI_F32) {
+      if (p.add) c += *reinterpret_cast<const f32x4_t*>(p.add + o);   // may be C itself: read before it is written
+      *reinterpret_cast<f32x4_t*>(p.C + o) = c;
+    } else {
+      const int id = checked_id(p.ids, m, p.E_rows, p.flag);
+      const f32x4_t e = *reinterpret_cast<const f32x4_t*>(p.E + (int64_t)id * p.N + n);
+      f32x4_t x, y;
+      if (EPI == EPI_GATE) {        // G (optional) and H = SiLU(G) * E
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = c[q] * sigmoid_f(c[q]) * e[q];
+        if (p.C) *reinterpret_cast<f32x4_t*>(p.C + o) = c;
+        *reinterpret_cast<f32x4_t*>(p.out0 + o) = x;
+      } else {                      // dU = dH * SiLU(G), dG = dH * E * SiLU'(G)
+        const f32x4_t g = *reinterpret_cast<const f32x4_t*>(p.inG + o);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float s = sigmoid_f(g[q]);
+          x[q] = c[q] * (g[q] * s);
+          y[q] = c[q] * e[q] * (s * (1.0f + g[q] * (1.0f - s)));
+        }
+        *reinterpret_cast<f32x4_t*>(p.out0 + o) = x;
+        *reinterpret_cast<f32x4_t*>(p.out1 + o) = y;
+      }
+    }
+  }
 }
 
 // fp32: one thread per 4 features of one token.
@@ -117,32 +242,6 @@ __global__ __launch_bounds__(256) void silu_gather_bf16_kernel(const bf16_t* __r
   }
 }
 
-__global__ void dh_epilogue_f32_kernel(const float* __restrict__ dH, const float* __restrict__ G,
-                                       const int32_t* __restrict__ ids, const float* __restrict__ E,
-                                       int E_rows, float* __restrict__ dU, float* __restrict__ dG, int64_t T,
-                                       int F, int32_t* flag) {
-  const int F4 = F >> 2;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= T * F4) return;
-  const int64_t t = i / F4;
-  const int c = (int)(i - t * F4) * 4;
-  const int id = checked_id(ids, t, E_rows, flag);
-  const float4 dh4 = *reinterpret_cast<const float4*>(dH + t * F + c);
-  const float4 g4 = *reinterpret_cast<const float4*>(G + t * F + c);
-  const float4 e4 = *reinterpret_cast<const float4*>(E + (int64_t)id * F + c);
-  const float dh[4] = {dh4.x, dh4.y, dh4.z, dh4.w}, g[4] = {g4.x, g4.y, g4.z, g4.w};
-  const float e[4] = {e4.x, e4.y, e4.z, e4.w};
-  float du[4], dg[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float s = sigmoid_f(g[q]);
-    du[q] = dh[q] * (g[q] * s);
-    dg[q] = dh[q] * e[q] * (s * (1.0f + g[q] * (1.0f - s)));
-  }
-  *reinterpret_cast<float4*>(dU + t * F + c) = make_float4(du[0], du[1], du[2], du[3]);
-  *reinterpret_cast<float4*>(dG + t * F + c) = make_float4(dg[0], dg[1], dg[2], dg[3]);
-}
-
 }  // namespace
 
 // Zero fill by a kernel rather than hipMemsetAsync, so that every call of the library can be recorded
@@ -158,12 +257,25 @@ hipError_t stem_fill_zero(void* p, size_t bytes, hipStream_t s) {   // bytes is 
   return hipGetLastError();
 }
 
-hipError_t stem_sgemm(stem_ctx* ctx, int kid, const float* A, int64_t sam, int64_t sak, const float* B,
-                      int64_t sbn, int64_t sbk, float* C, int M, int N, int K, int accumulate, hipStream_t s) {
-  if (M <= 0 || N <= 0) return hipSuccess;
+template <int LA, int LB, int EPI>
+static void launch_f32(const GemmF32Args& p, hipStream_t s) {
+  // 64x64 tiles once they fill the chip (gate / down product, us, 64x64 and 32x32 tiles: 128 tokens of 64 x 256
+  // 8.0, 11.0 and 6.6, 6.8; 1000 of 256 x 1024 15.3, 29.8 and 13.6, 14.7; 1000 of 512 x 2048 32.7, 56.0 and 33.5, 33.1;
+  // 4096 of 1024 x 2048 182, 174 and 190, 183)
+  const int64_t t64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64), t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32);
+  if (t64 >= 256) hipLaunchKernelGGL((gemm_f32_kernel<64, LA, LB, EPI>), dim3((unsigned)t64), dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((gemm_f32_kernel<32, LA, LB, EPI>), dim3((unsigned)t32), dim3(256), 0, s, p);
+}
+
+hipError_t stem_gemm_f32(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmF32Args& p, hipStream_t s) {
+  if (p.M <= 0 || p.N <= 0) return hipSuccess;
   ProfScope ps(ctx, kid, s);
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  hipLaunchKernelGGL(sgemm_kernel, grid, dim3(256), 0, s, A, sam, sak, B, sbn, sbk, C, M, N, K, accumulate);
+  if (la == OP_KC && lb == OP_KC && epi == EPI_F32) launch_f32<OP_KC, OP_KC, EPI_F32>(p, s);
+  else if (la == OP_KC && lb == OP_KC && epi == EPI_GATE) launch_f32<OP_KC, OP_KC, EPI_GATE>(p, s);
+  else if (la == OP_KC && lb == OP_MC && epi == EPI_F32) launch_f32<OP_KC, OP_MC, EPI_F32>(p, s);
+  else if (la == OP_KC && lb == OP_MC && epi == EPI_DH) launch_f32<OP_KC, OP_MC, EPI_DH>(p, s);
+  else if (la == OP_MC && lb == OP_MC && epi == EPI_F32) launch_f32<OP_MC, OP_MC, EPI_F32>(p, s);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -180,16 +292,5 @@ hipError_t stem_silu_gather(stem_ctx* ctx, int is_bf16, const void* G, const int
     hipLaunchKernelGGL(silu_gather_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                        (const float*)G, ids, (const float*)E, E_rows, (float*)H, T, F, ctx->flag);
   }
-  return hipGetLastError();
-}
-
-hipError_t stem_dh_epilogue_f32(stem_ctx* ctx, const float* dH, const float* G, const int32_t* ids,
-                                const float* E, int E_rows, float* dU, float* dG, int64_t T, int F,
-                                hipStream_t s) {
-  if (T <= 0) return hipSuccess;
-  ProfScope ps(ctx, K_DH_EPILOGUE, s);
-  const int64_t n = T * (F / 4);
-  hipLaunchKernelGGL(dh_epilogue_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dH, G, ids,
-                     E, E_rows, dU, dG, T, F, ctx->flag);
   return hipGetLastError();
 }

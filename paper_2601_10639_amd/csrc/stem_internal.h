@@ -17,7 +17,6 @@ enum StemKernelId {
   K_GEMM_DWDOWN,     // dWd = dY^T H
   K_GEMM_DWGATE,     // dWg = dG^T X
   K_SILU_GATHER,     // H = SiLU(G) * E[ids] (stand-alone)
-  K_DH_EPILOGUE,     // fp32 path: dU, dG from dH
   K_SORT_COUNT,
   K_SORT_SCAN,
   K_SORT_SCATTER,
@@ -47,7 +46,6 @@ struct stem_ctx {
   // scratch, all device memory unless noted
   void* H_ws;            // [max_tokens, F] context dtype
   void* dG_ws;           // [max_tokens, F] context dtype
-  void* dH_ws;           // [max_tokens, F] fp32, STEM_F32 only
   void* Up_ws;           // [max_tokens, F] bf16, allocated by the first stem_ffn_up_* call
   float* splitk_ws;      // fp32 partial products of GEMMs whose K range is cut into slices
   size_t splitk_bytes;   // its size; no launch splits beyond it
@@ -178,18 +176,27 @@ int stem_gemm_skinny_ksplit(int M, int N, int K);
 hipError_t stem_gemm_skinny_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s);
 
 // ---- fp32 path and element-wise kernels (kernels_f32.hip) -------------------------
-// C[m,n] (+)= sum_k A[m*sam + k*sak] * B[n*sbn + k*sbk]
-hipError_t stem_sgemm(stem_ctx* ctx, int kid, const float* A, int64_t sam, int64_t sak, const float* B,
-                      int64_t sbn, int64_t sbk, float* C, int M, int N, int K, int accumulate, hipStream_t s);
-// out[c,r] = in[r,c] (bf16), leading dimension ldo, zero padding beyond R
+struct GemmF32Args {
+  const float* A; // M-side operand, leading dimension lda
+  const float* B; // N-side operand
+  int64_t lda, ldb;
+  int M, N, K;
+  float* C;          // EPI_F32: output; EPI_GATE: G, may be null; ld = N
+  const float* add;  // EPI_F32: added to the product (C itself to accumulate, a residual), may be null
+  const int32_t* ids;
+  const float* E;
+  int E_rows;
+  const float* inG;  // EPI_DH
+  float* out0;       // EPI_GATE: H; EPI_DH: dU
+  float* out1;       // EPI_DH: dG
+  int32_t* flag;
+};
+// operand kinds and epilogues (EPI_F32, EPI_GATE, EPI_DH) as for the bf16 products
+hipError_t stem_gemm_f32(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmF32Args& p, hipStream_t s);
 hipError_t stem_fill_zero(void* p, size_t bytes, hipStream_t s);   // a kernel, not a memset node
 // H = SiLU(G) * E[ids]; is_bf16 selects the element type of G, E, H
 hipError_t stem_silu_gather(stem_ctx* ctx, int is_bf16, const void* G, const int32_t* ids, const void* E,
                             int E_rows, void* H, int64_t T, int F, hipStream_t s);
-// fp32: dU = dH * SiLU(G); dG = dH * E[ids] * SiLU'(G)
-hipError_t stem_dh_epilogue_f32(stem_ctx* ctx, const float* dH, const float* G, const int32_t* ids,
-                                const float* E, int E_rows, float* dU, float* dG, int64_t T, int F,
-                                hipStream_t s);
 
 // ---- table gradient (embed_grad.hip) ----------------------------------------------
 // Device scratch of the sort and the segmented sum: a context's own buffers, or pieces of the

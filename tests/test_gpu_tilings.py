@@ -49,3 +49,32 @@ def test_bf16_products_on_every_tiling(T, d, F, up):
     errs = {k: Hn.max_rel(out[k].float().cpu(), v) for k, v in ref.items()}
     assert all(v <= Hn.TOL["bf16"] for v in errs.values()), errs
     ctx.close()
+
+
+@pytest.mark.parametrize("T,d,F", [
+    (1030, 1028, 1028),   # every product on 64x64 tiles, ragged in M, N and K
+    (1030, 36, 1028),     # forward and dH on 64x64 tiles with K of one tile and a bit; dx, weight gradients on 32x32
+    (33, 4, 8),           # K of one 16-byte piece, one row in the last tile
+])
+def test_f32_products_on_both_tilings(T, d, F):
+    s = inputs.StemShape("f32-tilings", d, F, 300, 1, T, "f32")
+    inp = inputs.layer_inputs(s, seed=63, device=DEV, tokens=T)
+    ctx = Hn.make_ctx(s, T)
+    f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
+    ids = inp["ids"].cpu().numpy()
+    out = Hn.hip_forward_backward(ctx, inp)
+    y2 = torch.empty_like(out["y"])
+    L.stem_ffn_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"], y2)   # G and H not saved
+    acc = {k: out[k].clone() for k in ("dW_gate", "dW_down")}
+    dU2, dx2 = torch.empty_like(out["dU"]), torch.empty_like(out["dx"])
+    L.stem_ffn_backward(ctx, inp["dy"], inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"], out["G"], None, dx2,
+                        acc["dW_gate"], acc["dW_down"], dU2, accumulate=True)
+    L.stem_sync_status(ctx)
+    y, fw = O.ffn_forward(f64["x"], ids, f64["W_gate"], f64["W_down"], f64["E"])
+    bw = O.ffn_backward(f64["dy"], f64["x"], ids, f64["W_gate"], f64["W_down"], f64["E"])
+    ref = {"y": y, "G": fw["g"], "H": fw["h"], "dx": bw["dx"], "dU": bw["dU"], "dW_gate": bw["dW_gate"], "dW_down": bw["dW_down"]}
+    errs = {k: Hn.max_rel(out[k].cpu(), v) for k, v in ref.items()}
+    errs.update({k + " added": Hn.max_rel(v.cpu(), 2 * ref[k]) for k, v in acc.items()})
+    assert all(v <= Hn.TOL["f32"] for v in errs.values()), errs
+    assert torch.equal(out["y"], y2) and torch.equal(out["dU"], dU2) and torch.equal(out["dx"], dx2)
+    ctx.close()
