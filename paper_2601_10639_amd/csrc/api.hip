@@ -64,6 +64,7 @@ void release(stem_ctx* c) {
   (void)hipDeviceSynchronize();
   (void)hipFree(c->H_ws); (void)hipFree(c->dG_ws);
   (void)hipFree(c->splitk_ws);
+  (void)hipFree(c->tickets);
   (void)hipFree(c->Up_ws);
   for (int i = 0; i < 2; ++i) { (void)hipFree(c->sort_keys[i]); (void)hipFree(c->sort_vals[i]); }
   (void)hipFree(c->sort_counts); (void)hipFree(c->seg_of); (void)hipFree(c->seg_part);
@@ -168,6 +169,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
     // partial products of up to 8 K slices of a [T,d] or [d,F] output
     c->splitk_bytes = std::min<size_t>(STEM_SPLITK_WS_MAX, (size_t)8 * 4 * desc->d_model * std::max<int64_t>({max_tokens, desc->d_ff, 1}));
     ok(hipMalloc(reinterpret_cast<void**>(&c->splitk_ws), c->splitk_bytes));
+    ok(dmalloc(&c->tickets, STEM_TICKETS));
   }
   for (int i = 0; i < 2; ++i) {
     ok(dmalloc(&c->sort_keys[i], (size_t)max_tokens));
@@ -184,6 +186,10 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->uniq_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->remap_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+  if (e == hipSuccess && c->tickets) {
+    ok(stem_fill_zero(c->tickets, STEM_TICKETS * 4, c->side));
+    ok(hipStreamSynchronize(c->side));
+  }
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
   for (int i = 0; i < 2; ++i) ok(hipEventCreateWithFlags(&c->pack_done[i], hipEventDisableTiming));
   c->slot = static_cast<int32_t*>(malloc((size_t)desc->vocab * 4));
@@ -266,24 +272,27 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;
     a.M = (int)T; a.N = F; a.K = d;
     a.ids = ids; a.E = static_cast<const bf16_t*>(E); a.E_rows = (int)E_rows; a.flag = c->flag;
-    // A decode-sized call (a few hundred tokens) takes the few-row kernel: 128x64 tiles, the down
-    // product split along K so that both launches fill the chip.
-    const bool few = T <= STEM_SKINNY_MAX_M;
+    // A decode-sized product takes the decode kernel while one round of its workgroups covers it, then the few-row
+    // kernel (128x64 tiles, the down product split along K so that both launches fill the chip).
+    const bool few = T <= 512 && stem_gemm_skinny_fits((int)T, F);
+    const bool decode_gate = stem_gemm_decode_fits((int)T, F, d), decode_down = stem_gemm_decode_fits((int)T, d, F);
     GemmArgs b = {};
     b.A = static_cast<const bf16_t*>(H); b.lda = F;
     b.B = static_cast<const bf16_t*>(W_down); b.ldb = F;
     b.M = (int)T; b.N = d; b.K = F; b.C = y; b.flag = c->flag;
     b.residual = static_cast<const bf16_t*>(residual);
-    b.ws = c->splitk_ws; b.ws_bytes = c->splitk_bytes;
+    b.ws = c->splitk_ws; b.ws_bytes = c->splitk_bytes; b.tickets = c->tickets;
     const int down_epi = residual ? EPI_BF16_RES : EPI_BF16;
     if (!wait_event) {
       a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);
-      if (few) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
+      if (decode_gate) HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
+      else if (few) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
       else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE, OP_KC, OP_KC, EPI_GATE, a, s));
     } else {
       void* G = save_G ? save_G : c->dG_ws;
       a.C = G;
-      if (few) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE_PLAIN, EPI_BF16, a, s));
+      if (decode_gate) HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_GATE_PLAIN, EPI_BF16, a, s));
+      else if (few) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE_PLAIN, EPI_BF16, a, s));
       else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE_PLAIN, OP_KC, OP_KC, EPI_BF16, a, s));
       if (wait_event == c->ready && c->pf_chunks > 1 && c->pf_T == T) {
         // Rows arrive in order of first use: run the gather and the down product chunk by chunk,
@@ -305,7 +314,9 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
       HIP_TRY(c, hipStreamWaitEvent(s, static_cast<hipEvent_t>(wait_event), 0));
       HIP_TRY(c, stem_silu_gather(c, 1, G, ids, E, (int)E_rows, H, T, F, s));
     }
-    if (few) {
+    if (decode_down) {
+      HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_DOWN, EPI_BF16, b, s));
+    } else if (few) {
       b.ksplit = stem_gemm_skinny_ksplit(b.M, b.N, b.K);
       if ((size_t)b.ksplit * b.M * b.N * 4 > c->splitk_bytes) b.ksplit = 1;
       HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_DOWN, b.ksplit > 1 ? EPI_SPLITK : EPI_BF16, b, s));

@@ -278,6 +278,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 
 }  // namespace
 
+bool stem_gemm_skinny_fits(int M, int F) {
+  return M <= 256 || (M <= 512 && ((M + SBM - 1) / SBM) * ((F + SBN - 1) / SBN) <= 256);
+}
+
 int stem_gemm_skinny_ksplit(int M, int N, int K) {
   const int tiles = ((M + SBM - 1) / SBM) * ((N + SBN - 1) / SBN);
   const int nk = (K + SBK - 1) / SBK;

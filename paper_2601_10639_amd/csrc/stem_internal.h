@@ -49,6 +49,7 @@ struct stem_ctx {
   void* Up_ws;           // [max_tokens, F] bf16, allocated by the first stem_ffn_up_* call
   float* splitk_ws;      // fp32 partial products of GEMMs whose K range is cut into slices
   size_t splitk_bytes;   // its size; no launch splits beyond it
+  int32_t* tickets;      // [STEM_TICKETS] counters of finished K slices per output tile, zero between launches
   int32_t* sort_keys[2]; // [max_tokens]
   int32_t* sort_vals[2]; // [max_tokens]
   int32_t* sort_counts;  // [64 * waves]
@@ -153,19 +154,21 @@ struct GemmArgs {
   int32_t* flag;
   float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
   size_t ws_bytes; // capacity of ws
+  int32_t* tickets; // decode kernel: the context's tickets; null = never split
   int ksplit;      // number of k slices (few-row kernel: EPI_SPLITK; large kernel: chosen by its launcher)
   int kc_skip;     // set by the large kernel itself: elements a K slice starts after the operand's start
-  int mt, nt;      // few-row kernel: tile counts and exact float reciprocals, filled in by the launcher
+  int mt, nt;      // few-row and decode kernels: tile counts and exact float reciprocals, filled in by the launcher
   float inv_mt, inv_per_z;
 };
 
 hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmArgs& a, hipStream_t s);
 
 // ---- few-row bf16 GEMM (gemm_skinny_bf16.hip): both operands K-contiguous, K % 64 == 0 --------
-// 128x64 tiles; used when M is small enough that 256x256 tiles would leave most of the chip idle.
-// Up to 256 rows: at d_model 2048, d_ff 8192 the gate / down products take 17 / 17 us at 128 rows against 23 / 35 on
-// 128x128 tiles, 19 / 21 against 20 / 24 at 256 and 35 / 33 against 26 / 33 at 512.
-#define STEM_SKINNY_MAX_M 256
+// 128x64 tiles; used when M is small enough that larger tiles would leave most of the chip idle: up to 256 rows, and up
+// to 512 while the gate product is one round of its workgroups.  Layer forward, us, this / 128x128 tiles: d_model 2048,
+// d_ff 8192, 256 tokens 42 / 44, 320 tokens 59 / 48, 512 tokens 69 / 56; 1536 x 5120, 384 tokens 41.9 / 42.9, 512 tokens 55 / 44;
+// 1024 x 4096, 320 tokens 26 / 28, 512 tokens 27 / 34.
+bool stem_gemm_skinny_fits(int M, int F);
 #define STEM_SPLITK_WS_MAX ((size_t)64 << 20)   // more is never worth it: beyond it the tiles fill the chip
 // out = bf16(sum of the ksplit fp32 partial products in ws, in slice order (+ residual)); total elements each
 hipError_t stem_splitk_reduce(stem_ctx* ctx, const float* ws, int ksplit, int64_t total, const bf16_t* residual, void* out,
@@ -174,6 +177,12 @@ hipError_t stem_splitk_reduce(stem_ctx* ctx, const float* ws, int ksplit, int64_
 int stem_gemm_skinny_ksplit(int M, int N, int K);
 // epi: EPI_BF16, EPI_GATE, or EPI_SPLITK (a.ksplit slices through a.ws, then summed into a.C)
 hipError_t stem_gemm_skinny_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s);
+
+// ---- decode-sized bf16 GEMM (gemm_decode_bf16.hip): both operands K-contiguous --------------------
+#define STEM_TICKETS 256
+bool stem_gemm_decode_fits(int M, int N, int K);
+// epi: EPI_BF16 (+ residual; split along K through a.ws and a.tickets where that pays) or EPI_GATE
+hipError_t stem_gemm_decode_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s);
 
 // ---- fp32 path and element-wise kernels (kernels_f32.hip) -------------------------
 struct GemmF32Args {

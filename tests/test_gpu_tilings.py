@@ -78,3 +78,37 @@ def test_f32_products_on_both_tilings(T, d, F):
     assert all(v <= Hn.TOL["f32"] for v in errs.values()), errs
     assert torch.equal(out["y"], y2) and torch.equal(out["dU"], dU2) and torch.equal(out["dx"], dx2)
     ctx.close()
+
+
+@pytest.mark.parametrize("T,d,F", [
+    (1, 64, 64),          # one K tile: fewer than wavefronts and than K tiles in flight
+    (16, 192, 4160),      # 32 weight rows, a ragged last one; down: 16 weight rows, 65 K tiles
+    (17, 128, 8192),      # 32 tokens with one in the second fragment; down: 128 K tiles in two slices
+    (33, 64, 4096),       # 64-token tile
+    (129, 1088, 2112),    # 3 x 33 tiles of 64 x 64, ragged both ways
+    (64, 2048, 8256),     # down: 129 K tiles in two slices of 65 and 64
+    (500, 512, 1536),     # eight token tiles, the last ragged
+    (300, 1024, 2624),    # few-row kernel beyond 256 tokens
+])
+def test_decode_products_on_every_tile(T, d, F):
+    V = 300
+    s = inputs.StemShape("decode-tiles", d, F, V, 1, T, "bf16")
+    inp = inputs.layer_inputs(s, seed=65, device=DEV, tokens=T)
+    ctx = Hn.make_ctx(s, T)
+    a = (ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"])
+    e = lambda n: torch.empty(T, n, dtype=torch.bfloat16, device=DEV)  # noqa: E731
+    y, G, H, yr, xr = e(d), e(F), e(F), e(d), inp["x"].clone()
+    L.stem_ffn_forward(*a, y, G, H)
+    L.stem_ffn_forward_residual(*a, inp["x"], yr)
+    L.stem_ffn_forward_residual(ctx, xr, *a[2:], xr, xr)                # in place
+    reps = [torch.empty_like(y) for _ in range(3)]
+    for r in reps:
+        L.stem_ffn_forward(*a, r)
+    L.stem_sync_status(ctx)
+    f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
+    yo, fw = O.ffn_forward(f64["x"], inp["ids"].cpu().numpy(), f64["W_gate"], f64["W_down"], f64["E"])
+    ref = {"y": yo, "G": fw["g"], "H": fw["h"], "yr": f64["x"] + yo}
+    errs = {k: Hn.max_rel(v.float().cpu(), ref[k]) for k, v in (("y", y), ("G", G), ("H", H), ("yr", yr))}
+    assert all(v <= Hn.TOL["bf16"] for v in errs.values()), errs
+    assert torch.equal(yr, xr) and all(torch.equal(r, y) for r in reps)
+    ctx.close()
