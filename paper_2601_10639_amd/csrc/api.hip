@@ -20,7 +20,7 @@ const char* const kKernelNames[K_COUNT_] = {
     "gemm_gate_fused", "gemm_gate_plain", "gemm_down",    "gemm_dh_fused", "gemm_dx",      "gemm_dw_down",
     "gemm_dw_gate",    "silu_gather",      "sort_count",    "sort_scan",    "sort_scatter",
     "sort_fused",      "unique",          "seg_reduce",   "seg_combine",   "sparse_adamw", "row_copy",
-    "splitk_reduce",   "gemm_up",      "gemm_dw_up"};
+    "splitk_reduce",   "gemm_up",      "gemm_dw_up",   "sort_merge"};
 
 #define fail stem_fail
 

@@ -180,49 +180,70 @@ __global__ __launch_bounds__(1024) void unique_kernel(const int32_t* __restrict_
 }
 
 
-// ---- one-workgroup path: sort, unique and run index in a single launch ---------------
-// When bits(V-1) + bits(T-1) <= 32 the pair (id, position) packs into one 32-bit key, so
-// two 64 KB LDS buffers hold the whole problem (T <= 16384).  The passes run over the id
-// bits only; the position bits ride along and make the order total.
-constexpr int FUSED_MAX_T = 16384;
+// ---- sort in LDS ------------------------------------------------------------------------
+// The pair (id, position within the run) packs into one 32-bit key, so two LDS buffers hold a run of ITEMS * 1024
+// keys, sorted by one workgroup.  The passes run over the id bits only; the position bits ride along and make the
+// order total.  What bounds a pass is the instruction issue of one CU (6 ballots and a dozen more instructions per 64
+// keys and round, rounds = ITEMS) and, below, the chain through the barriers; so the kernel comes in the sizes that
+// occur, and a batch beyond the largest is cut into runs sorted side by side and merged by rank (below).
+// Exclusive sum of v over the workgroup's threads in order; wsum: 16 ints of LDS.  The total goes to *total.
+__device__ __forceinline__ int block_exclusive(int v, int* wsum, int lane, int wave, int* total = nullptr) {
+  int inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc, o);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) wsum[wave] = inc;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int t = wsum[w];
+    before += w < wave ? t : 0;
+    all += t;
+  }
+  if (total) *total = all;
+  return before + inc - v;
+}
 
-__global__ __launch_bounds__(1024) void sort_unique_fused_kernel(const int32_t* __restrict__ ids, int T, int V,
-                                                                 int pos_bits, int passes,
-                                                                 int32_t* __restrict__ sorted_ids,
-                                                                 int32_t* __restrict__ perm,
-                                                                 int32_t* __restrict__ uniq_ids,
-                                                                 int32_t* __restrict__ seg_offsets,
-                                                                 int32_t* __restrict__ n_uniq,
-                                                                 int32_t* __restrict__ seg_of, int32_t* flag) {
-  __shared__ uint32_t buf[2][FUSED_MAX_T];
+// RUNS: workgroup b sorts run b (keys [b * ITEMS * 1024, ...)) and writes only sorted_ids and perm (global positions).
+template <int ITEMS, bool RUNS>
+__global__ __launch_bounds__(1024) void sort_lds_kernel(const int32_t* __restrict__ ids, int T, int V, int pos_bits,
+                                                        int passes, int32_t* __restrict__ sorted_ids,
+                                                        int32_t* __restrict__ perm, int32_t* __restrict__ uniq_ids,
+                                                        int32_t* __restrict__ seg_offsets, int32_t* __restrict__ n_uniq,
+                                                        int32_t* __restrict__ seg_of, int32_t* flag) {
+  __shared__ uint32_t buf[2][ITEMS * 1024];
   __shared__ int table[RADIX * SORT_WAVES];  // [digit][wave], scanned in place
-  __shared__ __attribute__((aligned(16))) uint8_t cnt8[SORT_WAVES][RADIX][16];
+  __shared__ __attribute__((aligned(16))) uint8_t cnt8[SORT_WAVES][RADIX][ITEMS < 4 ? 4 : ITEMS];
   __shared__ int wsum[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int per_wave = (T + SORT_WAVES - 1) / SORT_WAVES;      // contiguous keys per wavefront
-  const int w0 = wave * per_wave, w1 = min(T, w0 + per_wave);
+  const int first = RUNS ? blockIdx.x * ITEMS * 1024 : 0;
+  const int n = min(T - first, ITEMS * 1024);
+  const int per_wave = (n + SORT_WAVES - 1) / SORT_WAVES;      // contiguous keys per wavefront
+  const int w0 = wave * per_wave, w1 = min(n, w0 + per_wave);
   const uint32_t pos_mask = (1u << pos_bits) - 1u;
-  constexpr int ITEMS = FUSED_MAX_T / 1024;
   {
     int kv[ITEMS];
 #pragma unroll
-    for (int u = 0; u < ITEMS; ++u) kv[u] = (tid + 1024 * u) < T ? ids[tid + 1024 * u] : 0;
+    for (int u = 0; u < ITEMS; ++u) kv[u] = (tid + 1024 * u) < n ? ids[first + tid + 1024 * u] : 0;
     bool bad = false;
 #pragma unroll
     for (int u = 0; u < ITEMS; ++u) {
       const int i = tid + 1024 * u;
       int k = kv[u];
       if ((unsigned)k >= (unsigned)V) { bad = true; k = k < 0 ? 0 : V - 1; }
-      if (i < T) buf[0][i] = ((uint32_t)k << pos_bits) | (uint32_t)i;
+      if (i < n) buf[0][i] = ((uint32_t)k << pos_bits) | (uint32_t)i;
     }
     if (bad) *flag = 1;
   }
   __syncthreads();
   const uint64_t below = (1ull << lane) - 1ull;
   int cur = 0;
-  // Per pass and wavefront: 16 rounds of 64 keys.  A key's rank among equal digits of its round
+  // Per pass and wavefront: ITEMS rounds of 64 keys.  A key's rank among equal digits of its round
   // comes from ballots; the per-round digit counts go to cnt8[wave][digit][round] (bytes), lane d
-  // then turns digit d's 16 counts into running offsets, so no round waits for the one before.
+  // then turns digit d's counts into running offsets, so no round waits for the one before.
   for (int p = 0; p < passes; ++p) {
     const int shift = pos_bits + p * RADIX_BITS;
     uint32_t key[ITEMS];
@@ -232,7 +253,10 @@ __global__ __launch_bounds__(1024) void sort_unique_fused_kernel(const int32_t* 
       const int i = w0 + r * 64 + lane;
       key[r] = i < w1 ? buf[cur][i] : 0u;
     }
-    *reinterpret_cast<uint4*>(&cnt8[wave][lane][0]) = make_uint4(0, 0, 0, 0);
+    uint32_t* const mine = reinterpret_cast<uint32_t*>(&cnt8[wave][lane][0]);
+#pragma unroll
+    for (int x = 0; x < (ITEMS + 3) / 4; ++x) mine[x] = 0;
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
       const bool valid = (w0 + r * 64 + lane) < w1;
@@ -250,8 +274,9 @@ __global__ __launch_bounds__(1024) void sort_unique_fused_kernel(const int32_t* 
     }
     __builtin_amdgcn_wave_barrier();
     // lane = digit: running offsets over the rounds
-    const uint4 cv = *reinterpret_cast<const uint4*>(&cnt8[wave][lane][0]);
-    const uint32_t cw[4] = {cv.x, cv.y, cv.z, cv.w};
+    uint32_t cw[(ITEMS + 3) / 4];
+#pragma unroll
+    for (int x = 0; x < (ITEMS + 3) / 4; ++x) cw[x] = mine[x];
     int pre[ITEMS];
     int tot = 0;
 #pragma unroll
@@ -261,23 +286,7 @@ __global__ __launch_bounds__(1024) void sort_unique_fused_kernel(const int32_t* 
     }
     table[lane * SORT_WAVES + wave] = tot;
     __syncthreads();
-    {  // exclusive scan of the 1024 table entries, one per thread
-      const int v = table[tid];
-      int inc = v;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-      }
-      if (lane == 63) wsum[wave] = inc;
-      __syncthreads();
-      if (tid == 0) {
-        int c = 0;
-        for (int w = 0; w < 16; ++w) { const int t = wsum[w]; wsum[w] = c; c += t; }
-      }
-      __syncthreads();
-      table[tid] = wsum[wave] + inc - v;
-    }
+    table[tid] = block_exclusive(table[tid], wsum, lane, wave);   // 1024 entries, one per thread
     __syncthreads();
     const int base = table[lane * SORT_WAVES + wave];  // first output slot of (digit = lane, this wavefront)
 #pragma unroll
@@ -289,11 +298,20 @@ __global__ __launch_bounds__(1024) void sort_unique_fused_kernel(const int32_t* 
     __syncthreads();
     cur ^= 1;
   }
-  // Unpack and number the runs, position k = u * 1024 + tid throughout (coalesced in global memory,
-  // conflict-free in LDS; with 16 consecutive positions per thread instead, every LDS access of this
-  // part was a 16-way bank conflict and the part took 14 of the kernel's 47 us).
-  // A position's run index is the number of run heads at or before it, minus one: heads of earlier
-  // (sweep, wavefront) pairs from a scanned table of ballot counts, heads of earlier lanes from the ballot.
+  if (RUNS) {
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u) {
+      const int k = tid + 1024 * u;
+      if (k < n) {
+        sorted_ids[first + k] = (int)(buf[cur][k] >> pos_bits);
+        perm[first + k] = first + (int)(buf[cur][k] & pos_mask);
+      }
+    }
+    return;
+  }
+  // Unpack and number the runs of equal ids, position k = u * 1024 + tid throughout (coalesced in global memory,
+  // conflict-free in LDS).  A position's run index is the number of run heads at or before it, minus one: heads of
+  // earlier (sweep, wavefront) pairs from a scanned table of ballot counts, heads of earlier lanes from the ballot.
   int* cnt = table;                     // [sweep * SORT_WAVES + wave], reused
   uint64_t headmask[ITEMS];
   int idv[ITEMS];
@@ -302,7 +320,7 @@ __global__ __launch_bounds__(1024) void sort_unique_fused_kernel(const int32_t* 
     const int k = tid + 1024 * u;
     bool head = false;
     idv[u] = 0;
-    if (k < T) {
+    if (k < n) {
       const uint32_t key = buf[cur][k];
       const int id = (int)(key >> pos_bits);
       idv[u] = id;
@@ -314,40 +332,97 @@ __global__ __launch_bounds__(1024) void sort_unique_fused_kernel(const int32_t* 
     if (lane == 0) cnt[u * SORT_WAVES + wave] = __popcll(headmask[u]);
   }
   __syncthreads();
-  {  // exclusive scan of the ITEMS * SORT_WAVES = 256 counts by the first four wavefronts
-    int v = 0, inc = 0;
-    if (tid < ITEMS * SORT_WAVES) {
-      v = cnt[tid];
-      inc = v;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-      }
-      if (lane == 63) wsum[wave] = inc;
-    }
-    __syncthreads();
-    if (tid < ITEMS * SORT_WAVES) {
-      int before = 0;
-      for (int w = 0; w < wave; ++w) before += wsum[w];
-      cnt[tid] = before + inc - v;
-      if (tid == ITEMS * SORT_WAVES - 1) {
-        const int total = before + inc;
-        seg_offsets[total] = T;
-        *n_uniq = total;
-      }
+  {
+    int total;
+    const int v = tid < ITEMS * SORT_WAVES ? cnt[tid] : 0;
+    const int before = block_exclusive(v, wsum, lane, wave, &total);
+    if (tid < ITEMS * SORT_WAVES) cnt[tid] = before;
+    if (tid == 0) {
+      seg_offsets[total] = n;
+      *n_uniq = total;
     }
   }
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < ITEMS; ++u) {
     const int k = tid + 1024 * u;
-    if (k < T) {
+    if (k < n) {
       const bool head = (headmask[u] >> lane) & 1ull;
       const int run = cnt[u * SORT_WAVES + wave] + __popcll(headmask[u] & below) + (head ? 0 : -1);
       if (head) { uniq_ids[run] = idv[u]; seg_offsets[run] = k; }
       seg_of[k] = run;
     }
+  }
+}
+
+// ---- larger batches: merge of the sorted runs by rank, then distinct ids and run index ---------------
+// A key's place in the whole order is its place in its own run, plus, of every earlier run, the keys at most as large,
+// plus, of every later run, the keys that are smaller: the merge is stable, needs no passes, and every key finds its
+// place alone, 16 binary searches of L2-resident runs in flight at a time (64 neighbouring keys take nearly the same
+// path through a run, so their loads coalesce).
+constexpr int MERGE_WAYS = 16;
+__global__ __launch_bounds__(256) void merge_runs_kernel(const int32_t* __restrict__ keys, const int32_t* __restrict__ vals,
+                                                         int T, int R, int32_t* __restrict__ sorted_ids,
+                                                         int32_t* __restrict__ perm) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int ic = min(i, T - 1);
+  const int id = keys[ic], val = vals[ic];
+  const int own = ic / R, nr = (T + R - 1) / R;
+  int rank = ic - own * R;
+  for (int q0 = 0; q0 < nr; q0 += MERGE_WAYS) {
+    int pos[MERGE_WAYS], len[MERGE_WAYS];
+#pragma unroll
+    for (int x = 0; x < MERGE_WAYS; ++x) {
+      const int q = q0 + x;
+      pos[x] = 0;
+      len[x] = q < nr && q != own ? min(R, T - q * R) : 0;
+    }
+    for (int step = R; step > 0; step >>= 1) {
+      int k[MERGE_WAYS];
+#pragma unroll
+      for (int x = 0; x < MERGE_WAYS; ++x)
+        k[x] = keys[min(q0 + x, nr - 1) * R + max(min(pos[x] + step, len[x]) - 1, 0)];
+#pragma unroll
+      for (int x = 0; x < MERGE_WAYS; ++x)
+        if (pos[x] + step <= len[x] && k[x] < id + (q0 + x < own ? 1 : 0)) pos[x] += step;
+    }
+#pragma unroll
+    for (int x = 0; x < MERGE_WAYS; ++x) rank += pos[x];
+  }
+  if (i < T) {
+    sorted_ids[rank] = id;
+    perm[rank] = val;
+  }
+}
+
+// Distinct ids, run offsets and run index of 1024 sorted positions per workgroup, which counts the run heads before its
+// own itself (T / 2 reads on average, from L2) instead of waiting for its predecessors.
+__global__ __launch_bounds__(1024) void unique_blocks_kernel(const int32_t* __restrict__ sorted, int T,
+                                                             int32_t* __restrict__ uniq_ids,
+                                                             int32_t* __restrict__ seg_offsets,
+                                                             int32_t* __restrict__ n_uniq, int32_t* __restrict__ seg_of) {
+  __shared__ int wsum[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int k0 = blockIdx.x * 1024, k = k0 + tid;
+  int key = 0;
+  bool head = false;
+  if (k < T) {
+    key = sorted[k];
+    head = k == 0 || sorted[k - 1] != key;
+  }
+  int mine = 0;
+#pragma unroll 8
+  for (int j = tid; j < k0; j += 1024) mine += j == 0 || sorted[j] != sorted[j - 1];
+  int earlier, here;
+  block_exclusive(mine, wsum[0], lane, wave, &earlier);
+  const int run = earlier + block_exclusive(head ? 1 : 0, wsum[1], lane, wave, &here) - (head ? 0 : 1);
+  if (k < T) {
+    if (head) { uniq_ids[run] = key; seg_offsets[run] = k; }
+    seg_of[k] = run;
+  }
+  if (tid == 0 && k0 + 1024 >= T) {
+    seg_offsets[earlier + here] = T;
+    *n_uniq = earlier + here;
   }
 }
 
@@ -543,10 +618,42 @@ hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t
                             int32_t* n_uniq, hipStream_t s) {
   const int passes = (bits_for(V) + RADIX_BITS - 1) / RADIX_BITS;
   const int pos_bits = bits_for((int)T);
-  if (T <= FUSED_MAX_T && bits_for(V) + pos_bits <= 32) {
+  const int vbits = bits_for(V);
+  // One workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 25 in a graph against 19).
+  // Then runs of 1024, while their number is one group of the merge's searches, and runs of 4096: 16384 ids 29 and 36 us
+  // (one workgroup 43, the digit passes below 140), 32768 ids 40 and 38, 65536 ids 62 and 42 (digit passes 182).  The
+  // digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
+  // (262144 ids: 130 us against 640).
+  if (T <= 4096 && vbits + pos_bits <= 32) {
     ProfScope ps(ctx, K_SORT_FUSED, s);
-    hipLaunchKernelGGL(sort_unique_fused_kernel, dim3(1), dim3(1024), 0, s, ids, (int)T, V, pos_bits, passes,
-                       sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
+    if (T <= 1024)
+      hipLaunchKernelGGL((sort_lds_kernel<1, false>), dim3(1), dim3(1024), 0, s, ids, (int)T, V, pos_bits, passes,
+                         sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
+    else
+      hipLaunchKernelGGL((sort_lds_kernel<4, false>), dim3(1), dim3(1024), 0, s, ids, (int)T, V, pos_bits, passes,
+                         sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
+    return hipGetLastError();
+  }
+  const int items = T <= MERGE_WAYS * 1024 ? 1 : 4, run_bits = items == 1 ? 10 : 12;
+  if (T <= 262144 && vbits + run_bits <= 32) {
+    const int R = items * 1024, runs = (int)((T + R - 1) / R);
+    {
+      ProfScope ps(ctx, K_SORT_FUSED, s);
+      if (items == 1)
+        hipLaunchKernelGGL((sort_lds_kernel<1, true>), dim3(runs), dim3(1024), 0, s, ids, (int)T, V, run_bits, passes,
+                           ws.sort_keys[0], ws.sort_vals[0], nullptr, nullptr, nullptr, nullptr, ws.flag);
+      else
+        hipLaunchKernelGGL((sort_lds_kernel<4, true>), dim3(runs), dim3(1024), 0, s, ids, (int)T, V, run_bits, passes,
+                           ws.sort_keys[0], ws.sort_vals[0], nullptr, nullptr, nullptr, nullptr, ws.flag);
+    }
+    {
+      ProfScope ps(ctx, K_SORT_MERGE, s);
+      hipLaunchKernelGGL(merge_runs_kernel, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, s, ws.sort_keys[0],
+                         ws.sort_vals[0], (int)T, R, sorted_ids, perm);
+    }
+    ProfScope ps(ctx, K_UNIQUE, s);
+    hipLaunchKernelGGL(unique_blocks_kernel, dim3((unsigned)((T + 1023) / 1024)), dim3(1024), 0, s, sorted_ids, (int)T,
+                       uniq_ids, seg_offsets, n_uniq, ws.seg_of);
     return hipGetLastError();
   }
   const int tiles = (int)((T + SORT_TILE - 1) / SORT_TILE);

@@ -29,6 +29,7 @@ enum StemKernelId {
   K_SPLITK_REDUCE,   // sum of split-K partial products
   K_GEMM_UP,         // Up = X Wu^T (dense SwiGLU and the additive variant)
   K_GEMM_DWUP,       // dWu = dV^T X
+  K_SORT_MERGE,
   K_COUNT_
 };
 

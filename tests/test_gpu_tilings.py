@@ -112,3 +112,22 @@ def test_decode_products_on_every_tile(T, d, F):
     assert all(v <= Hn.TOL["bf16"] for v in errs.values()), errs
     assert torch.equal(yr, xr) and all(torch.equal(r, y) for r in reps)
     ctx.close()
+
+
+@pytest.mark.parametrize("T,V", [
+    (1, 1), (63, 2), (1024, 128256), (1025, 128256),     # one workgroup, one and four rounds of keys
+    (4096, 1 << 20), (4097, 1 << 20), (4096, (1 << 20) + 1),   # runs of 1024; an id that leaves no room for 12 position bits
+    (16384, 50304), (16385, 50304),                      # the most runs of 1024; runs of 4096, the last with one key
+    (65537, 128256), (262144, 7),                        # more runs than searches in flight; long runs of equal ids
+    (5000, 5_000_000), (262145, 3),                      # digit passes: ids, then a batch, beyond the merge's
+])
+def test_sort_on_every_path(T, V):
+    ids = inputs.zipf_ids(T, V, seed=67)
+    ids[T // 2:] = np.random.default_rng(68).integers(0, V, T - T // 2)
+    ctx = L.stem_create(64, 64, V, L.STEM_BF16, T, 0)
+    for turn in range(2):                                # the second call finds the first one's scratch
+        eg = Hn.hip_embed_grad(ctx, torch.from_numpy(ids).to(DEV), None, V, with_rows=False)
+        L.stem_sync_status(ctx)
+        Hn.check_integers(eg, ids)
+        ids = ids[::-1].copy()
+    ctx.close()
