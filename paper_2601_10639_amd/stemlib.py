@@ -151,28 +151,31 @@ def _check(ctx, status: int, where: str):
         raise StemError(status, where, lib().stem_last_error(h).decode())
 
 
-def _stream(stream) -> ctypes.c_void_p:
+# Pointers and streams go to the library as plain integers, which its argument types convert; a small layer's call
+# spends as long here as on the GPU (24 tokens, d_model 1024: 14 us a call with a c_void_p object per argument and a
+# torch Stream per call).
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
-def _ptr(t, dtype=None, cuda=True, name="tensor") -> ctypes.c_void_p:
+def _ptr(t, dtype=None, cuda=True, name="tensor"):
     if t is None:
-        return ctypes.c_void_p(None)
-    if dtype is not None and t.dtype != dtype:
+        return None
+    if dtype is not None and t.dtype is not dtype:
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
-    if cuda == "or_pinned":
+    if cuda is True:
+        if not t.is_cuda:
+            raise ValueError(f"{name}: must be device memory")
+    elif cuda == "or_pinned":
         if not (t.is_cuda or t.is_pinned()):
             raise ValueError(f"{name}: must be device memory or pinned host memory")
-        return ctypes.c_void_p(t.data_ptr())
-    if cuda and not t.is_cuda:
-        raise ValueError(f"{name}: must be device memory")
-    if not cuda and t.is_cuda:
+    elif t.is_cuda:
         raise ValueError(f"{name}: must be host memory")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 STEM_RESERVE_UP, STEM_RESERVE_EDIT = 1, 2
@@ -218,7 +221,7 @@ def stem_ffn_forward(ctx: StemCtx, x, ids, W_gate, W_down, E, y, save_G=None, sa
                                 _ptr(W_gate, dt, name="W_gate"), _ptr(W_down, dt, name="W_down"),
                                 _ptr(E, dt, name="E"), E_rows, T, _ptr(y, dt, name="y"),
                                 _ptr(save_G, dt, name="save_G"), _ptr(save_H, dt, name="save_H"),
-                                ctypes.c_void_p(wait_event), _stream(stream))
+                                wait_event, _stream(stream))
     _check(ctx, st, "stem_ffn_forward")
 
 
