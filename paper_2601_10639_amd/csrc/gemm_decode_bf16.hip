@@ -55,11 +55,12 @@ __device__ __forceinline__ void lds_dma_16(rsrc_t rs, char* lds_dst, uint32_t of
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)lds_dst, 16, off, soff, 0, 0);
 }
 
-// Waits until at most min(younger, MOST) K tiles of LOADS loads each are outstanding; the count is an immediate.
-template <int LOADS, int MOST>
+// Waits until at most min(younger, MOST) K tiles of LOADS loads each and EXTRA more loads are outstanding; the count is
+// an immediate.
+template <int LOADS, int MOST, int EXTRA>
 __device__ __forceinline__ void wait_all_but(int younger) {
-  if (MOST == 0 || younger >= MOST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MOST * LOADS) : "memory");
-  else wait_all_but<LOADS, (MOST > 0 ? MOST - 1 : 0)>(younger);
+  if (MOST == 0 || younger >= MOST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MOST * LOADS + EXTRA) : "memory");
+  else wait_all_but<LOADS, (MOST > 0 ? MOST - 1 : 0), EXTRA>(younger);
 }
 
 // FA x 16 tokens, FB x 16 weight rows, W wavefronts with D K tiles in flight each
@@ -78,7 +79,6 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
   constexpr int QUADS = TM * TN / 4, QT = (QUADS + 64 * W - 1) / (64 * W);   // quads of 4 columns; per thread
   constexpr int LOADS = 2 * (FA + FB);                                       // per wavefront and K tile
   __shared__ __attribute__((aligned(16))) char smem[S::LDS_BYTES];
-  __shared__ int ticket_s;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -105,6 +105,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
   // right behind the first K tiles, so that both pass under the main loop.
   int ids_q[QT];
   uint2 ev[QT];
+  bool bad = false;
   if (EPI == EPI_GATE) {
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
@@ -148,24 +149,37 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
 #pragma unroll
     for (int b = 0; b < FB; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-#pragma unroll
-  for (int d = 0; d < D; ++d)
-    if (d < nw) request(d);
-  if (EPI == EPI_GATE) {
+  // The row pieces are younger than the first D K tiles and older than the rest: the waits for the first D allow for
+  // these QT loads (a row of a large table takes microseconds to arrive), which the barriers keep in this place.
+  auto load_rows = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
       int id = ids_q[q];
-      if ((unsigned)id >= (unsigned)p.E_rows) {   // reported to the host, clamped so no access leaves the table
-        *p.flag = 1;
-        id = id < 0 ? 0 : p.E_rows - 1;
-      }
+      bad |= (unsigned)id >= (unsigned)p.E_rows;   // reported to the host below, clamped so no access leaves the table
+      id = id < 0 ? 0 : id < p.E_rows ? id : p.E_rows - 1;
       const int n = n0 + ((q * 64 * W + tid) % (TN / 4)) * 4;
       ev[q] = *reinterpret_cast<const uint2*>(p.E + (size_t)id * p.N + (n < p.N ? n : 0));
     }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the usual case apart: behind conditional requests the compiler waits for all of them before it uses the ids
+  if (nw >= D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) request(d);
+    if (EPI == EPI_GATE) load_rows();
+  } else {
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+      if (d < nw) request(d);
+    if (EPI == EPI_GATE) load_rows();
   }
   int slot = 0;
   for (int i = 0; i < nw; ++i) {
-    wait_all_but<LOADS, D - 1>(nw - 1 - i);
+    if (EPI == EPI_GATE && i < D) wait_all_but<LOADS, D - 1, QT>(nw - 1 - i);
+    else wait_all_but<LOADS, D - 1, 0>(nw - 1 - i);
     const char* const f = frag + slot * S::SLOT;
     bf16x8_t xa[2][FA], xb[2][FB];
 #pragma unroll
@@ -188,8 +202,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
           acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[h][b], xa[h][a], acc[a][b], 0, 0, 0);
     slot = slot + 1 == D ? 0 : slot + 1;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing lands in LDS any more
-  __syncthreads();
+  asm volatile("s_barrier" ::: "memory");            // nothing lands in LDS any more: every K tile has been waited for
 
   // ---- sum of the wavefronts' tiles: a lane holds, for token fr of each fragment, columns 4 fg .. 4 fg + 3 ----
   float* const red = reinterpret_cast<float*>(smem);
@@ -221,23 +234,23 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (tid == 0) ticket_s = __hip_atomic_fetch_add(p.tickets + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int* const ticket = reinterpret_cast<int*>(smem);   // (a second shared variable makes the compiler drain the ring before every fragment read)
+    if (tid == 0) *ticket = __hip_atomic_fetch_add(p.tickets + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    if (ticket_s != p.ksplit - 1) return;
+    if (*ticket != p.ksplit - 1) return;
     if (tid == 0) __hip_atomic_store(p.tickets + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
       const int quad = q * 64 * W + tid;
       if (QUADS % (64 * W) && quad >= QUADS) continue;
-      f32x4_t v[MAX_SLICES];
+      f32x4_t v[MAX_SLICES];   // all in flight together; what is beyond the last slice reads as zero
 #pragma unroll
       for (int s = 0; s < MAX_SLICES; ++s)
-        if (s < p.ksplit) v[s] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rw, ((s * tiles + tile) * QUADS + quad) * 16, 0, SC1));
+        v[s] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rw, s < p.ksplit ? ((s * tiles + tile) * QUADS + quad) * 16 : OOB, 0, SC1));
       sum[q] = v[0];
 #pragma unroll
-      for (int s = 1; s < MAX_SLICES; ++s)
-        if (s < p.ksplit) sum[q] += v[s];
+      for (int s = 1; s < MAX_SLICES; ++s) sum[q] += v[s];
     }
   }
 
@@ -250,6 +263,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
     float c[4] = {sum[q][0], sum[q][1], sum[q][2], sum[q][3]};
     const size_t o = (size_t)m * p.N + n;
     if (EPI == EPI_GATE) {
+      if (bad) *p.flag = 1;
       const float e[4] = {__uint_as_float(ev[q].x << 16), __uint_as_float(ev[q].x & 0xffff0000u),
                           __uint_as_float(ev[q].y << 16), __uint_as_float(ev[q].y & 0xffff0000u)};
       float h[4];
