@@ -24,7 +24,7 @@
 // when it leaves vmcnt, and every wavefront waits for that before the workgroup's ticket is taken.  That orders the
 // exchange without a device-scope fence, which would write back or drop the whole L2 under the weight streams of the
 // other workgroups (20 -> 41 us when this was tried with fences).  2048 x 8192 down product, 16 tokens: 12.5 us
-// unsplit, 10.7 in two slices; against 10.6 + 3.9 for a split product and a kernel that sums.
+// unsplit, 9.9 in two slices; against 10.6 + 3.9 for a split product and a kernel that sums.
 #include "stem_internal.h"
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
@@ -288,8 +288,10 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
 // second round, fewer leave CUs without requests.  Gate product, us, 16 / 32 / 64 rows: d_model 2048, d_ff 8192, 16
 // tokens 10.7 / 8.2 / 12.2, 64 tokens 15.8 / 11.7 / 14.5, 128 tokens - / 18.8 / 14.2; 1024 x 4096, 16 tokens 4.5 / 4.6 / 8.0,
 // 128 tokens 8.3 / 6.4 / 7.7, 256 tokens - / 10.4 / 7.9.
-// K is cut where that still leaves at most one workgroup per CU and 64 K tiles per slice: 2048 x 8192 down product, 16
-// tokens, 1 / 2 / 4 slices 12.5 / 10.7 / 12.2 us, 64 tokens 22.2 / 17.0 / 17.9; 1024 x 4096, 16 tokens 5.3 / 6.3 / 7.3.
+// K is cut where that still leaves at most one workgroup per CU and as many K tiles per slice as outweigh the exchange
+// of the partial tiles (about 1.3 us): the more tokens, the longer a K tile takes.  Layer forward, us, least 64 / 32 / 16
+// K tiles: 1024 x 4096, 1 token 10.0 / 10.4 / 10.9, 16 tokens 11.3 / 11.0 / 11.0, 64 tokens 16.8 / 14.4 / 13.2; 1536 x 5120, 1 token
+// 14.8 / 13.7 / 13.8, 64 tokens 26.8 / 21.5 / 21.5.
 struct DecodePlan { int fa, fb, mt, nt, ksplit; };
 
 // K of more than 2048 (the down product of the larger layers) only with 16 weight rows: 2048 x 8192, 256 tokens, 25.0 us
@@ -302,7 +304,8 @@ bool decode_plan(int M, int N, int K, bool may_split, size_t ws_bytes, DecodePla
     if ((int64_t)mt * nt > 256 && !last) continue;
     if (fa == 4 && fb > 1 && K > 2048) break;
     int ks = 1;
-    while (may_split && ks < MAX_SLICES && mt * nt * ks * 2 <= 256 && K / BK / (ks * 2) >= 64 &&
+    const int least = M <= 8 ? 40 : M <= 16 ? 32 : 16;
+    while (may_split && ks < MAX_SLICES && mt * nt * ks * 2 <= 256 && K / BK / (ks * 2) >= least &&
            (size_t)mt * nt * ks * 2 * fa * fb * 1024 <= ws_bytes)
       ks *= 2;
     while (ks > 1 && (ks - 1) * ((K / BK + ks - 1) / ks) >= K / BK) ks /= 2;   // no empty slice
@@ -323,9 +326,9 @@ void launch(int epi, const GemmArgs& p, hipStream_t s) {
 }  // namespace
 
 // Worth it while one round of its workgroups covers the product; beyond, the few-row kernel's and the large kernel's
-// tiles load less per CU.  d_model 2048, d_ff 8192, gate + down product, us, this / few-row: 1 token 18.5 / 28.0,
-// 32 tokens 21.7 / 29.6, 64 tokens 28.1 / 31.5, 128 tokens 35.4 / 37.2, 256 tokens 45.2 / 42.3; 1024 x 4096: 32 tokens
-// 13.2 / 19.8, 256 tokens 21.1 / 27.1, 320 tokens 27.7 / 25.9; 512 x 1536: 512 tokens 14.2 / 19.4.
+// tiles load less per CU.  d_model 2048, d_ff 8192, gate + down product, us, this / few-row: 1 token 17.6 / 28.0,
+// 32 tokens 21.1 / 29.6, 64 tokens 26.6 / 31.5, 128 tokens 35.4 / 37.2, 256 tokens 45.2 / 42.3; 1024 x 4096: 32 tokens
+// 12.0 / 19.8, 256 tokens 21.1 / 27.1, 320 tokens 27.7 / 25.9; 512 x 1536: 512 tokens 14.2 / 19.4.
 bool stem_gemm_decode_fits(int M, int N, int K) {
   DecodePlan pl;
   return M <= 512 && K % BK == 0 && N % 4 == 0 && decode_plan(M, N, K, false, 0, &pl);

@@ -87,6 +87,7 @@ def test_f32_products_on_both_tilings(T, d, F):
     (33, 64, 4096),       # 64-token tile
     (129, 1088, 2112),    # 3 x 33 tiles of 64 x 64, ragged both ways
     (64, 2048, 8256),     # down: 129 K tiles in two slices of 65 and 64
+    (20, 1024, 4160),     # down: 65 K tiles in four slices, the last of 14
     (500, 512, 1536),     # eight token tiles, the last ragged
     (300, 1024, 2624),    # few-row kernel beyond 256 tokens
 ])
