@@ -19,75 +19,66 @@ __device__ __forceinline__ int checked_id(const int32_t* ids, int64_t t, int E_r
 // K-contiguous ([rows,K], OP_KC) or rows-contiguous ([K,rows], OP_MC); dimensions are multiples of 4 except the
 // token count, so every 16-byte piece is whole or absent.
 //
-// Workgroup = 4 wavefronts and a TS x TS tile.  TS = 64: each wavefront a 32x32 quadrant, K in tiles of 32.
-// TS = 32: all four share the 32x32 tile and take a quarter of each 64-wide K tile, summed through LDS in a fixed
-// order; four times the workgroups, and a quarter of the serial chain of MFMAs (64 cycles each), which is what a
-// small product waits for.  Tiles travel global -> registers -> LDS, four K tiles in flight in registers (a short K
-// range is requested whole before anything waits), two stages in LDS, one barrier per K tile.
+// A workgroup computes a TS x TS tile whose K tiles (32 wide) its W wavefronts share out: wavefront w takes every W-th,
+// for the whole tile, through a ring of D K tiles of its own in LDS, filled by direct loads in whole lines.  So the
+// main loop has no barrier, a short K range is requested whole before anything waits, and the chain of dependent MFMAs
+// (64 cycles each), which is what a small product waits for, is W times shorter.  The W partial tiles are added through
+// LDS in wavefront order; the element-wise part of the layer runs on the sums, its inputs requested behind the first
+// K tiles.
 // MFMA j of a group of 8 k takes k = 4 h + j from lane half h, for both operands alike, so a lane's four values of a
 // K-contiguous operand are one 16-byte LDS read; those of a rows-contiguous operand are four 4-byte reads.
-// The element-wise part of the layer runs in the epilogue, on rows read back from LDS.
 //
-// Against a 64x64 tile of scalar FMAs on 4-byte loads with nothing in flight across barriers, plus separate
-// element-wise kernels: d_model 64, d_ff 256, 128 tokens 13-47 us -> 4-5 us per product; d_model 256, d_ff 1024, 1000 tokens
-// 55-215 us -> 12-15 us.
+// Bound by the MFMAs from about 1000 tokens of 512 x 2048 on (82 to 126 TFLOP/s of 153), below by the launch and the
+// first loads.  Against four wavefronts on one K tile with a barrier per K tile and operands through registers, forward
+// and backward: 128 tokens of 64 x 256 25.3 -> 24.1 us, 600 of 128 x 400 41 -> 32, 1000 of 256 x 1024 76 -> 56, 1000 of
+// 512 x 2048 172 -> 150, 4096 of 1024 x 2048 951 -> 820.
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr int KT = 32;                  // K tile
+constexpr uint32_t OOB = 0x80000000u;   // a buffer offset beyond any window: reads as zero
 
+__device__ __forceinline__ void lds_dma_16(rsrc_t rs, char* lds_dst, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)lds_dst, 16, off, 0, 0, 0);
+}
+
+// One operand's K tile: TS x KT floats in LDS, KC as TS rows of 128 bytes (16-byte chunk c of row r at slot
+// c ^ (r >> 1): a fragment read's 16 rows touch all banks once), MC as KT rows of TS floats.  A load of 1 KB covers ROWS
+// of these rows; its window starts at the first of them (operands may exceed 2 GiB), and the lanes outside the matrix
+// are given an offset beyond it.
 template <int TS, int LOP>
 struct TileF32 {
-  static constexpr int KT = TS == 64 ? 32 : 64;     // K tile: 8 KB of one operand either way
-  static constexpr int ITEMS = 2;                   // 16-byte pieces per thread and K tile
-  const float* p;                                   // the piece's address at K tile 0
-  int64_t step;                                     // elements from one K tile to the next
-  int64_t dist;                                     // from piece 0 to piece 1
-  uint32_t lds0, lds1;
-  int k_of[ITEMS];
-  bool in[ITEMS];
-  __device__ __forceinline__ void init(const float* base, int64_t ld, int rows, int row0, int tid) {
-    if (LOP == OP_KC) {
-      constexpr int CH = KT / 4;
-      const int c = tid % CH, r = tid / CH;
-      constexpr int RSTEP = 256 / CH;
-      p = base + (int64_t)(row0 + r) * ld + c * 4;
-      step = KT;
-      dist = (int64_t)RSTEP * ld;
-      k_of[0] = k_of[1] = c * 4;
-      in[0] = row0 + r < rows;
-      in[1] = row0 + r + RSTEP < rows;
-      lds0 = slot(r, c);
-      lds1 = slot(r + RSTEP, c);
-    } else {
-      constexpr int CH = TS / 4;
-      const int c = tid % CH, k = tid / CH;
-      constexpr int KSTEP = 256 / CH;
-      p = base + (int64_t)k * ld + row0 + c * 4;
-      step = (int64_t)KT * ld;
-      dist = (int64_t)KSTEP * ld;
-      k_of[0] = k;
-      k_of[1] = k + KSTEP;
-      in[0] = in[1] = row0 + c * 4 < rows;
-      lds0 = (uint32_t)(k * TS + c * 4) * 4;
-      lds1 = (uint32_t)((k + KSTEP) * TS + c * 4) * 4;
+  static constexpr int LOADS = TS * KT * 4 / 1024, CH = LOP == OP_KC ? 8 : TS / 4, ROWS = 64 / CH;   // CH: chunks per row
+  const char* at;        // the next K tile's first row
+  int64_t group, step;   // bytes from one load's rows to the next one's, from one of this wavefront's K tiles to its next
+  uint32_t off[LOADS];
+  static __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
+  __device__ __forceinline__ void init(const float* p, int64_t ld, int rows, int row0, int lane, int wave, int waves) {
+    const int64_t pitch = ld * 4, kt = LOP == OP_KC ? KT * 4 : KT * pitch;
+    at = reinterpret_cast<const char*>(p + (LOP == OP_KC ? row0 * ld : row0)) + wave * kt;
+    group = ROWS * pitch;
+    step = waves * kt;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const int r = i * ROWS + lane / CH, c = lane % CH;                         // row in LDS, chunk slot
+      const uint32_t o = (uint32_t)(lane / CH * pitch) + (uint32_t)((LOP == OP_KC ? c ^ swz(r) : c) << 4);
+      off[i] = row0 + (LOP == OP_KC ? r : c * 4) < rows ? o : OOB;
     }
   }
-  // K-contiguous: 16-byte piece c of row r; the swizzle spreads a fragment read's 16 rows over all banks
-  static __device__ __forceinline__ uint32_t slot(int r, int c) {
-    return (uint32_t)(r * KT * 4 + ((c ^ (TS == 64 ? (r >> 1) & 7 : r & 15)) << 4));
-  }
-  __device__ __forceinline__ void load(int t, int K, f32x4_t (&v)[ITEMS]) const {
-    const float* q = p + t * step;
-    v[0] = v[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    if (in[0] && t * KT + k_of[0] < K) v[0] = *reinterpret_cast<const f32x4_t*>(q);
-    if (in[1] && t * KT + k_of[1] < K) v[1] = *reinterpret_cast<const f32x4_t*>(q + dist);
-  }
-  __device__ __forceinline__ void store(char* lds, const f32x4_t (&v)[ITEMS]) const {
-    *reinterpret_cast<f32x4_t*>(lds + lds0) = v[0];
-    *reinterpret_cast<f32x4_t*>(lds + lds1) = v[1];
+  // the K tile that `at` points to, of which `left` k exist, into `tile`; `at` moves on
+  __device__ __forceinline__ void request(int left, char* tile, int lane) {
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at + i * group), 0, 0x7fffffff, 0x00020000);
+      const int r = i * ROWS + lane / CH, k = LOP == OP_KC ? ((lane % CH) ^ swz(r)) << 2 : r;
+      lds_dma_16(rs, tile + i * 1024, k < left ? off[i] : OOB);
+    }
+    at += step;
   }
   // the lane's four k of group g (8 k of the tile), row `row`
   static __device__ __forceinline__ f32x4_t frag(const char* lds, int row, int half, int g) {
-    if (LOP == OP_KC) return *reinterpret_cast<const f32x4_t*>(lds + slot(row, g * 2 + half));
+    if (LOP == OP_KC) return *reinterpret_cast<const f32x4_t*>(lds + row * 128 + ((((g * 2 + half) ^ swz(row)) & 7) << 4));
     f32x4_t v;
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const float*>(lds + ((g * 8 + half * 4 + j) * TS + row) * 4);
@@ -95,95 +86,163 @@ struct TileF32 {
   }
 };
 
-template <int TS, int LA, int LB, int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args p) {
+// Waits until at most min(younger, MOST) K tiles of LOADS loads each and EXTRA more loads are outstanding; the count is
+// an immediate.
+template <int LOADS, int MOST, int EXTRA>
+__device__ __forceinline__ void wait_all_but(int younger) {
+  if (MOST == 0 || younger >= MOST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MOST * LOADS + EXTRA) : "memory");
+  else wait_all_but<LOADS, (MOST > 0 ? MOST - 1 : 0), EXTRA>(younger);
+}
+
+template <int TS, int W, int D, int LA, int LB, int EPI>
+__global__ __launch_bounds__(64 * W) void gemm_f32_kernel(GemmF32Args p) {
   typedef TileF32<TS, LA> TA;
   typedef TileF32<TS, LB> TB;
-  constexpr int KT = TA::KT, STAGE = 2 * TS * KT * 4;        // A and B of one K tile: 16 KB
-  constexpr int DEPTH = 4;
-  constexpr int PITCH = TS + 4;                              // epilogue row in LDS (floats)
-  constexpr int PARTS = TS == 64 ? 1 : 4;                    // K quarters to sum
-  constexpr int EPI_BYTES = PARTS * TS * PITCH * 4;
-  __shared__ __attribute__((aligned(16))) char smem[EPI_BYTES > 2 * STAGE ? EPI_BYTES : 2 * STAGE];
+  constexpr int NB = TS / 32, OPERAND = TS * KT * 4, SLOT = 2 * OPERAND, LOADS = TA::LOADS + TB::LOADS;
+  constexpr int PITCH = TS + 4;                              // row of a partial tile in LDS (floats)
+  constexpr int RING = W * D * SLOT, RED = W * TS * PITCH * 4;
+  constexpr int QUADS = TS * TS / 4, QT = (QUADS + 64 * W - 1) / (64 * W), LPR = TS / 4;
+  constexpr int EXTRA = EPI == EPI_F32 ? 0 : EPI == EPI_GATE ? QT : 2 * QT;
+  __shared__ __attribute__((aligned(16))) char smem[RING > RED ? RING : RED];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ntn = (p.N + TS - 1) / TS;
   const int tm = blockIdx.x / ntn, tn = blockIdx.x - tm * ntn;
   const int m0 = tm * TS, n0 = tn * TS;
-  const int wm = TS == 64 ? (wave >> 1) * 32 : 0, wn = TS == 64 ? (wave & 1) * 32 : 0;
   const int r = lane & 31, half = lane >> 5;
+  // rows and columns of this thread's quads, clamped into the matrix for the loads
+  int ids_q[QT], mq[QT], nq[QT];
+#pragma unroll
+  for (int q = 0; q < QT; ++q) {
+    const int quad = q * 64 * W + tid, m = m0 + quad / LPR, n = n0 + (quad % LPR) * 4;
+    mq[q] = m < p.M ? m : p.M - 1;
+    nq[q] = n < p.N ? n : 0;
+    ids_q[q] = EPI == EPI_F32 ? 0 : p.ids[mq[q]];
+  }
   TA ta;
   TB tb;
-  ta.init(p.A, p.lda, p.M, m0, tid);
-  tb.init(p.B, p.ldb, p.N, n0, tid);
-  f32x16_t acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  f32x4_t ra[DEPTH][2], rb[DEPTH][2];
+  ta.init(p.A, p.lda, p.M, m0, lane, wave, W);
+  tb.init(p.B, p.ldb, p.N, n0, lane, wave, W);
   const int nk = (p.K + KT - 1) / KT;
+  const int nw = nk > wave ? (nk - wave + W - 1) / W : 0;    // this wavefront's K tiles
+  char* const ring = smem + wave * (D * SLOT);
+  auto request = [&](int i, int slot) __attribute__((always_inline)) {
+    const int left = p.K - (wave + i * W) * KT;
+    ta.request(left, ring + slot * SLOT, lane);
+    tb.request(left, ring + slot * SLOT + OPERAND, lane);
+  };
+  f32x4_t ev[QT], gv[QT];
+  bool bad = false;
+  // Younger than the first D K tiles and older than the rest: the waits for the first D allow for these EXTRA loads,
+  // which the barriers keep in this place.
+  auto load_inputs = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int d = 0; d < DEPTH; ++d) {
-    ta.load(d, p.K, ra[d]);
-    tb.load(d, p.K, rb[d]);
-  }
-  for (int t0 = 0; t0 < nk; t0 += DEPTH) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      if (t0 + d < nk) {
-        char* st = smem + (d & 1) * STAGE;
-        ta.store(st, ra[d]);
-        tb.store(st + TS * KT * 4, rb[d]);
-        ta.load(t0 + d + DEPTH, p.K, ra[d]);
-        tb.load(t0 + d + DEPTH, p.K, rb[d]);
-        __syncthreads();
-        const int g0 = TS == 64 ? 0 : wave * 2, gn = TS == 64 ? 4 : 2;
-#pragma unroll
-        for (int g = 0; g < gn; ++g) {
-          const f32x4_t fa = TA::frag(st, wm + r, half, g0 + g);
-          const f32x4_t fb = TB::frag(st + TS * KT * 4, wn + r, half, g0 + g);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[j], fa[j], acc, 0, 0, 0);
-        }
-      }
+    for (int q = 0; q < QT; ++q) {
+      asm volatile("" : "+v"(ids_q[q]));   // keeps what follows behind the requests
+      int id = ids_q[q];
+      bad |= (unsigned)id >= (unsigned)p.E_rows;   // reported to the host below, clamped so no access leaves the table
+      id = id < 0 ? 0 : id < p.E_rows ? id : p.E_rows - 1;
+      ev[q] = *reinterpret_cast<const f32x4_t*>(p.E + (int64_t)id * p.N + nq[q]);
+      if (EPI == EPI_DH) gv[q] = *reinterpret_cast<const f32x4_t*>(p.inG + (int64_t)mq[q] * p.N + nq[q]);
     }
-  }
-  __syncthreads();
-  // lane holds, for row r of its 32x32 piece, columns 8 g + 4 half .. + 3
-  {
-    float* o = reinterpret_cast<float*>(smem) + (TS == 64 ? 0 : wave * TS * PITCH) + (wm + r) * PITCH + wn + half * 4;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the usual case apart: behind conditional requests the compiler waits for all of them before it uses the ids
+  if (nw >= D) {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) *reinterpret_cast<f32x4_t*>(o + g * 8) = f32x4_t{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    for (int d = 0; d < D; ++d) request(d, d);
+    if (EPI != EPI_F32) load_inputs();
+  } else {
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+      if (d < nw) request(d, d);
+    if (EPI != EPI_F32) load_inputs();
   }
+  f32x16_t acc[NB][NB];
+#pragma unroll
+  for (int a = 0; a < NB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+  int slot = 0;
+  for (int i = 0; i < nw; ++i) {
+    if (EPI != EPI_F32 && i < D) wait_all_but<LOADS, D - 1, EXTRA>(nw - 1 - i);
+    else wait_all_but<LOADS, D - 1, 0>(nw - 1 - i);
+    const char* const st = ring + slot * SLOT;
+    // the fragments of group g + 1 are read before the MFMAs of group g
+    f32x4_t fa[2][NB], fb[2][NB];
+    auto read = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+      for (int a = 0; a < NB; ++a) {
+        fa[g & 1][a] = TA::frag(st, a * 32 + r, half, g);
+        fb[g & 1][a] = TB::frag(st + OPERAND, a * 32 + r, half, g);
+      }
+    };
+    read(0);
+#pragma unroll
+    for (int g = 0; g < KT / 8; ++g) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (g + 1 < KT / 8) {
+        read(g + 1);
+      } else {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the slot has been read: it may be filled again
+        if (i + D < nw) request(i + D, slot);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int a = 0; a < NB; ++a)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[g & 1][b][j], fa[g & 1][a][j], acc[a][b], 0, 0, 0);
+    }
+    slot = slot + 1 == D ? 0 : slot + 1;
+  }
+  asm volatile("s_barrier" ::: "memory");                // nothing lands in LDS any more: every K tile has been waited for
+  // partial tiles: a lane holds, for row r of each 32x32 piece, columns 8 g + 4 half .. + 3
+  float* const red = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int a = 0; a < NB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4_t*>(red + (wave * TS + a * 32 + r) * PITCH + b * 32 + g * 8 + half * 4) =
+            f32x4_t{acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
   __syncthreads();
 #pragma unroll
-  for (int it = 0; it < TS * TS / 1024; ++it) {
-    constexpr int LPR = TS / 4;
-    const int row = it * (256 / LPR) + tid / LPR, col = (tid % LPR) * 4;
-    const int m = m0 + row, n = n0 + col;
+  for (int q = 0; q < QT; ++q) {
+    const int quad = q * 64 * W + tid;
+    const int m = m0 + quad / LPR, n = n0 + (quad % LPR) * 4;
+    if (QUADS % (64 * W) && quad >= QUADS) continue;
     if (m >= p.M || n >= p.N) continue;
-    const float* src = reinterpret_cast<const float*>(smem) + row * PITCH + col;
+    const float* src = red + (quad / LPR) * PITCH + (quad % LPR) * 4;
     f32x4_t c = *reinterpret_cast<const f32x4_t*>(src);
 #pragma unroll
-    for (int q = 1; q < PARTS; ++q) c += *reinterpret_cast<const f32x4_t*>(src + q * TS * PITCH);
+    for (int w = 1; w < W; ++w) c += *reinterpret_cast<const f32x4_t*>(src + w * TS * PITCH);
     const int64_t o = (int64_t)m * p.N + n;
     if (EPI == EPI_F32) {
       if (p.add) c += *reinterpret_cast<const f32x4_t*>(p.add + o);   // may be C itself: read before it is written
       *reinterpret_cast<f32x4_t*>(p.C + o) = c;
     } else {
-      const int id = checked_id(p.ids, m, p.E_rows, p.flag);
-      const f32x4_t e = *reinterpret_cast<const f32x4_t*>(p.E + (int64_t)id * p.N + n);
+      if (bad) *p.flag = 1;
+      const f32x4_t e = ev[q];
       f32x4_t x, y;
       if (EPI == EPI_GATE) {        // G (optional) and H = SiLU(G) * E
 #pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = c[q] * sigmoid_f(c[q]) * e[q];
+        for (int j = 0; j < 4; ++j) x[j] = c[j] * sigmoid_f(c[j]) * e[j];
         if (p.C) *reinterpret_cast<f32x4_t*>(p.C + o) = c;
         *reinterpret_cast<f32x4_t*>(p.out0 + o) = x;
       } else {                      // dU = dH * SiLU(G), dG = dH * E * SiLU'(G)
-        const f32x4_t g = *reinterpret_cast<const f32x4_t*>(p.inG + o);
+        const f32x4_t g = gv[q];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float s = sigmoid_f(g[q]);
-          x[q] = c[q] * (g[q] * s);
-          y[q] = c[q] * e[q] * (s * (1.0f + g[q] * (1.0f - s)));
+        for (int j = 0; j < 4; ++j) {
+          const float s = sigmoid_f(g[j]);
+          x[j] = c[j] * (g[j] * s);
+          y[j] = c[j] * e[j] * (s * (1.0f + g[j] * (1.0f - s)));
         }
         *reinterpret_cast<f32x4_t*>(p.out0 + o) = x;
         *reinterpret_cast<f32x4_t*>(p.out1 + o) = y;
@@ -259,16 +318,23 @@ hipError_t stem_fill_zero(void* p, size_t bytes, hipStream_t s) {   // bytes is 
 
 template <int LA, int LB, int EPI>
 static void launch_f32(const GemmF32Args& p, hipStream_t s) {
-  // 64x64 tiles once they fill the chip (gate / down product, us, 64x64 and 32x32 tiles: 128 tokens of 64 x 256
-  // 8.0, 11.0 and 6.6, 6.8; 1000 of 256 x 1024 15.3, 29.8 and 13.6, 14.7; 1000 of 512 x 2048 32.7, 56.0 and 33.5, 33.1;
-  // 4096 of 1024 x 2048 182, 174 and 190, 183)
+  // 64x64 tiles where rounds of two workgroups per CU come out nearly full; else 32x32, two K tiles in flight per
+  // wavefront (two workgroups per CU) up to 512 of them and one (four per CU) beyond.  us, 64x64 / 32x32 one / two in flight:
+  // gate 1000 x 256 x 1024 12.9 / 11.8 / 13.1, down 22.3 / 12.8 / 10.8; gate 2048 x 512 x 1536 (768 tiles of 64) 44.9 / 40.7 / 42.4;
+  // 4096 x 1024 x 2048 gate 151 / 154 / 176, down 137 / 146 / 156, dW 129 / 138 / 147.
   const int64_t t64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64), t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32);
-  if (t64 >= 256) hipLaunchKernelGGL((gemm_f32_kernel<64, LA, LB, EPI>), dim3((unsigned)t64), dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((gemm_f32_kernel<32, LA, LB, EPI>), dim3((unsigned)t32), dim3(256), 0, s, p);
+  const int64_t full64 = (t64 + 511) / 512 * 512;
+  if (t64 * 10 >= full64 * 9)
+    hipLaunchKernelGGL((gemm_f32_kernel<64, 4, 1, LA, LB, EPI>), dim3((unsigned)t64), dim3(256), 0, s, p);
+  else if (t32 <= 512)
+    hipLaunchKernelGGL((gemm_f32_kernel<32, 4, 2, LA, LB, EPI>), dim3((unsigned)t32), dim3(256), 0, s, p);
+  else
+    hipLaunchKernelGGL((gemm_f32_kernel<32, 4, 1, LA, LB, EPI>), dim3((unsigned)t32), dim3(256), 0, s, p);
 }
 
 hipError_t stem_gemm_f32(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmF32Args& p, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return hipSuccess;
+  if (std::max(p.lda, p.ldb) >= (1 << 26)) return hipErrorInvalidValue;   // 8 rows of an operand within a 2 GiB window
   ProfScope ps(ctx, kid, s);
   if (la == OP_KC && lb == OP_KC && epi == EPI_F32) launch_f32<OP_KC, OP_KC, EPI_F32>(p, s);
   else if (la == OP_KC && lb == OP_KC && epi == EPI_GATE) launch_f32<OP_KC, OP_KC, EPI_GATE>(p, s);

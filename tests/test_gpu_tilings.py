@@ -52,9 +52,11 @@ def test_bf16_products_on_every_tiling(T, d, F, up):
 
 
 @pytest.mark.parametrize("T,d,F", [
-    (1030, 1028, 1028),   # every product on 64x64 tiles, ragged in M, N and K
-    (1030, 36, 1028),     # forward and dH on 64x64 tiles with K of one tile and a bit; dx, weight gradients on 32x32
+    (1030, 1028, 1028),   # every product on 32x32 tiles with one K tile in flight, ragged in M, N and K
+    (1030, 36, 1028),     # forward and dH with K of one tile and a bit; dx, weight gradients with two K tiles in flight
     (33, 4, 8),           # K of one 16-byte piece, one row in the last tile
+    (2030, 1004, 2044),   # every product on 64x64 tiles, ragged in M, N and K
+    (2030, 36, 1020),     # forward and dH on 64x64 tiles with fewer K tiles than wavefronts
 ])
 def test_f32_products_on_both_tilings(T, d, F):
     s = inputs.StemShape("f32-tilings", d, F, 300, 1, T, "f32")
