@@ -20,7 +20,8 @@ const char* const kKernelNames[K_COUNT_] = {
     "gemm_gate_fused", "gemm_gate_plain", "gemm_down",    "gemm_dh_fused", "gemm_dx",      "gemm_dw_down",
     "gemm_dw_gate",    "silu_gather",      "sort_count",    "sort_scan",    "sort_scatter",
     "sort_fused",      "unique",          "seg_reduce",   "seg_combine",   "sparse_adamw", "row_copy",
-    "splitk_reduce",   "gemm_up",      "gemm_dw_up",   "sort_merge"};
+    "splitk_reduce",   "gemm_up",      "gemm_dw_up",   "sort_merge",
+    "grads_f32"};
 
 #define fail stem_fail
 
@@ -33,6 +34,10 @@ const char* const kKernelNames[K_COUNT_] = {
   } while (0)
 
 inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
+inline bool overlap(const void* a, size_t an, const void* b, size_t bn) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + bn && y < x + an;
+}
 inline size_t esize(const stem_ctx* c) { return c->desc.dtype == STEM_BF16 ? 2 : 4; }
 
 // Common entry checks; returns STEM_OK to proceed.
@@ -448,23 +453,23 @@ stem_status stem_ffn_backward(stem_ctx* c, const void* dy, const void* x, const 
       a.inG = static_cast<const float*>(saved_G); a.out0 = static_cast<float*>(dU); a.out1 = dG;
       HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DH, OP_KC, OP_MC, EPI_DH, a, s));
     }
-    {  // dW_down[d,F] = dy^T H
-      GemmF32Args a = {};
-      a.A = dyf; a.lda = d; a.B = static_cast<const float*>(H); a.ldb = F;
-      a.M = d; a.N = F; a.K = (int)T; a.C = dW_down; a.add = accumulate ? dW_down : nullptr;
-      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, a, s));
-    }
-    if (dx) {  // dx = dG W_gate
-      GemmF32Args a = {};
-      a.A = dG; a.lda = F; a.B = static_cast<const float*>(W_gate); a.ldb = d;
-      a.M = (int)T; a.N = d; a.K = F; a.C = static_cast<float*>(dx);
-      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DX, OP_KC, OP_MC, EPI_F32, a, s));
-    }
-    {  // dW_gate[F,d] = dG^T x
-      GemmF32Args a = {};
-      a.A = dG; a.lda = F; a.B = static_cast<const float*>(x); a.ldb = d;
-      a.M = F; a.N = d; a.K = (int)T; a.C = dW_gate; a.add = accumulate ? dW_gate : nullptr;
-      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, a, s));
+    GemmF32Args wd = {}, gx = {}, wg = {};
+    wd.A = dyf; wd.lda = d; wd.B = static_cast<const float*>(H); wd.ldb = F;   // dW_down[d,F] = dy^T H
+    wd.M = d; wd.N = F; wd.K = (int)T; wd.C = dW_down; wd.add = accumulate ? dW_down : nullptr;
+    gx.A = dG; gx.lda = F; gx.B = static_cast<const float*>(W_gate); gx.ldb = d;   // dx = dG W_gate
+    gx.M = (int)T; gx.N = d; gx.K = F; gx.C = static_cast<float*>(dx);
+    wg.A = dG; wg.lda = F; wg.B = static_cast<const float*>(x); wg.ldb = d;   // dW_gate[F,d] = dG^T x
+    wg.M = F; wg.N = d; wg.K = (int)T; wg.C = dW_gate; wg.add = accumulate ? dW_gate : nullptr;
+    // In one launch unless an output lies over an input that an earlier one of the three has read by then.
+    const size_t Td = (size_t)T * d * 4, TF = (size_t)T * F * 4, Fd = (size_t)F * d * 4;
+    const bool apart = !overlap(dx, Td, dy, Td) && !overlap(dx, Td, H, TF) && !overlap(dW_gate, Fd, dy, Td) &&
+                       !overlap(dW_gate, Fd, H, TF) && !(dx && overlap(dW_gate, Fd, W_gate, Fd));
+    if (apart && stem_grads_f32_fits(dx ? &gx : nullptr, wd, wg)) {
+      HIP_TRY(c, stem_grads_f32(c, dx ? &gx : nullptr, wd, wg, s));
+    } else {
+      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, wd, s));
+      if (dx) HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DX, OP_KC, OP_MC, EPI_F32, gx, s));
+      HIP_TRY(c, stem_gemm_f32(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, wg, s));
     }
   }
   return STEM_OK;

@@ -94,19 +94,24 @@ __device__ __forceinline__ void wait_all_but(int younger) {
   else wait_all_but<LOADS, (MOST > 0 ? MOST - 1 : 0), EXTRA>(younger);
 }
 
+template <int TS, int W, int D>
+struct ShapeF32 {
+  static constexpr int PITCH = TS + 4;                       // row of a partial tile in LDS (floats)
+  static constexpr int RING = W * D * 2 * TS * KT * 4, RED = W * TS * PITCH * 4, LDS_BYTES = RING > RED ? RING : RED;
+};
+
+// tile `block` of a product; smem: ShapeF32::LDS_BYTES of LDS
 template <int TS, int W, int D, int LA, int LB, int EPI>
-__global__ __launch_bounds__(64 * W) void gemm_f32_kernel(GemmF32Args p) {
+__device__ __forceinline__ void gemm_f32_tile(const GemmF32Args& p, int block, char* smem) {
   typedef TileF32<TS, LA> TA;
   typedef TileF32<TS, LB> TB;
   constexpr int NB = TS / 32, OPERAND = TS * KT * 4, SLOT = 2 * OPERAND, LOADS = TA::LOADS + TB::LOADS;
-  constexpr int PITCH = TS + 4;                              // row of a partial tile in LDS (floats)
-  constexpr int RING = W * D * SLOT, RED = W * TS * PITCH * 4;
+  constexpr int PITCH = ShapeF32<TS, W, D>::PITCH;
   constexpr int QUADS = TS * TS / 4, QT = (QUADS + 64 * W - 1) / (64 * W), LPR = TS / 4;
   constexpr int EXTRA = EPI == EPI_F32 ? 0 : EPI == EPI_GATE ? QT : 2 * QT;
-  __shared__ __attribute__((aligned(16))) char smem[RING > RED ? RING : RED];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ntn = (p.N + TS - 1) / TS;
-  const int tm = blockIdx.x / ntn, tn = blockIdx.x - tm * ntn;
+  const int tm = block / ntn, tn = block - tm * ntn;
   const int m0 = tm * TS, n0 = tn * TS;
   const int r = lane & 31, half = lane >> 5;
   // rows and columns of this thread's quads, clamped into the matrix for the loads
@@ -251,6 +256,28 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_kernel(GemmF32Args p) {
   }
 }
 
+template <int TS, int W, int D, int LA, int LB, int EPI>
+__global__ __launch_bounds__(64 * W) void gemm_f32_kernel(GemmF32Args p) {
+  __shared__ __attribute__((aligned(16))) char smem[ShapeF32<TS, W, D>::LDS_BYTES];
+  gemm_f32_tile<TS, W, D, LA, LB, EPI>(p, blockIdx.x, smem);
+}
+
+// The products of a backward pass that wait for nothing but dG, in one launch: dx first, the longest sum.  One after
+// another they leave CUs idle three times over (1000 tokens, 256 x 1024: 256 workgroups each where 512 to 1024 fit, 11.5 +
+// 10.7 + 10.8 us against 22.0; 128 tokens of 64 x 256, three launches against one, 6.5 + 6.4 + 6.1 against 6.3).
+struct GradArgs { GemmF32Args dx, w[2]; int n_dx, n_w0; };
+template <int D>
+__global__ __launch_bounds__(256) void grads_f32_kernel(GradArgs p) {
+  __shared__ __attribute__((aligned(16))) char smem[ShapeF32<32, 4, D>::LDS_BYTES];
+  const int b = blockIdx.x;
+  if (b < p.n_dx) {
+    gemm_f32_tile<32, 4, D, OP_KC, OP_MC, EPI_F32>(p.dx, b, smem);
+  } else {
+    const int second = b - p.n_dx >= p.n_w0;
+    gemm_f32_tile<32, 4, D, OP_MC, OP_MC, EPI_F32>(second ? p.w[1] : p.w[0], b - p.n_dx - (second ? p.n_w0 : 0), smem);
+  }
+}
+
 // fp32: one thread per 4 features of one token.
 __global__ void silu_gather_f32_kernel(const float* __restrict__ G, const int32_t* __restrict__ ids,
                                        const float* __restrict__ E, int E_rows, float* __restrict__ H,
@@ -316,13 +343,37 @@ hipError_t stem_fill_zero(void* p, size_t bytes, hipStream_t s) {   // bytes is 
   return hipGetLastError();
 }
 
+static int64_t tiles_f32(const GemmF32Args& p, int ts) { return (int64_t)((p.M + ts - 1) / ts) * ((p.N + ts - 1) / ts); }
+static bool wide_f32(const GemmF32Args& p) { return std::max(p.lda, p.ldb) >= (1 << 26); }   // 8 rows of an operand within a 2 GiB window
+
+// Up to here each product alone is at most one round of workgroups, two per CU; beyond, a launch each fills the chip and
+// may take the larger tiles.  Forward and backward, us, three launches / one: 600 tokens of 128 x 400 32.5 / 21.2, 1000 of
+// 256 x 1024 56 / 50, 2000 of 256 x 800 86 / 79.
+constexpr int64_t GRADS_MAX_TILES = 512;
+bool stem_grads_f32_fits(const GemmF32Args* dx, const GemmF32Args& w0, const GemmF32Args& w1) {
+  return (!dx || tiles_f32(*dx, 32) <= GRADS_MAX_TILES) && tiles_f32(w0, 32) <= GRADS_MAX_TILES && tiles_f32(w1, 32) <= GRADS_MAX_TILES;
+}
+
+hipError_t stem_grads_f32(stem_ctx* ctx, const GemmF32Args* dx, const GemmF32Args& w0, const GemmF32Args& w1, hipStream_t s) {
+  if ((dx && wide_f32(*dx)) || wide_f32(w0) || wide_f32(w1)) return hipErrorInvalidValue;
+  GradArgs g = {};
+  if (dx) { g.dx = *dx; g.n_dx = (int)tiles_f32(*dx, 32); }
+  g.w[0] = w0; g.w[1] = w1;
+  g.n_w0 = (int)tiles_f32(w0, 32);
+  ProfScope ps(ctx, K_GRADS_F32, s);
+  const unsigned n = (unsigned)(g.n_dx + g.n_w0 + tiles_f32(w1, 32));
+  if (n <= 512) hipLaunchKernelGGL(grads_f32_kernel<2>, dim3(n), dim3(256), 0, s, g);   // K tiles in flight: as for a product by itself
+  else hipLaunchKernelGGL(grads_f32_kernel<1>, dim3(n), dim3(256), 0, s, g);
+  return hipGetLastError();
+}
+
 template <int LA, int LB, int EPI>
 static void launch_f32(const GemmF32Args& p, hipStream_t s) {
   // 64x64 tiles where rounds of two workgroups per CU come out nearly full; else 32x32, two K tiles in flight per
   // wavefront (two workgroups per CU) up to 512 of them and one (four per CU) beyond.  us, 64x64 / 32x32 one / two in flight:
   // gate 1000 x 256 x 1024 12.9 / 11.8 / 13.1, down 22.3 / 12.8 / 10.8; gate 2048 x 512 x 1536 (768 tiles of 64) 44.9 / 40.7 / 42.4;
   // 4096 x 1024 x 2048 gate 151 / 154 / 176, down 137 / 146 / 156, dW 129 / 138 / 147.
-  const int64_t t64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64), t32 = (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32);
+  const int64_t t64 = tiles_f32(p, 64), t32 = tiles_f32(p, 32);
   const int64_t full64 = (t64 + 511) / 512 * 512;
   if (t64 * 10 >= full64 * 9)
     hipLaunchKernelGGL((gemm_f32_kernel<64, 4, 1, LA, LB, EPI>), dim3((unsigned)t64), dim3(256), 0, s, p);
@@ -334,7 +385,7 @@ static void launch_f32(const GemmF32Args& p, hipStream_t s) {
 
 hipError_t stem_gemm_f32(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmF32Args& p, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return hipSuccess;
-  if (std::max(p.lda, p.ldb) >= (1 << 26)) return hipErrorInvalidValue;   // 8 rows of an operand within a 2 GiB window
+  if (wide_f32(p)) return hipErrorInvalidValue;
   ProfScope ps(ctx, kid, s);
   if (la == OP_KC && lb == OP_KC && epi == EPI_F32) launch_f32<OP_KC, OP_KC, EPI_F32>(p, s);
   else if (la == OP_KC && lb == OP_KC && epi == EPI_GATE) launch_f32<OP_KC, OP_KC, EPI_GATE>(p, s);

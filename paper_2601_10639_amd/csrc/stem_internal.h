@@ -30,6 +30,7 @@ enum StemKernelId {
   K_GEMM_UP,         // Up = X Wu^T (dense SwiGLU and the additive variant)
   K_GEMM_DWUP,       // dWu = dV^T X
   K_SORT_MERGE,
+  K_GRADS_F32,       // dx, dWd and dWg of a small fp32 layer in one launch
   K_COUNT_
 };
 
@@ -203,6 +204,9 @@ struct GemmF32Args {
 };
 // operand kinds and epilogues (EPI_F32, EPI_GATE, EPI_DH) as for the bf16 products
 hipError_t stem_gemm_f32(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmF32Args& p, hipStream_t s);
+// dx (may be null), dW_down and dW_gate in one launch, where all three are small
+bool stem_grads_f32_fits(const GemmF32Args* dx, const GemmF32Args& w0, const GemmF32Args& w1);
+hipError_t stem_grads_f32(stem_ctx* ctx, const GemmF32Args* dx, const GemmF32Args& w0, const GemmF32Args& w1, hipStream_t s);
 hipError_t stem_fill_zero(void* p, size_t bytes, hipStream_t s);   // a kernel, not a memset node
 // H = SiLU(G) * E[ids]; is_bf16 selects the element type of G, E, H
 hipError_t stem_silu_gather(stem_ctx* ctx, int is_bf16, const void* G, const int32_t* ids, const void* E,

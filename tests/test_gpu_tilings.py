@@ -56,6 +56,7 @@ def test_bf16_products_on_every_tiling(T, d, F, up):
     (1030, 36, 1028),     # forward and dH with K of one tile and a bit; dx, weight gradients with two K tiles in flight
     (33, 4, 8),           # K of one 16-byte piece, one row in the last tile
     (2030, 1004, 2044),   # every product on 64x64 tiles, ragged in M, N and K
+    (1000, 256, 1028),    # the products behind dG in one launch of more than 512 workgroups
     (2030, 36, 1020),     # forward and dH on 64x64 tiles with fewer K tiles than wavefronts
 ])
 def test_f32_products_on_both_tilings(T, d, F):
@@ -133,4 +134,21 @@ def test_sort_on_every_path(T, V):
         L.stem_sync_status(ctx)
         Hn.check_integers(eg, ids)
         ids = ids[::-1].copy()
+    ctx.close()
+
+
+def test_f32_backward_without_dx_and_with_dx_over_its_inputs():
+    """dx may take the place of dy, which the products before it have read: then they are launches of their own."""
+    T, d, F = 300, 64, 192
+    s = inputs.StemShape("f32-alias", d, F, 300, 1, T, "f32")
+    inp = inputs.layer_inputs(s, seed=69, device=DEV, tokens=T)
+    ctx = Hn.make_ctx(s, T)
+    out = Hn.hip_forward_backward(ctx, inp)
+    for dx in (None, inp["dy"]):
+        g = {k: torch.empty_like(out[k]) for k in ("dW_gate", "dW_down", "dU")}
+        L.stem_ffn_backward(ctx, inp["dy"], inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"], out["G"], out["H"],
+                            dx, g["dW_gate"], g["dW_down"], g["dU"])
+        L.stem_sync_status(ctx)
+        assert all(torch.allclose(g[k], out[k], rtol=0, atol=1e-6 * float(out[k].abs().max())) for k in g)
+    assert torch.allclose(inp["dy"], out["dx"], rtol=0, atol=1e-6 * float(out["dx"].abs().max()))
     ctx.close()
