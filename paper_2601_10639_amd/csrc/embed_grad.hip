@@ -1,5 +1,5 @@
 // Gradient of the per-layer table, restricted to the rows a batch touches:
-// stable LSD radix sort of (token id, position), distinct ids with run offsets, and a
+// stable sort of (token id, position) by radix passes (in LDS, as merged runs, or digit by digit), distinct ids with run offsets, and a
 // fixed-order segmented sum of the per-token row gradients.  Integer results are unique,
 // floating sums use one fixed association, so every run gives the same bits.
 #include "stem_internal.h"
