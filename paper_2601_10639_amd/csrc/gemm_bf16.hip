@@ -63,27 +63,32 @@ __device__ __forceinline__ uint32_t lds_addr(const char* p) {   // p points into
 // apart, so the fragments of a wavefront's four 32-row blocks sit at one address plus immediates)
 __device__ __forceinline__ int lds_swz(int row) { return ((row >> 1) ^ (((row >> 3) & 3) << 1)) & 7; }
 
-// A buffer resource that moves along the operand: base advances, the record count shrinks.
+// A buffer resource that moves along the operand: base advances, the record count shrinks, to zero at the operand's end
+// and not below: the loaders request up to three K tiles beyond it, and three K tiles of an operand whose rows are
+// millions of elements long are more than an int holds.
 // The descriptor is rebuilt once per K tile (a handful of scalar instructions), not per load.
 struct Window {
   const char* base;
-  int left;  // bytes from base to the end of the operand (operands stay below 2 GiB; may go negative)
+  int left;  // bytes from base to the end of the operand (operands stay below 2 GiB), zero past it
   rsrc_t r;
   __device__ __forceinline__ void set(const void* p, int64_t bytes) {
     base = reinterpret_cast<const char*>(p);
-    left = (int)bytes;
+    left = bytes < 0 ? 0 : (int)bytes;
     rebuild();
   }
-  __device__ __forceinline__ void rebuild() {
-    r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, left < 0 ? 0 : left, 0x00020000);
-  }
+  __device__ __forceinline__ void rebuild() { r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, left, 0x00020000); }
   __device__ __forceinline__ rsrc_t rsrc() const { return r; }
   // the same descriptor as four words (base, stride 0, byte count, raw-buffer flags), for loads issued as assembly
   __device__ __forceinline__ u32x4_t words() const {
     const uint64_t b = reinterpret_cast<uint64_t>(base);
-    return u32x4_t{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, (uint32_t)(left < 0 ? 0 : left), 0x00020000u};
+    return u32x4_t{(uint32_t)b, (uint32_t)(b >> 32) & 0xffffu, (uint32_t)left, 0x00020000u};
   }
-  __device__ __forceinline__ void advance(int bytes) { base += bytes; left -= bytes; rebuild(); }
+  __device__ __forceinline__ void advance(int bytes) {   // bytes: a K tile, less than 2^30
+    base += bytes;
+    const int l = left - bytes;
+    left = l < 0 ? 0 : l;
+    rebuild();
+  }
 };
 
 // One direct-to-LDS load of 16 bytes per lane, written as assembly.  The compiler orders every

@@ -152,3 +152,37 @@ def test_f32_backward_without_dx_and_with_dx_over_its_inputs():
         assert all(torch.allclose(g[k], out[k], rtol=0, atol=1e-6 * float(out[k].abs().max())) for k in g)
     assert torch.allclose(inp["dy"], out["dx"], rtol=0, atol=1e-6 * float(out["dx"].abs().max()))
     ctx.close()
+
+
+def _reference64(inp):
+    """Forward and backward of the layer in 64-bit torch on the GPU (plain products; for layers too wide for the oracle's
+    host arrays)."""
+    x, dy, Wg, Wd, E = (inp[k].double() for k in ("x", "dy", "W_gate", "W_down", "E"))
+    Er = E[inp["ids"].long()]
+    G = x @ Wg.T
+    s = torch.sigmoid(G)
+    H, dH = G * s * Er, dy @ Wd
+    dG = dH * Er * s * (1 + G * (1 - s))
+    return {"y": H @ Wd.T, "G": G, "H": H, "dU": dH * G * s, "dx": dG @ Wg, "dW_gate": dG.T @ x, "dW_down": dy.T @ H}
+
+
+def _max_rel(got, ref):
+    return float((got.double() - ref).abs().max() / ref.abs().max())
+
+
+@pytest.mark.parametrize("T", [1, 65])   # a K tile of the weight gradients with 1 row, a second one with 1 row
+@pytest.mark.parametrize("wide_d", [False, True])
+def test_bf16_layer_with_the_longest_rows(T, wide_d):
+    """64 x 8388544, just below 2^31 bytes of fp32 weight gradient: a K tile of [T, d_ff] is 1 GiB, so the three K
+    tiles that the weight gradients' loaders request beyond the last one lie more than 2^31 bytes behind the operand."""
+    d, F = (8388544, 64) if wide_d else (64, 8388544)
+    s = inputs.StemShape("longest-rows", d, F, 3, 1, T, "bf16")
+    inp = inputs.layer_inputs(s, seed=71, device=DEV, tokens=T)
+    if wide_d:   # gate activations of order one
+        inp["W_gate"] *= 0.03
+    ctx = Hn.make_ctx(s, T)
+    out = Hn.hip_forward_backward(ctx, inp)
+    L.stem_sync_status(ctx)
+    errs = {k: _max_rel(out[k], v) for k, v in _reference64(inp).items()}
+    assert all(v <= Hn.TOL["bf16"] for v in errs.values()), errs
+    ctx.close()
