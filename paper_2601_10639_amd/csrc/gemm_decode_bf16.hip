@@ -55,12 +55,14 @@ __device__ __forceinline__ void lds_dma_16(rsrc_t rs, char* lds_dst, uint32_t of
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)lds_dst, 16, off, soff, 0, 0);
 }
 
-// Waits until at most min(younger, MOST) K tiles of LOADS loads each and EXTRA more loads are outstanding; the count is
-// an immediate.
-template <int LOADS, int MOST, int EXTRA>
+// Waits until at most min(younger, MOST) K tiles of LOADS loads each are outstanding; the count is an immediate.  It
+// counts the K tiles alone, each of them exactly LOADS instructions: whatever else a wavefront has in flight, and however
+// many instructions the compiler makes of it, only makes the wait longer.  (Counting the gate product's table-row loads in
+// as well is 0.1 us shorter where a wavefront has one K tile, and reads a K tile too early if they become fewer.)
+template <int LOADS, int MOST>
 __device__ __forceinline__ void wait_all_but(int younger) {
-  if (MOST == 0 || younger >= MOST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MOST * LOADS + EXTRA) : "memory");
-  else wait_all_but<LOADS, (MOST > 0 ? MOST - 1 : 0), EXTRA>(younger);
+  if (MOST == 0 || younger >= MOST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MOST * LOADS) : "memory");
+  else wait_all_but<LOADS, (MOST > 0 ? MOST - 1 : 0)>(younger);
 }
 
 // FA x 16 tokens, FB x 16 weight rows, W wavefronts with D K tiles in flight each
@@ -149,8 +151,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
 #pragma unroll
     for (int b = 0; b < FB; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  // The row pieces are younger than the first D K tiles and older than the rest: the waits for the first D allow for
-  // these QT loads (a row of a large table takes microseconds to arrive), which the barriers keep in this place.
+  // The row pieces are younger than the first D K tiles and older than the rest; the barriers keep them in this place.
   auto load_rows = [&]() __attribute__((always_inline)) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -178,8 +179,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
   }
   int slot = 0;
   for (int i = 0; i < nw; ++i) {
-    if (EPI == EPI_GATE && i < D) wait_all_but<LOADS, D - 1, QT>(nw - 1 - i);
-    else wait_all_but<LOADS, D - 1, 0>(nw - 1 - i);
+    wait_all_but<LOADS, D - 1>(nw - 1 - i);
     const char* const f = frag + slot * S::SLOT;
     bf16x8_t xa[2][FA], xb[2][FB];
 #pragma unroll

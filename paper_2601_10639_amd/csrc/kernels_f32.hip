@@ -86,12 +86,13 @@ struct TileF32 {
   }
 };
 
-// Waits until at most min(younger, MOST) K tiles of LOADS loads each and EXTRA more loads are outstanding; the count is
-// an immediate.
-template <int LOADS, int MOST, int EXTRA>
+// Waits until at most min(younger, MOST) K tiles of LOADS loads each are outstanding; the count is an immediate.  It
+// counts the K tiles alone, each of them exactly LOADS instructions: whatever else a wavefront has in flight, and however
+// many instructions the compiler makes of it, only makes the wait longer.
+template <int LOADS, int MOST>
 __device__ __forceinline__ void wait_all_but(int younger) {
-  if (MOST == 0 || younger >= MOST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MOST * LOADS + EXTRA) : "memory");
-  else wait_all_but<LOADS, (MOST > 0 ? MOST - 1 : 0), EXTRA>(younger);
+  if (MOST == 0 || younger >= MOST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MOST * LOADS) : "memory");
+  else wait_all_but<LOADS, (MOST > 0 ? MOST - 1 : 0)>(younger);
 }
 
 template <int TS, int W, int D>
@@ -108,7 +109,6 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Args& p, int block, c
   constexpr int NB = TS / 32, OPERAND = TS * KT * 4, SLOT = 2 * OPERAND, LOADS = TA::LOADS + TB::LOADS;
   constexpr int PITCH = ShapeF32<TS, W, D>::PITCH;
   constexpr int QUADS = TS * TS / 4, QT = (QUADS + 64 * W - 1) / (64 * W), LPR = TS / 4;
-  constexpr int EXTRA = EPI == EPI_F32 ? 0 : EPI == EPI_GATE ? QT : 2 * QT;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ntn = (p.N + TS - 1) / TS;
   const int tm = block / ntn, tn = block - tm * ntn;
@@ -137,8 +137,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Args& p, int block, c
   };
   f32x4_t ev[QT], gv[QT];
   bool bad = false;
-  // Younger than the first D K tiles and older than the rest: the waits for the first D allow for these EXTRA loads,
-  // which the barriers keep in this place.
+  // Younger than the first D K tiles and older than the rest; the barriers keep them in this place.
   auto load_inputs = [&]() __attribute__((always_inline)) {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -174,8 +173,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Args& p, int block, c
       for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
   int slot = 0;
   for (int i = 0; i < nw; ++i) {
-    if (EPI != EPI_F32 && i < D) wait_all_but<LOADS, D - 1, EXTRA>(nw - 1 - i);
-    else wait_all_but<LOADS, D - 1, 0>(nw - 1 - i);
+    wait_all_but<LOADS, D - 1>(nw - 1 - i);
     const char* const st = ring + slot * SLOT;
     // the fragments of group g + 1 are read before the MFMAs of group g
     f32x4_t fa[2][NB], fb[2][NB];
