@@ -46,12 +46,14 @@ __device__ __forceinline__ void lds_dma_16(rsrc_t rs, char* lds_dst, uint32_t of
 // One operand's K tile: TS x KT floats in LDS, KC as TS rows of 128 bytes (16-byte chunk c of row r at slot
 // c ^ (r >> 1): a fragment read's 16 rows touch all banks once), MC as KT rows of TS floats.  A load of 1 KB covers ROWS
 // of these rows; its window starts at the first of them (operands may exceed 2 GiB), and the lanes outside the matrix
-// are given an offset beyond it.
-template <int TS, int LOP>
+// are given an offset beyond it.  WIDE: rows so long that 8 of them exceed a window; each lane has a 64-bit address of
+// its own and the pieces pass through registers.
+template <int TS, int LOP, bool WIDE>
 struct TileF32 {
   static constexpr int LOADS = TS * KT * 4 / 1024, CH = LOP == OP_KC ? 8 : TS / 4, ROWS = 64 / CH;   // CH: chunks per row
   const char* at;        // the next K tile's first row
   int64_t group, step;   // bytes from one load's rows to the next one's, from one of this wavefront's K tiles to its next
+  int64_t lane_row;      // WIDE: bytes to this lane's row of a load
   uint32_t off[LOADS];
   static __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
   __device__ __forceinline__ void init(const float* p, int64_t ld, int rows, int row0, int lane, int wave, int waves) {
@@ -59,10 +61,11 @@ struct TileF32 {
     at = reinterpret_cast<const char*>(p + (LOP == OP_KC ? row0 * ld : row0)) + wave * kt;
     group = ROWS * pitch;
     step = waves * kt;
+    lane_row = lane / CH * pitch;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
       const int r = i * ROWS + lane / CH, c = lane % CH;                         // row in LDS, chunk slot
-      const uint32_t o = (uint32_t)(lane / CH * pitch) + (uint32_t)((LOP == OP_KC ? c ^ swz(r) : c) << 4);
+      const uint32_t o = (WIDE ? 0 : (uint32_t)lane_row) + (uint32_t)((LOP == OP_KC ? c ^ swz(r) : c) << 4);
       off[i] = row0 + (LOP == OP_KC ? r : c * 4) < rows ? o : OOB;
     }
   }
@@ -70,9 +73,16 @@ struct TileF32 {
   __device__ __forceinline__ void request(int left, char* tile, int lane) {
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at + i * group), 0, 0x7fffffff, 0x00020000);
       const int r = i * ROWS + lane / CH, k = LOP == OP_KC ? ((lane % CH) ^ swz(r)) << 2 : r;
-      lds_dma_16(rs, tile + i * 1024, k < left ? off[i] : OOB);
+      const uint32_t o = k < left ? off[i] : OOB;
+      if (WIDE) {
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+        if (o != OOB) v = *reinterpret_cast<const f32x4_t*>(at + i * group + lane_row + o);
+        *reinterpret_cast<f32x4_t*>(tile + i * 1024 + lane * 16) = v;
+      } else {
+        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(at + i * group), 0, 0x7fffffff, 0x00020000);
+        lds_dma_16(rs, tile + i * 1024, o);
+      }
     }
     at += step;
   }
@@ -102,15 +112,15 @@ struct ShapeF32 {
 };
 
 // tile `block` of a product; smem: ShapeF32::LDS_BYTES of LDS
-template <int TS, int W, int D, int LA, int LB, int EPI>
+template <int TS, int W, int D, int LA, int LB, int EPI, bool WIDE = false>
 __device__ __forceinline__ void gemm_f32_tile(const GemmF32Args& p, int block, char* smem) {
-  typedef TileF32<TS, LA> TA;
-  typedef TileF32<TS, LB> TB;
+  typedef TileF32<TS, LA, WIDE> TA;
+  typedef TileF32<TS, LB, WIDE> TB;
   constexpr int NB = TS / 32, OPERAND = TS * KT * 4, SLOT = 2 * OPERAND, LOADS = TA::LOADS + TB::LOADS;
   constexpr int PITCH = ShapeF32<TS, W, D>::PITCH;
   constexpr int QUADS = TS * TS / 4, QT = (QUADS + 64 * W - 1) / (64 * W), LPR = TS / 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ntn = (p.N + TS - 1) / TS;
+  const int ntn = (p.N - 1) / TS + 1;
   const int tm = block / ntn, tn = block - tm * ntn;
   const int m0 = tm * TS, n0 = tn * TS;
   const int r = lane & 31, half = lane >> 5;
@@ -127,7 +137,7 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Args& p, int block, c
   TB tb;
   ta.init(p.A, p.lda, p.M, m0, lane, wave, W);
   tb.init(p.B, p.ldb, p.N, n0, lane, wave, W);
-  const int nk = (p.K + KT - 1) / KT;
+  const int nk = (p.K - 1) / KT + 1;
   const int nw = nk > wave ? (nk - wave + W - 1) / W : 0;    // this wavefront's K tiles
   char* const ring = smem + wave * (D * SLOT);
   auto request = [&](int i, int slot) __attribute__((always_inline)) {
@@ -260,6 +270,17 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_kernel(GemmF32Args p) {
   gemm_f32_tile<TS, W, D, LA, LB, EPI>(p, blockIdx.x, smem);
 }
 
+// Rows of 2^26 elements and more, or more tiles than one launch takes (at most 4096 workgroups walk the tiles).  Bound by
+// one load after another where the long dimension is summed over: 35 tokens of 8 x 67108868, forward and backward, 3.8 s.
+template <int LA, int LB, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_wide_kernel(GemmF32Args p, int tiles) {
+  __shared__ __attribute__((aligned(16))) char smem[ShapeF32<32, 4, 1>::LDS_BYTES];
+  for (int b = blockIdx.x; b < tiles; b += gridDim.x) {
+    gemm_f32_tile<32, 4, 1, LA, LB, EPI, true>(p, b, smem);
+    __syncthreads();   // the partial tiles have been read
+  }
+}
+
 // The products of a backward pass that wait for nothing but dG, in one launch: dx first, the longest sum.  One after
 // another they leave CUs idle three times over (1000 tokens, 256 x 1024: 256 workgroups each where 512 to 1024 fit, 11.5 +
 // 10.7 + 10.8 us against 22.0; 128 tokens of 64 x 256, three launches against one, 6.5 + 6.4 + 6.1 against 6.3).
@@ -341,19 +362,19 @@ hipError_t stem_fill_zero(void* p, size_t bytes, hipStream_t s) {   // bytes is 
   return hipGetLastError();
 }
 
-static int64_t tiles_f32(const GemmF32Args& p, int ts) { return (int64_t)((p.M + ts - 1) / ts) * ((p.N + ts - 1) / ts); }
-static bool wide_f32(const GemmF32Args& p) { return std::max(p.lda, p.ldb) >= (1 << 26); }   // 8 rows of an operand within a 2 GiB window
+static int64_t tiles_f32(const GemmF32Args& p, int ts) { return (int64_t)((p.M - 1) / ts + 1) * ((p.N - 1) / ts + 1); }
+static bool wide_f32(const GemmF32Args& p) { return std::max(p.lda, p.ldb) >= (1 << 26); }   // 8 rows of an operand exceed a 2 GiB window
 
 // Up to here each product alone is at most one round of workgroups, two per CU; beyond, a launch each fills the chip and
 // may take the larger tiles.  Forward and backward, us, three launches / one: 600 tokens of 128 x 400 32.5 / 21.2, 1000 of
 // 256 x 1024 56 / 50, 2000 of 256 x 800 86 / 79.
 constexpr int64_t GRADS_MAX_TILES = 512;
 bool stem_grads_f32_fits(const GemmF32Args* dx, const GemmF32Args& w0, const GemmF32Args& w1) {
-  return (!dx || tiles_f32(*dx, 32) <= GRADS_MAX_TILES) && tiles_f32(w0, 32) <= GRADS_MAX_TILES && tiles_f32(w1, 32) <= GRADS_MAX_TILES;
+  auto small = [](const GemmF32Args& p) { return tiles_f32(p, 32) <= GRADS_MAX_TILES && !wide_f32(p); };
+  return (!dx || small(*dx)) && small(w0) && small(w1);
 }
 
 hipError_t stem_grads_f32(stem_ctx* ctx, const GemmF32Args* dx, const GemmF32Args& w0, const GemmF32Args& w1, hipStream_t s) {
-  if ((dx && wide_f32(*dx)) || wide_f32(w0) || wide_f32(w1)) return hipErrorInvalidValue;
   GradArgs g = {};
   if (dx) { g.dx = *dx; g.n_dx = (int)tiles_f32(*dx, 32); }
   g.w[0] = w0; g.w[1] = w1;
@@ -373,7 +394,10 @@ static void launch_f32(const GemmF32Args& p, hipStream_t s) {
   // 4096 x 1024 x 2048 gate 151 / 154 / 176, down 137 / 146 / 156, dW 129 / 138 / 147.
   const int64_t t64 = tiles_f32(p, 64), t32 = tiles_f32(p, 32);
   const int64_t full64 = (t64 + 511) / 512 * 512;
-  if (t64 * 10 >= full64 * 9)
+  const bool large = t64 * 10 >= full64 * 9;
+  if (wide_f32(p) || (large ? t64 : t32) >= (1 << 24))   // a launch has fewer than 2^32 threads
+    hipLaunchKernelGGL((gemm_f32_wide_kernel<LA, LB, EPI>), dim3((unsigned)std::min<int64_t>(t32, 4096)), dim3(256), 0, s, p, (int)t32);
+  else if (large)
     hipLaunchKernelGGL((gemm_f32_kernel<64, 4, 1, LA, LB, EPI>), dim3((unsigned)t64), dim3(256), 0, s, p);
   else if (t32 <= 512)
     hipLaunchKernelGGL((gemm_f32_kernel<32, 4, 2, LA, LB, EPI>), dim3((unsigned)t32), dim3(256), 0, s, p);
@@ -383,7 +407,6 @@ static void launch_f32(const GemmF32Args& p, hipStream_t s) {
 
 hipError_t stem_gemm_f32(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmF32Args& p, hipStream_t s) {
   if (p.M <= 0 || p.N <= 0) return hipSuccess;
-  if (wide_f32(p)) return hipErrorInvalidValue;
   ProfScope ps(ctx, kid, s);
   if (la == OP_KC && lb == OP_KC && epi == EPI_F32) launch_f32<OP_KC, OP_KC, EPI_F32>(p, s);
   else if (la == OP_KC && lb == OP_KC && epi == EPI_GATE) launch_f32<OP_KC, OP_KC, EPI_GATE>(p, s);

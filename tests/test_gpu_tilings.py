@@ -154,6 +154,13 @@ def test_f32_backward_without_dx_and_with_dx_over_its_inputs():
     ctx.close()
 
 
+def _sum_over_tokens(a, b):
+    """a^T b, the wider operand in pieces of fewer than 2^31 elements (the library product behind torch needs that)."""
+    if a.shape[1] > b.shape[1]:
+        return _sum_over_tokens(b, a).T
+    return torch.cat([a.T @ p.contiguous() for p in b.split(1 << 24, dim=1)], dim=1)
+
+
 def _reference64(inp):
     """Forward and backward of the layer in 64-bit torch on the GPU (plain products; for layers too wide for the oracle's
     host arrays)."""
@@ -163,7 +170,8 @@ def _reference64(inp):
     s = torch.sigmoid(G)
     H, dH = G * s * Er, dy @ Wd
     dG = dH * Er * s * (1 + G * (1 - s))
-    return {"y": H @ Wd.T, "G": G, "H": H, "dU": dH * G * s, "dx": dG @ Wg, "dW_gate": dG.T @ x, "dW_down": dy.T @ H}
+    return {"y": H @ Wd.T, "G": G, "H": H, "dU": dH * G * s, "dx": dG @ Wg, "dW_gate": _sum_over_tokens(dG, x),
+            "dW_down": _sum_over_tokens(dy, H)}
 
 
 def _max_rel(got, ref):
@@ -185,4 +193,24 @@ def test_bf16_layer_with_the_longest_rows(T, wide_d):
     L.stem_sync_status(ctx)
     errs = {k: _max_rel(out[k], v) for k, v in _reference64(inp).items()}
     assert all(v <= Hn.TOL["bf16"] for v in errs.values()), errs
+    ctx.close()
+
+
+@pytest.mark.parametrize("T,d,F", [(3, 1 << 26, 8), (35, 8, (1 << 26) + 4)])
+def test_f32_layer_with_rows_beyond_a_buffer_window(T, d, F):
+    """Eight rows of 2^26 floats are 2 GiB.  Small integers times a power of two make the sums over d_model exact, a table
+    of few nonzero columns those over d_ff short, so the tolerance is that of the other fp32 layers."""
+    g = torch.Generator(device=DEV).manual_seed(73)
+    r = lambda *sh: torch.randint(-1, 2, sh, generator=g, device=DEV, dtype=torch.int8).float()  # noqa: E731
+    inp = {"x": r(T, d), "dy": r(T, d), "W_gate": r(F, d).mul_(2.0 ** -12 if d > F else 1.0),
+           "W_down": r(d, F).mul_(2.0 ** -12 if d > F else 1.0), "E": torch.zeros(3, F, device=DEV),
+           "ids": torch.arange(T, device=DEV, dtype=torch.int32) % 3}
+    cols = torch.arange(F, device=DEV) if F < 100 else torch.cat([torch.tensor([0, 1, F - 2, F - 1], device=DEV),
+                                                                   torch.randint(0, F, (500,), generator=g, device=DEV)])
+    inp["E"][:, cols] = torch.randn(3, len(cols), generator=g, device=DEV)
+    ctx = Hn.make_ctx(inputs.StemShape("f32-wide", d, F, 3, 1, T, "f32"), T)
+    out = Hn.hip_forward_backward(ctx, inp)
+    L.stem_sync_status(ctx)
+    errs = {k: _max_rel(out[k], v) for k, v in _reference64(inp).items()}
+    assert all(v <= Hn.TOL["f32"] for v in errs.values()), errs
     ctx.close()
