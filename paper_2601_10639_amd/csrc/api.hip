@@ -97,19 +97,6 @@ void release(stem_ctx* c) {
   free(c);
 }
 
-// Tokens per chunk of a long host-table batch.  The down product of one chunk is about one round of 256x256 tiles
-// (STEM_PF_CHUNK_TILES; better than 224 for a call by itself), and two rounds from 2048 tiles on: the row copies of this
-// and, in a stack of layers, of the next call hold 32 CUs each, so a round of 256 tiles takes two turns of what is left.
-// 65536 tokens, d_model 2048, chunks of 256 / 512 / 1024 tiles: calls one after another 6.3 / 5.8 / 5.5 ms, one by itself
-// 4.99 / 4.88 / 5.46; 32768 tokens 3.5 / 3.2 / 3.3 and 2.92 / 3.16 / 3.56, where the first rows would be waited for too long.
-int64_t prefetch_chunk_tokens(const stem_ctx* c, int64_t T) {
-  const int64_t tile_cols = (c->desc.d_model + 255) / 256, tiles = (T + 255) / 256 * tile_cols;
-  const int64_t chunk_tiles = tiles >= 2048 ? 2 * STEM_PF_CHUNK_TILES : STEM_PF_CHUNK_TILES;
-  const int64_t tokens = std::max<int64_t>(1, chunk_tiles / tile_cols) * 256;
-  const int64_t chunks = (T + tokens - 1) / tokens;
-  return tokens * std::max<int64_t>(1, (chunks + STEM_PF_MAX_CHUNKS - 1) / STEM_PF_MAX_CHUNKS);
-}
-
 EmbedScratch embed_scratch(const stem_ctx* c) {
   EmbedScratch w;
   w.sort_keys[0] = c->sort_keys[0]; w.sort_keys[1] = c->sort_keys[1];
@@ -701,7 +688,11 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
   // first use, so that the rows the first tokens need cross the link first.  Long batches are cut
   // into chunks; an event after each chunk's rows lets the forward
   // call run the gather and the down product of a chunk while later rows are still on the link.
-  int64_t chunk_tokens = prefetch_chunk_tokens(c, T);
+  // Chunk size: the down product of one chunk is about one round of 256x256 tiles
+  // (STEM_PF_CHUNK_TILES); whole multiples of that if the batch is very long.
+  const int64_t tile_cols = (c->desc.d_model + 255) / 256;
+  int64_t chunk_tokens = std::max<int64_t>(1, STEM_PF_CHUNK_TILES / tile_cols) * 256;
+  chunk_tokens *= std::max<int64_t>(1, ((T + chunk_tokens - 1) / chunk_tokens + STEM_PF_MAX_CHUNKS - 1) / STEM_PF_MAX_CHUNKS);
   int nchunks = (int)((T + chunk_tokens - 1) / chunk_tokens);
   if (nchunks < 2) { nchunks = 1; chunk_tokens = std::max<int64_t>(T, 1); }
   int64_t chunk_end[STEM_PF_MAX_CHUNKS] = {0};
@@ -835,7 +826,9 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
   // One pass over the tokens.  c->slot marks the ids of this batch (-1 = not seen yet) and holds the
   // row each one reads: its cache slot, or a staging row behind the cache, numbered in order of
   // first use so that the rows the first tokens need cross the link first.
-  int64_t chunk_tokens = prefetch_chunk_tokens(c, T);
+  const int64_t tile_cols = (c->desc.d_model + 255) / 256;
+  int64_t chunk_tokens = std::max<int64_t>(1, STEM_PF_CHUNK_TILES / tile_cols) * 256;
+  chunk_tokens *= std::max<int64_t>(1, ((T + chunk_tokens - 1) / chunk_tokens + STEM_PF_MAX_CHUNKS - 1) / STEM_PF_MAX_CHUNKS);
   int nchunks = (int)((T + chunk_tokens - 1) / chunk_tokens);
   if (nchunks < 2) { nchunks = 1; chunk_tokens = std::max<int64_t>(T, 1); }
   int64_t chunk_end[STEM_PF_MAX_CHUNKS] = {0};

@@ -37,7 +37,7 @@ enum StemKernelId {
 #define STEM_MAX_PROF_EVENTS 8192
 #define STEM_PF_MAX_CHUNKS 16
 #define STEM_EDIT_MAX_TOKENS 64
-#define STEM_PF_CHUNK_TILES 256     // one round of 256x256 down-product tiles per chunk
+#define STEM_PF_CHUNK_TILES 256     // one round of 256x256 down-product tiles per chunk (measured better than 224 and 512)
 
 struct stem_ctx {
   stem_layer_desc desc;
