@@ -408,8 +408,9 @@ def _median_ms(fn, steps, warmup):
     """Wall-clock per call (device idle before and after each), median / p10 / p90 in ms."""
     import numpy as np
     import torch
-    for _ in range(warmup):
+    for _ in range(warmup):   # one after another: a host-table pass writes rows that the pass before it reads
         fn()
+        torch.cuda.synchronize()
     ts = []
     for _ in range(steps):
         torch.cuda.synchronize()
@@ -587,6 +588,7 @@ def _host_table_one(args, shape, dev, ids_kind, shared):
     L.stem_profile_reset(ctx)
     for _ in range(3):
         step()
+        torch.cuda.synchronize()
     prof = L.stem_profile_read(ctx)
     L.stem_profile_enable(ctx, False)
     kernels = {k: {"avg_ms": round(v[0] / v[1], 5), "launches": v[1]} for k, v in prof.items()}
@@ -665,6 +667,7 @@ def bench_host_training(args, shape, dev):
     L.stem_profile_reset(ctx)
     for _ in range(3):
         step()
+        torch.cuda.synchronize()
     prof = L.stem_profile_read(ctx)
     L.stem_profile_enable(ctx, False)
     kernels = {k: {"avg_ms": round(val[0] / val[1], 5), "launches": val[1]} for k, val in prof.items()}

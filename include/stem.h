@@ -240,6 +240,10 @@ stem_status stem_ffn_up_backward(stem_ctx* ctx, const void* dy, const void* x, c
  * is the same layer.  *n_uniq_host (host) is valid on return; uniq_ids_host (host, may be
  * NULL, capacity cap) receives the distinct ids.  *ready_event is a hipEvent_t owned by
  * the context, recorded after the copies, valid until the next stem_prefetch_rows call.
+ * The copies wait for nothing but this context's previous prefetch: a forward call that reads E_compact and remap
+ * must have finished on the device (the host has waited for its stream, or for an event behind it) before the next
+ * call writes the same buffers.  Calls that are to overlap each other, layers in a stack or batches in turn, take a
+ * context, an E_compact and a remap each.
  * Returns STEM_ERR_WORKSPACE if there are more than cap distinct ids, STEM_ERR_ID_RANGE if
  * an id is outside [0, V).  Blocks only for the host-side de-duplication. */
 stem_status stem_prefetch_rows(stem_ctx* ctx, const void* E_host, const int32_t* ids_host, int64_t T,

@@ -451,6 +451,40 @@ def test_prefetch_rows_chunked_with_ragged_last_chunk():
     assert Hn.max_rel(y.float().cpu(), ref) <= Hn.TOL["bf16"]
 
 
+def test_host_table_batches_in_turn_on_two_contexts():
+    """Batches of different ids follow each other on two contexts with their own E_compact and remap; a pair is written
+    again only after the forward that read it has finished, while the other pair's forward may still run."""
+    T, V, d, F = 20000, 5000, 2048, 128
+    s = inputs.StemShape("host-in-turn", d, F, V, 1, T, "bf16")
+    bf = torch.bfloat16
+    x, Wg, Wd = inputs.normal((T, d), 1.0, 46, bf, DEV), inputs.normal((F, d), 0.02, 47, bf, DEV), inputs.normal((d, F), 0.02, 48, bf, DEV)
+    E_host = torch.empty(V, F, dtype=bf, pin_memory=True)
+    E_host.copy_(inputs.normal((V, F), 0.02, 49, bf, DEV))
+    sides = [dict(ctx=Hn.make_ctx(s, T), E=torch.empty(V, F, dtype=bf, device=DEV), done=None,
+                  remap=torch.empty(T, dtype=torch.int32, device=DEV)) for _ in range(2)]
+    ids = [inputs.uniform_ids(T, V, seed=50 + k) if k % 2 else inputs.zipf_ids(T, V, seed=50 + k) for k in range(6)]
+    ys = []
+    for k, batch in enumerate(ids):
+        q = sides[k % 2]
+        if q["done"] is not None:
+            q["done"].synchronize()
+        n, ready = L.stem_prefetch_rows(q["ctx"], E_host, torch.from_numpy(batch), q["E"], q["remap"])
+        ys.append(torch.empty(T, d, dtype=bf, device=DEV))
+        L.stem_ffn_forward(q["ctx"], x, q["remap"], Wg, Wd, q["E"], ys[-1], wait_event=ready, E_rows=n)
+        q["done"] = torch.cuda.Event()
+        q["done"].record()
+    for q in sides:
+        L.stem_sync_status(q["ctx"])
+    E = E_host.to(DEV)
+    for batch, y in zip(ids, ys):
+        whole = torch.empty_like(y)
+        L.stem_ffn_forward(sides[0]["ctx"], x, torch.from_numpy(batch).to(DEV), Wg, Wd, E, whole)
+        L.stem_sync_status(sides[0]["ctx"])
+        assert float((y.float() - whole.float()).abs().max() / whole.float().abs().max()) <= Hn.TOL["bf16"]
+    for q in sides:
+        q["ctx"].close()
+
+
 @pytest.mark.parametrize("T,d", [(3000, 128), (20000, 2048)])   # 20000 tokens at d_model 2048: three chunks
 def test_lfu_row_cache_stream_matches_the_oracle_policy(T, d):
     """Ten batches of one Zipf stream through the cached prefetch: remap, miss count and the content
