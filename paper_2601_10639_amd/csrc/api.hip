@@ -97,6 +97,14 @@ void release(stem_ctx* c) {
   free(c);
 }
 
+// The kernel of a forward product [T,K] x [N,K]^T of a bf16 layer.  A decode-sized product takes the decode kernel while one
+// round of its workgroups covers it, then the few-row kernel (128x64 tiles, the down product split along K so that both
+// launches fill the chip).
+StemRoute forward_route(int64_t T, int N, int K, int d_ff) {
+  if (T <= 512 && stem_gemm_decode_fits((int)T, N, K)) return ROUTE_DECODE;
+  return T <= 512 && stem_gemm_skinny_fits((int)T, d_ff) ? ROUTE_FEW_ROW : ROUTE_TILES;
+}
+
 EmbedScratch embed_scratch(const stem_ctx* c) {
   EmbedScratch w;
   w.sort_keys[0] = c->sort_keys[0]; w.sort_keys[1] = c->sort_keys[1];
@@ -117,6 +125,24 @@ stem_status stem_fail(stem_ctx* c, stem_status st, const char* fmt, ...) {
 }
 
 extern "C" {
+
+int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens) {
+  // partial products of up to 8 K slices of a [T,d] or [d,F] output
+  return std::min<int64_t>(STEM_SPLITK_WS_MAX, (int64_t)8 * 4 * d_model * std::max<int64_t>({max_tokens, d_ff, 1}));
+}
+
+void stem_route_forward(int d, int F, int64_t T, int32_t* route) {
+  const int64_t ws = stem_route_splitk_bytes(d, F, T);
+  for (int down = 0; down < 2; ++down) {
+    const int N = down ? d : F, K = down ? F : d;
+    int32_t* r = route + 4 * down;
+    switch (forward_route(T, N, K, F)) {
+      case ROUTE_DECODE: stem_route_decode((int)T, N, K, down ? EPI_BF16 : EPI_GATE, ws, r); break;
+      case ROUTE_FEW_ROW: r[0] = ROUTE_FEW_ROW; r[1] = 128; r[2] = 64; r[3] = down ? stem_gemm_skinny_ksplit((int)T, N, K) : 1; break;
+      default: stem_route_tiles((int)T, N, K, 1, down ? EPI_BF16 : EPI_GATE, ws, r);
+    }
+  }
+}
 
 const char* stem_status_string(stem_status s) {
   switch (s) {
@@ -171,8 +197,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipMalloc(&c->H_ws, std::max<size_t>(TF * es, 16)));
   ok(hipMalloc(&c->dG_ws, std::max<size_t>(TF * es, 16)));
   if (desc->dtype == STEM_BF16) {
-    // partial products of up to 8 K slices of a [T,d] or [d,F] output
-    c->splitk_bytes = std::min<size_t>(STEM_SPLITK_WS_MAX, (size_t)8 * 4 * desc->d_model * std::max<int64_t>({max_tokens, desc->d_ff, 1}));
+    c->splitk_bytes = (size_t)stem_route_splitk_bytes(desc->d_model, desc->d_ff, max_tokens);
     ok(hipMalloc(reinterpret_cast<void**>(&c->splitk_ws), c->splitk_bytes));
     ok(dmalloc(&c->tickets, STEM_TICKETS));
   }
@@ -277,10 +302,7 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;
     a.M = (int)T; a.N = F; a.K = d;
     a.ids = ids; a.E = static_cast<const bf16_t*>(E); a.E_rows = (int)E_rows; a.flag = c->flag;
-    // A decode-sized product takes the decode kernel while one round of its workgroups covers it, then the few-row
-    // kernel (128x64 tiles, the down product split along K so that both launches fill the chip).
-    const bool few = T <= 512 && stem_gemm_skinny_fits((int)T, F);
-    const bool decode_gate = stem_gemm_decode_fits((int)T, F, d), decode_down = stem_gemm_decode_fits((int)T, d, F);
+    const StemRoute gate = forward_route(T, F, d, F), down = forward_route(T, d, F, F);
     GemmArgs b = {};
     b.A = static_cast<const bf16_t*>(H); b.lda = F;
     b.B = static_cast<const bf16_t*>(W_down); b.ldb = F;
@@ -290,14 +312,14 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     const int down_epi = residual ? EPI_BF16_RES : EPI_BF16;
     if (!wait_event) {
       a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);
-      if (decode_gate) HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
-      else if (few) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
+      if (gate == ROUTE_DECODE) HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
+      else if (gate == ROUTE_FEW_ROW) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
       else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE, OP_KC, OP_KC, EPI_GATE, a, s));
     } else {
       void* G = save_G ? save_G : c->dG_ws;
       a.C = G;
-      if (decode_gate) HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_GATE_PLAIN, EPI_BF16, a, s));
-      else if (few) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE_PLAIN, EPI_BF16, a, s));
+      if (gate == ROUTE_DECODE) HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_GATE_PLAIN, EPI_BF16, a, s));
+      else if (gate == ROUTE_FEW_ROW) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE_PLAIN, EPI_BF16, a, s));
       else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE_PLAIN, OP_KC, OP_KC, EPI_BF16, a, s));
       if (wait_event == c->ready && c->pf_chunks > 1 && c->pf_T == T) {
         // Rows arrive in order of first use: run the gather and the down product chunk by chunk,
@@ -319,9 +341,9 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
       HIP_TRY(c, hipStreamWaitEvent(s, static_cast<hipEvent_t>(wait_event), 0));
       HIP_TRY(c, stem_silu_gather(c, 1, G, ids, E, (int)E_rows, H, T, F, s));
     }
-    if (decode_down) {
+    if (down == ROUTE_DECODE) {
       HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_DOWN, EPI_BF16, b, s));
-    } else if (few) {
+    } else if (down == ROUTE_FEW_ROW) {
       b.ksplit = stem_gemm_skinny_ksplit(b.M, b.N, b.K);
       if ((size_t)b.ksplit * b.M * b.N * 4 > c->splitk_bytes) b.ksplit = 1;
       HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_DOWN, b.ksplit > 1 ? EPI_SPLITK : EPI_BF16, b, s));

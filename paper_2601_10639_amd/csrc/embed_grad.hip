@@ -613,20 +613,28 @@ int64_t stem_sort_count_entries(int64_t max_tokens) {
   return tiles * SORT_WAVES * RADIX;
 }
 
+// One workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 25 in a graph against 19).
+// Then runs of 1024, while their number is one group of the merge's searches, and runs of 4096: 16384 ids 29 and 36 us
+// (one workgroup 43, the digit passes below 140), 32768 ids 40 and 38, 65536 ids 62 and 42 (digit passes 182).  The
+// digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
+// (262144 ids: 130 us against 640).
+int stem_route_sort(int64_t T, int V) {
+  const int vbits = bits_for(V);
+  if (T <= 4096 && vbits + bits_for((int)T) <= 32) return T <= 1024 ? SORT_ONE_1024 : SORT_ONE_4096;
+  const bool short_runs = T <= MERGE_WAYS * 1024;
+  if (T <= 262144 && vbits + (short_runs ? 10 : 12) <= 32) return short_runs ? SORT_RUNS_1024 : SORT_RUNS_4096;
+  return SORT_DIGITS;
+}
+
 hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t* ids, int64_t T, int V,
                             int32_t* sorted_ids, int32_t* perm, int32_t* uniq_ids, int32_t* seg_offsets,
                             int32_t* n_uniq, hipStream_t s) {
   const int passes = (bits_for(V) + RADIX_BITS - 1) / RADIX_BITS;
-  const int pos_bits = bits_for((int)T);
-  const int vbits = bits_for(V);
-  // One workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 25 in a graph against 19).
-  // Then runs of 1024, while their number is one group of the merge's searches, and runs of 4096: 16384 ids 29 and 36 us
-  // (one workgroup 43, the digit passes below 140), 32768 ids 40 and 38, 65536 ids 62 and 42 (digit passes 182).  The
-  // digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
-  // (262144 ids: 130 us against 640).
-  if (T <= 4096 && vbits + pos_bits <= 32) {
+  const int route = stem_route_sort(T, V);
+  if (route == SORT_ONE_1024 || route == SORT_ONE_4096) {
+    const int pos_bits = bits_for((int)T);
     ProfScope ps(ctx, K_SORT_FUSED, s);
-    if (T <= 1024)
+    if (route == SORT_ONE_1024)
       hipLaunchKernelGGL((sort_lds_kernel<1, false>), dim3(1), dim3(1024), 0, s, ids, (int)T, V, pos_bits, passes,
                          sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
     else
@@ -634,8 +642,8 @@ hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t
                          sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
     return hipGetLastError();
   }
-  const int items = T <= MERGE_WAYS * 1024 ? 1 : 4, run_bits = items == 1 ? 10 : 12;
-  if (T <= 262144 && vbits + run_bits <= 32) {
+  if (route == SORT_RUNS_1024 || route == SORT_RUNS_4096) {
+    const int items = route == SORT_RUNS_1024 ? 1 : 4, run_bits = items == 1 ? 10 : 12;
     const int R = items * 1024, runs = (int)((T + R - 1) / R);
     {
       ProfScope ps(ctx, K_SORT_FUSED, s);

@@ -806,7 +806,8 @@ constexpr TilingCost kTilings[3] = {{256, 256, 0.95, 1.50, 8, 18, 18}, {256, 128
 struct Plan { int tiling, ksplit; };
 
 // fused: the epilogue carries the layer's element-wise work and cannot be split.  ops: operand pairs of the K range
-// (a split into an even number of slices gives each pair half of them).
+// (each pair is cut into the same number of slices).  Slices of which the last ones would be left without a K tile (33 K
+// tiles in 8 slices of 5) become as many as have one.
 Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_bytes) {
   Plan best = {0, 1};
   double best_us = 1e30;
@@ -816,13 +817,18 @@ Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_b
     const double tiles = (double)((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn);
     for (int ks = 1; ks <= 8; ks *= 2) {
       if (ks > 1 && (fused || (double)M * N * 4 * ks > (double)ws_bytes || nk / ks < 4 || tiles * ks > 512)) break;
-      const double wgs = tiles * ks, fixed = fused ? c.fixed_fused : f32 || ks > 1 ? c.fixed_f32 : c.fixed_plain;
-      const int kt = (nk + ks - 1) / ks, rounds = (int)(wgs / 256);
+      int kt = nk, slices = 1;
+      if (ks > 1) {
+        kt = (nk + ks - 1) / ks;
+        slices = ops * ((nk / ops + kt - 1) / kt);
+      }
+      const double wgs = tiles * slices, fixed = fused ? c.fixed_fused : f32 || ks > 1 ? c.fixed_f32 : c.fixed_plain;
+      const int rounds = (int)(wgs / 256);
       const double rest = wgs - rounds * 256.0;
       double us = rounds * (kt * c.full + fixed);
       if (rest > 0) us += kt * (rounds ? c.full : c.idle + (c.full - c.idle) * rest / 256) + fixed;
-      if (ks > 1) us += 3.5 + (ks + 1.0) * M * N * 4 / 5e6;   // the kernel that sums the slices: launch, and 5 TB/s
-      if (us < best_us) { best_us = us; best = {t, ks}; }
+      if (ks > 1) us += 3.5 + (slices + 1.0) * M * N * 4 / 5e6;   // the kernel that sums the slices: launch, and 5 TB/s
+      if (us < best_us) { best_us = us; best = {t, slices}; }
     }
   }
   return best;
@@ -865,6 +871,12 @@ hipError_t launch(stem_ctx* ctx, int kid, GemmArgs a, hipStream_t s) {
 }
 
 }  // namespace
+
+void stem_route_tiles(int M, int N, int K, int ops, int epi, int64_t ws_bytes, int32_t* route) {
+  const bool plain = epi == EPI_BF16 || epi == EPI_BF16_RES;
+  const Plan p = choose_plan(M, N, K, ops, !plain && epi != EPI_F32, epi == EPI_F32, (size_t)ws_bytes);
+  route[0] = ROUTE_TILES; route[1] = kTilings[p.tiling].tm; route[2] = kTilings[p.tiling].tn; route[3] = p.ksplit;
+}
 
 hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return hipSuccess;

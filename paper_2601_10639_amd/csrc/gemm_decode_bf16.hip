@@ -303,12 +303,11 @@ bool decode_plan(int M, int N, int K, bool may_split, size_t ws_bytes, DecodePla
     const bool last = fa < 4 && fb == 2;      // wide weight matrices and few tokens: several rounds
     if ((int64_t)mt * nt > 256 && !last) continue;
     if (fa == 4 && fb > 1 && K > 2048) break;
-    int ks = 1;
+    int ks = 1;   // (slices of at least 16 K tiles, 8 at most: none of them is empty)
     const int least = M <= 8 ? 40 : M <= 16 ? 32 : 16;
     while (may_split && ks < MAX_SLICES && mt * nt * ks * 2 <= 256 && K / BK / (ks * 2) >= least &&
            (size_t)mt * nt * ks * 2 * fa * fb * 1024 <= ws_bytes)
       ks *= 2;
-    while (ks > 1 && (ks - 1) * ((K / BK + ks - 1) / ks) >= K / BK) ks /= 2;   // no empty slice
     *plan = {fa, fb, mt, nt, ks};
     return true;
   }
@@ -332,6 +331,12 @@ void launch(int epi, const GemmArgs& p, hipStream_t s) {
 bool stem_gemm_decode_fits(int M, int N, int K) {
   DecodePlan pl;
   return M <= 512 && K % BK == 0 && N % 4 == 0 && decode_plan(M, N, K, false, 0, &pl);
+}
+
+void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* route) {
+  DecodePlan pl = {};
+  decode_plan(M, N, K, epi == EPI_BF16 && ws_bytes > 0, (size_t)ws_bytes, &pl);
+  route[0] = ROUTE_DECODE; route[1] = 16 * pl.fa; route[2] = 16 * pl.fb; route[3] = pl.ksplit;
 }
 
 hipError_t stem_gemm_decode_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s) {

@@ -169,6 +169,19 @@ struct GemmArgs {
 
 hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmArgs& a, hipStream_t s);
 
+// ---- which kernel a call takes, as its launcher decides it: exported for the tests, not part of stem.h ----
+enum StemRoute { ROUTE_DECODE = 0, ROUTE_FEW_ROW, ROUTE_TILES };
+extern "C" {
+// route: {StemRoute, tile rows, tile columns, K slices}.  epi: GemmEpilogue; ops: operand pairs
+void stem_route_tiles(int M, int N, int K, int ops, int epi, int64_t ws_bytes, int32_t* route);
+void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* route);
+// the gate (route[0..3]) and down (route[4..7]) products of a bf16 stem_ffn_forward call of T tokens, in a context made for as many
+void stem_route_forward(int d_model, int d_ff, int64_t T, int32_t* route);
+int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   // a context's room for K slices
+int stem_route_sort(int64_t T, int V);   // SortRoute
+}
+enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS };
+
 // ---- few-row bf16 GEMM (gemm_skinny_bf16.hip): both operands K-contiguous, K % 64 == 0 --------
 // 128x64 tiles; used when M is small enough that larger tiles would leave most of the chip idle: up to 256 rows, and up
 // to 512 while the gate product is one round of its workgroups.  Layer forward, us, this / 128x128 tiles: d_model 2048,

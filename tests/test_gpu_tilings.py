@@ -16,6 +16,7 @@ DEV = "cuda:0"
     (1300, 1152, 6016),   # gate, dH: 256x256; down, dx: 128x128 in 2 slices; weight gradients: 256x128, a ragged last K tile
     (520, 64, 8192),      # gate, dH on 256x128 tiles with one K tile, fewer than the stages in LDS
     (385, 128, 128),      # 128x128 with two K tiles, one row in the last tile
+    (600, 512, 2112),     # down, dx: 33 K tiles in 7 slices of 5, the last of 3
 ])
 @pytest.mark.parametrize("up", [False, True])
 def test_bf16_products_on_every_tiling(T, d, F, up):

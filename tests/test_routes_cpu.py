@@ -1,0 +1,37 @@
+"""CPU-only: the rules that choose a call's kernels, asked through the library itself."""
+import ctypes
+import random
+
+import pytest
+
+from paper_2601_10639_amd import stemlib as L
+
+DECODE, FEW_ROW, TILES = range(3)
+EPI_BF16, EPI_F32, EPI_GATE = range(3)
+
+
+def tiles(M, N, K, ops=1, epi=EPI_BF16, ws=64 << 20):
+    r = (ctypes.c_int32 * 4)()
+    L.lib().stem_route_tiles(M, N, K, ops, epi, ctypes.c_int64(ws), r)
+    return tuple(r)
+
+
+def test_no_k_slice_is_empty():
+    """Every slice of a split product has a K tile: 64-wide K tiles, dealt to the slices (of each operand pair) in runs
+    of equal length."""
+    rng = random.Random(1)
+    split = 0
+    for _ in range(20000):
+        M, N = rng.choice([rng.randint(1, 3000), 64 * rng.randint(1, 40)]), 64 * rng.randint(1, 64)
+        K, ops, epi = 64 * rng.randint(1, 140), rng.choice([1, 2]), rng.choice([EPI_BF16, EPI_F32])
+        if epi == EPI_F32:
+            K, ops = rng.randint(1, 9000), 1
+        _, _, _, ks = tiles(M, N, K, ops, epi)
+        if ks == 1:
+            continue
+        split += 1
+        assert ks % ops == 0 and 4 * M * N * ks <= 64 << 20, (M, N, K, ops, epi, ks)
+        nk, per_pair = -(-K // 64), ks // ops
+        assert (per_pair - 1) * -(-nk // per_pair) < nk, (M, N, K, ops, epi, ks)
+    assert split > 1000
+    assert tiles(600, 512, 33 * 64)[3] == 7      # 33 K tiles in runs of 5
