@@ -796,12 +796,17 @@ __global__ __launch_bounds__(256) void splitk_sum_f32_kernel(const float* __rest
 // ---- choice of the tiling and of the K split ----------------------------------------------------
 // A launch is priced as rounds of 256 workgroups: a round takes (K tiles per workgroup) x (time per K tile) plus a
 // fixed part (prologue, epilogue).  The time per K tile grows with the share of the chip that is busy (operand
-// loads, clock), from `idle` with a few workgroups to `full` with 256.  The constants (us) are fits to measured
-// launches of d_model 1024 and 2048, d_ff 4096 and 8192, 128 to 16384 tokens; the model is within 8 % of nearly all.
+// loads, clock), from `idle` with a few workgroups to `full` with 256, in the first round and in what is left for the
+// last: the chip is power-limited, and a last round with few workgroups runs at a higher clock.  The constants (us) are
+// chosen for what the choice loses against the best of the tilings and splits, over every product of forward and backward
+// of 237 layers (d_model 512 to 2048, d_ff 2.5 to 4 times that, 130 to 65536 tokens, with and without up projection): 0.3 %
+// in the mean, more than 5 % at 55 of 3204.  (With the last round at the full time, and constants fitted to two widths:
+// 0.7 %, 172 of 3204, the dearest of them 256x128 tiles where 256x256 ones end in half a round: gate product 1280 x 3328,
+// 16384 tokens, 180 us against 166; dx of the layer with up projection, 1536 x 5120, 24000 tokens, 732 against 646.)
 // Examples, us (Tile256 / Tile256x128 / Tile128): down product 2048 x 8192, 1999 tokens 146 / 92 / 70, 4096 tokens
 // 165 / 114 / 129, 16384 tokens 408 / 460 / 538; gate product 700 tokens 51 / 34 / 39, 1999 tokens 69 / 73 / 85.
 struct TilingCost { int tm, tn; double idle, full, fixed_plain, fixed_fused, fixed_f32; };
-constexpr TilingCost kTilings[3] = {{256, 256, 0.95, 1.50, 8, 18, 18}, {256, 128, 0.52, 0.86, 7, 10, 12}, {128, 128, 0.33, 0.54, 5, 6, 5}};
+constexpr TilingCost kTilings[3] = {{256, 256, 0.86, 1.39, 9, 21, 17.5}, {256, 128, 0.45, 0.86, 6, 11, 11}, {128, 128, 0.34, 0.56, 4, 6.5, 5.5}};
 
 struct Plan { int tiling, ksplit; };
 
@@ -826,8 +831,8 @@ Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_b
       const int rounds = (int)(wgs / 256);
       const double rest = wgs - rounds * 256.0;
       double us = rounds * (kt * c.full + fixed);
-      if (rest > 0) us += kt * (rounds ? c.full : c.idle + (c.full - c.idle) * rest / 256) + fixed;
-      if (ks > 1) us += 3.5 + (slices + 1.0) * M * N * 4 / 5e6;   // the kernel that sums the slices: launch, and 5 TB/s
+      if (rest > 0) us += kt * (c.idle + (c.full - c.idle) * rest / 256) + fixed;
+      if (ks > 1) us += 3 + (slices + 1.0) * M * N * 4 / 4.2e6;   // the kernel that sums the slices: launch, and 4.2 TB/s
       if (us < best_us) { best_us = us; best = {t, slices}; }
     }
   }

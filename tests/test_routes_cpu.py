@@ -35,3 +35,17 @@ def test_no_k_slice_is_empty():
         assert (per_pair - 1) * -(-nk // per_pair) < nk, (M, N, K, ops, epi, ks)
     assert split > 1000
     assert tiles(600, 512, 33 * 64)[3] == 7      # 33 K tiles in runs of 5
+
+
+@pytest.mark.parametrize("product,want", [
+    # 256x256 tiles that end in part of a round, against whole rounds of 256x128 ones: us, 256x256 / 256x128
+    ((16384, 3328, 1280, 1, EPI_GATE), (256, 256, 1)),      # 166 / 180
+    ((24000, 1536, 5120, 2, EPI_BF16), (256, 256, 1)),      # 646 / 732
+    ((49152, 512, 1536, 1, EPI_BF16), (256, 256, 1)),       # 83 / 99
+    ((1536, 5120, 16384, 1, EPI_F32), (256, 256, 2)),       # 214 / 245
+    # and where the smaller tiles are the better ones
+    ((1999, 2048, 8192, 1, EPI_BF16), (128, 128, 1)),       # 146 / 92 / 70 for 128x128
+    ((4096, 2048, 8192, 1, EPI_BF16), (256, 128, 1)),       # 165 / 114
+])
+def test_tiling_of_products_that_were_measured_on_each(product, want):
+    assert tiles(*product)[1:] == want
