@@ -2,6 +2,8 @@
 the oracle on the same seeded inputs.  No arithmetic of the method lives here."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -31,6 +33,30 @@ def max_rel(got, ref) -> float:
 def make_ctx(shape: inputs.StemShape, max_tokens: int, reserve: int = 0) -> L.StemCtx:
     dt = L.STEM_BF16 if shape.dtype == "bf16" else L.STEM_F32
     return L.stem_create(shape.d_model, shape.d_ff, shape.vocab, dt, max_tokens, 0, reserve=reserve)
+
+
+# Which kernel the library chooses, asked through the functions its launchers ask (not part of stem.h).
+DECODE, FEW_ROW, TILES = range(3)
+EPI_BF16, EPI_F32, EPI_GATE, EPI_DH = range(4)
+SORT_ONE_1024, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS = range(5)
+
+
+def route_tiles(M, N, K, ops=1, epi=EPI_BF16, ws=64 << 20):
+    """(kernel, tile rows, tile columns, K slices) of a bf16 product on the large tiles."""
+    r = (ctypes.c_int32 * 4)()
+    L.lib().stem_route_tiles(M, N, K, ops, epi, ctypes.c_int64(ws), r)
+    return tuple(r)
+
+
+def route_forward(T, d, F):
+    """The same for the gate and the down product of a bf16 forward call."""
+    r = (ctypes.c_int32 * 8)()
+    L.lib().stem_route_forward(d, F, ctypes.c_int64(T), r)
+    return tuple(r[:4]), tuple(r[4:])
+
+
+def route_sort(T, V):
+    return L.lib().stem_route_sort(ctypes.c_int64(T), V)
 
 
 def hip_forward_backward(ctx, inp, save_H=True, want_dx=True, after_forward=None):

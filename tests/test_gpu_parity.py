@@ -93,9 +93,9 @@ def test_fp32_ragged_token_counts(T):
 @pytest.mark.parametrize("T,d,F", [(600, 192, 576), (257, 64, 64), (1, 128, 320), (1100, 512, 256), (2100, 128, 320),
                                    (600, 1088, 1152)])
 def test_bf16_several_tiles_and_ragged_tails(T, d, F):
-    # 256-wide tiles: these sizes give full tiles plus a ragged last tile in every dimension; the
-    # weight-gradient products of the 4th and 5th are cut along K (2 slices; 4 slices of 9, 9, 9, 6 K tiles);
-    # the last has 17 and 18 K tiles in its forward and activation-gradient products, enough for the
+    # 128x128 tiles (the forward of the 2nd and 3rd: the decode kernel): full tiles plus a ragged last tile in
+    # every dimension; the weight-gradient products of the 4th and 5th are cut along K (4 slices of 5 K tiles, the
+    # last of 3; 7 of 5, the last of 3); the last has 17 and 18 K tiles in its forward and activation-gradient products, enough for the
     # workgroups to start their K loops at different K tiles (rotation per XCD) and wrap around
     s = inputs.StemShape("bf16-ragged", d, F, 1000, 1, T, "bf16")
     _pipeline_case(s, T, seed=3)
@@ -115,9 +115,9 @@ def test_bf16_all_tokens_same_id_and_all_distinct():
 @pytest.mark.parametrize("T,d,F", [(1, 64, 64), (37, 192, 320), (128, 256, 576), (129, 128, 1024), (256, 192, 4096),
                                    (300, 64, 2112), (512, 128, 640), (513, 128, 640)])
 def test_bf16_few_row_forward(T, d, F):
-    """Decode-sized calls take the 128x64-tile kernel (the down product split along K when d_ff is
-    long: 2 slices at F=1024, 8 at 4096, 4 uneven ones at 2112); T=513 is the first size on the
-    256x256-tile kernel again.  Forward only, with and without the saved G and H."""
+    """Calls of up to 512 tokens of small layers: the decode kernel (the down product split along K when d_ff is
+    long: 4 slices at F=4096, 2 uneven ones at 2112); T=513 is the first size on the 128x128 tiles.  Forward only,
+    with and without the saved G and H."""
     s = inputs.StemShape("bf16-few-rows", d, F, 500, 1, T, "bf16")
     inp = inputs.layer_inputs(s, seed=7, device=DEV, tokens=T)
     ctx = Hn.make_ctx(s, T)
@@ -217,7 +217,7 @@ def test_segmented_sum_is_bit_reproducible_and_conserves_column_sums():
     ctx.close()
 
 
-@pytest.mark.parametrize("T", [300, 700])   # the few-row and the 256x256-tile forward kernels
+@pytest.mark.parametrize("T", [300, 700])   # the decode kernel and the 128x128 tiles
 def test_bf16_saturated_gate_activations_stay_finite(T):
     """Pre-activations far beyond the range where exp() overflows in fp32 (|g| up to ~200): SiLU and
     its derivative must come out as their limits (0 or g, 0 or 1), never NaN or inf."""
@@ -376,8 +376,8 @@ def test_edge_cases_and_error_reporting():
 @pytest.mark.parametrize("dtype,T,d,F", [("bf16", 300, 128, 1024), ("bf16", 256, 192, 320), ("bf16", 700, 192, 576),
                                          ("f32", 100, 72, 132)])
 def test_forward_with_residual_out_of_place_and_in_place(dtype, T, d, F):
-    """y = residual + layer(x), the sum taken in the down product's epilogue: the few-row kernel with and
-    without a K split (T = 300, 256), the 256x256-tile kernel (T = 700), the fp32 path; with a separate
+    """y = residual + layer(x), the sum taken in the down product's epilogue: the decode kernel (T = 300, 256), the
+    128x128 tiles (T = 700), the fp32 path; with a separate
     residual and output, and in place on the layer's own input (a residual stream)."""
     s = inputs.StemShape("residual", d, F, 500, 1, T, dtype)
     inp = inputs.layer_inputs(s, seed=18, device=DEV, tokens=T)
@@ -438,9 +438,9 @@ def _expect_id_range(ctx):
 
 @pytest.mark.parametrize("T,d,F", [(700, 1088, 320), (300, 128, 320)])
 def test_bf16_out_of_range_ids_are_clamped_and_reported(T, d, F):
-    """Ids outside the table on the bf16 paths: the fused epilogues of the 256x256-tile products (T = 700;
-    d_model 1088 also reaches the early touch of the gathered rows, d_ff 320 = 64 mod 128 its narrow last
-    column block) and the few-row kernel (T = 300).  No access leaves the table (an id below zero reads
+    """Ids outside the table on the bf16 paths: the fused epilogues of the 128x128 tiles (T = 700; d_model 1088 also
+    reaches the early touch of the gathered rows, d_ff 320 = 64 mod 128 a last tile half outside) and the decode
+    kernel (T = 300).  No access leaves the table (an id below zero reads
     row 0, one beyond the end the last row), the sticky flag is reported once, every output is finite,
     and the rows of tokens with valid ids match the oracle."""
     V = 257
@@ -458,7 +458,7 @@ def test_bf16_out_of_range_ids_are_clamped_and_reported(T, d, F):
     f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
     ref, fw = O.ffn_forward(f64["x"], ids_good, f64["W_gate"], f64["W_down"], f64["E"])
     tol = Hn.TOL["bf16"]
-    if T <= 512:   # few-row kernel: forward only
+    if T <= 512:   # decode kernel: forward only
         y = torch.empty(T, d, dtype=dt, device=DEV)
         G, H = (torch.empty(T, F, dtype=dt, device=DEV) for _ in range(2))
         L.stem_ffn_forward(ctx, inp["x"], inp_bad["ids"], inp["W_gate"], inp["W_down"], inp["E"], y, G, H)
@@ -489,7 +489,7 @@ def test_bf16_out_of_range_ids_are_clamped_and_reported(T, d, F):
 
 @pytest.mark.parametrize("T", [16384, 20000])
 def test_sort_paths_clamp_and_report_out_of_range_ids(T):
-    """The one-workgroup sort (T = 16384) and the multi-kernel sort (T = 20000) with ids outside the
+    """The merged runs of 1024 ids (T = 16384) and of 4096 (T = 20000) with ids outside the
     table: the flag is raised, and sort, unique, offsets and the row sums are those of the clamped ids."""
     V, F = 5000, 64
     s = inputs.StemShape("bf16-bad-sort", 64, F, V, 1, T, "bf16")

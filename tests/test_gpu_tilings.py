@@ -11,17 +11,27 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("T,d,F", [
-    (1000, 512, 4160),    # gate, dH: 256x128 tiles with ragged last ones; down, dx: 128x128 in 8 K slices, the last one short
-    (1300, 1152, 6016),   # gate, dH: 256x256; down, dx: 128x128 in 2 slices; weight gradients: 256x128, a ragged last K tile
-    (520, 64, 8192),      # gate, dH on 256x128 tiles with one K tile, fewer than the stages in LDS
-    (385, 128, 128),      # 128x128 with two K tiles, one row in the last tile
-    (600, 512, 2112),     # down, dx: 33 K tiles in 7 slices of 5, the last of 3
+# tile and K slices of dH (and the gate product beyond 512 tokens), dx, dx of two operand pairs, the weight gradients
+@pytest.mark.parametrize("T,d,F,routes", [
+    # ragged last tiles; the last of 8 slices of 9 K tiles has two
+    (1000, 512, 4160, [(256, 128, 1), (128, 128, 8), (128, 128, 8), (128, 128, 1)]),
+    # a ragged last K tile in the weight gradients
+    (1300, 1152, 6016, [(256, 256, 1), (128, 128, 2), (256, 128, 4), (256, 128, 1)]),
+    # one K tile, fewer than the stages in LDS
+    (520, 64, 8192, [(256, 128, 1), (128, 128, 8), (128, 128, 8), (128, 128, 1)]),
+    # two K tiles, one row in the last tile
+    (385, 128, 128, [(128, 128, 1), (128, 128, 1), (128, 128, 1), (128, 128, 1)]),
+    # 33 K tiles in 7 slices of 5, the last of 3; with two operand pairs 4 slices of 9 each
+    (600, 512, 2112, [(128, 128, 1), (128, 128, 7), (128, 128, 8), (128, 128, 1)]),
 ])
 @pytest.mark.parametrize("up", [False, True])
-def test_bf16_products_on_every_tiling(T, d, F, up):
+def test_bf16_products_on_every_tiling(T, d, F, routes, up):
     """Forward and backward of the layer, and (up) of the additive variant, whose dx product sums two operand
     pairs and cuts them into K slices."""
+    assert [r[1:] for r in (Hn.route_tiles(T, F, d, 1, Hn.EPI_DH), Hn.route_tiles(T, d, F), Hn.route_tiles(T, d, F, 2),
+                            Hn.route_tiles(F, d, T, 1, Hn.EPI_F32))] == routes
+    if T > 512:
+        assert Hn.route_forward(T, d, F) == ((Hn.TILES, *routes[0]), (Hn.TILES, *routes[1]))
     V = 300
     s = inputs.StemShape("tilings", d, F, V, 1, T, "bf16")
     inp = inputs.layer_inputs(s, seed=61, device=DEV, tokens=T)
@@ -84,18 +94,22 @@ def test_f32_products_on_both_tilings(T, d, F):
     ctx.close()
 
 
-@pytest.mark.parametrize("T,d,F", [
-    (1, 64, 64),          # one K tile: fewer than wavefronts and than K tiles in flight
-    (16, 192, 4160),      # 32 weight rows, a ragged last one; down: 16 weight rows, 65 K tiles
-    (17, 128, 8192),      # 32 tokens with one in the second fragment; down: 128 K tiles in two slices
-    (33, 64, 4096),       # 64-token tile
-    (129, 1088, 2112),    # 3 x 33 tiles of 64 x 64, ragged both ways
-    (64, 2048, 8256),     # down: 129 K tiles in two slices of 65 and 64
-    (20, 1024, 4160),     # down: 65 K tiles in four slices, the last of 14
-    (500, 512, 1536),     # eight token tiles, the last ragged
-    (300, 1024, 2624),    # few-row kernel beyond 256 tokens
+# tile and K slices of the gate and the down product
+@pytest.mark.parametrize("T,d,F,gate,down", [
+    (1, 64, 64, (16, 16, 1), (16, 16, 1)),          # one K tile: fewer than wavefronts and than K tiles in flight
+    (16, 192, 4160, (16, 32, 1), (16, 16, 2)),      # 65 K tiles in slices of 33 and 32
+    (17, 128, 8192, (32, 32, 1), (32, 16, 8)),      # one token in the second fragment
+    (33, 64, 4096, (64, 16, 1), (64, 16, 4)),
+    (129, 1088, 2112, (64, 32, 1), (64, 16, 1)),    # three token tiles, the last with one row
+    (64, 2048, 8256, (64, 64, 1), (64, 16, 2)),     # 129 K tiles in slices of 65 and 64; a ragged last weight tile
+    (20, 1024, 4160, (32, 32, 1), (32, 16, 4)),     # 65 K tiles in four slices, the last of 14
+    (500, 512, 1536, (64, 64, 1), (64, 16, 1)),     # eight token tiles, the last ragged
+    (300, 1024, 2624, (64, 64, 1), "few"),          # the down product on the few-row kernel beyond 256 tokens
+    (250, 2048, 8192, "few", "few"),                # both there, a ragged second token tile
 ])
-def test_decode_products_on_every_tile(T, d, F):
+def test_decode_products_on_every_tile(T, d, F, gate, down):
+    for got, want in zip(Hn.route_forward(T, d, F), (gate, down)):
+        assert got[0] == Hn.FEW_ROW if want == "few" else got == (Hn.DECODE, *want)
     V = 300
     s = inputs.StemShape("decode-tiles", d, F, V, 1, T, "bf16")
     inp = inputs.layer_inputs(s, seed=65, device=DEV, tokens=T)
@@ -119,14 +133,16 @@ def test_decode_products_on_every_tile(T, d, F):
     ctx.close()
 
 
-@pytest.mark.parametrize("T,V", [
-    (1, 1), (63, 2), (1024, 128256), (1025, 128256),     # one workgroup, one and four rounds of keys
-    (4096, 1 << 20), (4097, 1 << 20), (4096, (1 << 20) + 1),   # runs of 1024; an id that leaves no room for 12 position bits
-    (16384, 50304), (16385, 50304),                      # the most runs of 1024; runs of 4096, the last with one key
-    (65537, 128256), (262144, 7),                        # more runs than searches in flight; long runs of equal ids
-    (5000, 5_000_000), (262145, 3),                      # digit passes: ids, then a batch, beyond the merge's
+@pytest.mark.parametrize("T,V,route", [
+    (1, 1, Hn.SORT_ONE_1024), (63, 2, Hn.SORT_ONE_1024), (1024, 128256, Hn.SORT_ONE_1024), (1025, 128256, Hn.SORT_ONE_4096),
+    (4096, 1 << 20, Hn.SORT_ONE_4096), (4097, 1 << 20, Hn.SORT_RUNS_1024),
+    (4096, (1 << 20) + 1, Hn.SORT_RUNS_1024),            # an id that leaves no room for 12 position bits
+    (16384, 50304, Hn.SORT_RUNS_1024), (16385, 50304, Hn.SORT_RUNS_4096),   # the most runs of 1024; a last run with one key
+    (65537, 128256, Hn.SORT_RUNS_4096), (262144, 7, Hn.SORT_RUNS_4096),   # more runs than searches in flight; long runs of equal ids
+    (5000, 5_000_000, Hn.SORT_DIGITS), (262145, 3, Hn.SORT_DIGITS),       # ids, then a batch, beyond the merge's
 ])
-def test_sort_on_every_path(T, V):
+def test_sort_on_every_path(T, V, route):
+    assert Hn.route_sort(T, V) == route
     ids = inputs.zipf_ids(T, V, seed=67)
     ids[T // 2:] = np.random.default_rng(68).integers(0, V, T - T // 2)
     ctx = L.stem_create(64, 64, V, L.STEM_BF16, T, 0)
@@ -214,4 +230,77 @@ def test_f32_layer_with_rows_beyond_a_buffer_window(T, d, F):
     L.stem_sync_status(ctx)
     errs = {k: _max_rel(out[k], v) for k, v in _reference64(inp).items()}
     assert all(v <= Hn.TOL["f32"] for v in errs.values()), errs
+    ctx.close()
+
+
+BAD_IDS = [300, -3, 2 ** 31 - 1, -2 ** 31, 307, -1, 257, 300]
+
+
+def _with_bad_ids(ids, at, V):
+    bad = ids.copy()
+    bad[at] = [b if b < 0 else max(b, V) for b in BAD_IDS]
+    return bad, np.clip(bad.astype(np.int64), 0, V - 1)
+
+
+def _expect_id_range(ctx):
+    with pytest.raises(L.StemError) as e:
+        L.stem_sync_status(ctx)
+    assert e.value.status == L.STEM_ERR_ID_RANGE
+    L.stem_sync_status(ctx)   # the flag was cleared
+
+
+@pytest.mark.parametrize("T,d,F,gate,wait", [
+    # d_ff 64 modulo 128: the last column block of a wavefront is half outside; 9 K tiles: early touch of the table rows
+    (1300, 576, 6208, (Hn.TILES, 256, 256), False),
+    (900, 576, 4160, (Hn.TILES, 256, 128), False),
+    (520, 576, 320, (Hn.TILES, 128, 128), False),
+    # gather in the gate product's epilogue, and (wait) the plain product with the gather behind it
+    (250, 1536, 5120, (Hn.FEW_ROW, 128, 64), False),
+    (250, 1536, 5120, (Hn.FEW_ROW, 128, 64), True),
+    (300, 128, 320, (Hn.DECODE, 64, 16), False),
+    (300, 128, 320, (Hn.DECODE, 64, 16), True),
+])
+def test_out_of_range_ids_on_every_forward_kernel(T, d, F, gate, wait):
+    """Ids outside the table read row 0 or the last one, are reported once, and leave everything else as it is: the
+    results are those of the clamped ids."""
+    V = 257
+    assert Hn.route_forward(T, d, F)[0][:3] == gate
+    s = inputs.StemShape("bad-ids", d, F, V, 1, T, "bf16")
+    inp = inputs.layer_inputs(s, seed=75, device=DEV, tokens=T)
+    ids, clamped = _with_bad_ids(inp["ids"].cpu().numpy(), [0, 5, 63, 64, 128, 249, T // 2, T - 1], V)
+    inp["ids"] = torch.from_numpy(ids).to(DEV)
+    f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
+    y, fw = O.ffn_forward(f64["x"], clamped, f64["W_gate"], f64["W_down"], f64["E"])
+    ref = {"y": y, "G": fw["g"], "H": fw["h"]}
+    ctx = Hn.make_ctx(s, T)
+    if gate[0] == Hn.TILES:
+        assert Hn.route_tiles(T, F, d, 1, Hn.EPI_DH)[1:3] == gate[1:]
+        # the forward call's report is collected first: the backward call would make it and do nothing else
+        out = Hn.hip_forward_backward(ctx, inp, after_forward=lambda: _expect_id_range(ctx))
+        bw = O.ffn_backward(f64["dy"], f64["x"], clamped, f64["W_gate"], f64["W_down"], f64["E"])
+        ref.update({k: bw[k] for k in ("dx", "dU", "dW_gate", "dW_down")})
+    else:
+        out = {k: torch.empty(T, n, dtype=torch.bfloat16, device=DEV) for k, n in (("y", d), ("G", F), ("H", F))}
+        ready = torch.cuda.Event()
+        ready.record()
+        L.stem_ffn_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"], out["y"], out["G"], out["H"],
+                           wait_event=ready.cuda_event if wait else None)
+    _expect_id_range(ctx)
+    errs = {k: Hn.max_rel(out[k].float().cpu(), v) for k, v in ref.items()}
+    assert all(v <= Hn.TOL["bf16"] for v in errs.values()), errs
+    ctx.close()
+
+
+@pytest.mark.parametrize("T,V,route", [(1000, 300, Hn.SORT_ONE_1024), (4000, 300, Hn.SORT_ONE_4096), (16000, 300, Hn.SORT_RUNS_1024),
+                                       (20000, 300, Hn.SORT_RUNS_4096), (5000, 5_000_000, Hn.SORT_DIGITS)])
+def test_out_of_range_ids_on_every_sort(T, V, route):
+    assert Hn.route_sort(T, V) == route
+    ids, clamped = _with_bad_ids(inputs.zipf_ids(T, V, seed=76), [0, 7, 63, 64, 255, 256, T // 2, T - 1], V)
+    ctx = L.stem_create(64, 64, V, L.STEM_BF16, T, 0)
+    dU = inputs.normal((T, 64), 1.0, 77, torch.bfloat16, DEV)
+    eg = Hn.hip_embed_grad(ctx, torch.from_numpy(ids).to(DEV), dU, V)
+    _expect_id_range(ctx)
+    clamped = clamped.astype(np.int32)
+    U = Hn.check_integers(eg, clamped)
+    assert Hn.max_rel(eg["dE_rows"][:U].cpu(), O.embed_grad(clamped, inputs.to_f64(dU))["dE_rows"]) <= 1e-5
     ctx.close()

@@ -156,7 +156,7 @@ def test_largest_token_count_a_bf16_context_accepts():
 
 def test_widest_layer_a_bf16_context_accepts():
     """d_model = 8192, d_ff = 65472: the fp32 weight gradients end 2 MiB below 2^31 bytes (stem_create
-    refuses d_ff = 65536).  600 tokens, so the 256x256-tile kernels run every product, with ragged row
+    refuses d_ff = 65536).  600 tokens, where 256x256 tiles run every product, with ragged row
     tiles, 1023 K tiles in dx and 8192 output tiles in each weight gradient.  Checked as in the test
     above: the whole layer on sampled tokens, and the layer cut down to sampled d_ff columns (first and
     last included) on all tokens."""

@@ -1,19 +1,9 @@
 """CPU-only: the rules that choose a call's kernels, asked through the library itself."""
-import ctypes
 import random
 
 import pytest
 
-from paper_2601_10639_amd import stemlib as L
-
-DECODE, FEW_ROW, TILES = range(3)
-EPI_BF16, EPI_F32, EPI_GATE = range(3)
-
-
-def tiles(M, N, K, ops=1, epi=EPI_BF16, ws=64 << 20):
-    r = (ctypes.c_int32 * 4)()
-    L.lib().stem_route_tiles(M, N, K, ops, epi, ctypes.c_int64(ws), r)
-    return tuple(r)
+from tests.harness import EPI_BF16, EPI_F32, EPI_GATE, route_tiles as tiles
 
 
 def test_no_k_slice_is_empty():

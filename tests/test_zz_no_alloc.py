@@ -28,8 +28,8 @@ def _noalloc(dtype, V, F, ids, dU):
 
 
 @pytest.mark.parametrize("dtype,V,F,sizes", [
-    ("bf16", 128256, 8192, (16384, 5000)),      # the 1B-shaped layer's batch (one-workgroup sort), then a smaller one
-    ("bf16", 50304, 1024, (40000, 16384)),      # multi-kernel sort, then the one-workgroup sort
+    ("bf16", 128256, 8192, (16384, 5000)),      # the 1B-shaped layer's batch (sorted in merged runs), then a smaller one
+    ("bf16", 50304, 1024, (40000, 16384)),      # runs of 4096 ids, then of 1024
     ("f32", 1000, 256, (3000, 128)),
 ])
 def test_no_alloc_entry_point_matches_the_context_one_on_two_calls_in_a_row(dtype, V, F, sizes):
