@@ -190,7 +190,7 @@ def bench_layer(args, shape, dev, steps, warmup, peaks, detail):
         dWu = torch.empty(F, d, dtype=torch.float32, device=dev)
     # The integer half of the table gradient (sort, distinct ids, offsets) needs the token ids only:
     # it is enqueued on a second stream after the forward call and joins the main stream before the
-    # row sums, so its one workgroup runs in the gaps of the backward products.
+    # row sums, so its few workgroups run in the gaps of the backward products.
     overlap_sort = variant == "stem" and not args.no_overlap_sort
     main_stream = torch.cuda.current_stream()
     side = torch.cuda.Stream() if overlap_sort else None
@@ -292,8 +292,8 @@ def bench_layer(args, shape, dev, steps, warmup, peaks, detail):
             k["gbs"] = round(algo_bytes[name] / (avg * 1e-3) / 1e9, 1)
             k["frac_hbm_peak"] = round(k["gbs"] / PEAK_HBM_GBS, 4)
             k["frac_of_measured_copy"] = round(k["gbs"] / peaks["hbm_copy_gbs"], 4)
-        if name == "sort_fused" and overlap_sort:
-            k["note"] = "one workgroup on a second stream under the backward GEMMs: wall time while it waits for a compute unit; 39 us when it runs alone"
+        if name in ("sort_fused", "sort_merge", "unique") and overlap_sort:
+            k["note"] = "on a second stream under the backward GEMMs: wall time while its workgroups wait for compute units; the sort's launches take 25 us together when they run alone (16384 ids)"
         kernels[name] = k
     # the segmented sum (G3) is everything it launches: the chunk sums and the sums over border-crossing runs
     if "seg_reduce" in kernels:

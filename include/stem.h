@@ -108,8 +108,8 @@ stem_status stem_sync_status(stem_ctx* ctx, void* stream);
  * stem_prefetch_rows returned for the same T (bf16 contexts), the wait is finer: the
  * rows were copied in order of first use with an event per chunk of tokens, and the
  * gather and the down GEMM of each chunk start as soon as that chunk's rows are there.
- * When NULL the gather is fused into the gate GEMM's epilogue.  Calls of at most 256
- * tokens (a decode step) use 128x64 tiles so that both products fill the chip. */
+ * When NULL the gather is fused into the gate GEMM's epilogue.  Calls of up to 512
+ * tokens (a decode step) take kernels with smaller tiles where these fill the chip. */
 stem_status stem_ffn_forward(stem_ctx* ctx, const void* x, const int32_t* ids, const void* W_gate,
                              const void* W_down, const void* E, int64_t E_rows, int64_t T, void* y,
                              void* save_G, void* save_H, void* wait_event, void* stream);

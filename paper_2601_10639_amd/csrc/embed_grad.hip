@@ -613,11 +613,11 @@ int64_t stem_sort_count_entries(int64_t max_tokens) {
   return tiles * SORT_WAVES * RADIX;
 }
 
-// One workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 25 in a graph against 19).
-// Then runs of 1024, while their number is one group of the merge's searches, and runs of 4096: 16384 ids 29 and 36 us
-// (one workgroup 43, the digit passes below 140), 32768 ids 40 and 38, 65536 ids 62 and 42 (digit passes 182).  The
-// digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
-// (262144 ids: 130 us against 640).
+// One workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 22 in a graph).  Then runs of
+// 1024, while their number is one group of the merge's searches, and runs of 4096, us in a graph: 6000 ids 22 / 29, 16384
+// ids 25 / 32 (one workgroup 43, the digit passes below 140), 32768 ids 36 / 34, 65536 ids 58 / 38 (digit passes 182).
+// The digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
+// (262144 ids: 126 us against 640).
 int stem_route_sort(int64_t T, int V) {
   const int vbits = bits_for(V);
   if (T <= 4096 && vbits + bits_for((int)T) <= 32) return T <= 1024 ? SORT_ONE_1024 : SORT_ONE_4096;
