@@ -710,7 +710,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
   // first use, so that the rows the first tokens need cross the link first.  Long batches are cut
   // into chunks; an event after each chunk's rows lets the forward
   // call run the gather and the down product of a chunk while later rows are still on the link.
-  // Chunk size: the down product of one chunk is about one round of 256x256 tiles
+  // Chunk size: the down product of one chunk is one round of 256x256 tiles beside the row copies
   // (STEM_PF_CHUNK_TILES); whole multiples of that if the batch is very long.
   const int64_t tile_cols = (c->desc.d_model + 255) / 256;
   int64_t chunk_tokens = std::max<int64_t>(1, STEM_PF_CHUNK_TILES / tile_cols) * 256;

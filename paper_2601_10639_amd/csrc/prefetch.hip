@@ -4,20 +4,61 @@
 
 namespace {
 
-// The host link, not the GPU, bounds this kernel (about 57 GB/s measured).  With one 16 KB row
-// in flight per workgroup, 4 / 8 / 16 / 32 workgroups reach 12 / 22 / 40 / 56 GB/s and more add
-// nothing, so 32 it is: the rest of the chip stays free for the gate product running beside it
-// (with 128 workgroups that product was measured 30 % slower).
-constexpr int COPY_WGS = 32;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
-__global__ __launch_bounds__(256) void copy_rows_kernel(const uint4* __restrict__ src,
-                                                        const int32_t* __restrict__ src_row,
-                                                        const int32_t* __restrict__ dst_slot, int64_t n,
-                                                        int64_t row_vecs, uint4* __restrict__ dst) {
-  for (int64_t j = blockIdx.x; j < n; j += gridDim.x) {
-    const uint4* s = src + (int64_t)src_row[j] * row_vecs;
-    uint4* d = dst + (int64_t)dst_slot[j] * row_vecs;
-    for (int64_t o = threadIdx.x; o < row_vecs; o += 256) d[o] = s[o];
+// The host link bounds this kernel (57 GB/s), as long as about 256 KB are requested at any time; a compute unit gets 5.3 GB/s
+// whatever it asks for.  So 16 workgroups, whose wavefronts each take 1 KB pieces of the rows, 4 in flight.
+//
+// What matters besides is whom the kernel keeps waiting.  A compute unit's loads return in order, so a GEMM tile that shares
+// its compute unit with a copy waits for the link with every K tile, and a round of tiles for the slowest of them: the
+// workgroups therefore claim LDS that no GEMM tile can do without (two of them fit a compute unit, and the copies of several
+// contexts gather there), and the products of a chunk leave 32 compute units free (STEM_PF_CHUNK_TILES).
+// 65536 tokens of 2048 x 8192, Zipf ids, ms: calls in turn on three contexts / two / by itself: 32 workgroups sharing with
+// the GEMMs, chunks of 256 tiles 6.40 / 5.80 / 4.85; now 5.22 / 4.83 / 4.61.  12 workgroups with 8 in flight 5.15 / 4.64 /
+// 4.72, 24 with 4 5.78 / 5.05 / 4.67, without the LDS 6.8 / 6.4 / 5.2.  24576 tokens 2.82 / 2.53 / 2.26 before, 2.12 / 1.97 /
+// 2.27 now; 4096 tokens 0.63 / 0.58 / 0.63 and 0.53 / 0.54 / 0.63.
+constexpr int COPY_WGS = 16, FLIGHT = 4;
+constexpr int COPY_LDS = 65 * 1024;   // two fit 160 KB, one and the smallest GEMM tile (96 KB) do not
+constexpr int BATCH = 64;             // pieces whose rows a wavefront looks up at a time, one per lane
+
+// pieces: n rows of row_pieces pieces, 64 vectors of 16 bytes each but for the last of a row
+__global__ __launch_bounds__(256) void copy_rows_kernel(const u32x4_t* __restrict__ src, const int32_t* __restrict__ src_row,
+                                                        const int32_t* __restrict__ dst_slot, uint32_t pieces, uint32_t row_vecs,
+                                                        uint32_t row_pieces, u32x4_t* __restrict__ dst) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t waves = gridDim.x * 4, wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave >= pieces) return;
+  // lane l: row, slot and first vector of piece first + l * waves
+  auto look_up = [&](uint32_t first, int& s, int& d, uint32_t& at) {
+    uint32_t p = first + lane * waves;
+    p = p < pieces ? p : pieces - 1;
+    const uint32_t row = p / row_pieces;
+    at = (p - row * row_pieces) * 64;
+    s = src_row[row];
+    d = dst_slot[row];
+  };
+  int src_l, dst_l;
+  uint32_t at_l;
+  look_up(wave, src_l, dst_l, at_l);
+  for (uint32_t first = wave; first < pieces; first += BATCH * waves) {
+    int src_n, dst_n;   // the next batch's, meanwhile
+    uint32_t at_n;
+    look_up(first + BATCH * waves < pieces ? first + BATCH * waves : first, src_n, dst_n, at_n);
+    for (int k = 0; k < BATCH && first + k * waves < pieces; k += FLIGHT) {
+      u32x4_t v[FLIGHT];
+#pragma unroll
+      for (int u = 0; u < FLIGHT; ++u) {
+        const uint32_t at = __builtin_amdgcn_readlane(at_l, k + u) + lane;
+        v[u] = src[(size_t)__builtin_amdgcn_readlane(src_l, k + u) * row_vecs + (at < row_vecs ? at : row_vecs - 1)];
+      }
+#pragma unroll
+      for (int u = 0; u < FLIGHT; ++u) {
+        const uint32_t at = __builtin_amdgcn_readlane(at_l, k + u) + lane;
+        if (at < row_vecs && first + (k + u) * waves < pieces)
+          dst[(size_t)__builtin_amdgcn_readlane(dst_l, k + u) * row_vecs + at] = v[u];
+      }
+    }
+    src_l = src_n; dst_l = dst_n; at_l = at_n;
   }
 }
 
@@ -27,8 +68,10 @@ hipError_t stem_copy_rows_kernel(stem_ctx* ctx, const void* E_host, const int32_
                                  int64_t n, int64_t row_bytes, void* E_compact, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   ProfScope ps(ctx, K_ROW_COPY, s);
-  const int grid = (int)(n < COPY_WGS ? n : COPY_WGS);
-  hipLaunchKernelGGL(copy_rows_kernel, dim3(grid), dim3(256), 0, s, (const uint4*)E_host, src_row, dst_slot, n,
-                     row_bytes / 16, (uint4*)E_compact);
+  const int64_t row_vecs = row_bytes / 16, row_pieces = (row_vecs + 63) / 64;
+  const int64_t pieces = n * row_pieces;   // below 2^31: at most 2^30 rows, and what device memory holds in whole pieces
+  const int grid = (int)std::min<int64_t>((pieces + 3) / 4, COPY_WGS);
+  hipLaunchKernelGGL(copy_rows_kernel, dim3(grid), dim3(256), COPY_LDS, s, (const u32x4_t*)E_host, src_row, dst_slot,
+                     (uint32_t)pieces, (uint32_t)row_vecs, (uint32_t)row_pieces, (u32x4_t*)E_compact);
   return hipGetLastError();
 }

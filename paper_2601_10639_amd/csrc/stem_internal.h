@@ -37,11 +37,10 @@ enum StemKernelId {
 #define STEM_MAX_PROF_EVENTS 8192
 #define STEM_PF_MAX_CHUNKS 16
 #define STEM_EDIT_MAX_TOKENS 64
-// One round of 256x256 down-product tiles per chunk of a host-table batch.  Chunks of two rounds make calls in turn on two
-// contexts shorter and a call by itself longer, whichever of batch, widths and distinct ids the line is drawn by.  us, one
-// round / two, d_model 2048, Zipf ids: 32768 tokens in turn 2786 / 2644, by itself 2803 / 3012; 65536 tokens 5149 / 4772
-// and 4824 / 4733; uniform ids, 65536 tokens by itself 15751 / 16000.
-#define STEM_PF_CHUNK_TILES 256
+// 256x256 down-product tiles per chunk of a host-table batch: one round on the compute units that the row copies of two
+// contexts leave free (prefetch.hip).  65536 tokens of 2048 x 8192, ms, calls in turn on two contexts / by itself: 256 tiles
+// 4.88 / 4.89, 240 tiles 4.97 / 4.69, 224 tiles 4.60 / 4.70.
+#define STEM_PF_CHUNK_TILES 224
 
 struct stem_ctx {
   stem_layer_desc desc;

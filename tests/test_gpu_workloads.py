@@ -441,7 +441,7 @@ def test_prefetch_rows_small(dtype, mode):
 
 
 def test_prefetch_rows_chunked_with_ragged_last_chunk():
-    """d_model 2048 gives chunks of 8192 tokens: 20000 tokens are two full chunks and one of 3616,
+    """d_model 2048 gives chunks of 7168 tokens: 20000 tokens are two full chunks and one of 5664,
     each waiting only for the rows its tokens use first.  Every token is checked."""
     T = 20000
     shape = inputs.StemShape("host-chunked", 2048, 128, 5000, 1, T, "bf16")
