@@ -68,16 +68,25 @@ __device__ __forceinline__ void wait_all_but(int younger) {
 // FA x 16 tokens, FB x 16 weight rows, W wavefronts with D K tiles in flight each
 template <int FA_, int FB_, int W_, int D_>
 struct Shape {
-  static constexpr int FA = FA_, FB = FB_, W = W_, D = D_, TM = 16 * FA, TN = 16 * FB;
-  static constexpr int SLOT = (TM + TN) * BK * 2;           // one K tile of both operands
-  static constexpr int PITCH = TN + 4;                      // floats per row of a partial tile in LDS
-  static constexpr int RING = W * D * SLOT, RED = W * TM * PITCH * 4;
+  static constexpr bool PAIR = false;
+  static constexpr int FA = FA_, FB = FB_, W = W_, D = D_, RM = 16 * FA, RN = 16 * FB;   // rows of a K tile in LDS
+  static constexpr int TM = RM, TN = RN, KW = BK;           // the output tile, K of a K tile
+  static constexpr int SLOT = (RM + RN) * BK * 2;           // one K tile of both operands
+  static constexpr int PITCH = RN + 4;                      // floats per row of a partial tile in LDS
+  static constexpr int RING = W * D * SLOT, RED = W * RM * PITCH * 4;
   static constexpr int LDS_BYTES = RING > RED ? RING : RED;
+};
+// 8 tokens x 8 weight rows, K tiles 128 wide: rows 0-7 of a fragment are the 8 rows at the first half of the K tile, rows
+// 8-15 the same rows at the second, and of the 16 x 16 products the two diagonal 8 x 8 blocks are the sums of the halves.
+template <int W_, int D_>
+struct PairShape : Shape<1, 1, W_, D_> {
+  static constexpr bool PAIR = true;
+  static constexpr int TM = 8, TN = 8, KW = 2 * BK;
 };
 
 template <class S, int EPI>
 __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
-  constexpr int FA = S::FA, FB = S::FB, W = S::W, D = S::D, TM = S::TM, TN = S::TN;
+  constexpr int FA = S::FA, FB = S::FB, W = S::W, D = S::D, TM = S::TM, TN = S::TN, RM = S::RM, KW = S::KW;
   constexpr int QUADS = TM * TN / 4, QT = (QUADS + 64 * W - 1) / (64 * W);   // quads of 4 columns; per thread
   constexpr int LOADS = 2 * (FA + FB);                                       // per wavefront and K tile
   __shared__ __attribute__((aligned(16))) char smem[S::LDS_BYTES];
@@ -100,7 +109,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
     tm = in - tn * p.mt;
   }
   const int m0 = tm * TM, n0 = tn * TN;
-  const int nk_all = p.K / BK, per = (nk_all + p.ksplit - 1) / p.ksplit, kt0 = z * per;
+  const int nk_all = p.K / KW, per = (nk_all + p.ksplit - 1) / p.ksplit, kt0 = z * per;
   const int nk = nk_all - kt0 < per ? nk_all - kt0 : per;      // at least 1
 
   // The gate epilogue multiplies by a gathered table row: its token ids are requested first of all, the row pieces
@@ -123,8 +132,9 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {
     const bool isA = i < 2 * FA;
-    const int row = (isA ? i : i - 2 * FA) * 8 + (lane >> 3), g = (isA ? m0 : n0) + row;
-    off[i] = g < (isA ? p.M : p.N) ? (uint32_t)((g * (isA ? p.lda : p.ldb) + ((lane & 7) ^ swz(row)) * 8) * 2) : OOB;
+    const int row = (isA ? i : i - 2 * FA) * 8 + (lane >> 3), g = (isA ? m0 : n0) + (S::PAIR ? row & 7 : row);
+    const int k = ((lane & 7) ^ swz(row)) * 8 + (S::PAIR ? (row >> 3) * BK : 0);
+    off[i] = g < (isA ? p.M : p.N) ? (uint32_t)((g * (isA ? p.lda : p.ldb) + k) * 2) : OOB;
   }
   // The walk over the K tiles starts at a place that differs from one weight tile to the next and wraps around:
   // operand rows are 2 to 16 KB apart, so their lines at one k sit in the same few memory channels.
@@ -133,7 +143,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
   const int nw = nk > wave ? (nk - wave + W - 1) / W : 0;      // this wavefront's K tiles
   char* const ring = smem + wave * (D * S::SLOT);
   auto request = [&](int slot) __attribute__((always_inline)) {
-    const int so = (kt0 + kpos) * (BK * 2);
+    const int so = (kt0 + kpos) * (KW * 2);
     char* const dst = ring + slot * S::SLOT;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) lds_dma_16(i < 2 * FA ? ra : rb, dst + i * 1024, off[i], so);
@@ -185,7 +195,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int b = 0; b < FB; ++b) xb[h][b] = *reinterpret_cast<const bf16x8_t*>(f + TM * 128 + b * 2048 + (h ? c1 : c0));
+      for (int b = 0; b < FB; ++b) xb[h][b] = *reinterpret_cast<const bf16x8_t*>(f + RM * 128 + b * 2048 + (h ? c1 : c0));
 #pragma unroll
       for (int a = 0; a < FA; ++a) xa[h][a] = *reinterpret_cast<const bf16x8_t*>(f + a * 2048 + (h ? c1 : c0));
     }
@@ -210,7 +220,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
   for (int a = 0; a < FA; ++a)
 #pragma unroll
     for (int b = 0; b < FB; ++b)
-      *reinterpret_cast<f32x4_t*>(red + (wave * TM + a * 16 + fr) * S::PITCH + b * 16 + fg * 4) = acc[a][b];
+      *reinterpret_cast<f32x4_t*>(red + (wave * RM + a * 16 + fr) * S::PITCH + b * 16 + fg * 4) = acc[a][b];
   __syncthreads();
   f32x4_t sum[QT];
 #pragma unroll
@@ -220,7 +230,10 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
     const float* src = red + (quad / (TN / 4)) * S::PITCH + (quad % (TN / 4)) * 4;
     sum[q] = *reinterpret_cast<const f32x4_t*>(src);
 #pragma unroll
-    for (int w = 1; w < W; ++w) sum[q] += *reinterpret_cast<const f32x4_t*>(src + w * TM * S::PITCH);
+    for (int w = 1; w < W; ++w) sum[q] += *reinterpret_cast<const f32x4_t*>(src + w * RM * S::PITCH);
+    if (S::PAIR)
+#pragma unroll
+      for (int w = 0; w < W; ++w) sum[q] += *reinterpret_cast<const f32x4_t*>(src + (w * RM + 8) * S::PITCH + 8);
   }
 
   if (EPI == EPI_SPLITK) {
@@ -292,12 +305,21 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
 // of the partial tiles (about 1.3 us): the more tokens, the longer a K tile takes.  Layer forward, us, least 64 / 32 / 16
 // K tiles: 1024 x 4096, 1 token 10.0 / 10.4 / 10.9, 16 tokens 11.3 / 11.0 / 11.0, 64 tokens 16.8 / 14.4 / 13.2; 1536 x 5120, 1 token
 // 14.8 / 13.7 / 13.8, 64 tokens 26.8 / 21.5 / 21.5.
-struct DecodePlan { int fa, fb, mt, nt, ksplit; };
+struct DecodePlan { int fa, fb, mt, nt, ksplit; bool pair; };
 
 // K of more than 2048 (the down product of the larger layers) only with 16 weight rows: 2048 x 8192, 256 tokens, 25.0 us
 // with 32 against 24.2 on the few-row kernel.
-bool decode_plan(int M, int N, int K, bool may_split, size_t ws_bytes, DecodePlan* plan) {
+bool decode_plan(int M, int N, int K, bool plain, bool may_split, size_t ws_bytes, DecodePlan* plan) {
   const int fa = M <= 16 ? 1 : M <= 32 ? 2 : 4, mt = (M + 16 * fa - 1) / (16 * fa);
+  // Up to 8 tokens: 8 weight rows per workgroup, so that K needs no slices and no exchange (2 to 3 us of a launch) while the
+  // weight tiles still give one workgroup per CU.  Layer forward, us, 16 weight rows in slices / 8: 2048 x 8192, 1 token 18.2 / 16.9,
+  // 4 tokens 19.1 / 18.0, 8 tokens 19.2 / 18.6; 1536 x 5120, 2 tokens 12.7 / 11.3; 1024 x 4096, 1 token 9.9 / 9.2, 8 tokens 10.2 / 9.6;
+  // 512 x 1536, 1 token 6.9 / 6.5.  (Each workgroup reads all tokens' rows whole, so the gain shrinks with the tokens.  16 wavefronts
+  // with 2 K tiles in flight 17.4, 8 with 5 17.1.)
+  if (plain && M <= 8 && N <= 8 * 256 && N % 8 == 0 && K % (2 * BK) == 0) {
+    *plan = {1, 1, 1, N / 8, 1, true};
+    return true;
+  }
   for (int fb = 1; fb <= (fa == 4 ? 4 : 2); fb *= 2) {
     const int nt = (N + 16 * fb - 1) / (16 * fb);
     const bool last = fa < 4 && fb == 2;      // wide weight matrices and few tokens: several rounds
@@ -308,7 +330,7 @@ bool decode_plan(int M, int N, int K, bool may_split, size_t ws_bytes, DecodePla
     while (may_split && ks < MAX_SLICES && mt * nt * ks * 2 <= 256 && K / BK / (ks * 2) >= least &&
            (size_t)mt * nt * ks * 2 * fa * fb * 1024 <= ws_bytes)
       ks *= 2;
-    *plan = {fa, fb, mt, nt, ks};
+    *plan = {fa, fb, mt, nt, ks, false};
     return true;
   }
   return false;
@@ -330,13 +352,13 @@ void launch(int epi, const GemmArgs& p, hipStream_t s) {
 // 12.0 / 19.8, 256 tokens 21.1 / 27.1, 320 tokens 27.7 / 25.9; 512 x 1536: 512 tokens 14.2 / 19.4.
 bool stem_gemm_decode_fits(int M, int N, int K) {
   DecodePlan pl;
-  return M <= 512 && K % BK == 0 && N % 4 == 0 && decode_plan(M, N, K, false, 0, &pl);
+  return M <= 512 && K % BK == 0 && N % 4 == 0 && decode_plan(M, N, K, false, false, 0, &pl);
 }
 
 void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* route) {
   DecodePlan pl = {};
-  decode_plan(M, N, K, epi == EPI_BF16 && ws_bytes > 0, (size_t)ws_bytes, &pl);
-  route[0] = ROUTE_DECODE; route[1] = 16 * pl.fa; route[2] = 16 * pl.fb; route[3] = pl.ksplit;
+  decode_plan(M, N, K, epi == EPI_BF16, epi == EPI_BF16 && ws_bytes > 0, (size_t)ws_bytes, &pl);
+  route[0] = ROUTE_DECODE; route[1] = pl.pair ? 8 : 16 * pl.fa; route[2] = pl.pair ? 8 : 16 * pl.fb; route[3] = pl.ksplit;
 }
 
 hipError_t stem_gemm_decode_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s) {
@@ -345,7 +367,7 @@ hipError_t stem_gemm_decode_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs
   if ((int64_t)a.M * a.lda * 2 > lim || (int64_t)a.N * a.ldb * 2 > lim) return hipErrorInvalidValue;
   DecodePlan pl;
   if (!stem_gemm_decode_fits(a.M, a.N, a.K) ||
-      !decode_plan(a.M, a.N, a.K, epi == EPI_BF16 && a.ws && a.tickets, a.ws_bytes, &pl))
+      !decode_plan(a.M, a.N, a.K, epi == EPI_BF16, epi == EPI_BF16 && a.ws && a.tickets, a.ws_bytes, &pl))
     return hipErrorInvalidValue;
   if (epi != EPI_GATE && epi != EPI_BF16) return hipErrorInvalidValue;
   GemmArgs p = a;
@@ -353,7 +375,8 @@ hipError_t stem_gemm_decode_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs
   p.inv_mt = 1.0f / (float)p.mt;
   p.inv_per_z = 1.0f / (float)(p.mt * p.nt);
   ProfScope ps(ctx, kid, s);
-  if (pl.fa == 1 && pl.fb == 1) launch<Shape<1, 1, 8, 4>>(epi, p, s);
+  if (pl.pair) hipLaunchKernelGGL((gemm_decode_kernel<PairShape<8, 4>, EPI_BF16>), dim3((unsigned)p.nt), dim3(512), 0, s, p);
+  else if (pl.fa == 1 && pl.fb == 1) launch<Shape<1, 1, 8, 4>>(epi, p, s);
   else if (pl.fa == 1) launch<Shape<1, 2, 4, 6>>(epi, p, s);
   else if (pl.fa == 2 && pl.fb == 1) launch<Shape<2, 1, 8, 3>>(epi, p, s);
   else if (pl.fa == 2) launch<Shape<2, 2, 4, 4>>(epi, p, s);

@@ -32,3 +32,15 @@ def test_waits_allow_for_no_loads_but_the_younger_k_tiles(source, pattern, tmp_p
         assert waits and max(waits) == (depth - 1) * per_tile, (name, waits)
         seen += 1
     assert seen >= 7
+
+
+def test_waits_of_the_kernel_with_paired_k_halves(tmp_path):
+    out = str(tmp_path / "kernels.s")
+    subprocess.run([build._hipcc(), *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, "gemm_decode_bf16.hip"),
+                    "-o", out], check=True, capture_output=True)
+    kernels = [(int(m.group(1)), m.group(2)) for m in
+               re.finditer(r"^_Z\S+gemm_decode_kernelINS_9PairShapeILi\d+ELi(\d+)EEE[^\n]*:[^\n]*\n(.*?)\.Lfunc_end", open(out).read(), re.S | re.M)]
+    assert kernels
+    for depth, body in kernels:
+        waits = [int(n) for block in re.findall(r";#ASMSTART(.*?);#ASMEND", body, re.S) for n in re.findall(r"vmcnt\((\d+)\)", block)]
+        assert waits and max(waits) == (depth - 1) * 4, waits    # 16 rows of each operand: two loads each
