@@ -599,6 +599,55 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int32_t* __restr
   }
 }
 
+// Small batches, where a chunk's row loads and the second launch are all latency: one launch, a workgroup for every sorted
+// position and slab of 64 * COLS columns; those of a run's first position sum the run, the others end at once.  A run of up to
+// SHORT_RUN rows is one round of loads of one wavefront; a longer one is cut into four consecutive stretches, one per wavefront,
+// each summed in ascending position, and the four sums are added in order.
+constexpr int SHORT_RUN = 16;
+template <bool BF16>
+__global__ __launch_bounds__(256) void seg_runs_kernel(const void* __restrict__ dU, const int32_t* __restrict__ perm,
+                                                       const int32_t* __restrict__ seg_of,
+                                                       const int32_t* __restrict__ seg_offsets, int F,
+                                                       float* __restrict__ dE_rows) {
+  constexpr int COLS = RowVec<BF16>::COLS;
+  __shared__ float red[3][64][COLS + 1];
+  const int k = blockIdx.x;
+  const int j = seg_of[k], before = k > 0 ? seg_of[k - 1] : -1;
+  if (before == j) return;
+  const int n = seg_offsets[j + 1] - k;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = n <= SHORT_RUN ? n : (n + 3) >> 2;
+  const int r0 = wave * q, r1 = min(n, r0 + q);
+  const int col = (blockIdx.y * 64 + lane) * COLS;
+  const bool live = col < F;
+  const int colc = live ? col : 0;
+  float acc[COLS];
+#pragma unroll
+  for (int x = 0; x < COLS; ++x) acc[x] = 0.f;
+  for (int rb = r0; rb < r1; rb += SHORT_RUN) {
+    typename RowVec<BF16>::raw_t data[SHORT_RUN];
+#pragma unroll
+    for (int u = 0; u < SHORT_RUN; ++u)
+      if (rb + u < r1) data[u] = RowVec<BF16>::load(dU, perm[k + rb + u], F, colc);
+#pragma unroll
+    for (int u = 0; u < SHORT_RUN; ++u)
+      if (rb + u < r1) RowVec<BF16>::add(data[u], acc);
+  }
+  if (n > SHORT_RUN) {
+    if (wave > 0) {
+#pragma unroll
+      for (int x = 0; x < COLS; ++x) red[wave - 1][lane][x] = acc[x];
+    }
+    __syncthreads();
+    if (wave == 0)
+      for (int w = 1; w < 4; ++w)
+        if (w * q < n)
+#pragma unroll
+          for (int x = 0; x < COLS; ++x) acc[x] += red[w - 1][lane][x];
+  }
+  if (wave == 0 && live) store_cols<COLS>(dE_rows + (int64_t)j * F + col, acc);
+}
+
 int bits_for(int V) {
   int b = 1;
   while (b < 31 && (1ll << b) < (long long)V) ++b;
@@ -701,6 +750,18 @@ hipError_t stem_seg_reduce(stem_ctx* ctx, const EmbedScratch& ws, int is_bf16, c
                            const int32_t* seg_offsets, int64_t T, int F, float* dE_rows, hipStream_t s) {
   const int chunks = (int)((T + SEG_ROWS - 1) / SEG_ROWS);
   const int cols = is_bf16 ? 8 : 4;
+  // One launch while its workgroups, most of which end at once, and the longest run cost less than the second launch and the
+  // partial sums.  us in a graph, two launches / one, Zipf ids: fp32 128 x 256 9.4 / 2.8, 1000 x 1024 12.8 / 5.6, 1024 x 2048
+  // 13.1 / 7.0, 2048 x 2048 14.1 / 13.7, 4096 x 512 12.5 / 13.4; bf16 130 x 8192 11.5 / 4.0, 500 x 8192 12.5 / 7.0, 1000 x 4096 12.6 / 10.2,
+  // 2000 x 2048 12.5 / 14.4, 1999 x 8192 19.2 / 27.4.
+  const int64_t run_slabs = (F + 64 * cols - 1) / (64 * cols);
+  if (T <= 1024 && T * run_slabs <= 8192) {
+    ProfScope ps(ctx, K_SEG_REDUCE, s);
+    const dim3 grid((unsigned)T, (unsigned)run_slabs);
+    if (is_bf16) hipLaunchKernelGGL(seg_runs_kernel<true>, grid, dim3(256), 0, s, dU, perm, ws.seg_of, seg_offsets, F, dE_rows);
+    else hipLaunchKernelGGL(seg_runs_kernel<false>, grid, dim3(256), 0, s, dU, perm, ws.seg_of, seg_offsets, F, dE_rows);
+    return hipGetLastError();
+  }
   const int slabs = (F + 256 * cols - 1) / (256 * cols);
   {
     ProfScope ps(ctx, K_SEG_REDUCE, s);
