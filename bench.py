@@ -281,7 +281,8 @@ def bench_layer(args, shape, dev, steps, warmup, peaks, detail):
         avg = ms / n
         k = {"avg_ms": round(avg, 5), "launches": n}
         if name.startswith("gemm_"):
-            fl = gemm_flop * (2 if (name == "gemm_dx" and variant != "stem") else 1)   # dx spans both projections
+            # dx spans both projections; gemm_dw: the layer's weight gradients in one launch
+            fl = gemm_flop * ((2 if variant == "stem" else 3) if name == "gemm_dw" else 2 if (name == "gemm_dx" and variant != "stem") else 1)
             k["tflops"] = round(fl / (avg * 1e-3) / 1e12, 2)
             k["frac_mfma_peak"] = round(k["tflops"] / peak_tf, 4)
             if bf16:

@@ -21,7 +21,7 @@ const char* const kKernelNames[K_COUNT_] = {
     "gemm_dw_gate",    "silu_gather",      "sort_count",    "sort_scan",    "sort_scatter",
     "sort_fused",      "unique",          "seg_reduce",   "seg_combine",   "sparse_adamw", "row_copy",
     "splitk_reduce",   "gemm_up",      "gemm_dw_up",   "sort_merge",
-    "grads_f32"};
+    "grads_f32", "gemm_dw"};
 
 #define fail stem_fail
 
@@ -431,26 +431,27 @@ stem_status stem_ffn_backward(stem_ctx* c, const void* dy, const void* x, const 
       a.inG = static_cast<const bf16_t*>(saved_G); a.outdU = static_cast<bf16_t*>(dU); a.outdG = dGb;
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DH, OP_KC, OP_MC, EPI_DH, a, s));
     }
-    {  // dW_down[d,F] = dy^T H
-      GemmArgs a = {};
-      a.A = dyb; a.lda = d; a.B = Hb; a.ldb = F;
-      a.M = d; a.N = F; a.K = (int)T; a.C = dW_down; a.accumulate = accumulate; a.flag = c->flag;
+    GemmArgs w[2] = {};
+    w[0].A = dyb; w[0].lda = d; w[0].B = Hb; w[0].ldb = F;   // dW_down[d,F] = dy^T H
+    w[0].M = d; w[0].N = F; w[0].C = dW_down;
+    w[1].A = dGb; w[1].lda = F; w[1].B = static_cast<const bf16_t*>(x); w[1].ldb = d;   // dW_gate[F,d] = dG^T x
+    w[1].M = F; w[1].N = d; w[1].C = dW_gate;
+    for (GemmArgs& a : w) {
+      a.K = (int)T; a.accumulate = accumulate; a.flag = c->flag;
       a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
-      HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, a, s));
     }
+    // The two together, and before dx, unless dW_gate lies over something that is read by then or beside it.
+    const size_t Td = (size_t)T * d * 2, TF = (size_t)T * F * 2, Fd = (size_t)F * d * 4;
+    const bool apart = !overlap(dW_gate, Fd, dy, Td) && !overlap(dW_gate, Fd, H, TF) && !(dx && overlap(dW_gate, Fd, W_gate, Fd / 2));
+    static const int kids[2] = {K_GEMM_DWDOWN, K_GEMM_DWGATE};
+    HIP_TRY(c, stem_gemm_bf16_group(c, kids, w, apart ? 2 : 1, s));
     if (dx) {  // dx = dG W_gate
       GemmArgs a = {};
       a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;
       a.M = (int)T; a.N = d; a.K = F; a.C = dx; a.flag = c->flag; a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DX, OP_KC, OP_MC, EPI_BF16, a, s));
     }
-    {  // dW_gate[F,d] = dG^T x
-      GemmArgs a = {};
-      a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(x); a.ldb = d;
-      a.M = F; a.N = d; a.K = (int)T; a.C = dW_gate; a.accumulate = accumulate; a.flag = c->flag;
-      a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
-      HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, a, s));
-    }
+    if (!apart) HIP_TRY(c, stem_gemm_bf16_group(c, kids + 1, w + 1, 1, s));
   } else {
     const float* dyf = static_cast<const float*>(dy);
     float* dG = static_cast<float*>(c->dG_ws);
@@ -577,13 +578,25 @@ stem_status stem_ffn_up_backward(stem_ctx* c, const void* dy, const void* x, con
     a.outdU = dVb; a.outdG = dGb;
     HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DH, OP_KC, OP_MC, E ? EPI_DH_UPE : EPI_DH_UP, a, s));
   }
-  {  // dW_down[d,F] = dy^T H
-    GemmArgs a = {};
-    a.A = dyb; a.lda = d; a.B = static_cast<const bf16_t*>(saved_H); a.ldb = F;
-    a.M = d; a.N = F; a.K = (int)T; a.C = dW_down; a.accumulate = accumulate; a.flag = c->flag;
-      a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
-    HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, a, s));
+  GemmArgs w[3] = {};
+  w[0].A = dyb; w[0].lda = d; w[0].B = static_cast<const bf16_t*>(saved_H); w[0].ldb = F;   // dW_down[d,F] = dy^T H
+  w[0].M = d; w[0].N = F; w[0].C = dW_down;
+  w[1].A = dGb; w[1].C = dW_gate;   // dW_gate[F,d] = dG^T x
+  w[2].A = dVb; w[2].C = dW_up;     // dW_up[F,d] = dV^T x
+  for (GemmArgs& a : w) {
+    if (&a != w) { a.lda = F; a.B = static_cast<const bf16_t*>(x); a.ldb = d; a.M = F; a.N = d; }
+    a.K = (int)T; a.accumulate = accumulate; a.flag = c->flag;
+    a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
   }
+  // The three together, and before dx, unless one lies over something that is read by then or beside it.
+  const size_t Td = (size_t)T * d * 2, TF = (size_t)T * F * 2, Fd = (size_t)F * d * 4;
+  bool apart = true;
+  for (const float* g : {dW_gate, dW_up})
+    apart = apart && !overlap(g, Fd, dy, Td) && !overlap(g, Fd, saved_H, TF) &&
+            !(dx && (overlap(g, Fd, W_gate, Fd / 2) || overlap(g, Fd, W_up, Fd / 2) || overlap(g, Fd, dV, TF)));
+  apart = apart && !overlap(dW_gate, Fd, dV, TF);
+  static const int kids[3] = {K_GEMM_DWDOWN, K_GEMM_DWGATE, K_GEMM_DWUP};
+  HIP_TRY(c, stem_gemm_bf16_group(c, kids, w, apart ? 3 : 1, s));
   if (dx) {  // dx = dG W_gate + dV W_up: one product over the concatenated K range
     GemmArgs a = {};
     a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;
@@ -591,14 +604,9 @@ stem_status stem_ffn_up_backward(stem_ctx* c, const void* dy, const void* x, con
     a.M = (int)T; a.N = d; a.K = F; a.C = dx; a.flag = c->flag; a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
     HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DX, OP_KC, OP_MC, EPI_BF16, a, s));
   }
-  {  // dW_gate[F,d] = dG^T x and dW_up[F,d] = dV^T x
-    GemmArgs a = {};
-    a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(x); a.ldb = d;
-    a.M = F; a.N = d; a.K = (int)T; a.C = dW_gate; a.accumulate = accumulate; a.flag = c->flag;
-      a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
-    HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, a, s));
-    a.A = dVb; a.C = dW_up;
-    HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWUP, OP_MC, OP_MC, EPI_F32, a, s));
+  if (!apart) {
+    HIP_TRY(c, stem_gemm_bf16_group(c, kids + 1, w + 1, 1, s));
+    HIP_TRY(c, stem_gemm_bf16_group(c, kids + 2, w + 2, 1, s));
   }
   return STEM_OK;
 }

@@ -217,11 +217,13 @@ __device__ __forceinline__ void unpack8(uint4 u, float (&f)[8]) {
 // their epilogues (each reads a G tile and writes two tiles) meet less often: 0.565 ms with
 // 8, 0.545 with 4 or 6, 0.537 with 3 or 5, 0.532 with 7, 0.545-0.55 with 9, 11, 13
 // (d_model 2048, d_ff 8192, 16384 tokens).
-template <int GM>
-__device__ __forceinline__ void tile_of_block(int b, int nb, int ntm, int ntn, int& tm, int& tn) {
+__device__ __forceinline__ int xcd_major(int b, int nb) {
   const int q = nb >> 3, r = nb & 7;
   const int xcd = b & 7, idx = b >> 3;
-  const int L = xcd * q + (xcd < r ? xcd : r) + idx;
+  return xcd * q + (xcd < r ? xcd : r) + idx;
+}
+template <int GM>
+__device__ __forceinline__ void tile_at(int L, int ntm, int ntn, int& tm, int& tn) {
   const int per_group = GM * ntn;
   const int group = L / per_group;
   const int first = group * GM;
@@ -273,16 +275,34 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   const bool load_wave = C::LW && wave_id >= C::WAVES;
   const int wave = load_wave ? wave_id - C::WAVES : wave_id;
   const int wm = wave / C::WN, wn = wave % C::WN;
-  const int ntm = (p.M + C::TM - 1) / C::TM, ntn = (p.N + C::TN - 1) / C::TN;
-  constexpr int BAND = (EPI == EPI_DH || EPI == EPI_DH_UP || EPI == EPI_DH_UPE) ? 7 : 4;   // see tile_of_block
-  int tm, tn;
+  int ntm = (p.M + C::TM - 1) / C::TM, ntn = (p.N + C::TN - 1) / C::TN;
+  constexpr int BAND = (EPI == EPI_DH || EPI == EPI_DH_UP || EPI == EPI_DH_UPE) ? 7 : 4;   // see tile_at
+  int tm, tn, L = xcd_major(blockIdx.x, gridDim.x), z = 0;
+  if (EPI == EPI_F32 && LA == OP_MC && LB == OP_MC) {   // which of the launch's products
+    const int all = gridDim.x / p.ksplit;
+    int in = L % all;
+    size_t before = 0;
+    for (int e = 0; e < 2; ++e) {
+      const int here = ntm * ntn;
+      if (e >= p.n_more || in < here) break;
+      in -= here;
+      before += (size_t)p.M * p.N;
+      p.A = p.more[e].A; p.B = p.more[e].B; p.C = p.more[e].C; p.M = p.more[e].M; p.N = p.more[e].N;
+      p.lda = p.more[e].lda; p.ldb = p.more[e].ldb;
+      ntm = (p.M + C::TM - 1) / C::TM; ntn = (p.N + C::TN - 1) / C::TN;
+    }
+    p.ws += before;
+    L = L / all * all + in;
+  }
   if (EPI == EPI_F32 && p.ksplit > 1) {
     // Split along K (few output tiles, long K): slice z of the K tiles, its product stored plainly to
     // slice z of the partial buffer; a second kernel sums the slices in order.  The slice is
-    // expressed by moving the operands and shrinking K.
-    const int ntiles = ntm * ntn;
-    const int z = blockIdx.x / ntiles;
-    tile_of_block<BAND>(blockIdx.x - z * ntiles, ntiles, ntm, ntn, tm, tn);
+    // expressed by moving the operands and shrinking K.  The slices follow each other in the XCDs' runs of tiles, so an XCD
+    // works on one or two of them (1024 x 4096 weight gradient, 16384 tokens, 4 slices: 123.5 us with every slice on every
+    // XCD, 122.2).
+    const int ntiles = gridDim.x / p.ksplit;
+    z = L / ntiles;
+    L -= z * ntiles;
     int zk = z, slices = p.ksplit;
     if (LA == OP_KC && p.A2) {   // two operand pairs of the same K: half of the slices each
       slices >>= 1;
@@ -299,11 +319,10 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
     p.B += LB == OP_KC ? (size_t)k0 : (size_t)k0 * p.ldb;
     p.K = klen;
     p.kc_skip = k0;                                          // K-contiguous windows end k0 elements earlier
-    p.C = p.ws + (size_t)z * p.M * p.N;
+    p.C = p.ws + (size_t)z * p.elems;
     p.accumulate = 0;
-  } else {
-    tile_of_block<BAND>(blockIdx.x, gridDim.x, ntm, ntn, tm, tn);
   }
+  tile_at<BAND>(L, ntm, ntn, tm, tn);
   const int m0 = tm * C::TM, n0 = tn * C::TN;
   // K rotation.  Workgroups on XCD x start their K loop x eighths of the way in and wrap around, so
   // the eight XCDs stream eight different stretches of the operands' rows at any moment instead of
@@ -783,10 +802,12 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
 }
 
 // C[i] = (accumulate ? C[i] : 0) + (sum over the K slices, in slice order, of ws[z][i]); 4 elements per thread
+struct SumOut { float* C[3]; int64_t end[3]; };   // the products' outputs, and where each ends in a slice
 __global__ __launch_bounds__(256) void splitk_sum_f32_kernel(const float* __restrict__ ws, int ksplit, int64_t total,
-                                                             float* __restrict__ C, int accumulate) {
+                                                             SumOut out, int accumulate) {
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= total) return;
+  float* const C = i < out.end[0] ? out.C[0] : i < out.end[1] ? out.C[1] - out.end[0] : out.C[2] - out.end[1];
   f32x4_t s = *reinterpret_cast<const f32x4_t*>(ws + i);
   for (int z = 1; z < ksplit; ++z) s += *reinterpret_cast<const f32x4_t*>(ws + (size_t)z * total + i);
   if (accumulate) s += *reinterpret_cast<const f32x4_t*>(C + i);
@@ -808,20 +829,23 @@ __global__ __launch_bounds__(256) void splitk_sum_f32_kernel(const float* __rest
 struct TilingCost { int tm, tn; double idle, full, fixed_plain, fixed_fused, fixed_f32; };
 constexpr TilingCost kTilings[3] = {{256, 256, 0.86, 1.39, 9, 21, 17.5}, {256, 128, 0.45, 0.86, 6, 11, 11}, {128, 128, 0.34, 0.56, 4, 6.5, 5.5}};
 
-struct Plan { int tiling, ksplit; };
+struct Plan { int tiling, ksplit; double us; };
 
 // fused: the epilogue carries the layer's element-wise work and cannot be split.  ops: operand pairs of the K range
 // (each pair is cut into the same number of slices).  Slices of which the last ones would be left without a K tile (33 K
-// tiles in 8 slices of 5) become as many as have one.
-Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_bytes) {
-  Plan best = {0, 1};
-  double best_us = 1e30;
+// tiles in 8 slices of 5) become as many as have one.  n: products in the launch, of M x N outputs or N x M.
+Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_bytes, int n = 1, const bool* turned = nullptr) {
+  Plan best = {0, 1, 1e30};
   const int nk = ops * ((K + BK - 1) / BK);
   for (int t = 0; t < 3; ++t) {
     const TilingCost& c = kTilings[t];
-    const double tiles = (double)((M + c.tm - 1) / c.tm) * ((N + c.tn - 1) / c.tn);
+    double tiles = 0;
+    for (int q = 0; q < n; ++q) {
+      const int m = turned && turned[q] ? N : M, w = turned && turned[q] ? M : N;
+      tiles += (double)((m + c.tm - 1) / c.tm) * ((w + c.tn - 1) / c.tn);
+    }
     for (int ks = 1; ks <= 8; ks *= 2) {
-      if (ks > 1 && (fused || (double)M * N * 4 * ks > (double)ws_bytes || nk / ks < 4 || tiles * ks > 512)) break;
+      if (ks > 1 && (fused || (double)M * N * n * 4 * ks > (double)ws_bytes || nk / ks < 4 || tiles * ks > 512)) break;
       int kt = nk, slices = 1;
       if (ks > 1) {
         kt = (nk + ks - 1) / ks;
@@ -832,8 +856,8 @@ Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_b
       const double rest = wgs - rounds * 256.0;
       double us = rounds * (kt * c.full + fixed);
       if (rest > 0) us += kt * (c.idle + (c.full - c.idle) * rest / 256) + fixed;
-      if (ks > 1) us += 3 + (slices + 1.0) * M * N * 4 / 4.2e6;   // the kernel that sums the slices: launch, and 4.2 TB/s
-      if (us < best_us) { best_us = us; best = {t, slices}; }
+      if (ks > 1) us += 3 + (slices + 1.0) * M * N * n * 4 / 4.2e6;   // the kernel that sums the slices: launch, and 4.2 TB/s
+      if (us < best.us) best = {t, slices, us};
     }
   }
   return best;
@@ -841,9 +865,10 @@ Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_b
 
 template <class C, int LA, int LB, int EPI>
 hipError_t launch_tiles(stem_ctx* ctx, int kid, const GemmArgs& a, hipStream_t s) {
-  const int ntm = (a.M + C::TM - 1) / C::TM, ntn = (a.N + C::TN - 1) / C::TN;
+  int tiles = ((a.M + C::TM - 1) / C::TM) * ((a.N + C::TN - 1) / C::TN);
+  for (int e = 0; e < a.n_more; ++e) tiles += ((a.more[e].M + C::TM - 1) / C::TM) * ((a.more[e].N + C::TN - 1) / C::TN);
   ProfScope ps(ctx, kid, s);
-  hipLaunchKernelGGL((gemm_bf16_kernel<C, LA, LB, EPI>), dim3(ntm * ntn * a.ksplit), dim3((C::WAVES + C::LW) * 64), 0, s, a);
+  hipLaunchKernelGGL((gemm_bf16_kernel<C, LA, LB, EPI>), dim3(tiles * a.ksplit), dim3((C::WAVES + C::LW) * 64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -854,22 +879,33 @@ hipError_t launch_tiling(int tiling, stem_ctx* ctx, int kid, const GemmArgs& a, 
   return launch_tiles<Tile256, LA, LB, EPI>(ctx, kid, a, s);
 }
 
+hipError_t sum_slices_f32(stem_ctx* ctx, const GemmArgs& a, hipStream_t s) {
+  SumOut out;
+  int64_t end = 0;
+  for (int e = 0; e < 3; ++e) {
+    if (e <= a.n_more) end += e == 0 ? (int64_t)a.M * a.N : (int64_t)a.more[e - 1].M * a.more[e - 1].N;
+    out.C[e] = static_cast<float*>(e == 0 || e > a.n_more ? a.C : a.more[e - 1].C);
+    out.end[e] = end;
+  }
+  ProfScope ps(ctx, K_SPLITK_REDUCE, s);
+  hipLaunchKernelGGL(splitk_sum_f32_kernel, dim3((unsigned)((a.elems / 4 + 255) / 256)), dim3(256), 0, s, a.ws, a.ksplit,
+                     a.elems, out, a.accumulate);
+  return hipGetLastError();
+}
+
 template <int LA, int LB, int EPI>
 hipError_t launch(stem_ctx* ctx, int kid, GemmArgs a, hipStream_t s) {
   constexpr bool PLAIN = (EPI == EPI_BF16 || EPI == EPI_BF16_RES), F32 = (EPI == EPI_F32);
   const size_t ws_bytes = a.ws && (int64_t)a.M * a.N % 4 == 0 && (!a.A2 || a.K2 == a.K) ? a.ws_bytes : 0;
   const Plan plan = choose_plan(a.M, a.N, a.K, a.A2 ? 2 : 1, !PLAIN && !F32, F32, ws_bytes);
   a.ksplit = plan.ksplit;
+  a.elems = (int64_t)a.M * a.N;
   if constexpr (PLAIN || F32) {
     if (plan.ksplit > 1) {   // fp32 partial products, one per K slice, and a kernel that sums them in slice order
       hipError_t e = launch_tiling<LA, LB, EPI_F32>(plan.tiling, ctx, kid, a, s);
       if (e != hipSuccess) return e;
-      const int64_t total = (int64_t)a.M * a.N;
-      if (PLAIN) return stem_splitk_reduce(ctx, a.ws, plan.ksplit, total, EPI == EPI_BF16_RES ? a.residual : nullptr, a.C, s);
-      ProfScope ps(ctx, K_SPLITK_REDUCE, s);
-      hipLaunchKernelGGL(splitk_sum_f32_kernel, dim3((unsigned)((total / 4 + 255) / 256)), dim3(256), 0, s, a.ws,
-                         plan.ksplit, total, static_cast<float*>(a.C), a.accumulate);
-      return hipGetLastError();
+      if (PLAIN) return stem_splitk_reduce(ctx, a.ws, plan.ksplit, a.elems, EPI == EPI_BF16_RES ? a.residual : nullptr, a.C, s);
+      return sum_slices_f32(ctx, a, s);
     }
   }
   return launch_tiling<LA, LB, EPI>(plan.tiling, ctx, kid, a, s);
@@ -908,4 +944,60 @@ hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const
     if (epi == EPI_F32) return launch<OP_MC, OP_MC, EPI_F32>(ctx, kid, a, s);
   }
   return hipErrorInvalidValue;
+}
+
+// Weight gradients of one K whose tiles leave part of the chip idle, or need K slices to fill it, share a launch: fewer
+// slices (whose partial products cost as much to sum as to write), one prologue and epilogue per round instead of one per
+// product, and one last round.  Taken where the cost model prices the one launch 4 % below the several (and 3 us a launch: the gap
+// and the slowest XCD's tail), or where the rounds stay the same.  Backward, us, apart / together: 1024 x 4096, 16384 tokens dW 2 x (117 + 15) / 220 + 18; additive layer,
+// 1024 x 4096, 4096 tokens dW 123 / 98.  Over 107 layers (d_model 512 to 2048, 130 to 65536 tokens) the backward call takes
+// 0.925 of the time, with an up projection 0.88; the dearest choice loses 1.7 % (without the 4 %: 7 %, 1728 x 5120, 31068 tokens).
+struct GroupPlan { bool together; Plan plan; };
+static GroupPlan plan_group(const GemmArgs* a, int n, size_t ws_bytes) {
+  bool turned[3] = {}, alike = n <= 3;
+  double apart = 0;
+  Plan one[3] = {};
+  for (int e = 0; e < n && alike; ++e) {
+    turned[e] = a[e].M != a[0].M;
+    alike = a[e].K == a[0].K && a[e].accumulate == a[0].accumulate &&
+            (turned[e] ? a[e].M == a[0].N && a[e].N == a[0].M : a[e].N == a[0].N);
+    one[e] = choose_plan(a[e].M, a[e].N, a[e].K, 1, false, true, ws_bytes);
+    apart += one[e].us;
+  }
+  if (n < 2 || !alike) return {false, {}};
+  const Plan p = choose_plan(a[0].M, a[0].N, a[0].K, 1, false, true, ws_bytes, n, turned);
+  bool whole = p.us <= apart * 1.0001;   // the same rounds, one after another: nothing but the launches between them is lost
+  for (int e = 0; e < n; ++e) whole = whole && one[e].tiling == p.tiling && one[e].ksplit == p.ksplit;
+  return {whole || p.us <= 0.96 * apart + 3 * (n - 1), p};
+}
+
+void stem_route_weight_grads(int d, int F, int64_t T, int n, int64_t ws_bytes, int32_t* route) {
+  GemmArgs a[3] = {};
+  for (int e = 0; e < 3; ++e) { a[e].M = e ? F : d; a[e].N = e ? d : F; a[e].K = (int)T; }
+  const GroupPlan g = plan_group(a, n, (size_t)ws_bytes);
+  route[0] = g.together;
+  route[1] = kTilings[g.plan.tiling].tm; route[2] = kTilings[g.plan.tiling].tn; route[3] = g.plan.ksplit;
+}
+
+hipError_t stem_gemm_bf16_group(stem_ctx* ctx, const int* kids, const GemmArgs* a, int n, hipStream_t s) {
+  const int64_t lim = 0x7fffffff;   // operands and outputs below 2 GiB, as for each product by itself
+  bool fits = true;
+  for (int e = 0; e < n; ++e)
+    fits = fits && a[e].M > 0 && a[e].N > 0 && a[e].K > 0 && (int64_t)a[e].K * a[e].lda * 2 <= lim &&
+           (int64_t)a[e].K * a[e].ldb * 2 <= lim && (int64_t)a[e].M * a[e].N * 4 <= lim;
+  const GroupPlan plan = plan_group(a, n, a[0].ws && (int64_t)a[0].M * a[0].N % 4 == 0 ? a[0].ws_bytes : 0);
+  if (fits && plan.together) {
+    GemmArgs g = a[0];
+    g.n_more = n - 1;
+    for (int e = 1; e < n; ++e) g.more[e - 1] = {a[e].A, a[e].B, a[e].C, a[e].M, a[e].N, a[e].lda, a[e].ldb};
+    g.ksplit = plan.plan.ksplit;
+    g.elems = (int64_t)g.M * g.N * n;
+    const hipError_t r = launch_tiling<OP_MC, OP_MC, EPI_F32>(plan.plan.tiling, ctx, K_GEMM_DW, g, s);
+    return r != hipSuccess || g.ksplit == 1 ? r : sum_slices_f32(ctx, g, s);
+  }
+  for (int e = 0; e < n; ++e) {
+    const hipError_t r = stem_gemm_bf16(ctx, kids[e], OP_MC, OP_MC, EPI_F32, a[e], s);
+    if (r != hipSuccess) return r;
+  }
+  return hipSuccess;
 }

@@ -31,6 +31,7 @@ enum StemKernelId {
   K_GEMM_DWUP,       // dWu = dV^T X
   K_SORT_MERGE,
   K_GRADS_F32,       // dx, dWd and dWg of a small fp32 layer in one launch
+  K_GEMM_DW,         // two or three weight gradients in one launch
   K_COUNT_
 };
 
@@ -160,6 +161,10 @@ struct GemmArgs {
   float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
   size_t ws_bytes; // capacity of ws
   int32_t* tickets; // decode kernel: the context's tickets; null = never split
+  // Further products of the same K in the launch (weight gradients only, stem_gemm_bf16_group)
+  struct { const bf16_t* A; const bf16_t* B; void* C; int M, N, lda, ldb; } more[2];
+  int n_more;
+  int64_t elems;   // outputs of all of the launch's products, filled in by the launcher
   int ksplit;      // number of k slices (few-row kernel: EPI_SPLITK; large kernel: chosen by its launcher)
   int kc_skip;     // set by the large kernel itself: elements a K slice starts after the operand's start
   int mt, nt;      // few-row and decode kernels: tile counts and exact float reciprocals, filled in by the launcher
@@ -167,12 +172,16 @@ struct GemmArgs {
 };
 
 hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmArgs& a, hipStream_t s);
+// n weight gradients (both operands OP_MC, EPI_F32) of one K, in one launch where that is the shorter way
+hipError_t stem_gemm_bf16_group(stem_ctx* ctx, const int* kids, const GemmArgs* a, int n, hipStream_t s);
 
 // ---- which kernel a call takes, as its launcher decides it: exported for the tests, not part of stem.h ----
 enum StemRoute { ROUTE_DECODE = 0, ROUTE_FEW_ROW, ROUTE_TILES };
 extern "C" {
 // route: {StemRoute, tile rows, tile columns, K slices}.  epi: GemmEpilogue; ops: operand pairs
 void stem_route_tiles(int M, int N, int K, int ops, int epi, int64_t ws_bytes, int32_t* route);
+// the n = 2 (dW_down, dW_gate) or 3 (dW_up too) weight gradients of a layer: {one launch, tile rows, tile columns, K slices}
+void stem_route_weight_grads(int d_model, int d_ff, int64_t T, int n, int64_t ws_bytes, int32_t* route);
 void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* route);
 // the gate (route[0..3]) and down (route[4..7]) products of a bf16 stem_ffn_forward call of T tokens, in a context made for as many
 void stem_route_forward(int d_model, int d_ff, int64_t T, int32_t* route);

@@ -55,6 +55,13 @@ def route_forward(T, d, F):
     return tuple(r[:4]), tuple(r[4:])
 
 
+def route_weight_grads(T, d, F, n, ws=64 << 20):
+    """(one launch, tile rows, tile columns, K slices) of a layer's n weight gradients."""
+    r = (ctypes.c_int32 * 4)()
+    L.lib().stem_route_weight_grads(d, F, ctypes.c_int64(T), n, ctypes.c_int64(ws), r)
+    return tuple(r)
+
+
 def route_sort(T, V):
     return L.lib().stem_route_sort(ctypes.c_int64(T), V)
 
