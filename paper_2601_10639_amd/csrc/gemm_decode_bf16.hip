@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
     tm = in - tn * p.mt;
   }
   const int m0 = tm * TM, n0 = tn * TN;
-  const int nk_all = p.K / KW, per = (nk_all + p.ksplit - 1) / p.ksplit, kt0 = z * per;
+  const int nk_all = (p.K + KW - 1) / KW, per = (nk_all + p.ksplit - 1) / p.ksplit, kt0 = z * per;
   const int nk = nk_all - kt0 < per ? nk_all - kt0 : per;      // at least 1
 
   // The gate epilogue multiplies by a gathered table row: its token ids are requested first of all, the row pieces
@@ -145,8 +145,18 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
   auto request = [&](int slot) __attribute__((always_inline)) {
     const int so = (kt0 + kpos) * (KW * 2);
     char* const dst = ring + slot * S::SLOT;
+    if (S::PAIR) {   // the second half of the last K tile may lie beyond K: read as zero
+      const bool whole = so + KW * 2 <= p.K * 2;
+      const rsrc_t ra2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.A), 0, whole ? p.M * p.lda * 2 : 0, 0x00020000);
+      const rsrc_t rb2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.B), 0, whole ? p.N * p.ldb * 2 : 0, 0x00020000);
+      lds_dma_16(ra, dst, off[0], so);
+      lds_dma_16(ra2, dst + 1024, off[1], so);
+      lds_dma_16(rb, dst + 2048, off[2], so);
+      lds_dma_16(rb2, dst + 3072, off[3], so);
+    } else {
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) lds_dma_16(i < 2 * FA ? ra : rb, dst + i * 1024, off[i], so);
+      for (int i = 0; i < LOADS; ++i) lds_dma_16(i < 2 * FA ? ra : rb, dst + i * 1024, off[i], so);
+    }
     kpos += W;
     if (kpos >= nk) kpos -= nk;
   };
@@ -316,7 +326,7 @@ bool decode_plan(int M, int N, int K, bool plain, bool may_split, size_t ws_byte
   // 4 tokens 19.1 / 18.0, 8 tokens 19.2 / 18.6; 1536 x 5120, 2 tokens 12.7 / 11.3; 1024 x 4096, 1 token 9.9 / 9.2, 8 tokens 10.2 / 9.6;
   // 512 x 1536, 1 token 6.9 / 6.5.  (Each workgroup reads all tokens' rows whole, so the gain shrinks with the tokens.  16 wavefronts
   // with 2 K tiles in flight 17.4, 8 with 5 17.1.)
-  if (plain && M <= 8 && N <= 8 * 256 && N % 8 == 0 && K % (2 * BK) == 0) {
+  if (plain && M <= 8 && N <= 8 * 256 && N % 8 == 0 && K >= 2 * BK) {
     *plan = {1, 1, 1, N / 8, 1, true};
     return true;
   }
