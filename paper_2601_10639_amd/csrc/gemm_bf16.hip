@@ -256,6 +256,10 @@ struct Tiling {
 typedef Tiling<4, 4, 2, 2, 0, 0> Tile256;
 typedef Tiling<4, 2, 2, 2, 3, 4> Tile256x128;
 typedef Tiling<2, 2, 2, 2, 3, 4> Tile128;
+// 700 tokens of an 8192-wide gate product are 96 tiles of 256x256, 192 of 256x128, 384 of 128x128 and 256 of these.  A compute
+// unit is fed at 60 to 70 GB/s whatever the others do, so what counts is the bytes of the busiest one: 40 KB a K tile here
+// against 48 or 64 (gate 34.1 -> 30.7 us; down product in four slices 39.3 -> 33.4).
+typedef Tiling<3, 2, 2, 2, 3, 4> Tile192x128;
 
 template <class C, int LA, int LB, int EPI>
 __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(GemmArgs p) {
@@ -371,16 +375,16 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   // The touching loads return asynchronously into their destination registers, so these stay
   // reserved (never reused by the compiler) until the wait that follows the main loop.
   constexpr bool TOUCH = (EPI == EPI_GATE);
-  // Token ids of this wavefront's output rows (128 or 64), lane l holding rows l and 64 + l, fetched here so
+  // Token ids of this wavefront's output rows (128, 96 or 64), lane l holding rows l and 64 + l, fetched here so
   // that their latency passes under the main loop.  The epilogue takes each row's id from these
   // registers by a lane permute: loading ids there would put a wait for the newest loads in front of
   // every block of table-row requests, and with it a wait for all the stores issued before them
   // (loads and stores return through one in-order counter), 3 to 4 us per block.
   constexpr bool NEED_IDS = (EPI == EPI_GATE || EPI == EPI_DH || EPI == EPI_GATE_UPE || EPI == EPI_DH_UPE);
-  int row_id[MI / 2] = {};
+  int row_id[(MI + 1) / 2] = {};
   if (NEED_IDS && !load_wave) {
 #pragma unroll
-    for (int h = 0; h < MI / 2; ++h) {
+    for (int h = 0; h < (MI + 1) / 2; ++h) {
       const int m = m0 + wm * WSM + h * 64 + lane;
       int id = p.ids[m < p.M ? m : p.M - 1];
       if ((unsigned)id >= (unsigned)p.E_rows) {   // reported to the host, clamped so no access leaves the table
@@ -396,7 +400,7 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
     const int ncol = n0 + wn * WSN;
     const int col = ncol < p.N ? ncol : 0;
 #pragma unroll
-    for (int h = 0; h < MI / 2; ++h) {
+    for (int h = 0; h < (MI + 1) / 2; ++h) {
       const int id = row_id[h];
       const bf16_t* e = p.E + (size_t)id * p.N + col;
       if (NJ == 2) {   // 64 columns: one line
@@ -827,7 +831,7 @@ __global__ __launch_bounds__(256) void splitk_sum_f32_kernel(const float* __rest
 // Examples, us (Tile256 / Tile256x128 / Tile128): down product 2048 x 8192, 1999 tokens 146 / 92 / 70, 4096 tokens
 // 165 / 114 / 129, 16384 tokens 408 / 460 / 538; gate product 700 tokens 51 / 34 / 39, 1999 tokens 69 / 73 / 85.
 struct TilingCost { int tm, tn; double idle, full, fixed_plain, fixed_fused, fixed_f32; };
-constexpr TilingCost kTilings[3] = {{256, 256, 0.86, 1.39, 9, 21, 17.5}, {256, 128, 0.45, 0.86, 6, 11, 11}, {128, 128, 0.34, 0.56, 4, 6.5, 5.5}};
+constexpr TilingCost kTilings[4] = {{256, 256, 0.86, 1.39, 9, 21, 17.5}, {256, 128, 0.45, 0.86, 6, 11, 11}, {128, 128, 0.34, 0.56, 4, 6.5, 5.5}, {192, 128, 0.33, 0.69, 4.5, 8.5, 8}};
 
 struct Plan { int tiling, ksplit; double us; };
 
@@ -837,7 +841,8 @@ struct Plan { int tiling, ksplit; double us; };
 Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_bytes, int n = 1, const bool* turned = nullptr) {
   Plan best = {0, 1, 1e30};
   const int nk = ops * ((K + BK - 1) / BK);
-  for (int t = 0; t < 3; ++t) {
+  for (int t = 0; t < 4; ++t) {
+    if (t == 3 && (f32 || ops > 1)) break;
     const TilingCost& c = kTilings[t];
     double tiles = 0;
     for (int q = 0; q < n; ++q) {
@@ -851,13 +856,16 @@ Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_b
         kt = (nk + ks - 1) / ks;
         slices = ops * ((nk / ops + kt - 1) / kt);
       }
+      // 192x128 tiles where they make one round and fill it, K is more than 8 K tiles (512: 3 to 5 % slower than 256x128) and
+      // slices are long enough to be worth their sum; at least 4 % below the others, for what the model is off.
+      if (t == 3 && (tiles * slices > 256 || tiles * slices <= 224 || nk <= 8 || (ks > 1 && kt < 32))) continue;
       const double wgs = tiles * slices, fixed = fused ? c.fixed_fused : f32 || ks > 1 ? c.fixed_f32 : c.fixed_plain;
       const int rounds = (int)(wgs / 256);
       const double rest = wgs - rounds * 256.0;
       double us = rounds * (kt * c.full + fixed);
       if (rest > 0) us += kt * (c.idle + (c.full - c.idle) * rest / 256) + fixed;
       if (ks > 1) us += 3 + (slices + 1.0) * M * N * n * 4 / 4.2e6;   // the kernel that sums the slices: launch, and 4.2 TB/s
-      if (us < best.us) best = {t, slices, us};
+      if (us * (t == 3 ? 1.04 : 1.0) < best.us) best = {t, slices, us};
     }
   }
   return best;
@@ -874,6 +882,8 @@ hipError_t launch_tiles(stem_ctx* ctx, int kid, const GemmArgs& a, hipStream_t s
 
 template <int LA, int LB, int EPI>
 hipError_t launch_tiling(int tiling, stem_ctx* ctx, int kid, const GemmArgs& a, hipStream_t s) {
+  if constexpr (LA == OP_KC)   // a rows-contiguous operand's K rows do not divide 192 rows into loads
+    if (tiling == 3) return launch_tiles<Tile192x128, LA, LB, EPI>(ctx, kid, a, s);
   if (tiling == 2) return launch_tiles<Tile128, LA, LB, EPI>(ctx, kid, a, s);
   if (tiling == 1) return launch_tiles<Tile256x128, LA, LB, EPI>(ctx, kid, a, s);
   return launch_tiles<Tile256, LA, LB, EPI>(ctx, kid, a, s);

@@ -62,6 +62,32 @@ def test_bf16_products_on_every_tiling(T, d, F, routes, up):
     ctx.close()
 
 
+@pytest.mark.parametrize("T,d,F,routes,up", [
+    (1345, 576, 4096, [(192, 128, 1), (128, 128, 4), (128, 128, 4), (128, 128, 1)], False),   # one row in the last tile; 9 K tiles
+    (1535, 1088, 4032, [(192, 128, 1), (128, 128, 2), (128, 128, 2), (256, 128, 1)], True),   # ragged in both, a dense third row block
+    (1345, 1024, 8128, [(256, 256, 1), (192, 128, 4), (256, 128, 4), (256, 128, 1)], False),  # slices of 32 K tiles, the last of 31
+    (2690, 1984, 640, [(128, 128, 1), (192, 128, 1), (256, 128, 1), (128, 128, 2)], False),   # plain products, unsplit
+])
+def test_bf16_products_on_192_row_tiles(T, d, F, routes, up):
+    test_bf16_products_on_every_tiling(T, d, F, routes, up)
+
+
+def test_residual_on_192_row_tiles():
+    T, d, F = 2690, 1984, 640
+    inp = inputs.layer_inputs(inputs.StemShape("res", d, F, 300, 1, T, "bf16"), seed=67, device=DEV, tokens=T)
+    ctx = Hn.make_ctx(inputs.StemShape("res", d, F, 300, 1, T, "bf16"), T)
+    a = (ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"])
+    y, yr = torch.empty_like(inp["x"]), torch.empty_like(inp["x"])
+    L.stem_ffn_forward(*a, y)
+    L.stem_ffn_forward_residual(*a, inp["x"], yr)
+    L.stem_sync_status(ctx)
+    f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
+    yo, _ = O.ffn_forward(f64["x"], inp["ids"].cpu().numpy(), f64["W_gate"], f64["W_down"], f64["E"])
+    assert Hn.max_rel(y.float().cpu(), yo) <= Hn.TOL["bf16"]
+    assert Hn.max_rel(yr.float().cpu(), f64["x"] + yo) <= Hn.TOL["bf16"]
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,d,F", [
     (1030, 1028, 1028),   # every product on 32x32 tiles with one K tile in flight, ragged in M, N and K
     (1030, 36, 1028),     # forward and dH with K of one tile and a bit; dx, weight gradients with two K tiles in flight
