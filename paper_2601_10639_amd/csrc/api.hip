@@ -518,7 +518,7 @@ stem_status stem_ffn_up_forward(stem_ctx* c, const void* x, const int32_t* ids, 
   GemmArgs u = {};   // Up = x W_up^T
   u.A = static_cast<const bf16_t*>(x); u.lda = d;
   u.B = static_cast<const bf16_t*>(W_up); u.ldb = d;
-  u.M = (int)T; u.N = F; u.K = d; u.C = Up; u.flag = c->flag;
+  u.M = (int)T; u.N = F; u.K = d; u.C = Up; u.flag = c->flag; u.ws = c->splitk_ws; u.ws_bytes = c->splitk_bytes;
   HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_UP, OP_KC, OP_KC, EPI_BF16, u, s));
   GemmArgs a = u;    // G = x W_gate^T;  H = SiLU(G) * (Up [+ E[ids]])
   a.B = static_cast<const bf16_t*>(W_gate); a.C = nullptr;
@@ -529,7 +529,7 @@ stem_status stem_ffn_up_forward(stem_ctx* c, const void* x, const int32_t* ids, 
   GemmArgs b = {};   // y = H W_down^T
   b.A = static_cast<const bf16_t*>(H); b.lda = F;
   b.B = static_cast<const bf16_t*>(W_down); b.ldb = F;
-  b.M = (int)T; b.N = d; b.K = F; b.C = y; b.flag = c->flag;
+  b.M = (int)T; b.N = d; b.K = F; b.C = y; b.flag = c->flag; b.ws = c->splitk_ws; b.ws_bytes = c->splitk_bytes;
   HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DOWN, OP_KC, OP_KC, EPI_BF16, b, s));
   return STEM_OK;
 }
