@@ -2,7 +2,7 @@
 // for gfx950, with the layer's element-wise work fused into the epilogues.
 //
 // One kernel template computes  C[m,n] = sum_k Aop[m,k] * Bop[n,k]  on one output tile per
-// workgroup: 256x256 for products with enough of them to fill the chip, else 256x128 or 128x128
+// workgroup: 256x256 for products with enough of them to fill the chip, else 256x128, 192x128 or 128x128
 // (see Tiling; choose_plan decides, and may also cut K into slices).  The 256x256 tile: 4 wavefronts,
 // each a 128x128 quadrant held as 4x4 accumulators of v_mfma_f32_32x32x16_bf16, K stepped by 64
 // through a ring of five 32 KB LDS slots (one operand tile each), so that every global request is made
