@@ -436,6 +436,9 @@ template <> struct RowVec<true> {
   static __device__ __forceinline__ raw_t load(const void* base, int64_t row, int F, int col) {
     return __builtin_nontemporal_load(reinterpret_cast<const raw_t*>(reinterpret_cast<const bf16_t*>(base) + row * F + col));
   }
+  static __device__ __forceinline__ raw_t load_plain(const void* base, int64_t row, int F, int col) {
+    return *reinterpret_cast<const raw_t*>(reinterpret_cast<const bf16_t*>(base) + row * F + col);
+  }
   static __device__ __forceinline__ void add(const raw_t& v, float (&acc)[8]) {
     const uint32_t w[4] = {v[0], v[1], v[2], v[3]};
 #pragma unroll
@@ -451,6 +454,7 @@ template <> struct RowVec<false> {
   static __device__ __forceinline__ raw_t load(const void* base, int64_t row, int F, int col) {
     return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + row * F + col);
   }
+  static __device__ __forceinline__ raw_t load_plain(const void* base, int64_t row, int F, int col) { return load(base, row, F, col); }
   static __device__ __forceinline__ void add(const raw_t& v, float (&acc)[4]) {
     acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
   }
@@ -600,52 +604,119 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int32_t* __restr
 }
 
 // Small batches, where a chunk's row loads and the second launch are all latency: one launch, a workgroup for every sorted
-// position and slab of 64 * COLS columns; those of a run's first position sum the run, the others end at once.  A run of up to
-// SHORT_RUN rows is one round of loads of one wavefront; a longer one is cut into four consecutive stretches, one per wavefront,
-// each summed in ascending position, and the four sums are added in order.
-constexpr int SHORT_RUN = 16;
+// position and slab of 64 * COLS columns.  A run is summed by the workgroups of its first positions, the others end at once.
+//
+// A run of up to 16 rows is one round of loads of one wavefront.  Longer ones are dealt to 4 * PARTS row groups, PARTS = 1, 2, 4,
+// 8 up to 64, 128, 256 rows and beyond, in which PARTS workgroups take 1 / PARTS of the slab's columns each: a lane then has 16
+// rows at most (32 of 1024), and a long run is read by as many more compute units.  Rows are added in ascending position, four
+// at a time, then the groups of a wavefront in order, then the wavefronts: no term of 1024 meets more than 20 additions.
+// us in a graph, two launches / four wavefronts of one workgroup for the whole run / now:
+//                    bf16 1024 x 4096     bf16 256 x 8192      fp32 1024 x 2048     fp32 256 x 1024
+//   Zipf ids         11.6 / 11.7 / 7.9    11.3 / 5.0 / 5.0     12.6 / 7.5 / 6.8     12.0 / 3.4 / 3.3
+//   one id for half  12.0 / 25.1 / 7.1    11.2 / 15.5 / 6.0    12.7 / 15.7 / 6.2    12.1 / 6.1 / 4.0
+//   one id for all   10.5 / 58.5 / 8.1    10.4 / 27.8 / 6.0     8.3 / 40.3 / 8.4     8.0 / 10.0 / 5.1
+// The relative error of fp32 unit normals, all of one id, 1024 rows: 1.20e-7 / 2.92e-7 / 1.04e-7.
+// (Row loads that bypass the caches, as the large batches' do: one id for all, bf16 1024 x 4096 15.5.)
+constexpr int ROUND = 16;        // rows a lane requests together
+constexpr int MAX_PARTS = 8;     // a part of a slab is no narrower than 8 lanes: 128 bytes of a row
+
+template <bool BF16>
+__device__ __forceinline__ void add_quad(const typename RowVec<BF16>::raw_t* rows, int n, float (&acc)[RowVec<BF16>::COLS]) {
+  constexpr int COLS = RowVec<BF16>::COLS;
+  if (n <= 0) return;
+  float t[COLS];
+#pragma unroll
+  for (int x = 0; x < COLS; ++x) t[x] = 0.f;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (u < n) RowVec<BF16>::add(rows[u], t);
+#pragma unroll
+  for (int x = 0; x < COLS; ++x) acc[x] += t[x];
+}
+
+// Adds `rows` (at most R) rows of a run of n, from its r-th on.  Loads carry no conditions, or the compiler waits for those it
+// cannot count; what lies beyond the rows is read for nothing, within the run.
+template <bool BF16, int R>
+__device__ __forceinline__ void add_rows(const void* dU, const int32_t* perm, int r, int rows, int n, int F, int col,
+                                         float (&acc)[RowVec<BF16>::COLS]) {
+  int row[R];
+  typename RowVec<BF16>::raw_t data[R];
+#pragma unroll
+  for (int u = 0; u < R; ++u) row[u] = perm[min(r + u, n - 1)];
+#pragma unroll
+  for (int u = 0; u < R; ++u) data[u] = RowVec<BF16>::load_plain(dU, row[u], F, col);
+#pragma unroll
+  for (int u = 0; u < R; u += 4) add_quad<BF16>(data + u, rows - u, acc);
+}
+
 template <bool BF16>
 __global__ __launch_bounds__(256) void seg_runs_kernel(const void* __restrict__ dU, const int32_t* __restrict__ perm,
                                                        const int32_t* __restrict__ seg_of,
                                                        const int32_t* __restrict__ seg_offsets, int F,
                                                        float* __restrict__ dE_rows) {
   constexpr int COLS = RowVec<BF16>::COLS;
-  __shared__ float red[3][64][COLS + 1];
+  __shared__ float red[256 * (COLS + 1)];   // a thread's sums, one float apart
   const int k = blockIdx.x;
-  const int j = seg_of[k], before = k > 0 ? seg_of[k - 1] : -1;
-  if (before == j) return;
-  const int n = seg_offsets[j + 1] - k;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int q = n <= SHORT_RUN ? n : (n + 3) >> 2;
-  const int r0 = wave * q, r1 = min(n, r0 + q);
-  const int col = (blockIdx.y * 64 + lane) * COLS;
-  const bool live = col < F;
-  const int colc = live ? col : 0;
+  const int j = seg_of[k], before = k > 0 ? seg_of[k - 1] : -1, far = k >= MAX_PARTS ? seg_of[k - MAX_PARTS] : -1;
+  if (far == j) return;
+  const int start = before == j ? seg_offsets[j] : k, n = seg_offsets[j + 1] - start;
+  const int shift = n <= 4 * ROUND ? 0 : n <= 8 * ROUND ? 1 : n <= 16 * ROUND ? 2 : 3;
+  // which part: another one in each slab, or the workgroups of all slabs would be on the XCDs of the first positions
+  const int part = n <= ROUND ? k - start : (k - start - (int)blockIdx.y) & (MAX_PARTS - 1);
+  if (part >= 1 << shift) return;
+  const int tid = threadIdx.x;
   float acc[COLS];
 #pragma unroll
   for (int x = 0; x < COLS; ++x) acc[x] = 0.f;
-  for (int rb = r0; rb < r1; rb += SHORT_RUN) {
-    typename RowVec<BF16>::raw_t data[SHORT_RUN];
+
+  if (shift == 0) {   // rows of whole wavefronts: their numbers come through scalar loads
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (n <= ROUND && wave > 0) return;
+    const int q = n <= ROUND ? n : (n + 3) >> 2, r = wave * q, rows = min(q, n - r);
+    const int col = (blockIdx.y * 64 + lane) * COLS, colc = col < F ? col : 0;
+    typename RowVec<BF16>::raw_t data[ROUND];
 #pragma unroll
-    for (int u = 0; u < SHORT_RUN; ++u)
-      if (rb + u < r1) data[u] = RowVec<BF16>::load(dU, perm[k + rb + u], F, colc);
+    for (int u = 0; u < ROUND; ++u)
+      if (u < rows) data[u] = RowVec<BF16>::load_plain(dU, perm[start + r + u], F, colc);
 #pragma unroll
-    for (int u = 0; u < SHORT_RUN; ++u)
-      if (rb + u < r1) RowVec<BF16>::add(data[u], acc);
-  }
-  if (n > SHORT_RUN) {
-    if (wave > 0) {
+    for (int u = 0; u < ROUND; u += 4) add_quad<BF16>(data + u, rows - u, acc);
+    if (n > ROUND) {
+      if (wave > 0) {
 #pragma unroll
-      for (int x = 0; x < COLS; ++x) red[wave - 1][lane][x] = acc[x];
+        for (int x = 0; x < COLS; ++x) red[tid * (COLS + 1) + x] = acc[x];
+      }
+      __syncthreads();
+      if (wave == 0)
+        for (int w = 1; w < 4; ++w)
+#pragma unroll
+          for (int x = 0; x < COLS; ++x) acc[x] += red[(w * 64 + lane) * (COLS + 1) + x];
     }
-    __syncthreads();
-    if (wave == 0)
-      for (int w = 1; w < 4; ++w)
-        if (w * q < n)
-#pragma unroll
-          for (int x = 0; x < COLS; ++x) acc[x] += red[w - 1][lane][x];
+    if (wave == 0 && col < F) store_cols<COLS>(dE_rows + (int64_t)j * F + col, acc);
+    return;
   }
-  if (wave == 0 && live) store_cols<COLS>(dE_rows + (int64_t)j * F + col, acc);
+
+  const int width = 64 >> shift, groups = 4 << shift;      // lanes of a part, row groups
+  const int first_col = (blockIdx.y * 64 + part * width) * COLS;
+  const int col = first_col + (tid & (width - 1)) * COLS, colc = col < F ? col : 0;
+  const int q = (n + groups - 1) >> (2 + shift);           // rows of a group (the last ones may have fewer, or none)
+  const int r = (tid >> (6 - shift)) * q, rows = min(q, n - r);
+  if (q <= ROUND / 2) add_rows<BF16, ROUND / 2>(dU, perm + start, r, rows, n, F, colc, acc);
+  else
+    for (int rb = 0; rb < q; rb += ROUND) add_rows<BF16, ROUND>(dU, perm + start, r + rb, rows - rb, n, F, colc, acc);
+#pragma unroll
+  for (int x = 0; x < COLS; ++x) red[tid * (COLS + 1) + x] = acc[x];
+  __syncthreads();
+  // a column: the groups of each wavefront in order, then the wavefronts
+  for (int c = tid; c < width * COLS && first_col + c < F; c += 256) {
+    const float* from = red + (c / COLS) * (COLS + 1) + c % COLS;
+    float sum = 0.f;
+    for (int w = 0; w < 4; ++w) {
+      float s = 0.f;
+      for (int g = 0; g < 1 << shift; ++g) s += from[(w * 64 + g * width) * (COLS + 1)];
+      sum += s;
+    }
+    dE_rows[(int64_t)j * F + first_col + c] = sum;
+  }
 }
 
 int bits_for(int V) {
@@ -750,10 +821,11 @@ hipError_t stem_seg_reduce(stem_ctx* ctx, const EmbedScratch& ws, int is_bf16, c
                            const int32_t* seg_offsets, int64_t T, int F, float* dE_rows, hipStream_t s) {
   const int chunks = (int)((T + SEG_ROWS - 1) / SEG_ROWS);
   const int cols = is_bf16 ? 8 : 4;
-  // One launch while its workgroups, most of which end at once, and the longest run cost less than the second launch and the
-  // partial sums.  us in a graph, two launches / one, Zipf ids: fp32 128 x 256 9.4 / 2.8, 1000 x 1024 12.8 / 5.6, 1024 x 2048
-  // 13.1 / 7.0, 2048 x 2048 14.1 / 13.7, 4096 x 512 12.5 / 13.4; bf16 130 x 8192 11.5 / 4.0, 500 x 8192 12.5 / 7.0, 1000 x 4096 12.6 / 10.2,
-  // 2000 x 2048 12.5 / 14.4, 1999 x 8192 19.2 / 27.4.
+  // One launch up to 1024 positions, where it is no slower even with one id for all of them; what that costs beyond depends on the
+  // ids.  us in a graph, two launches / one, Zipf ids: fp32 128 x 256 11.2 / 2.8, 1000 x 1024 12.3 / 5.0, 2048 x 2048 13.4 / 10.1;
+  // bf16 130 x 8192 11.4 / 3.7, 500 x 8192 11.9 / 7.9, 1024 x 8192 13.6 / 11.9, 1999 x 8192 16.6 / 18.0.  One id for all: fp32
+  // 1024 x 2048 8.3 / 8.4, 2048 x 2048 9.8 / 14.7; bf16 1024 x 4096 10.5 / 8.1, 1999 x 8192 13.2 / 19.7.  Most workgroups end at
+  // once: 8192 of them at most.
   const int64_t run_slabs = (F + 64 * cols - 1) / (64 * cols);
   if (T <= 1024 && T * run_slabs <= 8192) {
     ProfScope ps(ctx, K_SEG_REDUCE, s);
