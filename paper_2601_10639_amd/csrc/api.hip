@@ -443,15 +443,17 @@ stem_status stem_ffn_backward(stem_ctx* c, const void* dy, const void* x, const 
     // The two together, and before dx, unless dW_gate lies over something that is read by then or beside it.
     const size_t Td = (size_t)T * d * 2, TF = (size_t)T * F * 2, Fd = (size_t)F * d * 4;
     const bool apart = !overlap(dW_gate, Fd, dy, Td) && !overlap(dW_gate, Fd, H, TF) && !(dx && overlap(dW_gate, Fd, W_gate, Fd / 2));
-    static const int kids[2] = {K_GEMM_DWDOWN, K_GEMM_DWGATE};
-    HIP_TRY(c, stem_gemm_bf16_group(c, kids, w, apart ? 2 : 1, s));
+    GroupPlan plan = {};
+    const bool together = apart && stem_weight_grads_together(w, 2, &plan);
+    if (together) HIP_TRY(c, stem_weight_grads(c, w, 2, plan, s));
+    else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, w[0], s));
     if (dx) {  // dx = dG W_gate
       GemmArgs a = {};
       a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;
       a.M = (int)T; a.N = d; a.K = F; a.C = dx; a.flag = c->flag; a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DX, OP_KC, OP_MC, EPI_BF16, a, s));
     }
-    if (!apart) HIP_TRY(c, stem_gemm_bf16_group(c, kids + 1, w + 1, 1, s));
+    if (!together) HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, w[1], s));
   } else {
     const float* dyf = static_cast<const float*>(dy);
     float* dG = static_cast<float*>(c->dG_ws);
@@ -595,8 +597,10 @@ stem_status stem_ffn_up_backward(stem_ctx* c, const void* dy, const void* x, con
     apart = apart && !overlap(g, Fd, dy, Td) && !overlap(g, Fd, saved_H, TF) &&
             !(dx && (overlap(g, Fd, W_gate, Fd / 2) || overlap(g, Fd, W_up, Fd / 2) || overlap(g, Fd, dV, TF)));
   apart = apart && !overlap(dW_gate, Fd, dV, TF);
-  static const int kids[3] = {K_GEMM_DWDOWN, K_GEMM_DWGATE, K_GEMM_DWUP};
-  HIP_TRY(c, stem_gemm_bf16_group(c, kids, w, apart ? 3 : 1, s));
+  GroupPlan plan = {};
+  const bool together = apart && stem_weight_grads_together(w, 3, &plan);
+  if (together) HIP_TRY(c, stem_weight_grads(c, w, 3, plan, s));
+  else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, w[0], s));
   if (dx) {  // dx = dG W_gate + dV W_up: one product over the concatenated K range
     GemmArgs a = {};
     a.A = dGb; a.lda = F; a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;
@@ -604,9 +608,9 @@ stem_status stem_ffn_up_backward(stem_ctx* c, const void* dy, const void* x, con
     a.M = (int)T; a.N = d; a.K = F; a.C = dx; a.flag = c->flag; a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
     HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DX, OP_KC, OP_MC, EPI_BF16, a, s));
   }
-  if (!apart) {
-    HIP_TRY(c, stem_gemm_bf16_group(c, kids + 1, w + 1, 1, s));
-    HIP_TRY(c, stem_gemm_bf16_group(c, kids + 2, w + 2, 1, s));
+  if (!together) {
+    HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWGATE, OP_MC, OP_MC, EPI_F32, w[1], s));
+    HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWUP, OP_MC, OP_MC, EPI_F32, w[2], s));
   }
   return STEM_OK;
 }

@@ -958,13 +958,20 @@ hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const
 
 // Weight gradients of one K whose tiles leave part of the chip idle, or need K slices to fill it, share a launch: fewer
 // slices (whose partial products cost as much to sum as to write), one prologue and epilogue per round instead of one per
-// product, and one last round.  Taken where the cost model prices the one launch 4 % below the several (and 3 us a launch: the gap
-// and the slowest XCD's tail), or where the rounds stay the same.  Backward, us, apart / together: 1024 x 4096, 16384 tokens dW 2 x (117 + 15) / 220 + 18; additive layer,
-// 1024 x 4096, 4096 tokens dW 123 / 98.  Over 107 layers (d_model 512 to 2048, 130 to 65536 tokens) the backward call takes
-// 0.925 of the time, with an up projection 0.88; the dearest choice loses 1.7 % (without the 4 %: 7 %, 1728 x 5120, 31068 tokens).
-struct GroupPlan { bool together; Plan plan; };
-static GroupPlan plan_group(const GemmArgs* a, int n, size_t ws_bytes) {
-  bool turned[3] = {}, alike = n <= 3;
+// product, and one last round.  Taken where the cost model prices the one launch 4 % below the several, and 3 us for each launch
+// saved.  Where tiles, slices and rounds stay the same, up to 250 us: beyond, the saved launches are worth less than what the
+// products lose that the XCDs then read the operands of two or three of them at a time, and dx and dW_gate that dG was not read
+// just before.  Backward, us, apart / together: 1920 x 6400, 1013 tokens 130 / 126; 1984 x 7296, 5702 tokens 604 / 599; 1344 x
+// 5312 with an up projection, 6773 tokens 601 / 617, 1472 x 3840, 7961 tokens 542 / 568; 1792 x 7104, 21592 tokens 1915 / 1952;
+// 2048 x 8192, 16384 tokens 1704 / 1709.  With fewer rounds or slices: 1024 x 4096, 16384 tokens 541 / 508; with an up
+// projection, 4096 tokens 225 / 211.  Over 260 layers (d_model 512 to 2048, 128 to 65536 tokens) the rule takes 0.895 of the
+// time that launches of their own take, with an up projection 0.862, and loses 1.1 % at worst.
+//
+// Half the slices are sums of twice the length: a gradient's distance from the exact sum of the same bf16 operands goes from
+// 4.1e-7 to 5.8e-7 of it (1024 x 4096, 16384 tokens; 1472 x 5568, never cut, has 8.3e-7 at 16768).  Its distance from the
+// layer's in 64 bits, 1.6587e-3 from the rounding of H or dG to bf16, is the same to six digits.
+static bool plan_together(const GemmArgs* a, int n, size_t ws_bytes, GroupPlan* plan) {
+  bool turned[3] = {}, alike = n == 2 || n == 3;
   double apart = 0;
   Plan one[3] = {};
   for (int e = 0; e < n && alike; ++e) {
@@ -974,40 +981,37 @@ static GroupPlan plan_group(const GemmArgs* a, int n, size_t ws_bytes) {
     one[e] = choose_plan(a[e].M, a[e].N, a[e].K, 1, false, true, ws_bytes);
     apart += one[e].us;
   }
-  if (n < 2 || !alike) return {false, {}};
+  if (!alike) return false;
   const Plan p = choose_plan(a[0].M, a[0].N, a[0].K, 1, false, true, ws_bytes, n, turned);
-  bool whole = p.us <= apart * 1.0001;   // the same rounds, one after another: nothing but the launches between them is lost
+  *plan = {p.tiling, p.ksplit};
+  bool whole = p.us <= apart * 1.0001 && p.us <= 250;   // the same rounds, one after another
   for (int e = 0; e < n; ++e) whole = whole && one[e].tiling == p.tiling && one[e].ksplit == p.ksplit;
-  return {whole || p.us <= 0.96 * apart + 3 * (n - 1), p};
+  return whole || p.us <= 0.96 * apart + 3 * (n - 1);
 }
 
 void stem_route_weight_grads(int d, int F, int64_t T, int n, int64_t ws_bytes, int32_t* route) {
   GemmArgs a[3] = {};
   for (int e = 0; e < 3; ++e) { a[e].M = e ? F : d; a[e].N = e ? d : F; a[e].K = (int)T; }
-  const GroupPlan g = plan_group(a, n, (size_t)ws_bytes);
-  route[0] = g.together;
-  route[1] = kTilings[g.plan.tiling].tm; route[2] = kTilings[g.plan.tiling].tn; route[3] = g.plan.ksplit;
+  GroupPlan plan = {};
+  route[0] = plan_together(a, n, (size_t)ws_bytes, &plan);
+  route[1] = kTilings[plan.tiling].tm; route[2] = kTilings[plan.tiling].tn; route[3] = plan.ksplit;
 }
 
-hipError_t stem_gemm_bf16_group(stem_ctx* ctx, const int* kids, const GemmArgs* a, int n, hipStream_t s) {
+bool stem_weight_grads_together(const GemmArgs* a, int n, GroupPlan* plan) {
   const int64_t lim = 0x7fffffff;   // operands and outputs below 2 GiB, as for each product by itself
-  bool fits = true;
   for (int e = 0; e < n; ++e)
-    fits = fits && a[e].M > 0 && a[e].N > 0 && a[e].K > 0 && (int64_t)a[e].K * a[e].lda * 2 <= lim &&
-           (int64_t)a[e].K * a[e].ldb * 2 <= lim && (int64_t)a[e].M * a[e].N * 4 <= lim;
-  const GroupPlan plan = plan_group(a, n, a[0].ws && (int64_t)a[0].M * a[0].N % 4 == 0 ? a[0].ws_bytes : 0);
-  if (fits && plan.together) {
-    GemmArgs g = a[0];
-    g.n_more = n - 1;
-    for (int e = 1; e < n; ++e) g.more[e - 1] = {a[e].A, a[e].B, a[e].C, a[e].M, a[e].N, a[e].lda, a[e].ldb};
-    g.ksplit = plan.plan.ksplit;
-    g.elems = (int64_t)g.M * g.N * n;
-    const hipError_t r = launch_tiling<OP_MC, OP_MC, EPI_F32>(plan.plan.tiling, ctx, K_GEMM_DW, g, s);
-    return r != hipSuccess || g.ksplit == 1 ? r : sum_slices_f32(ctx, g, s);
-  }
-  for (int e = 0; e < n; ++e) {
-    const hipError_t r = stem_gemm_bf16(ctx, kids[e], OP_MC, OP_MC, EPI_F32, a[e], s);
-    if (r != hipSuccess) return r;
-  }
-  return hipSuccess;
+    if (a[e].M <= 0 || a[e].N <= 0 || a[e].K <= 0 || (int64_t)a[e].K * a[e].lda * 2 > lim || (int64_t)a[e].K * a[e].ldb * 2 > lim ||
+        (int64_t)a[e].M * a[e].N * 4 > lim)
+      return false;
+  return plan_together(a, n, a[0].ws && (int64_t)a[0].M * a[0].N % 4 == 0 ? a[0].ws_bytes : 0, plan);
+}
+
+hipError_t stem_weight_grads(stem_ctx* ctx, const GemmArgs* a, int n, const GroupPlan& plan, hipStream_t s) {
+  GemmArgs g = a[0];
+  g.n_more = n - 1;
+  for (int e = 1; e < n; ++e) g.more[e - 1] = {a[e].A, a[e].B, a[e].C, a[e].M, a[e].N, a[e].lda, a[e].ldb};
+  g.ksplit = plan.ksplit;
+  g.elems = (int64_t)g.M * g.N * n;
+  const hipError_t r = launch_tiling<OP_MC, OP_MC, EPI_F32>(plan.tiling, ctx, K_GEMM_DW, g, s);
+  return r != hipSuccess || g.ksplit == 1 ? r : sum_slices_f32(ctx, g, s);
 }

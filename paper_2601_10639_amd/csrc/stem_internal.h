@@ -161,7 +161,7 @@ struct GemmArgs {
   float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
   size_t ws_bytes; // capacity of ws
   int32_t* tickets; // decode kernel: the context's tickets; null = never split
-  // Further products of the same K in the launch (weight gradients only, stem_gemm_bf16_group)
+  // Further products of the same K in the launch (weight gradients only, stem_weight_grads)
   struct { const bf16_t* A; const bf16_t* B; void* C; int M, N, lda, ldb; } more[2];
   int n_more;
   int64_t elems;   // outputs of all of the launch's products, filled in by the launcher
@@ -172,8 +172,10 @@ struct GemmArgs {
 };
 
 hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmArgs& a, hipStream_t s);
-// n weight gradients (both operands OP_MC, EPI_F32) of one K, in one launch where that is the shorter way
-hipError_t stem_gemm_bf16_group(stem_ctx* ctx, const int* kids, const GemmArgs* a, int n, hipStream_t s);
+// n = 2 or 3 weight gradients of a layer (both operands OP_MC, EPI_F32) in one launch: whether that is the shorter way, and the launch
+struct GroupPlan { int tiling, ksplit; };
+bool stem_weight_grads_together(const GemmArgs* a, int n, GroupPlan* plan);
+hipError_t stem_weight_grads(stem_ctx* ctx, const GemmArgs* a, int n, const GroupPlan& plan, hipStream_t s);
 
 // ---- which kernel a call takes, as its launcher decides it: exported for the tests, not part of stem.h ----
 enum StemRoute { ROUTE_DECODE = 0, ROUTE_FEW_ROW, ROUTE_TILES };

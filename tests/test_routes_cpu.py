@@ -3,7 +3,7 @@ import random
 
 import pytest
 
-from tests.harness import EPI_BF16, EPI_F32, EPI_GATE, route_tiles as tiles
+from tests.harness import EPI_BF16, EPI_F32, EPI_GATE, route_tiles as tiles, route_weight_grads
 
 
 def test_no_k_slice_is_empty():
@@ -39,3 +39,20 @@ def test_no_k_slice_is_empty():
 ])
 def test_tiling_of_products_that_were_measured_on_each(product, want):
     assert tiles(*product)[1:] == want
+
+
+@pytest.mark.parametrize("T,d,F,n,together", [
+    # as many rounds either way: backward, us, launches of their own / one launch
+    (6773, 1344, 5312, 3, False),      # 601 / 617
+    (7961, 1472, 3840, 3, False),      # 542 / 568
+    (21592, 1792, 7104, 2, False),     # 1915 / 1952
+    (24323, 1984, 5696, 2, False),     # 1924 / 1945
+    (1999, 2048, 8192, 2, True),       # 271 / 270
+    (1013, 1920, 6400, 2, True),       # 130 / 126
+    # fewer rounds or slices
+    (16384, 1024, 4096, 2, True),      # 541 / 508
+    (4096, 1024, 4096, 3, True),       # 225 / 211
+    (395, 576, 1728, 2, True),         # 36 / 30
+])
+def test_weight_gradients_share_a_launch_where_that_was_measured_shorter(T, d, F, n, together):
+    assert bool(route_weight_grads(T, d, F, n, min(64 << 20, 32 * d * max(T, F)))[0]) == together
