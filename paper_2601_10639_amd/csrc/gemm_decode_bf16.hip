@@ -324,9 +324,10 @@ bool decode_plan(int M, int N, int K, bool plain, bool may_split, size_t ws_byte
   // Up to 8 tokens: 8 weight rows per workgroup, so that K needs no slices and no exchange (2 to 3 us of a launch) while the
   // weight tiles still give one workgroup per CU.  Layer forward, us, 16 weight rows in slices / 8: 2048 x 8192, 1 token 18.2 / 16.9,
   // 4 tokens 19.1 / 18.0, 8 tokens 19.2 / 18.6; 1536 x 5120, 2 tokens 12.7 / 11.3; 1024 x 4096, 1 token 9.9 / 9.2, 8 tokens 10.2 / 9.6;
-  // 512 x 1536, 1 token 6.9 / 6.5.  (Each workgroup reads all tokens' rows whole, so the gain shrinks with the tokens.  16 wavefronts
+  // 512 x 1536, 1 token 6.9 / 6.5.  From K of 832 on, 13 K tiles of the other shape for its 8
+  // wavefronts: 64 x 128, 4 tokens 5.2 / 5.4, 512 x 768, 5 tokens 5.8 / 5.9, 832 x 832, 7 tokens 6.4 / 6.2.  (Each workgroup reads all tokens' rows whole, so the gain shrinks with the tokens.  16 wavefronts
   // with 2 K tiles in flight 17.4, 8 with 5 17.1.)
-  if (plain && M <= 8 && N <= 8 * 256 && N % 8 == 0 && K >= 2 * BK) {
+  if (plain && M <= 8 && N <= 8 * 256 && N % 8 == 0 && K > 12 * BK) {
     *plan = {1, 1, 1, N / 8, 1, true};
     return true;
   }

@@ -160,14 +160,17 @@ def test_decode_products_on_every_tile(T, d, F, gate, down):
 
 
 @pytest.mark.parametrize("T,d,F,gate,down", [
-    (1, 64, 128, (16, 16, 1), (8, 8, 1)),           # one K tile of 128, eight weight tiles
+    (1, 64, 832, (16, 16, 1), (8, 8, 1)),           # 6.5 K tiles of 128, the fewest, for 8 wavefronts; eight weight tiles
+    (1, 64, 768, (16, 16, 1), (16, 16, 1)),         # fewer, which whole fragments multiply faster
+    (1, 64, 128, (16, 16, 1), (16, 16, 1)),
     (8, 2048, 8192, (16, 32, 1), (8, 8, 1)),        # the most tokens, weight tiles and K tiles in flight
     (7, 1088, 2176, (16, 16, 1), (8, 8, 1)),        # 17 K tiles over 8 wavefronts
     (3, 192, 4224, (16, 32, 1), (8, 8, 1)),         # 33: one wavefront has a fifth
     (8, 512, 1344, (16, 16, 1), (8, 8, 1)),         # 10.5 K tiles of 128
-    (2, 64, 192, (16, 16, 1), (8, 8, 1)),           # 1.5
-    (5, 2112, 256, (16, 16, 1), (16, 16, 1)),       # more weight rows than 256 workgroups of 8
-    (9, 256, 512, (16, 16, 1), (16, 16, 1)),        # a ninth token
+    (2, 64, 960, (16, 16, 1), (8, 8, 1)),           # 7.5
+    (2, 64, 192, (16, 16, 1), (16, 16, 1)),
+    (5, 2112, 1024, (16, 16, 1), (16, 16, 1)),      # more weight rows than 256 workgroups of 8
+    (9, 256, 1024, (16, 16, 1), (16, 16, 1)),       # a ninth token
 ])
 def test_down_product_of_up_to_eight_tokens(T, d, F, gate, down):
     test_decode_products_on_every_tile(T, d, F, gate, down)
