@@ -313,8 +313,8 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
 // 128 tokens 8.3 / 6.4 / 7.7, 256 tokens - / 10.4 / 7.9.
 // K is cut where that still leaves at most one workgroup per CU and as many K tiles per slice as outweigh the exchange
 // of the partial tiles (about 1.3 us): the more tokens, the longer a K tile takes.  Layer forward, us, least 64 / 32 / 16
-// K tiles: 1024 x 4096, 1 token 10.0 / 10.4 / 10.9, 16 tokens 11.3 / 11.0 / 11.0, 64 tokens 16.8 / 14.4 / 13.2; 1536 x 5120, 1 token
-// 14.8 / 13.7 / 13.8, 64 tokens 26.8 / 21.5 / 21.5.
+// K tiles: 1024 x 4096, 16 tokens 11.3 / 11.0 / 11.0, 64 tokens 16.8 / 14.4 / 13.2; 1536 x 5120, 64 tokens 26.8 / 21.5 / 21.5.
+// (Up to 8 tokens no product is cut: 2048 weight rows and fewer take tiles of 8, more are over 128 workgroups.)
 struct DecodePlan { int fa, fb, mt, nt, ksplit; bool pair; };
 
 // K of more than 2048 (the down product of the larger layers) only with 16 weight rows: 2048 x 8192, 256 tokens, 25.0 us
@@ -324,9 +324,9 @@ bool decode_plan(int M, int N, int K, bool plain, bool may_split, size_t ws_byte
   // Up to 8 tokens: 8 weight rows per workgroup, so that K needs no slices and no exchange (2 to 3 us of a launch) while the
   // weight tiles still give one workgroup per CU.  Layer forward, us, 16 weight rows in slices / 8: 2048 x 8192, 1 token 18.2 / 16.9,
   // 4 tokens 19.1 / 18.0, 8 tokens 19.2 / 18.6; 1536 x 5120, 2 tokens 12.7 / 11.3; 1024 x 4096, 1 token 9.9 / 9.2, 8 tokens 10.2 / 9.6;
-  // 512 x 1536, 1 token 6.9 / 6.5.  From K of 832 on, 13 K tiles of the other shape for its 8
-  // wavefronts: 64 x 128, 4 tokens 5.2 / 5.4, 512 x 768, 5 tokens 5.8 / 5.9, 832 x 832, 7 tokens 6.4 / 6.2.  (Each workgroup reads all tokens' rows whole, so the gain shrinks with the tokens.  16 wavefronts
-  // with 2 K tiles in flight 17.4, 8 with 5 17.1.)
+  // 512 x 1536, 1 token 6.9 / 6.5.  From K of 832 on, 13 K tiles of 64 for 8 wavefronts: 64 x 128, 4 tokens 5.2 / 5.4, 64 x 192,
+  // 6 tokens 5.2 / 5.4, 832 x 832, 7 tokens 6.4 / 6.2.  (Each workgroup reads all tokens' rows whole, so the gain shrinks with the
+  // tokens.  16 wavefronts with 2 K tiles in flight 17.4, 8 with 5 17.1.)
   if (plain && M <= 8 && N <= 8 * 256 && N % 8 == 0 && K > 12 * BK) {
     *plan = {1, 1, 1, N / 8, 1, true};
     return true;
@@ -337,7 +337,7 @@ bool decode_plan(int M, int N, int K, bool plain, bool may_split, size_t ws_byte
     if ((int64_t)mt * nt > 256 && !last) continue;
     if (fa == 4 && fb > 1 && K > 2048) break;
     int ks = 1;   // (slices of at least 16 K tiles, 8 at most: none of them is empty)
-    const int least = M <= 8 ? 40 : M <= 16 ? 32 : 16;
+    const int least = M <= 16 ? 32 : 16;
     while (may_split && ks < MAX_SLICES && mt * nt * ks * 2 <= 256 && K / BK / (ks * 2) >= least &&
            (size_t)mt * nt * ks * 2 * fa * fb * 1024 <= ws_bytes)
       ks *= 2;
