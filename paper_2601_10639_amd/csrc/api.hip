@@ -21,7 +21,7 @@ const char* const kKernelNames[K_COUNT_] = {
     "gemm_dw_gate",    "silu_gather",      "sort_count",    "sort_scan",    "sort_scatter",
     "sort_fused",      "unique",          "seg_reduce",   "seg_combine",   "sparse_adamw", "row_copy",
     "splitk_reduce",   "gemm_up",      "gemm_dw_up",   "sort_merge",
-    "grads_f32", "gemm_dw"};
+    "grads_f32", "gemm_dw", "list_copy"};
 
 #define fail stem_fail
 
@@ -757,8 +757,8 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
     return fail(c, STEM_ERR_WORKSPACE, "stem_prefetch_rows: %lld distinct ids but E_compact holds %lld rows",
                 (long long)U, (long long)cap);
 
-  if (T > 0) HIP_TRY(c, hipMemcpyAsync(remap, c->remap_pinned, (size_t)T * 4, hipMemcpyHostToDevice, c->side));
   if (c->prefetch_mode == STEM_PREFETCH_MEMCPY) {
+    if (T > 0) HIP_TRY(c, hipMemcpyAsync(remap, c->remap_pinned, (size_t)T * 4, hipMemcpyHostToDevice, c->side));
     // Pack the rows into pinned staging with a few host threads and copy chunk by chunk,
     // packing chunk i+1 while chunk i is on the link (staging allocated by stem_set_prefetch_mode).
     const size_t half = c->pack_bytes / 2;
@@ -783,8 +783,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
       HIP_TRY(c, hipEventRecord(c->pack_done[chunk & 1], c->side));
     }
   } else if (U > 0) {
-    HIP_TRY(c, hipMemcpyAsync(c->order_dev, src_row, (size_t)U * 4, hipMemcpyHostToDevice, c->side));
-    HIP_TRY(c, hipMemcpyAsync(c->order_dev + c->max_tokens, dst_slot, (size_t)U * 4, hipMemcpyHostToDevice, c->side));
+    HIP_TRY(c, stem_copy_lists_kernel(c, c->remap_pinned, remap, T, c->order_pinned, c->order_dev, U, c->max_tokens, c->side));
     int64_t k0 = 0;
     for (int k = 0; k < nchunks; ++k) {
       HIP_TRY(c, stem_copy_rows_kernel(c, E_host, c->order_dev + k0, c->order_dev + c->max_tokens + k0,
@@ -895,11 +894,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
                 (long long)n_miss, (long long)cap);
   }
 
-  if (T > 0) HIP_TRY(c, hipMemcpyAsync(remap, c->remap_pinned, (size_t)T * 4, hipMemcpyHostToDevice, c->side));
-  if (n_miss > 0) {
-    HIP_TRY(c, hipMemcpyAsync(c->order_dev, src_row, (size_t)n_miss * 4, hipMemcpyHostToDevice, c->side));
-    HIP_TRY(c, hipMemcpyAsync(c->order_dev + c->max_tokens, dst_row, (size_t)n_miss * 4, hipMemcpyHostToDevice, c->side));
-  }
+  HIP_TRY(c, stem_copy_lists_kernel(c, c->remap_pinned, remap, T, c->order_pinned, c->order_dev, n_miss, c->max_tokens, c->side));
   {
     int64_t k0 = 0;
     for (int k = 0; k < nchunks; ++k) {

@@ -62,7 +62,31 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const u32x4_t* __restric
   }
 }
 
+// The copy's lists and remap.  Three hipMemcpyAsync calls take 25 to 35 us (above 16 KB through a copy engine and a handover to the
+// next kernel), in which the gate product of the same call takes every compute unit: the row copy, which needs some for itself,
+// then waits for a round of its tiles.  1024 x 4096, by itself / in turn on two contexts, us, row copies that share compute units /
+// behind three memcpys / behind this kernel: 6000 tokens 430 / 452 / 418 and 342 / 381 / 344; 8192 tokens 532 / 554 / 519 and 425 /
+// 475 / 433.  2048 x 8192, 16 tokens by itself 62 / 62 / 57.
+__global__ __launch_bounds__(256) void copy_lists_kernel(const int32_t* __restrict__ remap_host, int32_t* __restrict__ remap, int64_t T,
+                                                         const int32_t* __restrict__ order_host, int32_t* __restrict__ order,
+                                                         int64_t n, int64_t second) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < T + 2 * n; i += (int64_t)gridDim.x * 256) {
+    if (i < T) { remap[i] = remap_host[i]; continue; }
+    const int64_t k = i - T < n ? i - T : i - T - n + second;
+    order[k] = order_host[k];
+  }
+}
+
 }  // namespace
+
+hipError_t stem_copy_lists_kernel(stem_ctx* ctx, const int32_t* remap_host, int32_t* remap, int64_t T, const int32_t* order_host,
+                                  int32_t* order, int64_t n, int64_t second, hipStream_t s) {
+  if (T + n <= 0) return hipSuccess;
+  ProfScope ps(ctx, K_LIST_COPY, s);
+  const int grid = (int)std::min<int64_t>((T + 2 * n + 255) / 256, 1024);
+  hipLaunchKernelGGL(copy_lists_kernel, dim3(grid), dim3(256), 0, s, remap_host, remap, T, order_host, order, n, second);
+  return hipGetLastError();
+}
 
 hipError_t stem_copy_rows_kernel(stem_ctx* ctx, const void* E_host, const int32_t* src_row, const int32_t* dst_slot,
                                  int64_t n, int64_t row_bytes, void* E_compact, hipStream_t s) {

@@ -32,6 +32,7 @@ enum StemKernelId {
   K_SORT_MERGE,
   K_GRADS_F32,       // dx, dWd and dWg of a small fp32 layer in one launch
   K_GEMM_DW,         // two or three weight gradients in one launch
+  K_LIST_COPY,       // host-resident table: remap and the row copy's lists
   K_COUNT_
 };
 
@@ -266,6 +267,9 @@ hipError_t stem_adamw(stem_ctx* ctx, int is_bf16, const int32_t* uniq_ids, const
                       const stem_adamw_hparams& hp, hipStream_t s);
 
 // ---- host-resident rows (prefetch.hip) ----------------------------------------------
+// From pinned host memory to the device: remap [T], and entries [0, n) and [second, second + n) of order
+hipError_t stem_copy_lists_kernel(stem_ctx* ctx, const int32_t* remap_host, int32_t* remap, int64_t T, const int32_t* order_host,
+                                  int32_t* order, int64_t n, int64_t second, hipStream_t s);
 // E_compact[dst_slot[k]] = E_host[src_row[k]] for k in [0, n)
 hipError_t stem_copy_rows_kernel(stem_ctx* ctx, const void* E_host, const int32_t* src_row, const int32_t* dst_slot,
                                  int64_t n, int64_t row_bytes, void* E_compact, hipStream_t s);

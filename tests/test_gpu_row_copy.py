@@ -30,3 +30,32 @@ def test_rows_arrive_whole_and_nothing_else_is_written(dtype, F, n):
     assert torch.equal(E_compact[:T].cpu(), E_host[torch.from_numpy(np.sort(ids)).long()])
     assert bool((E_compact[T:] == 7.0).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("T,max_tokens,V", [(1, 7, 5), (255, 70001, 300), (257, 70001, 300), (66001, 70001, 300), (300001, 300003, 1000)])
+def test_remap_of_long_batches_and_of_batches_without_a_miss(T, max_tokens, V):
+    """Lists shorter than the context's arrays, and longer than one sweep of the kernel that brings them."""
+    F = 4
+    shape = inputs.StemShape("lists", 64, F, V, 1, max_tokens, "f32")
+    ids = np.random.default_rng(T).integers(0, V, T).astype(np.int32)
+    distinct, want = np.unique(ids, return_inverse=True)
+    E_host = inputs.normal((V, F), 1.0, 6, torch.float32, "cpu").pin_memory()
+    ctx = Hn.make_ctx(shape, max_tokens)
+    E_compact = torch.empty(V, F, dtype=torch.float32, device=DEV)
+    remap = torch.full((T + 3,), -7, dtype=torch.int32, device=DEV)
+    n, _ = L.stem_prefetch_rows(ctx, E_host, torch.from_numpy(ids), E_compact, remap, T=T)
+    torch.cuda.synchronize()
+    assert n == distinct.size
+    np.testing.assert_array_equal(remap[:T].cpu().numpy(), want)
+    assert bool((remap[T:] == -7).all())
+    assert torch.equal(E_compact[:n].cpu(), E_host[torch.from_numpy(distinct).long()])
+    L.stem_cache_init(ctx, V)
+    E_dev = torch.empty(2 * V, F, dtype=torch.float32, device=DEV)
+    for batch in range(2):   # the second finds every row in the cache
+        remap.fill_(-7)
+        _, misses, _ = L.stem_prefetch_rows_cached(ctx, E_host, torch.from_numpy(ids), E_dev, V, remap, T=T)
+        torch.cuda.synchronize()
+        assert misses == (0 if batch else distinct.size)
+        assert torch.equal(E_dev[remap[:T].long()].cpu(), E_host[torch.from_numpy(ids).long()])
+        assert bool((remap[T:] == -7).all())
+    ctx.close()
