@@ -144,6 +144,18 @@ void stem_route_forward(int d, int F, int64_t T, int32_t* route) {
   }
 }
 
+int stem_route_weight_grads_apart(int d, int F, int64_t T, const void* dy, const void* H, const void* dx, const void* W_gate,
+                                  const void* W_up, const void* dV, const float* dW_gate, const float* dW_up) {
+  // One after the other, dW_down reads dy and H first, then dx the weights and dV, then dW_gate dG and x, then dW_up dV and x: a
+  // gradient may lie over what was read before it.  Together and before dx, that is read beside it or later.
+  const size_t Td = (size_t)T * d * 2, TF = (size_t)T * F * 2, Fd = (size_t)F * d * 4;
+  for (const float* g : {dW_gate, dW_up})
+    if (overlap(g, Fd, dy, Td) || overlap(g, Fd, H, TF) ||
+        (dx && (overlap(g, Fd, W_gate, Fd / 2) || overlap(g, Fd, W_up, Fd / 2) || overlap(g, Fd, dV, TF))))
+      return 0;
+  return !overlap(dW_gate, Fd, dV, TF);
+}
+
 const char* stem_status_string(stem_status s) {
   switch (s) {
     case STEM_OK: return "STEM_OK";
@@ -440,11 +452,9 @@ stem_status stem_ffn_backward(stem_ctx* c, const void* dy, const void* x, const 
       a.K = (int)T; a.accumulate = accumulate; a.flag = c->flag;
       a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
     }
-    // The two together, and before dx, unless dW_gate lies over something that is read by then or beside it.
-    const size_t Td = (size_t)T * d * 2, TF = (size_t)T * F * 2, Fd = (size_t)F * d * 4;
-    const bool apart = !overlap(dW_gate, Fd, dy, Td) && !overlap(dW_gate, Fd, H, TF) && !(dx && overlap(dW_gate, Fd, W_gate, Fd / 2));
     GroupPlan plan = {};
-    const bool together = apart && stem_weight_grads_together(w, 2, &plan);
+    const bool together = stem_route_weight_grads_apart(d, F, T, dy, H, dx, W_gate, nullptr, nullptr, dW_gate, nullptr) &&
+                          stem_weight_grads_together(w, 2, &plan);
     if (together) HIP_TRY(c, stem_weight_grads(c, w, 2, plan, s));
     else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, w[0], s));
     if (dx) {  // dx = dG W_gate
@@ -590,15 +600,9 @@ stem_status stem_ffn_up_backward(stem_ctx* c, const void* dy, const void* x, con
     a.K = (int)T; a.accumulate = accumulate; a.flag = c->flag;
     a.ws = c->splitk_ws; a.ws_bytes = c->splitk_bytes;
   }
-  // The three together, and before dx, unless one lies over something that is read by then or beside it.
-  const size_t Td = (size_t)T * d * 2, TF = (size_t)T * F * 2, Fd = (size_t)F * d * 4;
-  bool apart = true;
-  for (const float* g : {dW_gate, dW_up})
-    apart = apart && !overlap(g, Fd, dy, Td) && !overlap(g, Fd, saved_H, TF) &&
-            !(dx && (overlap(g, Fd, W_gate, Fd / 2) || overlap(g, Fd, W_up, Fd / 2) || overlap(g, Fd, dV, TF)));
-  apart = apart && !overlap(dW_gate, Fd, dV, TF);
   GroupPlan plan = {};
-  const bool together = apart && stem_weight_grads_together(w, 3, &plan);
+  const bool together = stem_route_weight_grads_apart(d, F, T, dy, saved_H, dx, W_gate, W_up, dV, dW_gate, dW_up) &&
+                        stem_weight_grads_together(w, 3, &plan);
   if (together) HIP_TRY(c, stem_weight_grads(c, w, 3, plan, s));
   else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DWDOWN, OP_MC, OP_MC, EPI_F32, w[0], s));
   if (dx) {  // dx = dG W_gate + dV W_up: one product over the concatenated K range

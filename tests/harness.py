@@ -62,6 +62,13 @@ def route_weight_grads(T, d, F, n, ws=64 << 20):
     return tuple(r)
 
 
+def route_weight_grads_apart(T, d, F, **at):
+    """Whether they may share a launch, as the buffers lie that are given by name: byte addresses, None for one not there."""
+    names = ("dy", "H", "dx", "W_gate", "W_up", "dV", "dW_gate", "dW_up")
+    assert set(at) <= set(names)
+    return bool(L.lib().stem_route_weight_grads_apart(d, F, ctypes.c_int64(T), *[ctypes.c_void_p(at.get(k)) for k in names]))
+
+
 def route_sort(T, V):
     return L.lib().stem_route_sort(ctypes.c_int64(T), V)
 

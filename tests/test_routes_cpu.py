@@ -3,7 +3,7 @@ import random
 
 import pytest
 
-from tests.harness import EPI_BF16, EPI_F32, EPI_GATE, route_tiles as tiles, route_weight_grads
+from tests.harness import EPI_BF16, EPI_F32, EPI_GATE, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
 
 
 def test_no_k_slice_is_empty():
@@ -56,3 +56,21 @@ def test_tiling_of_products_that_were_measured_on_each(product, want):
 ])
 def test_weight_gradients_share_a_launch_where_that_was_measured_shorter(T, d, F, n, together):
     assert bool(route_weight_grads(T, d, F, n, min(64 << 20, 32 * d * max(T, F)))[0]) == together
+
+
+def test_weight_gradients_over_buffers_that_are_read_before_them_do_not_share_a_launch():
+    T, d, F = 700, 192, 576
+    size = dict(dy=T * d * 2, H=T * F * 2, dx=T * d * 2, W_gate=F * d * 2, W_up=F * d * 2, dV=T * F * 2, dW_gate=F * d * 4, dW_up=F * d * 4)
+    for up in (False, True):
+        names = [k for k in size if up or k not in ("W_up", "dV", "dW_up")]
+        lie = {k: (i + 1) << 24 for i, k in enumerate(names)}
+        assert route_weight_grads_apart(T, d, F, **lie)
+        for grad in ("dW_gate", "dW_up") if up else ("dW_gate",):
+            for over in set(names) - {grad, "dx", "dW_gate", "dW_up"}:
+                before_dx = over in ("dy", "H")   # read by dW_down; the others by dx, and dV by dW_up
+                for with_dx in (True, False):
+                    q = {**lie, "dx": lie["dx"] if with_dx else None}
+                    refused = before_dx or with_dx or (over == "dV" and grad == "dW_gate")
+                    for at, shares in ((lie[over] - size[grad], True), (lie[over] - size[grad] + 16, not refused),
+                                       (lie[over] + size[over] - 16, not refused), (lie[over] + size[over], True)):
+                        assert route_weight_grads_apart(T, d, F, **{**q, grad: at}) == shares, (up, grad, over, with_dx, at)
