@@ -217,20 +217,37 @@ __device__ __forceinline__ void unpack8(uint4 u, float (&f)[8]) {
 // their epilogues (each reads a G tile and writes two tiles) meet less often: 0.565 ms with
 // 8, 0.545 with 4 or 6, 0.537 with 3 or 5, 0.532 with 7, 0.545-0.55 with 9, 11, 13
 // (d_model 2048, d_ff 8192, 16384 tokens).
-__device__ __forceinline__ int xcd_major(int b, int nb) {
+__host__ __device__ __forceinline__ int xcd_major(int b, int nb) {
   const int q = nb >> 3, r = nb & 7;
   const int xcd = b & 7, idx = b >> 3;
   return xcd * q + (xcd < r ? xcd : r) + idx;
 }
-template <int GM>
-__device__ __forceinline__ void tile_at(int L, int ntm, int ntn, int& tm, int& tn) {
-  const int per_group = GM * ntn;
+__host__ __device__ __forceinline__ void tile_at(int gm, int L, int ntm, int ntn, int& tm, int& tn) {
+  const int per_group = gm * ntn;
   const int group = L / per_group;
-  const int first = group * GM;
-  const int gsize = (ntm - first) < GM ? (ntm - first) : GM;
+  const int first = group * gm;
+  const int gsize = (ntm - first) < gm ? (ntm - first) : gm;
   const int in = L - group * per_group;
   tm = first + in % gsize;
   tn = in / gsize;
+}
+// Workgroup -> K slice, product and place in the product's bands, for launches of several products (n_more beyond the first, of
+// which tiles0 and tiles1 are the tiles of the first two) or K slices: the slices follow each other in the XCDs' runs of tiles, so
+// that an XCD works on one or two of them (1024 x 4096 weight gradient, 16384 tokens, 4 slices: 123.5 us with every slice on
+// every XCD, 122.2), and in each slice the products.
+struct Place { int slice, product, in; };
+__host__ __device__ __forceinline__ Place place_of(int b, int nb, int ksplit, int n_more, int tiles0, int tiles1) {
+  const int all = nb / ksplit, L = xcd_major(b, nb);
+  Place q = {L / all, 0, L % all};
+  if (n_more > 0 && q.in >= tiles0) {
+    q.product = 1;
+    q.in -= tiles0;
+    if (n_more > 1 && q.in >= tiles1) {
+      q.product = 2;
+      q.in -= tiles1;
+    }
+  }
+  return q;
 }
 
 // A tiling: a wavefront holds MI x NJ accumulators of 32 x 32, WM x WN wavefronts multiply, and the operand
@@ -281,32 +298,31 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   const int wm = wave / C::WN, wn = wave % C::WN;
   int ntm = (p.M + C::TM - 1) / C::TM, ntn = (p.N + C::TN - 1) / C::TN;
   constexpr int BAND = (EPI == EPI_DH || EPI == EPI_DH_UP || EPI == EPI_DH_UPE) ? 7 : 4;   // see tile_at
-  int tm, tn, L = xcd_major(blockIdx.x, gridDim.x), z = 0;
-  if (EPI == EPI_F32 && LA == OP_MC && LB == OP_MC) {   // which of the launch's products
-    const int all = gridDim.x / p.ksplit;
-    int in = L % all;
-    size_t before = 0;
-    for (int e = 0; e < 2; ++e) {
-      const int here = ntm * ntn;
-      if (e >= p.n_more || in < here) break;
-      in -= here;
-      before += (size_t)p.M * p.N;
-      p.A = p.more[e].A; p.B = p.more[e].B; p.C = p.more[e].C; p.M = p.more[e].M; p.N = p.more[e].N;
-      p.lda = p.more[e].lda; p.ldb = p.more[e].ldb;
-      ntm = (p.M + C::TM - 1) / C::TM; ntn = (p.N + C::TN - 1) / C::TN;
+  int tm, tn;
+  Place at;
+  if (EPI == EPI_F32) {
+    constexpr bool SEVERAL = LA == OP_MC && LB == OP_MC;
+    const int second = SEVERAL ? ((p.more[0].M + C::TM - 1) / C::TM) * ((p.more[0].N + C::TN - 1) / C::TN) : 0;
+    at = place_of(blockIdx.x, gridDim.x, p.ksplit, SEVERAL ? p.n_more : 0, ntm * ntn, second);
+    if (SEVERAL) {
+      auto next = [&](const auto& m) __attribute__((always_inline)) {
+        p.ws += (size_t)p.M * p.N;
+        p.A = m.A; p.B = m.B; p.C = m.C; p.M = m.M; p.N = m.N; p.lda = m.lda; p.ldb = m.ldb;
+        ntm = (p.M + C::TM - 1) / C::TM; ntn = (p.N + C::TN - 1) / C::TN;
+      };
+      if (at.product > 0) {
+        next(p.more[0]);
+        if (at.product > 1) next(p.more[1]);
+      }
     }
-    p.ws += before;
-    L = L / all * all + in;
+  } else {
+    at = {0, 0, xcd_major(blockIdx.x, gridDim.x)};
   }
   if (EPI == EPI_F32 && p.ksplit > 1) {
     // Split along K (few output tiles, long K): slice z of the K tiles, its product stored plainly to
     // slice z of the partial buffer; a second kernel sums the slices in order.  The slice is
-    // expressed by moving the operands and shrinking K.  The slices follow each other in the XCDs' runs of tiles, so an XCD
-    // works on one or two of them (1024 x 4096 weight gradient, 16384 tokens, 4 slices: 123.5 us with every slice on every
-    // XCD, 122.2).
-    const int ntiles = gridDim.x / p.ksplit;
-    z = L / ntiles;
-    L -= z * ntiles;
+    // expressed by moving the operands and shrinking K.
+    const int z = at.slice;
     int zk = z, slices = p.ksplit;
     if (LA == OP_KC && p.A2) {   // two operand pairs of the same K: half of the slices each
       slices >>= 1;
@@ -326,7 +342,7 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
     p.C = p.ws + (size_t)z * p.elems;
     p.accumulate = 0;
   }
-  tile_at<BAND>(L, ntm, ntn, tm, tn);
+  tile_at(BAND, at.in, ntm, ntn, tm, tn);
   const int m0 = tm * C::TM, n0 = tn * C::TN;
   // K rotation.  Workgroups on XCD x start their K loop x eighths of the way in and wrap around, so
   // the eight XCDs stream eight different stretches of the operands' rows at any moment instead of
@@ -871,12 +887,16 @@ Plan choose_plan(int M, int N, int K, int ops, bool fused, bool f32, size_t ws_b
   return best;
 }
 
+int grid_of(const GemmArgs& a, int tm, int tn) {
+  int tiles = ((a.M + tm - 1) / tm) * ((a.N + tn - 1) / tn);
+  for (int e = 0; e < a.n_more; ++e) tiles += ((a.more[e].M + tm - 1) / tm) * ((a.more[e].N + tn - 1) / tn);
+  return tiles * a.ksplit;
+}
+
 template <class C, int LA, int LB, int EPI>
 hipError_t launch_tiles(stem_ctx* ctx, int kid, const GemmArgs& a, hipStream_t s) {
-  int tiles = ((a.M + C::TM - 1) / C::TM) * ((a.N + C::TN - 1) / C::TN);
-  for (int e = 0; e < a.n_more; ++e) tiles += ((a.more[e].M + C::TM - 1) / C::TM) * ((a.more[e].N + C::TN - 1) / C::TN);
   ProfScope ps(ctx, kid, s);
-  hipLaunchKernelGGL((gemm_bf16_kernel<C, LA, LB, EPI>), dim3(tiles * a.ksplit), dim3((C::WAVES + C::LW) * 64), 0, s, a);
+  hipLaunchKernelGGL((gemm_bf16_kernel<C, LA, LB, EPI>), dim3(grid_of(a, C::TM, C::TN)), dim3((C::WAVES + C::LW) * 64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -995,6 +1015,19 @@ void stem_route_weight_grads(int d, int F, int64_t T, int n, int64_t ws_bytes, i
   GroupPlan plan = {};
   route[0] = plan_together(a, n, (size_t)ws_bytes, &plan);
   route[1] = kTilings[plan.tiling].tm; route[2] = kTilings[plan.tiling].tn; route[3] = plan.ksplit;
+}
+
+int stem_route_tile(const int32_t* M, const int32_t* N, int n, int tile_rows, int tile_cols, int band, int ksplit, int block, int32_t* at) {
+  GemmArgs a = {};
+  a.M = M[0]; a.N = N[0]; a.ksplit = ksplit; a.n_more = n - 1;
+  for (int e = 1; e < n; ++e) { a.more[e - 1].M = M[e]; a.more[e - 1].N = N[e]; }
+  int tiles[2] = {};
+  for (int e = 0; e < 2 && e < n; ++e) tiles[e] = ((M[e] + tile_rows - 1) / tile_rows) * ((N[e] + tile_cols - 1) / tile_cols);
+  const int grid = grid_of(a, tile_rows, tile_cols);
+  const Place q = place_of(block, grid, ksplit, a.n_more, tiles[0], tiles[1]);
+  at[0] = q.product; at[1] = q.slice;
+  tile_at(band, q.in, (M[q.product] + tile_rows - 1) / tile_rows, (N[q.product] + tile_cols - 1) / tile_cols, at[2], at[3]);
+  return grid;
 }
 
 bool stem_weight_grads_together(const GemmArgs* a, int n, GroupPlan* plan) {

@@ -185,7 +185,9 @@ extern "C" {
 void stem_route_tiles(int M, int N, int K, int ops, int epi, int64_t ws_bytes, int32_t* route);
 // the n = 2 (dW_down, dW_gate) or 3 (dW_up too) weight gradients of a layer: {one launch, tile rows, tile columns, K slices}
 void stem_route_weight_grads(int d_model, int d_ff, int64_t T, int n, int64_t ws_bytes, int32_t* route);
-// whether they may share a launch before dx (null: not wanted) as their buffers lie; W_up, dV, dW_up: null without an up projection
+// workgroup `block` of a tile launch of n products of M x N outputs: {product, K slice, tile row, tile column}; returns the grid
+int stem_route_tile(const int32_t* M, const int32_t* N, int n, int tile_rows, int tile_cols, int band, int ksplit, int block, int32_t* at);
+// whether the weight gradients may share a launch before dx (null: not wanted) as their buffers lie; W_up, dV, dW_up: null without an up projection
 int stem_route_weight_grads_apart(int d_model, int d_ff, int64_t T, const void* dy, const void* H, const void* dx, const void* W_gate,
                                   const void* W_up, const void* dV, const float* dW_gate, const float* dW_up);
 void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* route);

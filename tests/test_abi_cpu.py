@@ -113,29 +113,30 @@ def test_early_touch_of_gathered_rows_stays_inside_the_table():
                     assert 0 <= first_elem and first_elem * 2 + 4 <= F * 2, (F, tn, wn, first_elem)
 
 
-def test_tile_map_model_covers_every_tile_once():
-    """The large GEMM maps workgroup ids to output tiles in XCD-major runs walked in bands of tile rows
-    (4, or 7 in the dH product).  Host-side model of that map over ragged and full grids, incl. fewer
-    workgroups than XCDs and band heights that do not divide the number of tile rows: every tile is
-    produced by exactly one workgroup."""
-    def tile_of_block(b, nb, ntm, ntn, gm):
-        q, r = nb >> 3, nb & 7
-        xcd, idx = b & 7, b >> 3
-        lin = xcd * q + min(xcd, r) + idx
-        per_group = gm * ntn
-        group = lin // per_group
-        first = group * gm
-        gsize = min(ntm - first, gm)
-        inside = lin - group * per_group
-        return first + inside % gsize, inside // gsize
+def _places(lib, M, N, rows, cols, band, ksplit):
+    m, n_ = (ctypes.c_int32 * 3)(*M), (ctypes.c_int32 * 3)(*N)
+    at = (ctypes.c_int32 * 4)()
+    grid = lib.stem_route_tile(m, n_, len(M), rows, cols, band, ksplit, 0, at)
+    for b in range(grid):
+        assert lib.stem_route_tile(m, n_, len(M), rows, cols, band, ksplit, b, at) == grid
+        yield tuple(at)
 
-    for gm in (4, 7):
+
+def test_tile_map_covers_every_tile_of_every_product_and_slice_once():
+    """The large GEMM maps workgroup ids to K slices, products and output tiles in XCD-major runs walked in bands of tile rows
+    (4, or 7 in the dH product).  The kernel's own map, asked on the host, over ragged and full grids, incl. fewer workgroups
+    than XCDs and band heights that do not divide the number of tile rows: every tile is produced by exactly one workgroup."""
+    lib = L.lib()
+    for band in (4, 7):
         for ntm in (1, 2, 3, 5, 7, 8, 9, 13, 64):
             for ntn in (1, 2, 3, 8, 31, 32):
-                nb = ntm * ntn
-                seen = set()
-                for b in range(nb):
-                    tm, tn = tile_of_block(b, nb, ntm, ntn, gm)
-                    assert 0 <= tm < ntm and 0 <= tn < ntn, (gm, ntm, ntn, b, tm, tn)
-                    seen.add((tm, tn))
-                assert len(seen) == nb, (gm, ntm, ntn)
+                seen = sorted(_places(lib, [ntm * 256 - 100], [ntn * 128 - 64], 256, 128, band, 1))
+                assert seen == [(0, 0, m, n) for m in range(ntm) for n in range(ntn)], (band, ntm, ntn)
+    for d, F in ((64, 64), (128, 320), (576, 1728), (704, 2816), (1088, 4032)):   # dW_down, dW_gate, dW_up
+        for n in (1, 2, 3):
+            M, N = [d, F, F][:n], [F, d, d][:n]
+            for rows, cols in ((256, 256), (256, 128), (128, 128)):
+                for ksplit in (1, 2, 3, 4, 5, 6, 7, 8):
+                    seen = sorted(_places(lib, M, N, rows, cols, 4, ksplit))
+                    assert seen == [(e, z, m, c) for e in range(n) for z in range(ksplit)
+                                    for m in range(-(-M[e] // rows)) for c in range(-(-N[e] // cols))], (d, F, n, rows, cols, ksplit)
