@@ -25,9 +25,9 @@ DEV = "cuda:0"
     (600, 512, 2112, [(128, 128, 1), (128, 128, 7), (128, 128, 8), (128, 128, 1)]),
 ])
 @pytest.mark.parametrize("up", [False, True])
-def test_bf16_products_on_every_tiling(T, d, F, routes, up):
+def test_bf16_products_on_every_tiling(T, d, F, routes, up, table=True):
     """Forward and backward of the layer, and (up) of the additive variant, whose dx product sums two operand
-    pairs and cuts them into K slices."""
+    pairs and cuts them into K slices; without `table`, of the dense layer."""
     assert [r[1:] for r in (Hn.route_tiles(T, F, d, 1, Hn.EPI_DH), Hn.route_tiles(T, d, F), Hn.route_tiles(T, d, F, 2),
                             Hn.route_tiles(F, d, T, 1, Hn.EPI_F32))] == routes
     if T > 512:
@@ -49,13 +49,15 @@ def test_bf16_products_on_every_tiling(T, d, F, routes, up):
         out = {"y": e(T, d), "dx": e(T, d), "dU": e(T, F), "dW_gate": e(F, d, dt=torch.float32),
                "dW_up": e(F, d, dt=torch.float32), "dW_down": e(d, F, dt=torch.float32)}
         G, Up, H = e(T, F), e(T, F), e(T, F)
-        L.stem_ffn_up_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], Wu, inp["W_down"], inp["E"], out["y"], G, Up, H)
-        L.stem_ffn_up_backward(ctx, inp["dy"], inp["x"], inp["ids"], inp["W_gate"], Wu, inp["W_down"], inp["E"], G, Up, H,
+        E, e64 = (inp["E"], f64["E"]) if table else (None, None)
+        L.stem_ffn_up_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], Wu, inp["W_down"], E, out["y"], G, Up, H)
+        L.stem_ffn_up_backward(ctx, inp["dy"], inp["x"], inp["ids"], inp["W_gate"], Wu, inp["W_down"], E, G, Up, H,
                                out["dx"], out["dW_gate"], out["dW_up"], out["dW_down"], out["dU"])
         wu = inputs.to_f64(Wu)
-        y, _ = O.up_forward(f64["x"], ids, f64["W_gate"], wu, f64["W_down"], f64["E"])
-        bw = O.up_backward(f64["dy"], f64["x"], ids, f64["W_gate"], wu, f64["W_down"], f64["E"])
-        ref = {"y": y, "dx": bw["dx"], "dU": bw["dV"], "dW_gate": bw["dW_gate"], "dW_up": bw["dW_up"], "dW_down": bw["dW_down"]}
+        y, fw = O.up_forward(f64["x"], ids, f64["W_gate"], wu, f64["W_down"], e64)
+        bw = O.up_backward(f64["dy"], f64["x"], ids, f64["W_gate"], wu, f64["W_down"], e64)
+        out.update(G=G, Up=Up, H=H)
+        ref = {"G": fw["g"], "Up": fw["up"], "H": fw["h"], "y": y, "dx": bw["dx"], "dU": bw["dV"], "dW_gate": bw["dW_gate"], "dW_up": bw["dW_up"], "dW_down": bw["dW_down"]}
     L.stem_sync_status(ctx)
     errs = {k: Hn.max_rel(out[k].float().cpu(), v) for k, v in ref.items()}
     assert all(v <= Hn.TOL["bf16"] for v in errs.values()), errs
@@ -70,6 +72,14 @@ def test_bf16_products_on_every_tiling(T, d, F, routes, up):
 ])
 def test_bf16_products_on_192_row_tiles(T, d, F, routes, up):
     test_bf16_products_on_every_tiling(T, d, F, routes, up)
+
+
+@pytest.mark.parametrize("T,d,F,routes", [
+    (1535, 1088, 4032, [(192, 128, 1), (128, 128, 2), (128, 128, 2), (256, 128, 1)]),
+    (1345, 576, 4096, [(192, 128, 1), (128, 128, 4), (128, 128, 4), (128, 128, 1)]),
+])
+def test_dense_layers_on_192_row_tiles(T, d, F, routes):
+    test_bf16_products_on_every_tiling(T, d, F, routes, up=True, table=False)
 
 
 def test_residual_on_192_row_tiles():
