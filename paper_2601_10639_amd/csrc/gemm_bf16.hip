@@ -273,9 +273,10 @@ struct Tiling {
 typedef Tiling<4, 4, 2, 2, 0, 0> Tile256;
 typedef Tiling<4, 2, 2, 2, 3, 4> Tile256x128;
 typedef Tiling<2, 2, 2, 2, 3, 4> Tile128;
-// 700 tokens of an 8192-wide gate product are 96 tiles of 256x256, 192 of 256x128, 384 of 128x128 and 256 of these.  A compute
-// unit is fed at 60 to 70 GB/s whatever the others do, so what counts is the bytes of the busiest one: 40 KB a K tile here
-// against 48 or 64 (gate 34.1 -> 30.7 us; down product in four slices 39.3 -> 33.4).
+// 700 tokens of an 8192-wide gate product are 96 tiles of 256x256, 192 of 256x128, 384 of 128x128 and 256 of these.  A whole product
+// keeps a compute unit at about 60 GB/s once all 256 load (40 KB a K tile in 0.69 us, the model's `full`; 0.33 us, 124 GB/s, with a
+// few), so in one full round the bytes of a tile count: 40 KB a K tile here against 48 on 192 units, or 32 in one and a half rounds
+// (gate 34.1 -> 30.7 us; down product in four slices 39.3 -> 33.4).
 typedef Tiling<3, 2, 2, 2, 3, 4> Tile192x128;
 
 template <class C, int LA, int LB, int EPI>
