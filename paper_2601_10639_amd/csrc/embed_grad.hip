@@ -450,9 +450,9 @@ template <> struct RowVec<true> {
 };
 template <> struct RowVec<false> {
   static constexpr int COLS = 4;
-  typedef float4 raw_t;
+  typedef __attribute__((ext_vector_type(4))) float raw_t;
   static __device__ __forceinline__ raw_t load(const void* base, int64_t row, int F, int col) {
-    return *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(base) + row * F + col);
+    return *reinterpret_cast<const raw_t*>(reinterpret_cast<const float*>(base) + row * F + col);
   }
   static __device__ __forceinline__ raw_t load_plain(const void* base, int64_t row, int F, int col) { return load(base, row, F, col); }
   static __device__ __forceinline__ void add(const raw_t& v, float (&acc)[4]) {
@@ -612,9 +612,10 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int32_t* __restr
 // at a time, then the groups of a wavefront in order, then the wavefronts: no term of 1024 meets more than 20 additions.
 // us in a graph, two launches / four wavefronts of one workgroup for the whole run / now:
 //                    bf16 1024 x 4096     bf16 256 x 8192      fp32 1024 x 2048     fp32 256 x 1024
-//   Zipf ids         11.6 / 11.7 / 7.9    11.3 / 5.0 / 5.0     12.6 / 7.5 / 6.8     12.0 / 3.4 / 3.3
-//   one id for half  12.0 / 25.1 / 7.1    11.2 / 15.5 / 6.0    12.7 / 15.7 / 6.2    12.1 / 6.1 / 4.0
-//   one id for all   10.5 / 58.5 / 8.1    10.4 / 27.8 / 6.0     8.3 / 40.3 / 8.4     8.0 / 10.0 / 5.1
+//   Zipf ids         11.6 / 11.7 / 7.6    11.3 / 5.0 / 4.8     12.6 / 7.5 / 6.5     12.0 / 3.4 / 3.0
+//   one id for half  12.0 / 25.1 / 6.9    11.2 / 15.5 / 5.8    12.7 / 15.7 / 5.9    12.1 / 6.1 / 4.0
+//   one id for all   10.6 / 58.5 / 8.2    10.4 / 27.8 / 6.4     8.7 / 40.3 / 9.1     8.0 / 10.0 / 5.1
+// (9.1: 1024 rows of 8 KB, of which the row groups read every 32nd, in the same memory channels; 900 rows 8.4 / - / 5.9.)
 // The relative error of fp32 unit normals, all of one id, 1024 rows: 1.20e-7 / 2.92e-7 / 1.04e-7.
 // (Row loads that bypass the caches, as the large batches' do: one id for all, bf16 1024 x 4096 15.5.)
 constexpr int ROUND = 16;        // rows a lane requests together
@@ -657,9 +658,9 @@ __global__ __launch_bounds__(256) void seg_runs_kernel(const void* __restrict__ 
   constexpr int COLS = RowVec<BF16>::COLS;
   __shared__ float red[256 * (COLS + 1)];   // a thread's sums, one float apart
   const int k = blockIdx.x;
-  const int j = seg_of[k], before = k > 0 ? seg_of[k - 1] : -1, far = k >= MAX_PARTS ? seg_of[k - MAX_PARTS] : -1;
-  if (far == j) return;
-  const int start = before == j ? seg_offsets[j] : k, n = seg_offsets[j + 1] - start;
+  const int j = seg_of[k], far = seg_of[max(k - MAX_PARTS, 0)];
+  if (k >= MAX_PARTS && far == j) return;
+  const int start = seg_offsets[j], n = seg_offsets[j + 1] - start;
   const int shift = n <= 4 * ROUND ? 0 : n <= 8 * ROUND ? 1 : n <= 16 * ROUND ? 2 : 3;
   // which part: another one in each slab, or the workgroups of all slabs would be on the XCDs of the first positions
   const int part = n <= ROUND ? k - start : (k - start - (int)blockIdx.y) & (MAX_PARTS - 1);
@@ -678,6 +679,8 @@ __global__ __launch_bounds__(256) void seg_runs_kernel(const void* __restrict__ 
 #pragma unroll
     for (int u = 0; u < ROUND; ++u)
       if (u < rows) data[u] = RowVec<BF16>::load_plain(dU, perm[start + r + u], F, colc);
+#pragma unroll
+    for (int u = 0; u < ROUND; ++u) asm("" : "+v"(data[u]));   // or additions move to the loads, and wait there for each by itself
 #pragma unroll
     for (int u = 0; u < ROUND; u += 4) add_quad<BF16>(data + u, rows - u, acc);
     if (n > ROUND) {
@@ -821,10 +824,10 @@ hipError_t stem_seg_reduce(stem_ctx* ctx, const EmbedScratch& ws, int is_bf16, c
                            const int32_t* seg_offsets, int64_t T, int F, float* dE_rows, hipStream_t s) {
   const int chunks = (int)((T + SEG_ROWS - 1) / SEG_ROWS);
   const int cols = is_bf16 ? 8 : 4;
-  // One launch up to 1024 positions, where it is no slower even with one id for all of them; what that costs beyond depends on the
-  // ids.  us in a graph, two launches / one, Zipf ids: fp32 128 x 256 11.2 / 2.8, 1000 x 1024 12.3 / 5.0, 2048 x 2048 13.4 / 10.1;
-  // bf16 130 x 8192 11.4 / 3.7, 500 x 8192 11.9 / 7.9, 1024 x 8192 13.6 / 11.9, 1999 x 8192 16.6 / 18.0.  One id for all: fp32
-  // 1024 x 2048 8.3 / 8.4, 2048 x 2048 9.8 / 14.7; bf16 1024 x 4096 10.5 / 8.1, 1999 x 8192 13.2 / 19.7.  Most workgroups end at
+  // One launch up to 1024 positions, where it is as fast even with one id for all of them; what that costs beyond depends on the
+  // ids.  us in a graph, two launches / one, Zipf ids: fp32 128 x 256 11.2 / 2.5, 1000 x 1024 12.3 / 4.8, 2048 x 2048 13.4 / 10.1;
+  // bf16 130 x 8192 11.4 / 3.6, 500 x 8192 11.9 / 7.5, 1024 x 8192 13.6 / 11.9, 1999 x 8192 16.6 / 18.0.  One id for all: fp32
+  // 1024 x 2048 8.7 / 9.1, 2048 x 2048 9.8 / 14.7; bf16 1024 x 4096 10.6 / 8.2, 1999 x 8192 13.2 / 19.7.  Most workgroups end at
   // once: 8192 of them at most.
   const int64_t run_slabs = (F + 64 * cols - 1) / (64 * cols);
   if (T <= 1024 && T * run_slabs <= 8192) {
