@@ -988,9 +988,10 @@ hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const
 // projection, 4096 tokens 225 / 211.  Over 260 layers (d_model 512 to 2048, 128 to 65536 tokens) the rule takes 0.895 of the
 // time that launches of their own take, with an up projection 0.862, and loses 1.1 % at worst.
 //
-// Half the slices are sums of twice the length: a gradient's distance from the exact sum of the same bf16 operands goes from
-// 4.1e-7 to 5.8e-7 of it (1024 x 4096, 16384 tokens; 1472 x 5568, never cut, has 8.3e-7 at 16768).  Its distance from the
-// layer's in 64 bits, 1.6587e-3 from the rounding of H or dG to bf16, is the same to six digits.
+// Fewer slices are sums of twice the length, or four times: a gradient's distance from the exact sum of the same bf16 operands
+// goes from 4.1e-7 to 5.8e-7 of it (1024 x 4096, 16384 tokens), from 3.7e-7 to 7.6e-7 (640 x 2496 with an up projection, 14279
+// tokens; 1472 x 5568, never cut, has 8.3e-7 at 16768).  Its distance from the layer's in 64 bits, 1.6587e-3 from the rounding of
+// H or dG to bf16, is the same to six digits.
 static bool plan_together(const GemmArgs* a, int n, size_t ws_bytes, GroupPlan* plan) {
   bool turned[3] = {}, alike = n == 2 || n == 3;
   double apart = 0;
