@@ -30,11 +30,13 @@
  *     stem_sync_status) reports as STEM_ERR_ID_RANGE; the results of the tokens with
  *     valid ids are unaffected.
  *   - The context owns only scratch memory (sort buffers, partial sums, the
- *     internal H and dG buffers, pinned staging, one side stream and its events),
+ *     internal H and dG buffers, pinned staging, events),
  *     all sized from max_tokens.  Memory is allocated by the set-up calls only:
  *     stem_create, stem_reserve, stem_set_prefetch_mode, stem_cache_init,
  *     stem_profile_enable.  No call that enqueues work allocates or frees.
  *     Calls on one context must not overlap in time (they share that scratch).
+ *   - The contexts of a device share one side stream, on which rows of host-resident
+ *     tables are copied; it lives as long as there is a context on the device.
  */
 #ifndef STEM_H
 #define STEM_H
@@ -233,14 +235,15 @@ stem_status stem_ffn_up_backward(stem_ctx* ctx, const void* dy, const void* x, c
 
 /* E_host [V,F] lives in pinned host memory (hipHostMalloc); ids_host [T] is host memory.
  * De-duplicates ids on the host (distinct ids ascending), copies row uniq[j] of E_host to
- * E_compact[j] (device, capacity `cap` rows) on the context's side stream (rows travel in
- * the order in which the tokens first use them), and writes
+ * E_compact[j] (device, capacity `cap` rows) on the device's side stream (rows travel in
+ * the order in which the tokens first use them, those of calls on several contexts one call's
+ * after another's, in the order of the calls), and writes
  * remap[i] = j with uniq[j] == ids[i] (device [T]) there too, so that
  *   stem_ffn_forward(E = E_compact, ids = remap, E_rows = *n_uniq_host, wait_event = *ready_event)
  * is the same layer.  *n_uniq_host (host) is valid on return; uniq_ids_host (host, may be
  * NULL, capacity cap) receives the distinct ids.  *ready_event is a hipEvent_t owned by
  * the context, recorded after the copies, valid until the next stem_prefetch_rows call.
- * The copies wait for nothing but this context's previous prefetch: a forward call that reads E_compact and remap
+ * The copies wait for nothing but earlier prefetches: a forward call that reads E_compact and remap
  * must have finished on the device (the host has waited for its stream, or for an event behind it) before the next
  * call writes the same buffers.  Calls that are to overlap each other, layers in a stack or batches in turn, take a
  * context, an E_compact and a remap each.

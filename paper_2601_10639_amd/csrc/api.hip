@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <thread>
 #include <vector>
 
@@ -56,6 +57,37 @@ stem_status enter(stem_ctx* c, int64_t T) {
   return STEM_OK;
 }
 
+// The stream on which the contexts of a device copy rows from host memory: one for all of them, made with the first context and
+// destroyed with the last.  The rows of calls that follow each other then cross the link one call's after another's, in the
+// order in which the forward passes wait for them, and one copy's workgroups are all that the copies keep from the GEMMs.  With
+// a stream per context the copies of three contexts shared the link, all of them late and on 48 compute units, and some of
+// these streams shared a hardware queue with the caller's, which runs copy and products one after the other.
+struct CopyStream { hipStream_t stream; int64_t users; };
+constexpr int MAX_DEVICES = 64;
+CopyStream g_copy[MAX_DEVICES];
+std::mutex g_copy_mutex;
+
+hipError_t copy_stream_get(int device, hipStream_t* out) {
+  if (device < 0 || device >= MAX_DEVICES) return hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lock(g_copy_mutex);
+  CopyStream& q = g_copy[device];
+  if (!q.stream) {
+    hipError_t e = hipStreamCreateWithFlags(&q.stream, hipStreamNonBlocking);
+    if (e != hipSuccess) { q.stream = nullptr; return e; }
+  }
+  ++q.users;
+  *out = q.stream;
+  return hipSuccess;
+}
+
+void copy_stream_put(int device) {   // the device is current and idle
+  std::lock_guard<std::mutex> lock(g_copy_mutex);
+  CopyStream& q = g_copy[device];
+  if (--q.users > 0) return;
+  (void)hipStreamDestroy(q.stream);
+  q.stream = nullptr;
+}
+
 template <typename T>
 hipError_t dmalloc(T** p, size_t n) {
   *p = nullptr;
@@ -87,8 +119,9 @@ void release(stem_ctx* c) {
   (void)hipFree(c->edit_idx_dev); (void)hipFree(c->edit_rep_dev);
   if (c->inst_pinned) (void)hipHostFree(c->inst_pinned);
   (void)hipFree(c->inst_dev);
-  if (c->side) (void)hipStreamDestroy(c->side);
+  if (c->side) copy_stream_put(c->device);
   if (c->ready) (void)hipEventDestroy(c->ready);
+  if (c->copied) (void)hipEventDestroy(c->copied);
   for (int i = 0; i < 2; ++i) if (c->pack_done[i]) (void)hipEventDestroy(c->pack_done[i]);
   if (c->prof_ev) {
     for (int i = 0; i < 2 * STEM_MAX_PROF_EVENTS; ++i) if (c->prof_ev[i]) (void)hipEventDestroy(c->prof_ev[i]);
@@ -227,12 +260,13 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->flag), 64, hipHostMallocDefault));
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->uniq_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->remap_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
-  ok(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+  ok(copy_stream_get(device, &c->side));
   if (e == hipSuccess && c->tickets) {
     ok(stem_fill_zero(c->tickets, STEM_TICKETS * 4, c->side));
     ok(hipStreamSynchronize(c->side));
   }
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
+  ok(hipEventCreateWithFlags(&c->copied, hipEventDisableTiming));
   for (int i = 0; i < 2; ++i) ok(hipEventCreateWithFlags(&c->pack_done[i], hipEventDisableTiming));
   c->slot = static_cast<int32_t*>(malloc((size_t)desc->vocab * 4));
   if (e != hipSuccess || !c->slot) {
@@ -696,7 +730,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
   const size_t row_bytes = (size_t)c->desc.d_ff * esize(c);
 
   // The pinned staging arrays are reused: wait until the previous prefetch's copies are done.
-  HIP_TRY(c, hipStreamSynchronize(c->side));
+  HIP_TRY(c, hipEventSynchronize(c->copied));
 
   // De-duplicate: mark, then walk the marked ids in ascending order.
   for (int64_t i = 0; i < T; ++i) {
@@ -798,6 +832,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
     if (nchunks > 1) { c->pf_chunks = nchunks; c->pf_T = T; c->pf_chunk_tokens = chunk_tokens; }
   }
   HIP_TRY(c, hipEventRecord(c->ready, c->side));
+  HIP_TRY(c, hipEventRecord(c->copied, c->side));
   *ready_event = c->ready;
   return STEM_OK;
 }
@@ -810,7 +845,7 @@ stem_status stem_cache_init(stem_ctx* c, int64_t n_slots) {
     return fail(c, STEM_ERR_SHAPE, "stem_cache_init: n_slots = %lld", (long long)n_slots);
   const int V = c->desc.vocab;
   HIP_TRY(c, hipSetDevice(c->device));
-  HIP_TRY(c, hipStreamSynchronize(c->side));
+  HIP_TRY(c, hipEventSynchronize(c->copied));
   free(c->cache_id_in_slot); free(c->cache_slot_of); free(c->cache_freq);
   c->cache_id_in_slot = nullptr; c->cache_slot_of = nullptr; c->cache_freq = nullptr;
   c->cache_slots = 0;
@@ -853,7 +888,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
   const int V = c->desc.vocab;
   const int64_t NS = c->cache_slots;
   const size_t row_bytes = (size_t)c->desc.d_ff * esize(c);
-  HIP_TRY(c, hipStreamSynchronize(c->side));   // pinned staging arrays are reused
+  HIP_TRY(c, hipEventSynchronize(c->copied));   // pinned staging arrays are reused
 
   for (int64_t i = 0; i < T; ++i)
     if ((uint32_t)ids_host[i] >= (uint32_t)V)
@@ -971,6 +1006,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
     HIP_TRY(c, stem_copy_rows_kernel(c, E_dev, c->inst_dev, c->inst_dev + c->max_tokens, n_inst, (int64_t)row_bytes,
                                      E_dev, c->side));
   }
+  HIP_TRY(c, hipEventRecord(c->copied, c->side));
   return STEM_OK;
 }
 

@@ -39,9 +39,10 @@ enum StemKernelId {
 #define STEM_MAX_PROF_EVENTS 8192
 #define STEM_PF_MAX_CHUNKS 16
 #define STEM_EDIT_MAX_TOKENS 64
-// 256x256 down-product tiles per chunk of a host-table batch: one round on the compute units that the row copies of two
-// contexts leave free (prefetch.hip).  65536 tokens of 2048 x 8192, ms, calls in turn on two contexts / by itself: 256 tiles
-// 4.88 / 4.89, 240 tiles 4.97 / 4.69, 224 tiles 4.60 / 4.70.
+// 256x256 down-product tiles per chunk of a host-table batch: one round on the compute units that a row copy leaves free, with
+// room to spare (prefetch.hip).  65536 tokens of 2048 x 8192, ms, calls in turn on two contexts / by itself: 256 tiles 4.88 / 4.89
+// with a copy stream per context, 240 tiles 4.97 / 4.69 and 4.13 / 4.59 with one for all, 224 tiles 4.60 / 4.70 and 4.11 / 4.64; 16384
+// tokens 240 tiles 1.42 / 1.74, 224 tiles 1.42 / 1.69; 1024 x 4096, 16384 tokens 0.652 / 0.870 and 0.648 / 0.843.
 #define STEM_PF_CHUNK_TILES 224
 
 struct stem_ctx {
@@ -66,8 +67,9 @@ struct stem_ctx {
   int32_t* flag;         // pinned host int, device-visible: sticky id-range flag
 
   // host-resident table mode
-  hipStream_t side;
-  hipEvent_t ready;
+  hipStream_t side;      // the device's copy stream, shared by its contexts
+  hipEvent_t ready;      // rows and remap of the last prefetch are there
+  hipEvent_t copied;     // and everything else the call has put on the side stream is done
   int32_t* slot;         // host [V], -1 = absent
   int32_t* uniq_pinned;  // pinned host [max_tokens]
   int32_t* remap_pinned; // pinned host [max_tokens]
