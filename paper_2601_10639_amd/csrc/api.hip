@@ -101,7 +101,7 @@ void release(stem_ctx* c) {
   (void)hipDeviceSynchronize();
   (void)hipFree(c->H_ws); (void)hipFree(c->dG_ws);
   (void)hipFree(c->splitk_ws);
-  (void)hipFree(c->tickets);
+  (void)hipFree(c->tickets); (void)hipFree(c->rounds);
   (void)hipFree(c->Up_ws);
   for (int i = 0; i < 2; ++i) { (void)hipFree(c->sort_keys[i]); (void)hipFree(c->sort_vals[i]); }
   (void)hipFree(c->sort_counts); (void)hipFree(c->seg_of); (void)hipFree(c->seg_part);
@@ -171,11 +171,13 @@ void stem_route_forward(int d, int F, int64_t T, int32_t* route) {
     int32_t* r = route + 4 * down;
     switch (forward_route(T, N, K, F)) {
       case ROUTE_DECODE: stem_route_decode((int)T, N, K, down ? EPI_BF16 : EPI_GATE, ws, r); break;
-      case ROUTE_FEW_ROW: r[0] = ROUTE_FEW_ROW; r[1] = 128; r[2] = 64; r[3] = down ? stem_gemm_skinny_ksplit((int)T, N, K) : 1; break;
+      case ROUTE_FEW_ROW: r[0] = ROUTE_FEW_ROW; r[1] = 128; r[2] = 64; r[3] = down ? stem_gemm_skinny_ksplit((int)T, N, K, (size_t)ws) : 1; break;
       default: stem_route_tiles((int)T, N, K, 1, down ? EPI_BF16 : EPI_GATE, ws, r);
     }
   }
 }
+
+void stem_exchange_polls(stem_ctx* c, int polls) { c->polls = polls; }
 
 int stem_route_weight_grads_apart(int d, int F, int64_t T, const void* dy, const void* H, const void* dx, const void* W_gate,
                                   const void* W_up, const void* dV, const float* dW_gate, const float* dW_up) {
@@ -245,6 +247,8 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
     c->splitk_bytes = (size_t)stem_route_splitk_bytes(desc->d_model, desc->d_ff, max_tokens);
     ok(hipMalloc(reinterpret_cast<void**>(&c->splitk_ws), c->splitk_bytes));
     ok(dmalloc(&c->tickets, STEM_TICKETS));
+    ok(dmalloc(&c->rounds, STEM_TICKETS));
+    c->polls = STEM_POLLS;
   }
   for (int i = 0; i < 2; ++i) {
     ok(dmalloc(&c->sort_keys[i], (size_t)max_tokens));
@@ -263,6 +267,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(copy_stream_get(device, &c->side));
   if (e == hipSuccess && c->tickets) {
     ok(stem_fill_zero(c->tickets, STEM_TICKETS * 4, c->side));
+    ok(stem_fill_zero(c->rounds, STEM_TICKETS * 8, c->side));
     ok(hipStreamSynchronize(c->side));
   }
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
@@ -355,6 +360,7 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     b.M = (int)T; b.N = d; b.K = F; b.C = y; b.flag = c->flag;
     b.residual = static_cast<const bf16_t*>(residual);
     b.ws = c->splitk_ws; b.ws_bytes = c->splitk_bytes; b.tickets = c->tickets;
+    b.rounds = c->rounds; b.polls = c->polls;
     const int down_epi = residual ? EPI_BF16_RES : EPI_BF16;
     if (!wait_event) {
       a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);
@@ -390,9 +396,7 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     if (down == ROUTE_DECODE) {
       HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_DOWN, EPI_BF16, b, s));
     } else if (down == ROUTE_FEW_ROW) {
-      b.ksplit = stem_gemm_skinny_ksplit(b.M, b.N, b.K);
-      if ((size_t)b.ksplit * b.M * b.N * 4 > c->splitk_bytes) b.ksplit = 1;
-      HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_DOWN, b.ksplit > 1 ? EPI_SPLITK : EPI_BF16, b, s));
+      HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_DOWN, EPI_BF16, b, s));
     } else {
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DOWN, OP_KC, OP_KC, down_epi, b, s));
     }

@@ -58,6 +58,8 @@ struct stem_ctx {
   float* splitk_ws;      // fp32 partial products of GEMMs whose K range is cut into slices
   size_t splitk_bytes;   // its size; no launch splits beyond it
   int32_t* tickets;      // [STEM_TICKETS] counters of finished K slices per output tile, zero between launches
+  unsigned long long* rounds; // [STEM_TICKETS] the same for the few-row kernel, which counts on from launch to launch
+  int polls;             // how often a workgroup of it looks for the other slices of its tile
   int32_t* sort_keys[2]; // [max_tokens]
   int32_t* sort_vals[2]; // [max_tokens]
   int32_t* sort_counts;  // [64 * waves]
@@ -133,7 +135,7 @@ enum GemmEpilogue {
   EPI_F32,      // C -> fp32 [M,N], optional +=
   EPI_GATE,     // G (optional) and H = SiLU(C) * E[ids[m], n], both bf16
   EPI_DH,       // dU = C * SiLU(G), dG = C * E[ids[m], n] * SiLU'(G), both bf16
-  EPI_SPLITK,   // few-row kernel only: fp32 partial products per k slice, summed into bf16 C
+  EPI_SPLITK,   // decode kernel only: EPI_BF16 of a product in K slices
   // dense SwiGLU (UP) and the additive variant (UPE): SiLU(C) is multiplied by Up or Up + E[ids]
   EPI_GATE_UP, EPI_GATE_UPE,
   EPI_DH_UP, EPI_DH_UPE,
@@ -164,11 +166,13 @@ struct GemmArgs {
   float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
   size_t ws_bytes; // capacity of ws
   int32_t* tickets; // decode kernel: the context's tickets; null = never split
+  unsigned long long* rounds; // few-row kernel: the context's rounds (null = never split) and polls
+  int polls;
   // Further products of the same K in the launch (weight gradients only, stem_weight_grads)
   struct { const bf16_t* A; const bf16_t* B; void* C; int M, N, lda, ldb; } more[2];
   int n_more;
   int64_t elems;   // outputs of all of the launch's products, filled in by the launcher
-  int ksplit;      // number of k slices (few-row kernel: EPI_SPLITK; large kernel: chosen by its launcher)
+  int ksplit;      // number of k slices, chosen by the launcher
   int kc_skip;     // set by the large kernel itself: elements a K slice starts after the operand's start
   int mt, nt;      // few-row and decode kernels: tile counts and exact float reciprocals, filled in by the launcher
   float inv_mt, inv_per_z;
@@ -197,6 +201,7 @@ void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* 
 void stem_route_forward(int d_model, int d_ff, int64_t T, int32_t* route);
 int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   // a context's room for K slices
 int stem_route_sort(int64_t T, int V);   // SortRoute
+void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
 }
 enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS };
 
@@ -211,12 +216,13 @@ bool stem_gemm_skinny_fits(int M, int F);
 hipError_t stem_splitk_reduce(stem_ctx* ctx, const float* ws, int ksplit, int64_t total, const bf16_t* residual, void* out,
                               hipStream_t s);
 // k slices that bring the launch to about one workgroup per compute unit (1 = no split)
-int stem_gemm_skinny_ksplit(int M, int N, int K);
-// epi: EPI_BF16, EPI_GATE, or EPI_SPLITK (a.ksplit slices through a.ws, then summed into a.C)
+int stem_gemm_skinny_ksplit(int M, int N, int K, size_t ws_bytes);
+// epi: EPI_BF16 (+ residual; split along K through a.ws and a.rounds) or EPI_GATE
 hipError_t stem_gemm_skinny_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s);
 
 // ---- decode-sized bf16 GEMM (gemm_decode_bf16.hip): both operands K-contiguous --------------------
 #define STEM_TICKETS 256
+#define STEM_POLLS 2000   // 1 to 2 ms: the slices of a tile are some us apart unless other streams hold the compute units
 bool stem_gemm_decode_fits(int M, int N, int K);
 // epi: EPI_BF16 (+ residual; split along K through a.ws and a.tickets where that pays) or EPI_GATE
 hipError_t stem_gemm_decode_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s);

@@ -1,0 +1,78 @@
+"""The few-row kernel's K slices: each workgroup of a tile finishes a share of its rows, or leaves it to the last to arrive."""
+import pytest
+import torch
+
+from oracle import stem_oracle as O
+from paper_2601_10639_amd import inputs, stemlib as L
+from tests import harness as Hn
+
+DEV = "cuda:0"
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d,F,slices", [
+    (129, 1408, 2112, 4),     # a second token tile with one row: three of its shares are empty; 33 K tiles
+    (256, 2048, 8192, 4),     # 256 workgroups
+    (250, 1536, 5120, 4),
+    (385, 1344, 2112, 2),     # a last token tile with one row, 33 K tiles in slices of 16 and 17
+    (512, 1024, 2624, 4),
+    (40, 4160, 2112, 2),      # one token tile, a third full
+])
+def test_shares_waited_for_and_left_behind(T, d, F, slices):
+    assert Hn.route_forward(T, d, F)[1] == (Hn.FEW_ROW, 128, 64, slices)
+    V = 300
+    s = inputs.StemShape("slice-shares", d, F, V, 1, T, "bf16")
+    inp = inputs.layer_inputs(s, seed=81, device=DEV, tokens=T)
+    ctx = Hn.make_ctx(s, T)
+    a = (ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"])
+    y, yr = torch.empty_like(inp["x"]), torch.empty_like(inp["x"])
+    L.stem_ffn_forward(*a, y)
+    L.stem_ffn_forward_residual(*a, inp["x"], yr)
+    L.stem_sync_status(ctx)
+    f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
+    yo, _ = O.ffn_forward(f64["x"], inp["ids"].cpu().numpy(), f64["W_gate"], f64["W_down"], f64["E"])
+    assert Hn.max_rel(y.float().cpu(), yo) <= Hn.TOL["bf16"]
+    assert Hn.max_rel(yr.float().cpu(), f64["x"] + yo) <= Hn.TOL["bf16"]
+    # The same bits whoever adds a share, and whatever the launches before: nobody waits, one look, some, as in use.
+    for polls in (0, 1, 3, 0, 2000, 0, 2000):
+        L.lib().stem_exchange_polls(ctx.handle, polls)
+        for _ in range(4):
+            out, xr = torch.empty_like(y), inp["x"].clone()
+            L.stem_ffn_forward(*a, out)
+            L.stem_ffn_forward_residual(ctx, xr, *a[2:], xr, xr)    # in place: a row added twice would show
+            assert torch.equal(out, y) and torch.equal(xr, yr)
+    ctx.close()
+
+
+def test_slices_of_products_of_several_sizes_count_on_one_word():
+    """Calls of few and many tokens on one context use the same words with two and with four slices."""
+    d, F, V = 1408, 2112, 300
+    s = inputs.StemShape("slice-words", d, F, V, 1, 512, "bf16")
+    inp = inputs.layer_inputs(s, seed=82, device=DEV, tokens=512)
+    ctx = Hn.make_ctx(s, 512)
+    sizes = (129, 512, 200, 385, 256)
+    assert {Hn.route_forward(T, d, F)[1][3] for T in sizes} == {2, 4}
+
+    def forward(T):
+        y = torch.empty(T, d, dtype=torch.bfloat16, device=DEV)
+        L.stem_ffn_forward(ctx, inp["x"][:T], inp["ids"][:T], inp["W_gate"], inp["W_down"], inp["E"], y)
+        return y
+
+    first = {T: forward(T) for T in sizes}
+    for T in sizes[::-1] + sizes:
+        assert torch.equal(forward(T), first[T])
+    graph, ys = torch.cuda.CUDAGraph(), {}
+    with torch.cuda.graph(graph):
+        for T in sizes:
+            ys[T] = torch.empty(T, d, dtype=torch.bfloat16, device=DEV)
+            L.stem_ffn_forward(ctx, inp["x"][:T], inp["ids"][:T], inp["W_gate"], inp["W_down"], inp["E"], ys[T],
+                               stream=torch.cuda.current_stream())
+    for _ in range(4):
+        graph.replay()
+        torch.cuda.synchronize()
+        for T in sizes:
+            assert torch.equal(ys[T], first[T])
+            ys[T].zero_()
+        forward(200)
+    ctx.close()
