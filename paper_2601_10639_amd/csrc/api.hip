@@ -364,6 +364,7 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     const int down_epi = residual ? EPI_BF16_RES : EPI_BF16;
     if (!wait_event) {
       a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);
+      a.next = static_cast<const bf16_t*>(W_down); a.next_bytes = stem_touch_bytes((int)T, d, F);
       if (gate == ROUTE_DECODE) HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
       else if (gate == ROUTE_FEW_ROW) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
       else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE, OP_KC, OP_KC, EPI_GATE, a, s));

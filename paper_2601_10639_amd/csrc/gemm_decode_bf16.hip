@@ -197,6 +197,15 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
       if (d < nw) request(d);
     if (EPI == EPI_GATE) load_rows();
   }
+  // lines past the end are empty loads, lines that a small grid does not come to are left out
+  constexpr bool TOUCH = EPI == EPI_GATE && FA == 4;   // stem_touch_bytes: not for a few tokens
+  uint32_t touched[4] = {};
+  if (TOUCH && p.next_bytes) {
+    const rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.next), 0, p.next_bytes, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      touched[i] = __builtin_amdgcn_raw_buffer_load_b32(rn, ((i * gridDim.x + blockIdx.x) * blockDim.x + tid) * 128, 0, 0);
+  }
   int slot = 0;
   for (int i = 0; i < nw; ++i) {
     wait_all_but<LOADS, D - 1>(nw - 1 - i);
@@ -223,6 +232,11 @@ __global__ __launch_bounds__(64 * S::W) void gemm_decode_kernel(GemmArgs p) {
     slot = slot + 1 == D ? 0 : slot + 1;
   }
   asm volatile("s_barrier" ::: "memory");            // nothing lands in LDS any more: every K tile has been waited for
+
+  if (TOUCH) {   // the touching loads end here
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" ::"v"(touched[i]));
+  }
 
   // ---- sum of the wavefronts' tiles: a lane holds, for token fr of each fragment, columns 4 fg .. 4 fg + 3 ----
   float* const red = reinterpret_cast<float*>(smem);

@@ -191,6 +191,14 @@ __global__ __launch_bounds__(512) void gemm_skinny_kernel(GemmArgs p) {
       ev[it] = *reinterpret_cast<const uint2*>(p.E + (size_t)id * p.N + n_ld);
     }
   }
+  // stem_touch_bytes; lines past the end are empty loads, lines that a small grid does not come to are left out
+  uint32_t touched[3] = {};
+  if (EPI == EPI_GATE && p.next_bytes) {
+    const rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.next), 0, p.next_bytes, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      touched[i] = __builtin_amdgcn_raw_buffer_load_b32(rn, ((i * gridDim.x + blockIdx.x) * blockDim.x + tid) * 128, 0, 0);
+  }
   commit(ring[0], 0);
   request(ring[0]);
   __syncthreads();
@@ -220,6 +228,10 @@ __global__ __launch_bounds__(512) void gemm_skinny_kernel(GemmArgs p) {
 #pragma unroll
   for (int u = 0; u < DEPTH - 1; ++u)
     if (t + u < nk) iteration(ring[(u + 1) % DEPTH], u & 1);
+  if (EPI == EPI_GATE) {   // the touching loads end here
+#pragma unroll
+    for (int i = 0; i < 3; ++i) asm volatile("" ::"v"(touched[i]));
+  }
   __syncthreads();   // nobody reads a stage any more
 
   // ---- accumulators -> LDS: quarter kq, row, 64 fp32 columns ------------------------------------

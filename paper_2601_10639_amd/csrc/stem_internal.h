@@ -162,6 +162,8 @@ struct GemmArgs {
   const bf16_t* inG; // EPI_DH
   bf16_t* outdU;   // EPI_DH
   bf16_t* outdG;   // EPI_DH
+  const bf16_t* next; // EPI_GATE in the decode and few-row kernels: the weights of the product behind it, and how many of
+  int next_bytes;     // their bytes to bring closer meanwhile (stem_touch_bytes)
   int32_t* flag;
   float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
   size_t ws_bytes; // capacity of ws
@@ -204,6 +206,19 @@ int stem_route_sort(int64_t T, int V);   // SortRoute
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
 }
 enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS };
+
+// Bytes of W_down that the gate product of a decode-sized call touches, a dword per 128-byte line behind its first K tiles, so that
+// the down product finds them in the memory-side cache: all or none.  L2 serves hits and misses in turn, so what the touches cost
+// the gate product is what they save the down product in misses, and they pay where that one waits for its misses besides: from
+// 112 tokens (below, the gate product waits for them itself) and 8 MB of weights (below, the launches are latency) to 16 MB, or 34
+// up to 128 tokens, where the down product is the decode kernel's (above, the gate product is bound by L2).  Layer forward, us,
+// without / with: 1024 x 4096, 112 tokens 16.9 / 16.7, 192 tokens 22.4 / 20.7, 384 tokens 27.7 / 26.0; 1280 x 5120, 128 tokens 28.0 /
+// 25.3, 450 tokens 39.6 / 39.4; 1536 x 5120, 384 tokens 41.2 / 37.4; 2048 x 8192, 128 tokens 35.3 / 34.3; against 1024 x 4096, 24
+// tokens 12.4 / 13.4; 896 x 3584, 128 tokens 15.0 / 15.6; 2048 x 8192, 192 tokens 37.7 / 40.0; 1792 x 7168, 192 tokens 34.4 / 36.0.
+inline int stem_touch_bytes(int M, int d, int F) {
+  const int64_t w = (int64_t)d * F * 2;
+  return M >= 112 && w >= 7900000 && w <= (M <= 128 ? 34 : 16) * 1000000ll ? (int)w : 0;
+}
 
 // ---- few-row bf16 GEMM (gemm_skinny_bf16.hip): both operands K-contiguous, K % 64 == 0 --------
 // 128x64 tiles; used when M is small enough that larger tiles would leave most of the chip idle: up to 256 rows, and up

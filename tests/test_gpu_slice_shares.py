@@ -76,3 +76,24 @@ def test_slices_of_products_of_several_sizes_count_on_one_word():
             ys[T].zero_()
         forward(200)
     ctx.close()
+
+
+@pytest.mark.parametrize("T,d,F", [
+    (112, 1024, 3904),        # the fewest tokens, 7.99 MB of weights
+    (128, 2048, 8192),        # all lines of the largest, four by each thread
+    (129, 1536, 5184),        # just below the most from 129 tokens on
+    (384, 1536, 5120),        # few-row gate product, whose grid does not come to all lines
+])
+def test_gate_product_that_touches_the_down_products_weights(T, d, F):
+    V = 300
+    s = inputs.StemShape("touch", d, F, V, 1, T, "bf16")
+    inp = inputs.layer_inputs(s, seed=83, device=DEV, tokens=T)
+    ctx = Hn.make_ctx(s, T)
+    y, G, H = (torch.empty(T, n, dtype=torch.bfloat16, device=DEV) for n in (d, F, F))
+    L.stem_ffn_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"], y, G, H)
+    L.stem_sync_status(ctx)
+    f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
+    yo, fw = O.ffn_forward(f64["x"], inp["ids"].cpu().numpy(), f64["W_gate"], f64["W_down"], f64["E"])
+    for got, want in ((y, yo), (G, fw["g"]), (H, fw["h"])):
+        assert Hn.max_rel(got.float().cpu(), want) <= Hn.TOL["bf16"]
+    ctx.close()
