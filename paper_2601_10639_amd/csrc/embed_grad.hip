@@ -2,6 +2,8 @@
 // stable sort of (token id, position) by radix passes (in LDS, as merged runs, or digit by digit), distinct ids with run offsets, and a
 // fixed-order segmented sum of the per-token row gradients.  Integer results are unique,
 // floating sums use one fixed association, so every run gives the same bits.
+#include <algorithm>
+
 #include "stem_internal.h"
 
 namespace {
@@ -353,6 +355,89 @@ __global__ __launch_bounds__(1024) void sort_lds_kernel(const int32_t* __restric
       seg_of[k] = run;
     }
   }
+}
+
+// ---- up to 4096 ids: ranks by counting ----------------------------------------------------------------
+// One workgroup's passes are a chain of barriers, and it has one compute unit of the chip.  Here each workgroup places 8 or 16 ids and
+// looks at all of them: an id's place is the number of smaller (id, position) keys, counted by ballots, 64 keys a compare; where its run
+// begins, the number of keys below (id, 0); the number of its run, the distinct ids below it, from a bitmap of the ids in LDS and its
+// prefix sums.  Nothing passes between workgroups, so one launch does it all.  What bounds it is the launch, the id loads and
+// five barriers, from some 2000 ids on the scalar unit, which counts each compare's bits.  us in a graph, before (one workgroup's passes,
+// beyond 4096 ids runs and their merge) / this, Zipf ids: 128 ids 5.8 / 4.1, 1000 7.5 / 4.4, 1999 12.6 / 5.3, 4096 13.4 / 7.6, 8192
+// 22.4 / 15.7; one id for all: 4096 13.2 / 7.8.  (16 ids a workgroup up to 2048: 1000 ids 4.9, 1999 6.1; 32: 6.0 and 7.7.)
+constexpr int RANK_WORDS = 8192;                 // 32 KB of bitmap: vocabularies up to 2^18
+constexpr int RANK_MAX = 8192;                   // ids
+template <int CHUNKS, int OWN>                   // T <= CHUNKS * 1024; ids a workgroup places, at most a wavefront's lanes
+__global__ __launch_bounds__(1024) void sort_ranks_kernel(const int32_t* __restrict__ ids, int T, int V, int pos_bits,
+                                                          int32_t* __restrict__ sorted_ids, int32_t* __restrict__ perm,
+                                                          int32_t* __restrict__ uniq_ids, int32_t* __restrict__ seg_offsets,
+                                                          int32_t* __restrict__ n_uniq, int32_t* __restrict__ seg_of, int32_t* flag) {
+  constexpr int WORDS = RANK_WORDS / 1024;       // per thread
+  __shared__ __attribute__((aligned(16))) uint32_t bitmap[RANK_WORDS];
+  __shared__ int pre[1024];                      // ids set before a thread's words
+  __shared__ int counts[SORT_WAVES][OWN];
+  __shared__ int wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i0 = blockIdx.x * OWN, own_i = min(i0 + (lane & (OWN - 1)), T - 1);
+  int kv[CHUNKS], own_id = ids[own_i];
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) kv[c] = tid + 1024 * c < T ? ids[tid + 1024 * c] : 0;
+  for (int w = tid; w < (V + 31) / 32; w += 1024) bitmap[w] = 0;
+  __syncthreads();
+  auto clamped = [&](int id) { return (unsigned)id < (unsigned)V ? id : id < 0 ? 0 : V - 1; };
+  own_id = clamped(own_id);
+  uint32_t key[CHUNKS];
+  bool bad = false;
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    const int i = tid + 1024 * c, id = clamped(kv[c]);
+    key[c] = 0xffffffffu;                        // beyond the batch: smaller than no key
+    if (i < T) {
+      bad |= id != kv[c];
+      key[c] = ((uint32_t)id << pos_bits) | (uint32_t)i;
+      // (a look first: a frequent id would queue all its lanes at one word)
+      if (!(bitmap[id >> 5] >> (id & 31) & 1u)) atomicOr(&bitmap[id >> 5], 1u << (id & 31));
+    }
+  }
+  if (bad) *flag = 1;
+  const uint32_t own_key = ((uint32_t)own_id << pos_bits) | (uint32_t)own_i;
+  int mine = 0;
+#pragma unroll 2                                 // (unrolled whole, the compiler keeps all counts to the end, and spills)
+  for (int q = 0; q < OWN; ++q) {
+    const uint32_t k = __builtin_amdgcn_readlane(own_key, q), k_id = k >> pos_bits << pos_bits;
+    int below = 0, start = 0;
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+      below += __popcll(__ballot(key[c] < k));
+      start += __popcll(__ballot(key[c] < k_id));
+    }
+    mine = lane == q ? below | start << 16 : mine;   // sums up to 4096 each
+  }
+  if (lane < OWN) counts[wave][lane] = mine;
+  __syncthreads();                               // counts, and all ids are in the bitmap
+  int set = 0, distinct;
+  if (tid * WORDS * 32 < V)
+#pragma unroll
+    for (int x = 0; x < WORDS; ++x)
+      if ((tid * WORDS + x) * 32 < V) set += __popc(bitmap[tid * WORDS + x]);
+  pre[tid] = block_exclusive(set, wsum, lane, wave, &distinct);
+  __syncthreads();
+  if (blockIdx.x == 0 && tid == 0) {
+    seg_offsets[distinct] = T;
+    *n_uniq = distinct;
+  }
+  if (tid >= OWN || i0 + tid >= T) return;
+  int sum = 0;
+#pragma unroll
+  for (int w = 0; w < SORT_WAVES; ++w) sum += counts[w][tid];
+  const int place = sum & 0xffff, start = sum >> 16;
+  const int word = own_id >> 5, first = word & ~(WORDS - 1);
+  int run = pre[word / WORDS] + __popc(bitmap[word] & ((1u << (own_id & 31)) - 1u));
+  for (int x = first; x < word; ++x) run += __popc(bitmap[x]);
+  sorted_ids[place] = own_id;
+  perm[place] = own_i;
+  seg_of[place] = run;
+  if (place == start) { uniq_ids[run] = own_id; seg_offsets[run] = start; }
 }
 
 // ---- larger batches: merge of the sorted runs by rank, then distinct ids and run index ---------------
@@ -736,7 +821,10 @@ int64_t stem_sort_count_entries(int64_t max_tokens) {
   return tiles * SORT_WAVES * RADIX;
 }
 
-// One workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 22 in a graph).  Then runs of
+// One launch up to 8192 ids, of workgroups that count ranks, while the vocabulary's bitmap is at most 32 KB (2^18 ids); beyond that
+// vocabulary, or with an output that lies over the ids, which those workgroups read while others write, one workgroup up to
+// 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 22 in a graph).  Counting is quadratic: 8192 ids
+// 15.7 us against 22.3 on merged runs, 16384 ids 45 against 24.  Then runs of
 // 1024, while their number is one group of the merge's searches, and runs of 4096, us in a graph: 6000 ids 22 / 29, 16384
 // ids 25 / 32 (one workgroup 43, the digit passes below 140), 32768 ids 36 / 34, 65536 ids 58 / 38 (digit passes 182).
 // The digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
@@ -744,18 +832,41 @@ int64_t stem_sort_count_entries(int64_t max_tokens) {
 int stem_route_sort(int64_t T, int V) {
   const int vbits = bits_for(V);
   if (T <= 4096 && vbits + bits_for((int)T) <= 32) return T <= 1024 ? SORT_ONE_1024 : SORT_ONE_4096;
+  if (T <= RANK_MAX && V <= RANK_WORDS * 32) return SORT_RANKS_8192;
   const bool short_runs = T <= MERGE_WAYS * 1024;
   if (T <= 262144 && vbits + (short_runs ? 10 : 12) <= 32) return short_runs ? SORT_RUNS_1024 : SORT_RUNS_4096;
   return SORT_DIGITS;
+}
+
+// whether no output of the sort lies over the ids
+static bool ids_apart(const int32_t* ids, int64_t T, int V, const void* sorted_ids, const void* perm, const void* uniq_ids,
+                      const void* seg_offsets, const void* n_uniq, const void* seg_of) {
+  const int64_t cap = std::min<int64_t>(T, V);
+  const struct { const void* at; int64_t n; } out[] = {{sorted_ids, T}, {perm, T}, {uniq_ids, cap}, {seg_offsets, cap + 1}, {n_uniq, 1}, {seg_of, T}};
+  const uintptr_t a = reinterpret_cast<uintptr_t>(ids);
+  for (const auto& o : out) {
+    const uintptr_t b = reinterpret_cast<uintptr_t>(o.at);
+    if (a < b + (size_t)o.n * 4 && b < a + (size_t)T * 4) return false;
+  }
+  return true;
 }
 
 hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t* ids, int64_t T, int V,
                             int32_t* sorted_ids, int32_t* perm, int32_t* uniq_ids, int32_t* seg_offsets,
                             int32_t* n_uniq, hipStream_t s) {
   const int passes = (bits_for(V) + RADIX_BITS - 1) / RADIX_BITS;
+  const bool ranked = T <= RANK_MAX && V <= RANK_WORDS * 32;
   const int route = stem_route_sort(T, V);
+  const int pos_bits = bits_for((int)std::min<int64_t>(T, 1 << 30));
+  if (ranked && ids_apart(ids, T, V, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of)) {
+    ProfScope ps(ctx, K_SORT_FUSED, s);
+    const int own = T <= 2048 ? 8 : 16;
+    auto* const kernel = T <= 1024 ? sort_ranks_kernel<1, 8> : T <= 2048 ? sort_ranks_kernel<2, 8> : T <= 4096 ? sort_ranks_kernel<4, 16> : sort_ranks_kernel<8, 16>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((T + own - 1) / own)), dim3(1024), 0, s, ids, (int)T, V, pos_bits, sorted_ids, perm,
+                       uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
+    return hipGetLastError();
+  }
   if (route == SORT_ONE_1024 || route == SORT_ONE_4096) {
-    const int pos_bits = bits_for((int)T);
     ProfScope ps(ctx, K_SORT_FUSED, s);
     if (route == SORT_ONE_1024)
       hipLaunchKernelGGL((sort_lds_kernel<1, false>), dim3(1), dim3(1024), 0, s, ids, (int)T, V, pos_bits, passes,
@@ -765,8 +876,8 @@ hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t
                          sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
     return hipGetLastError();
   }
-  if (route == SORT_RUNS_1024 || route == SORT_RUNS_4096) {
-    const int items = route == SORT_RUNS_1024 ? 1 : 4, run_bits = items == 1 ? 10 : 12;
+  if (route == SORT_RUNS_1024 || route == SORT_RUNS_4096 || route == SORT_RANKS_8192) {   // (the last: outputs over the ids)
+    const int items = route == SORT_RUNS_4096 ? 4 : 1, run_bits = items == 1 ? 10 : 12;
     const int R = items * 1024, runs = (int)((T + R - 1) / R);
     {
       ProfScope ps(ctx, K_SORT_FUSED, s);

@@ -205,7 +205,8 @@ int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   //
 int stem_route_sort(int64_t T, int V);   // SortRoute
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
 }
-enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS };
+// SORT_ONE_*: one launch, ranks by counting or, for vocabularies beyond 2^18, the passes of one workgroup; SORT_RANKS_8192: ranks by counting
+enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS, SORT_RANKS_8192 };
 
 // Bytes of W_down that the gate product of a decode-sized call touches, a dword per 128-byte line behind its first K tiles, so that
 // the down product finds them in the memory-side cache: all or none.  L2 serves hits and misses in turn, so what the touches cost
