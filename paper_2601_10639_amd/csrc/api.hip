@@ -570,13 +570,24 @@ stem_status stem_ffn_up_forward(stem_ctx* c, const void* x, const int32_t* ids, 
   u.A = static_cast<const bf16_t*>(x); u.lda = d;
   u.B = static_cast<const bf16_t*>(W_up); u.ldb = d;
   u.M = (int)T; u.N = F; u.K = d; u.C = Up; u.flag = c->flag; u.ws = c->splitk_ws; u.ws_bytes = c->splitk_bytes;
-  HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_UP, OP_KC, OP_KC, EPI_BF16, u, s));
+  // One launch for both products, unless the buffers lie so that it matters which is first: G and H are stored while W_up is read and
+  // beside Up, and Up while E and the ids are read.  (G or H in Up's place is fine: a lane stores Up first.)
+  const size_t TF = (size_t)T * F * 2, Fd = (size_t)F * d * 2;
+  auto over = [&](const void* p, const void* q) { return p != q && overlap(p, TF, q, TF); };
+  const bool together = !overlap(save_G, TF, W_up, Fd) && !overlap(H, TF, W_up, Fd) &&
+                        !over(save_G, Up) && !over(H, Up) && !(E && (overlap(Up, TF, E, (size_t)E_rows * F * 2) || overlap(Up, TF, ids, (size_t)T * 4)));
+  if (!together) HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_UP, OP_KC, OP_KC, EPI_BF16, u, s));
   GemmArgs a = u;    // G = x W_gate^T;  H = SiLU(G) * (Up [+ E[ids]])
   a.B = static_cast<const bf16_t*>(W_gate); a.C = nullptr;
   a.ids = ids; a.E = static_cast<const bf16_t*>(E); a.E_rows = (int)E_rows;
   a.inUp = static_cast<const bf16_t*>(Up);
   a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);
-  HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE, OP_KC, OP_KC, E ? EPI_GATE_UPE : EPI_GATE_UP, a, s));
+  if (together) {
+    a.Bup = static_cast<const bf16_t*>(W_up); a.outUp = static_cast<bf16_t*>(Up);
+    HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE, OP_KC, OP_KC, E ? EPI_GATE_DUALE : EPI_GATE_DUAL, a, s));
+  } else {
+    HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE, OP_KC, OP_KC, E ? EPI_GATE_UPE : EPI_GATE_UP, a, s));
+  }
   GemmArgs b = {};   // y = H W_down^T
   b.A = static_cast<const bf16_t*>(H); b.lda = F;
   b.B = static_cast<const bf16_t*>(W_down); b.ldb = F;

@@ -297,7 +297,16 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   const bool load_wave = C::LW && wave_id >= C::WAVES;
   const int wave = load_wave ? wave_id - C::WAVES : wave_id;
   const int wm = wave / C::WN, wn = wave % C::WN;
-  int ntm = (p.M + C::TM - 1) / C::TM, ntn = (p.N + C::TN - 1) / C::TN;
+  // Gate and up product in one: half of a wavefront's columns are C's, the other half Up's, so that the tile's B rows are, 32 * NJ / 2 at
+  // a time, of W_gate and of W_up in turn: what loader w brings (LOADERS is 4, WN 2) is of one of them.  As two launches the second
+  // read Up back in an epilogue under which nothing else runs, all tiles at once, and small batches paid a launch, a prologue and a
+  // split product's sum more.  Forward call, us, two launches / one, additive and dense layer: 1024 x 4096, 300 tokens 36.1 / 26.2 and
+  // 34.6 / 25.9, 4096 tokens 123.2 / 116.5 and 107.8 / 102.2, 16384 tokens 425 / 398 and 401 / 378; 1216 x 3328, 5000 tokens 167 / 144 and
+  // 161 / 141; 2048 x 8192, 700 tokens 95.2 / 91.3 and 93.5 / 89.3, 16384 tokens 1352 / 1319 and 1308 / 1286.  The tiling is choose_plan's
+  // for a product of twice the width, and the best of the four or within 3 % of it at 16 layers.
+  constexpr bool DUAL = EPI == EPI_GATE_DUAL || EPI == EPI_GATE_DUALE;
+  constexpr int OUT_TN = DUAL ? C::TN / 2 : C::TN;   // columns of the output per tile
+  int ntm = (p.M + C::TM - 1) / C::TM, ntn = (p.N + OUT_TN - 1) / OUT_TN;
   constexpr int BAND = (EPI == EPI_DH || EPI == EPI_DH_UP || EPI == EPI_DH_UPE) ? 7 : 4;   // see tile_at
   int tm, tn;
   Place at;
@@ -344,7 +353,8 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
     p.accumulate = 0;
   }
   tile_at(BAND, at.in, ntm, ntn, tm, tn);
-  const int m0 = tm * C::TM, n0 = tn * C::TN;
+  const int m0 = tm * C::TM, n0 = tn * OUT_TN;
+  if (DUAL && (wave & 1)) p.B = p.Bup;
   // K rotation.  Workgroups on XCD x start their K loop x eighths of the way in and wrap around, so
   // the eight XCDs stream eight different stretches of the operands' rows at any moment instead of
   // the same one (measured: the down product, whose two operands have the same 16 KB row pitch, ran
@@ -374,7 +384,7 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   LoadAMC da;
   LoadBMC db;
   if (LA == OP_KC) ka.init(p.A, p.lda, p.M, m0, wave, lane, p.kc_skip); else da.init(p.A, p.lda, p.M, p.K, m0, wave, lane);
-  if (LB == OP_KC) kb_.init(p.B, p.ldb, p.N, n0, wave, lane, p.kc_skip); else db.init(p.B, p.ldb, p.N, p.K, n0, wave, lane);
+  if (LB == OP_KC) kb_.init(p.B, p.ldb, p.N, DUAL ? n0 - ((wave + 1) >> 1) * (LOADS_B * 8) : n0, wave, lane, p.kc_skip); else db.init(p.B, p.ldb, p.N, p.K, n0, wave, lane);
 
   // fragments: lane -> row (lane & 31) of a 32-row block, k half (lane >> 5) of a k-step
   const int frow = lane & 31, fk = lane >> 5;
@@ -397,7 +407,7 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   // registers by a lane permute: loading ids there would put a wait for the newest loads in front of
   // every block of table-row requests, and with it a wait for all the stores issued before them
   // (loads and stores return through one in-order counter), 3 to 4 us per block.
-  constexpr bool NEED_IDS = (EPI == EPI_GATE || EPI == EPI_DH || EPI == EPI_GATE_UPE || EPI == EPI_DH_UPE);
+  constexpr bool NEED_IDS = (EPI == EPI_GATE || EPI == EPI_DH || EPI == EPI_GATE_UPE || EPI == EPI_DH_UPE || EPI == EPI_GATE_DUALE);
   int row_id[(MI + 1) / 2] = {};
   if (NEED_IDS && !load_wave) {
 #pragma unroll
@@ -680,18 +690,19 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
 
   // ---- epilogue: per wavefront, 32 rows at a time through LDS ----------------------------
   constexpr int SROW = WSN * 4 + 16;           // staged row: fp32 values + 16 bytes of padding
-  constexpr int LPR = WSN / 8;                // lanes per row, 8 columns each
+  constexpr int OUTW = DUAL ? WSN / 2 : WSN;  // output columns of a wavefront
+  constexpr int LPR = OUTW / 8;               // lanes per row, 8 columns each
   constexpr int RPP = 64 / LPR;               // rows per pass of the wavefront
   constexpr int PASSES = 32 / RPP;
   char* stg = smem + wave * (32 * SROW);
   const int srow = lane / LPR;                // row within a pass
   const int scol = (lane & (LPR - 1)) * 8;    // first of this lane's 8 consecutive columns
-  const int n = n0 + wn * WSN + scol;
+  const int n = n0 + wn * OUTW + scol;
   const bool n_ok = n < p.N;
   const int n_ld = n_ok ? n : 0;              // in-bounds column for the prefetching loads
-  constexpr bool GATE_LIKE = (EPI == EPI_GATE || EPI == EPI_GATE_UP || EPI == EPI_GATE_UPE);
+  constexpr bool GATE_LIKE = (EPI == EPI_GATE || EPI == EPI_GATE_UP || EPI == EPI_GATE_UPE || DUAL);
   constexpr bool DH_LIKE = (EPI == EPI_DH || EPI == EPI_DH_UP || EPI == EPI_DH_UPE);
-  constexpr bool USE_E = (EPI == EPI_GATE || EPI == EPI_DH || EPI == EPI_GATE_UPE || EPI == EPI_DH_UPE);
+  constexpr bool USE_E = (EPI == EPI_GATE || EPI == EPI_DH || EPI == EPI_GATE_UPE || EPI == EPI_DH_UPE || EPI == EPI_GATE_DUALE);
   constexpr bool USE_UP = (EPI == EPI_GATE_UP || EPI == EPI_GATE_UPE || EPI == EPI_DH_UP || EPI == EPI_DH_UPE);
   constexpr bool FUSED = GATE_LIKE || DH_LIKE;
 
@@ -724,6 +735,7 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   auto out_rsrc = [&](void* ptr, int esize) {
     return __builtin_amdgcn_make_buffer_rsrc(ptr, 0, ptr ? (int)((int64_t)p.M * p.N * esize) : 0, 0x00020000);
   };
+  const rsrc_t r_up = out_rsrc(DUAL ? p.outUp : nullptr, 2);
   rsrc_t r0, r1;   // EPI_BF16 / EPI_F32: C;  gate-like: G (may be absent), H;  dH-like: dU, dG
   if (EPI == EPI_BF16) r0 = r1 = out_rsrc(p.C, 2);
   else if (EPI == EPI_BF16_RES) { r0 = out_rsrc(p.C, 2); r1 = out_rsrc(const_cast<bf16_t*>(p.residual), 2); }
@@ -750,12 +762,16 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    f32x4_t cv[PASSES][2];
+    f32x4_t cv[PASSES][2], cu[PASSES][2];
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
       const int r = pass * RPP + srow;
       cv[pass][0] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + scol * 4);
       cv[pass][1] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + scol * 4 + 16);
+      if (DUAL) {
+        cu[pass][0] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + (OUTW + scol) * 4);
+        cu[pass][1] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + (OUTW + scol) * 4 + 16);
+      }
     }
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
@@ -791,6 +807,15 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
         if (USE_UP) {
           float u[8];
           unpack8(uv[i & 1][pass], u);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) e[q] = USE_E ? e[q] + u[q] : u[q];
+        }
+        if (DUAL) {   // Up as it is stored, in front of G and H, which may lie over it
+          const f32x4_t u0 = cu[pass][0], u1 = cu[pass][1];
+          float u[8] = {u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]};
+          const uint4 up = pack8(u);
+          store16(r_up, o2, up);
+          unpack8(up, u);
 #pragma unroll
           for (int q = 0; q < 8; ++q) e[q] = USE_E ? e[q] + u[q] : u[q];
         }
@@ -897,7 +922,7 @@ int grid_of(const GemmArgs& a, int tm, int tn) {
 template <class C, int LA, int LB, int EPI>
 hipError_t launch_tiles(stem_ctx* ctx, int kid, const GemmArgs& a, hipStream_t s) {
   ProfScope ps(ctx, kid, s);
-  hipLaunchKernelGGL((gemm_bf16_kernel<C, LA, LB, EPI>), dim3(grid_of(a, C::TM, C::TN)), dim3((C::WAVES + C::LW) * 64), 0, s, a);
+  hipLaunchKernelGGL((gemm_bf16_kernel<C, LA, LB, EPI>), dim3(grid_of(a, C::TM, EPI == EPI_GATE_DUAL || EPI == EPI_GATE_DUALE ? C::TN / 2 : C::TN)), dim3((C::WAVES + C::LW) * 64), 0, s, a);
   return hipGetLastError();
 }
 
@@ -928,7 +953,8 @@ template <int LA, int LB, int EPI>
 hipError_t launch(stem_ctx* ctx, int kid, GemmArgs a, hipStream_t s) {
   constexpr bool PLAIN = (EPI == EPI_BF16 || EPI == EPI_BF16_RES), F32 = (EPI == EPI_F32);
   const size_t ws_bytes = a.ws && (int64_t)a.M * a.N % 4 == 0 && (!a.A2 || a.K2 == a.K) ? a.ws_bytes : 0;
-  const Plan plan = choose_plan(a.M, a.N, a.K, a.A2 ? 2 : 1, !PLAIN && !F32, F32, ws_bytes);
+  constexpr int WIDTH = EPI == EPI_GATE_DUAL || EPI == EPI_GATE_DUALE ? 2 : 1;
+  const Plan plan = choose_plan(a.M, a.N * WIDTH, a.K, a.A2 ? 2 : 1, !PLAIN && !F32, F32, ws_bytes);
   a.ksplit = plan.ksplit;
   a.elems = (int64_t)a.M * a.N;
   if constexpr (PLAIN || F32) {
@@ -966,6 +992,8 @@ hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const
     if (epi == EPI_GATE) return launch<OP_KC, OP_KC, EPI_GATE>(ctx, kid, a, s);
     if (epi == EPI_GATE_UP) return launch<OP_KC, OP_KC, EPI_GATE_UP>(ctx, kid, a, s);
     if (epi == EPI_GATE_UPE) return launch<OP_KC, OP_KC, EPI_GATE_UPE>(ctx, kid, a, s);
+    if (epi == EPI_GATE_DUAL) return launch<OP_KC, OP_KC, EPI_GATE_DUAL>(ctx, kid, a, s);
+    if (epi == EPI_GATE_DUALE) return launch<OP_KC, OP_KC, EPI_GATE_DUALE>(ctx, kid, a, s);
   } else if (la == OP_KC && lb == OP_MC) {  // activation gradients: the weight as stored, rows-contiguous
     if (epi == EPI_BF16) return launch<OP_KC, OP_MC, EPI_BF16>(ctx, kid, a, s);
     if (epi == EPI_DH) return launch<OP_KC, OP_MC, EPI_DH>(ctx, kid, a, s);

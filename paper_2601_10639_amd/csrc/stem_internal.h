@@ -139,6 +139,7 @@ enum GemmEpilogue {
   // dense SwiGLU (UP) and the additive variant (UPE): SiLU(C) is multiplied by Up or Up + E[ids]
   EPI_GATE_UP, EPI_GATE_UPE,
   EPI_DH_UP, EPI_DH_UPE,
+  EPI_GATE_DUAL, EPI_GATE_DUALE,  // the same with Up computed beside C, in the same launch
   EPI_BF16_RES  // C + residual -> bf16 [M,N] (decode chains: the layer's output joins the residual stream)
 };
 
@@ -156,6 +157,8 @@ struct GemmArgs {
   bf16_t* outG;    // EPI_GATE: may be null
   bf16_t* outH;    // EPI_GATE
   const bf16_t* inUp; // *_UP, *_UPE: the up projection x W_up^T, [M,N] bf16
+  const bf16_t* Bup; // *_DUAL*: W_up, as B
+  bf16_t* outUp;     // and its product
   const bf16_t* A2;  // optional second operand pair of a (KC,KC) product: C = A B^T + A2 B2^T
   const bf16_t* B2;
   int K2;
