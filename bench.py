@@ -282,7 +282,7 @@ def bench_layer(args, shape, dev, steps, warmup, peaks, detail):
         k = {"avg_ms": round(avg, 5), "launches": n}
         if name.startswith("gemm_"):
             # dx spans both projections; gemm_dw: the layer's weight gradients in one launch
-            fl = gemm_flop * ((2 if variant == "stem" else 3) if name == "gemm_dw" else 2 if (name == "gemm_dx" and variant != "stem") else 1)
+            fl = gemm_flop * ((2 if variant == "stem" else 3) if name == "gemm_dw" else 2 if (name in ("gemm_dx", "gemm_gate_fused") and variant != "stem") else 1)
             k["tflops"] = round(fl / (avg * 1e-3) / 1e12, 2)
             k["frac_mfma_peak"] = round(k["tflops"] / peak_tf, 4)
             if bf16:

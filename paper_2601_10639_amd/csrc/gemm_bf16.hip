@@ -735,7 +735,6 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   auto out_rsrc = [&](void* ptr, int esize) {
     return __builtin_amdgcn_make_buffer_rsrc(ptr, 0, ptr ? (int)((int64_t)p.M * p.N * esize) : 0, 0x00020000);
   };
-  const rsrc_t r_up = out_rsrc(DUAL ? p.outUp : nullptr, 2);
   rsrc_t r0, r1;   // EPI_BF16 / EPI_F32: C;  gate-like: G (may be absent), H;  dH-like: dU, dG
   if (EPI == EPI_BF16) r0 = r1 = out_rsrc(p.C, 2);
   else if (EPI == EPI_BF16_RES) { r0 = out_rsrc(p.C, 2); r1 = out_rsrc(const_cast<bf16_t*>(p.residual), 2); }
@@ -762,13 +761,14 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    f32x4_t cv[PASSES][2], cu[PASSES][2];
+    f32x4_t cv[PASSES][2];
+    f32x4_t cu[DUAL ? PASSES : 1][2];
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
       const int r = pass * RPP + srow;
       cv[pass][0] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + scol * 4);
       cv[pass][1] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + scol * 4 + 16);
-      if (DUAL) {
+      if constexpr (DUAL) {
         cu[pass][0] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + (OUTW + scol) * 4);
         cu[pass][1] = *reinterpret_cast<const f32x4_t*>(stg + r * SROW + (OUTW + scol) * 4 + 16);
       }
@@ -810,11 +810,11 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
 #pragma unroll
           for (int q = 0; q < 8; ++q) e[q] = USE_E ? e[q] + u[q] : u[q];
         }
-        if (DUAL) {   // Up as it is stored, in front of G and H, which may lie over it
+        if constexpr (DUAL) {   // Up as it is stored, in front of G and H, which may lie over it
           const f32x4_t u0 = cu[pass][0], u1 = cu[pass][1];
           float u[8] = {u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]};
           const uint4 up = pack8(u);
-          store16(r_up, o2, up);
+          store16(out_rsrc(p.outUp, 2), o2, up);
           unpack8(up, u);
 #pragma unroll
           for (int q = 0; q < 8; ++q) e[q] = USE_E ? e[q] + u[q] : u[q];

@@ -139,8 +139,8 @@ enum GemmEpilogue {
   // dense SwiGLU (UP) and the additive variant (UPE): SiLU(C) is multiplied by Up or Up + E[ids]
   EPI_GATE_UP, EPI_GATE_UPE,
   EPI_DH_UP, EPI_DH_UPE,
-  EPI_GATE_DUAL, EPI_GATE_DUALE,  // the same with Up computed beside C, in the same launch
-  EPI_BF16_RES  // C + residual -> bf16 [M,N] (decode chains: the layer's output joins the residual stream)
+  EPI_BF16_RES, // C + residual -> bf16 [M,N] (decode chains: the layer's output joins the residual stream)
+  EPI_GATE_DUAL, EPI_GATE_DUALE  // EPI_GATE_UP, EPI_GATE_UPE with Up computed beside C, in the same launch
 };
 
 struct GemmArgs {
@@ -157,22 +157,16 @@ struct GemmArgs {
   bf16_t* outG;    // EPI_GATE: may be null
   bf16_t* outH;    // EPI_GATE
   const bf16_t* inUp; // *_UP, *_UPE: the up projection x W_up^T, [M,N] bf16
-  const bf16_t* Bup; // *_DUAL*: W_up, as B
-  bf16_t* outUp;     // and its product
   const bf16_t* A2;  // optional second operand pair of a (KC,KC) product: C = A B^T + A2 B2^T
   const bf16_t* B2;
   int K2;
   const bf16_t* inG; // EPI_DH
   bf16_t* outdU;   // EPI_DH
   bf16_t* outdG;   // EPI_DH
-  const bf16_t* next; // EPI_GATE in the decode and few-row kernels: the weights of the product behind it, and how many of
-  int next_bytes;     // their bytes to bring closer meanwhile (stem_touch_bytes)
   int32_t* flag;
   float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
   size_t ws_bytes; // capacity of ws
   int32_t* tickets; // decode kernel: the context's tickets; null = never split
-  unsigned long long* rounds; // few-row kernel: the context's rounds (null = never split) and polls
-  int polls;
   // Further products of the same K in the launch (weight gradients only, stem_weight_grads)
   struct { const bf16_t* A; const bf16_t* B; void* C; int M, N, lda, ldb; } more[2];
   int n_more;
@@ -181,6 +175,12 @@ struct GemmArgs {
   int kc_skip;     // set by the large kernel itself: elements a K slice starts after the operand's start
   int mt, nt;      // few-row and decode kernels: tile counts and exact float reciprocals, filled in by the launcher
   float inv_mt, inv_per_z;
+  unsigned long long* rounds; // few-row kernel: the context's rounds (null = never split) and polls
+  int polls;
+  int next_bytes;     // EPI_GATE in the decode and few-row kernels: how many bytes of the weights of the product behind it to bring
+  const bf16_t* next; // closer meanwhile (stem_touch_bytes)
+  const bf16_t* Bup;  // *_DUAL*: W_up, as B
+  bf16_t* outUp;      // and its product
 };
 
 hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmArgs& a, hipStream_t s);
