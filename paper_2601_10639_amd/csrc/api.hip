@@ -101,7 +101,7 @@ void release(stem_ctx* c) {
   (void)hipDeviceSynchronize();
   (void)hipFree(c->H_ws); (void)hipFree(c->dG_ws);
   (void)hipFree(c->splitk_ws);
-  (void)hipFree(c->tickets); (void)hipFree(c->rounds);
+  (void)hipFree(c->rounds);
   (void)hipFree(c->Up_ws);
   for (int i = 0; i < 2; ++i) { (void)hipFree(c->sort_keys[i]); (void)hipFree(c->sort_vals[i]); }
   (void)hipFree(c->sort_counts); (void)hipFree(c->seg_of); (void)hipFree(c->seg_part);
@@ -246,8 +246,8 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   if (desc->dtype == STEM_BF16) {
     c->splitk_bytes = (size_t)stem_route_splitk_bytes(desc->d_model, desc->d_ff, max_tokens);
     ok(hipMalloc(reinterpret_cast<void**>(&c->splitk_ws), c->splitk_bytes));
-    ok(dmalloc(&c->tickets, STEM_TICKETS));
-    ok(dmalloc(&c->rounds, STEM_TICKETS));
+    ok(dmalloc(&c->rounds, STEM_TICKETS * 3 / 2));   // the tickets behind them
+    if (c->rounds) c->tickets = reinterpret_cast<int32_t*>(c->rounds + STEM_TICKETS);
     c->polls = STEM_POLLS;
   }
   for (int i = 0; i < 2; ++i) {
@@ -266,8 +266,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->remap_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(copy_stream_get(device, &c->side));
   if (e == hipSuccess && c->tickets) {
-    ok(stem_fill_zero(c->tickets, STEM_TICKETS * 4, c->side));
-    ok(stem_fill_zero(c->rounds, STEM_TICKETS * 8, c->side));
+    ok(stem_fill_zero(c->rounds, STEM_TICKETS * 12, c->side));
     ok(hipStreamSynchronize(c->side));
   }
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
@@ -359,8 +358,9 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     b.B = static_cast<const bf16_t*>(W_down); b.ldb = F;
     b.M = (int)T; b.N = d; b.K = F; b.C = y; b.flag = c->flag;
     b.residual = static_cast<const bf16_t*>(residual);
-    b.ws = c->splitk_ws; b.ws_bytes = c->splitk_bytes; b.tickets = c->tickets;
-    b.rounds = c->rounds; b.polls = c->polls;
+    b.ws = c->splitk_ws; b.ws_bytes = c->splitk_bytes;
+    if (down == ROUTE_DECODE) b.tickets = c->tickets;
+    else if (down == ROUTE_FEW_ROW) { b.rounds = c->rounds; b.polls = c->polls; }
     const int down_epi = residual ? EPI_BF16_RES : EPI_BF16;
     if (!wait_event) {
       a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);

@@ -150,23 +150,38 @@ struct GemmArgs {
   int lda, ldb;    // leading dimensions of the stored operands
   void* C;         // EPI_BF16 / EPI_F32 output, ld = N
   const bf16_t* residual;  // EPI_BF16_RES (and the few-row kernel when not null): [M,N] bf16 added in fp32 before rounding
-  int accumulate;  // EPI_F32: add to C
+  // What one kernel has and others have not shares its place: every launch copies the whole block.
+  union {
+    int accumulate;  // EPI_F32: add to C
+    int next_bytes;  // EPI_GATE in the decode and few-row kernels: how many bytes of `next` to bring closer (stem_touch_bytes)
+    int polls;       // EPI_BF16 in the few-row kernel: the context's
+  };
   const int32_t* ids;
   const bf16_t* E;
   int E_rows;
   bf16_t* outG;    // EPI_GATE: may be null
   bf16_t* outH;    // EPI_GATE
-  const bf16_t* inUp; // *_UP, *_UPE: the up projection x W_up^T, [M,N] bf16
+  union {
+    const bf16_t* inUp; // *_UP, *_UPE: the up projection x W_up^T, [M,N] bf16
+    bf16_t* outUp;      // *_DUAL*: where it goes
+  };
   const bf16_t* A2;  // optional second operand pair of a (KC,KC) product: C = A B^T + A2 B2^T
   const bf16_t* B2;
   int K2;
-  const bf16_t* inG; // EPI_DH
+  union {
+    const bf16_t* inG;  // EPI_DH
+    const bf16_t* Bup;  // *_DUAL*: W_up, as B
+    const bf16_t* next; // EPI_GATE in the decode and few-row kernels: the weights of the product behind it
+  };
   bf16_t* outdU;   // EPI_DH
   bf16_t* outdG;   // EPI_DH
   int32_t* flag;
   float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
   size_t ws_bytes; // capacity of ws
-  int32_t* tickets; // decode kernel: the context's tickets; null = never split
+  union {
+    int32_t* tickets;           // decode kernel: the context's tickets; null = never split
+    unsigned long long* rounds; // few-row kernel: the context's rounds; null = never split
+  };
   // Further products of the same K in the launch (weight gradients only, stem_weight_grads)
   struct { const bf16_t* A; const bf16_t* B; void* C; int M, N, lda, ldb; } more[2];
   int n_more;
@@ -175,12 +190,6 @@ struct GemmArgs {
   int kc_skip;     // set by the large kernel itself: elements a K slice starts after the operand's start
   int mt, nt;      // few-row and decode kernels: tile counts and exact float reciprocals, filled in by the launcher
   float inv_mt, inv_per_z;
-  unsigned long long* rounds; // few-row kernel: the context's rounds (null = never split) and polls
-  int polls;
-  int next_bytes;     // EPI_GATE in the decode and few-row kernels: how many bytes of the weights of the product behind it to bring
-  const bf16_t* next; // closer meanwhile (stem_touch_bytes)
-  const bf16_t* Bup;  // *_DUAL*: W_up, as B
-  bf16_t* outUp;      // and its product
 };
 
 hipError_t stem_gemm_bf16(stem_ctx* ctx, int kid, int la, int lb, int epi, const GemmArgs& a, hipStream_t s);
@@ -221,7 +230,7 @@ enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_409
 // tokens 12.4 / 13.4; 896 x 3584, 128 tokens 15.0 / 15.6; 2048 x 8192, 192 tokens 37.7 / 40.0; 1792 x 7168, 192 tokens 34.4 / 36.0.
 inline int stem_touch_bytes(int M, int d, int F) {
   const int64_t w = (int64_t)d * F * 2;
-  return M >= 112 && w >= 7900000 && w <= (M <= 128 ? 34 : 16) * 1000000ll ? (int)w : 0;
+  return M >= 112 && M <= 512 && w >= 7900000 && w <= (M <= 128 ? 34 : 16) * 1000000ll ? (int)w : 0;
 }
 
 // ---- few-row bf16 GEMM (gemm_skinny_bf16.hip): both operands K-contiguous, K % 64 == 0 --------
