@@ -373,7 +373,7 @@ void launch(int epi, const GemmArgs& p, hipStream_t s) {
 
 // Worth it while one round of its workgroups covers the product; beyond, the few-row kernel's and the large kernel's
 // tiles load less per CU.  d_model 2048, d_ff 8192, gate + down product, us, this / few-row: 1 token 17.6 / 28.0,
-// 32 tokens 21.1 / 29.6, 64 tokens 26.6 / 31.5, 128 tokens 35.4 / 37.2, 256 tokens 45.2 / 42.3; 1024 x 4096: 32 tokens
+// 32 tokens 21.1 / 29.6, 64 tokens 26.6 / 31.5, 128 tokens 35.4 / 37.2, 256 tokens 45.2 / 40.8; 1024 x 4096: 32 tokens
 // 12.0 / 19.8, 256 tokens 21.1 / 27.1, 320 tokens 27.7 / 25.9; 512 x 1536: 512 tokens 14.2 / 19.4.
 bool stem_gemm_decode_fits(int M, int N, int K) {
   DecodePlan pl;

@@ -236,8 +236,8 @@ inline int stem_touch_bytes(int M, int d, int F) {
 // ---- few-row bf16 GEMM (gemm_skinny_bf16.hip): both operands K-contiguous, K % 64 == 0 --------
 // 128x64 tiles; used when M is small enough that larger tiles would leave most of the chip idle: up to 256 rows, and up
 // to 512 while the gate product is one round of its workgroups.  Layer forward, us, this / 128x128 tiles: d_model 2048,
-// d_ff 8192, 256 tokens 42 / 44, 320 tokens 59 / 48, 512 tokens 69 / 56; 1536 x 5120, 384 tokens 41.9 / 42.9, 512 tokens 55 / 44;
-// 1024 x 4096, 320 tokens 26 / 28, 512 tokens 27 / 34.
+// d_ff 8192, 256 tokens 41 / 44, 320 tokens 59 / 48, 512 tokens 69 / 56; 1536 x 5120, 384 tokens 37.3 / 42.9, 512 tokens 55 / 44;
+// 1024 x 4096, 320 tokens 26 / 28, 512 tokens 26 / 34.
 bool stem_gemm_skinny_fits(int M, int F);
 #define STEM_SPLITK_WS_MAX ((size_t)64 << 20)   // more is never worth it: beyond it the tiles fill the chip
 // out = bf16(sum of the ksplit fp32 partial products in ws, in slice order (+ residual)); total elements each
