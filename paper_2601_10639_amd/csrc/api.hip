@@ -88,6 +88,14 @@ void copy_stream_put(int device) {   // the device is current and idle
   q.stream = nullptr;
 }
 
+// Waits for the copies of this context's last prefetch, before its pinned arrays are written again.  A call that ended with an error
+// between its copies and their event has left copies that no event stands for: then the whole stream is waited for.
+hipError_t copies_done(stem_ctx* c) {
+  const hipError_t e = c->copies_open ? hipStreamSynchronize(c->side) : hipEventSynchronize(c->copied);
+  if (e == hipSuccess) c->copies_open = 1;
+  return e;
+}
+
 template <typename T>
 hipError_t dmalloc(T** p, size_t n) {
   *p = nullptr;
@@ -746,7 +754,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
   const size_t row_bytes = (size_t)c->desc.d_ff * esize(c);
 
   // The pinned staging arrays are reused: wait until the previous prefetch's copies are done.
-  HIP_TRY(c, hipEventSynchronize(c->copied));
+  HIP_TRY(c, copies_done(c));
 
   // De-duplicate: mark, then walk the marked ids in ascending order.
   for (int64_t i = 0; i < T; ++i) {
@@ -849,6 +857,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
   }
   HIP_TRY(c, hipEventRecord(c->ready, c->side));
   HIP_TRY(c, hipEventRecord(c->copied, c->side));
+  c->copies_open = 0;
   *ready_event = c->ready;
   return STEM_OK;
 }
@@ -861,7 +870,8 @@ stem_status stem_cache_init(stem_ctx* c, int64_t n_slots) {
     return fail(c, STEM_ERR_SHAPE, "stem_cache_init: n_slots = %lld", (long long)n_slots);
   const int V = c->desc.vocab;
   HIP_TRY(c, hipSetDevice(c->device));
-  HIP_TRY(c, hipEventSynchronize(c->copied));
+  HIP_TRY(c, copies_done(c));
+  c->copies_open = 0;
   free(c->cache_id_in_slot); free(c->cache_slot_of); free(c->cache_freq);
   c->cache_id_in_slot = nullptr; c->cache_slot_of = nullptr; c->cache_freq = nullptr;
   c->cache_slots = 0;
@@ -904,7 +914,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
   const int V = c->desc.vocab;
   const int64_t NS = c->cache_slots;
   const size_t row_bytes = (size_t)c->desc.d_ff * esize(c);
-  HIP_TRY(c, hipEventSynchronize(c->copied));   // pinned staging arrays are reused
+  HIP_TRY(c, copies_done(c));   // pinned staging arrays are reused
 
   for (int64_t i = 0; i < T; ++i)
     if ((uint32_t)ids_host[i] >= (uint32_t)V)
@@ -1023,6 +1033,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
                                      E_dev, c->side));
   }
   HIP_TRY(c, hipEventRecord(c->copied, c->side));
+  c->copies_open = 0;
   return STEM_OK;
 }
 
