@@ -96,6 +96,17 @@ hipError_t copies_done(stem_ctx* c) {
   return e;
 }
 
+// Clears device memory before it returns, on a stream of its own: on the copy stream it would wait for all other contexts' rows.
+hipError_t zero_now(void* p, size_t bytes) {
+  hipStream_t s;
+  hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e != hipSuccess) return e;
+  e = stem_fill_zero(p, bytes, s);
+  const hipError_t done = hipStreamSynchronize(s);
+  (void)hipStreamDestroy(s);
+  return e != hipSuccess ? e : done;
+}
+
 template <typename T>
 hipError_t dmalloc(T** p, size_t n) {
   *p = nullptr;
@@ -273,10 +284,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->uniq_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->remap_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(copy_stream_get(device, &c->side));
-  if (e == hipSuccess && c->tickets) {
-    ok(stem_fill_zero(c->rounds, STEM_TICKETS * 12, c->side));
-    ok(hipStreamSynchronize(c->side));
-  }
+  if (e == hipSuccess && c->tickets) ok(zero_now(c->rounds, STEM_TICKETS * 12));
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
   ok(hipEventCreateWithFlags(&c->copied, hipEventDisableTiming));
   for (int i = 0; i < 2; ++i) ok(hipEventCreateWithFlags(&c->pack_done[i], hipEventDisableTiming));

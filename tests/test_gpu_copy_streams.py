@@ -1,0 +1,78 @@
+"""Contexts whose host-resident rows cross the link at the same time: what a call on one waits for, and what it leaves to the other."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2601_10639_amd import inputs, stemlib as L
+from tests import harness as Hn
+
+DEV = "cuda:0"
+NOT_READY = 600   # hipErrorNotReady
+
+pytestmark = pytest.mark.gpu
+
+
+class LongCopy:
+    """A context of 128 KB rows and a call whose rows, 2 GiB, take some 38 ms over the link."""
+
+    def __init__(self):
+        T, F = 16384, 32768
+        self.E_host = torch.empty(T, F, dtype=torch.float32, pin_memory=True)
+        self.E_host[:, 0] = torch.arange(T, dtype=torch.float32)
+        self.ids = torch.arange(T, dtype=torch.int32)
+        self.E, self.remap = torch.empty(T, F, device=DEV), torch.empty(T, dtype=torch.int32, device=DEV)
+        self.ctx = L.stem_create(4, F, T, L.STEM_F32, T, 0)
+
+    def begin(self):
+        torch.cuda.synchronize()
+        _, self.ready = L.stem_prefetch_rows(self.ctx, self.E_host, self.ids, self.E, self.remap)
+
+    def under_way(self):
+        return L.lib().hipEventQuery(ctypes.c_void_p(self.ready)) == NOT_READY
+
+    def end(self):
+        torch.cuda.synchronize()
+        assert torch.equal(self.E[:, 0].cpu(), self.E_host[:, 0])
+        self.E.zero_()
+
+
+class Layer:
+    """A bf16 layer on a host-resident table, checked against the same layer on a device-resident one."""
+    T, V, d, F = 500, 3000, 128, 256
+
+    def __init__(self, seed):
+        s = inputs.StemShape("beside-a-copy", self.d, self.F, self.V, 1, self.T, "bf16")
+        self.inp = inputs.layer_inputs(s, seed=seed, device=DEV, tokens=self.T)
+        self.E_host = self.inp["E"].cpu().pin_memory()
+        self.E = torch.zeros(2 * self.T, self.F, dtype=torch.bfloat16, device=DEV)
+        self.remap = torch.empty(self.T, dtype=torch.int32, device=DEV)
+        self.y, self.want = torch.empty_like(self.inp["x"]), torch.empty_like(self.inp["x"])
+        self.ctx = Hn.make_ctx(s, self.T)
+        L.stem_ffn_forward(self.ctx, self.inp["x"], self.inp["ids"], self.inp["W_gate"], self.inp["W_down"], self.inp["E"], self.want)
+        L.stem_sync_status(self.ctx)
+
+    def prefetch(self, ids=None, E=None):
+        ids = self.inp["ids"].cpu() if ids is None else ids
+        self.n, self.ready = L.stem_prefetch_rows(self.ctx, self.E_host, ids, self.E if E is None else E, self.remap)
+
+    def check(self):
+        L.stem_ffn_forward(self.ctx, self.inp["x"], self.remap, self.inp["W_gate"], self.inp["W_down"], self.E, self.y,
+                           wait_event=self.ready, E_rows=self.n)
+        L.stem_sync_status(self.ctx)
+        assert Hn.max_rel(self.y.float().cpu(), self.want.float().cpu()) <= Hn.TOL["bf16"]
+
+
+@pytest.fixture(scope="module")
+def copy():
+    c = LongCopy()
+    yield c
+    c.ctx.close()
+
+
+def test_a_context_is_made_while_another_ones_rows_are_under_way(copy):
+    copy.begin()
+    ctx = L.stem_create(64, 64, 64, L.STEM_BF16, 64, 0)
+    assert copy.under_way()
+    copy.end()
+    ctx.close()
