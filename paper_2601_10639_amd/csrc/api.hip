@@ -89,10 +89,10 @@ void copy_stream_put(int device) {   // the device is current and idle
 }
 
 // Waits for the copies of this context's last prefetch, before its pinned arrays are written again.  A call that ended with an error
-// between its copies and their event has left copies that no event stands for: then the whole stream is waited for.
+// between its first copy and their event has left copies that no event stands for: then the whole stream is waited for.
 hipError_t copies_done(stem_ctx* c) {
   const hipError_t e = c->copies_open ? hipStreamSynchronize(c->side) : hipEventSynchronize(c->copied);
-  if (e == hipSuccess) c->copies_open = 1;
+  if (e == hipSuccess) c->copies_open = 0;
   return e;
 }
 
@@ -827,6 +827,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
     return fail(c, STEM_ERR_WORKSPACE, "stem_prefetch_rows: %lld distinct ids but E_compact holds %lld rows",
                 (long long)U, (long long)cap);
 
+  c->copies_open = 1;
   if (c->prefetch_mode == STEM_PREFETCH_MEMCPY) {
     if (T > 0) HIP_TRY(c, hipMemcpyAsync(remap, c->remap_pinned, (size_t)T * 4, hipMemcpyHostToDevice, c->side));
     // Pack the rows into pinned staging with a few host threads and copy chunk by chunk,
@@ -879,7 +880,6 @@ stem_status stem_cache_init(stem_ctx* c, int64_t n_slots) {
   const int V = c->desc.vocab;
   HIP_TRY(c, hipSetDevice(c->device));
   HIP_TRY(c, copies_done(c));
-  c->copies_open = 0;
   free(c->cache_id_in_slot); free(c->cache_slot_of); free(c->cache_freq);
   c->cache_id_in_slot = nullptr; c->cache_slot_of = nullptr; c->cache_freq = nullptr;
   c->cache_slots = 0;
@@ -967,6 +967,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
                 (long long)n_miss, (long long)cap);
   }
 
+  c->copies_open = 1;
   HIP_TRY(c, stem_copy_lists_kernel(c, c->remap_pinned, remap, T, c->order_pinned, c->order_dev, n_miss, c->max_tokens, c->side));
   {
     int64_t k0 = 0;

@@ -72,7 +72,7 @@ struct stem_ctx {
   hipStream_t side;      // the device's copy stream, shared by its contexts
   hipEvent_t ready;      // rows and remap of the last prefetch are there
   hipEvent_t copied;     // and everything else the call has put on the side stream is done
-  int copies_open;       // a prefetch has begun and not recorded `copied`
+  int copies_open;       // a prefetch has put copies on the side stream and not recorded `copied`
   int32_t* slot;         // host [V], -1 = absent
   int32_t* uniq_pinned;  // pinned host [max_tokens]
   int32_t* remap_pinned; // pinned host [max_tokens]

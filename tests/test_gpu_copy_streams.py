@@ -76,3 +76,27 @@ def test_a_context_is_made_while_another_ones_rows_are_under_way(copy):
     assert copy.under_way()
     copy.end()
     ctx.close()
+
+
+@pytest.mark.parametrize("cached", [False, True])
+def test_a_refused_call_leaves_the_next_one_nothing_to_wait_for(copy, cached):
+    q = Layer(1)
+    bad = q.inp["ids"].cpu()
+    bad[-1] = q.V
+    if cached:
+        L.stem_cache_init(q.ctx, q.T)
+
+    def prefetch(ids, cap):
+        if cached:
+            return L.stem_prefetch_rows_cached(q.ctx, q.E_host, ids, q.E[:q.T + cap], q.T, q.remap)
+        return L.stem_prefetch_rows(q.ctx, q.E_host, ids, q.E[:cap], q.remap)
+
+    copy.begin()
+    for ids, cap, status in ((bad, q.T, L.STEM_ERR_ID_RANGE), (q.inp["ids"].cpu(), 3, L.STEM_ERR_WORKSPACE)):
+        with pytest.raises(L.StemError) as e:
+            prefetch(ids, cap)
+        assert e.value.status == status
+    prefetch(q.inp["ids"].cpu(), q.T)
+    assert copy.under_way()
+    copy.end()
+    q.ctx.close()
