@@ -35,8 +35,8 @@
  *     stem_create, stem_reserve, stem_set_prefetch_mode, stem_cache_init,
  *     stem_profile_enable.  No call that enqueues work allocates or frees.
  *     Calls on one context must not overlap in time (they share that scratch).
- *   - The contexts of a device share one side stream, on which rows of host-resident
- *     tables are copied; it lives as long as there is a context on the device.
+ *   - The contexts of a device share two side streams, on which rows of host-resident
+ *     tables are copied; they live as long as there is a context on the device.
  */
 #ifndef STEM_H
 #define STEM_H
@@ -235,15 +235,15 @@ stem_status stem_ffn_up_backward(stem_ctx* ctx, const void* dy, const void* x, c
 
 /* E_host [V,F] lives in pinned host memory (hipHostMalloc); ids_host [T] is host memory.
  * De-duplicates ids on the host (distinct ids ascending), copies row uniq[j] of E_host to
- * E_compact[j] (device, capacity `cap` rows) on the device's side stream (rows travel in
- * the order in which the tokens first use them, those of calls on several contexts one call's
- * after another's, in the order of the calls), and writes
+ * E_compact[j] (device, capacity `cap` rows) on one of the device's side streams (rows travel in
+ * the order in which the tokens first use them; those of a call of 128 MiB of rows and more behind those of
+ * such calls made before it on the device's contexts, while shorter calls share the link two at a time), and writes
  * remap[i] = j with uniq[j] == ids[i] (device [T]) there too, so that
  *   stem_ffn_forward(E = E_compact, ids = remap, E_rows = *n_uniq_host, wait_event = *ready_event)
  * is the same layer.  *n_uniq_host (host) is valid on return; uniq_ids_host (host, may be
  * NULL, capacity cap) receives the distinct ids.  *ready_event is a hipEvent_t owned by
  * the context, recorded after the copies, valid until the next stem_prefetch_rows call.
- * The copies wait for nothing but earlier prefetches: a forward call that reads E_compact and remap
+ * The copies wait for nothing but earlier prefetches of the device's contexts: a forward call that reads E_compact and remap
  * must have finished on the device (the host has waited for its stream, or for an event behind it) before the next
  * call writes the same buffers.  Calls that are to overlap each other, layers in a stack or batches in turn, take a
  * context, an E_compact and a remap each.
@@ -254,7 +254,7 @@ stem_status stem_prefetch_rows(stem_ctx* ctx, const void* E_host, const int32_t*
                                int32_t* uniq_ids_host, void** ready_event);
 
 /* How stem_prefetch_rows moves the rows (a set-up call; the default is STEM_PREFETCH_KERNEL).
- *   STEM_PREFETCH_KERNEL  a copy kernel on the side stream reads the pinned table directly, row by row in
+ *   STEM_PREFETCH_KERNEL  a copy kernel on a side stream reads the pinned table directly, row by row in
  *                         order of first use; the call blocks only for the host-side de-duplication.
  *   STEM_PREFETCH_MEMCPY  the form the paper's system section describes: the distinct rows are packed into
  *                         pinned staging by host threads and sent with hipMemcpyAsync, 32 MiB at a time,
@@ -276,7 +276,7 @@ stem_status stem_set_prefetch_mode(stem_ctx* ctx, int mode);
  *
  * stem_prefetch_rows_cached: counts every token of ids_host, maps each distinct id to its
  * cache slot (hit) or to staging row n_slots + k, k numbering the misses in order of first
- * use, copies the missed rows from E_host there on the side stream, writes remap (device
+ * use, copies the missed rows from E_host there on a side stream, writes remap (device
  * [T]) so that stem_ffn_forward(E = E_dev, ids = remap, E_rows = n_slots + cap,
  * wait_event = *ready_event) is the same layer, and then updates the cache for later
  * batches: the missed rows are offered in order (frequency descending, id ascending); each

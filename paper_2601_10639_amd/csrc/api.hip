@@ -57,35 +57,49 @@ stem_status enter(stem_ctx* c, int64_t T) {
   return STEM_OK;
 }
 
-// The stream on which the contexts of a device copy rows from host memory: one for all of them, made with the first context and
-// destroyed with the last.  The rows of calls that follow each other then cross the link one call's after another's, in the
-// order in which the forward passes wait for them, and one copy's workgroups are all that the copies keep from the GEMMs.  With
-// a stream per context the copies of three contexts shared the link, all of them late and on 48 compute units, and some of
-// these streams shared a hardware queue with the caller's, which runs copy and products one after the other.
-struct CopyStream { hipStream_t stream; int64_t users; };
+// The streams on which the contexts of a device copy rows from host memory: two for all of them, made with the first context and
+// destroyed with the last.  Calls of STEM_PF_LONG bytes of rows and more all go on the first: their rows cross the link one call's
+// after another's, in the order in which the forward passes wait for them.  Shorter calls take both in turn, so that one call's rows
+// are on the link while it would stand still between the rows of two others, and only the second
+// while a long call's are under way on the first.  Never more than two copies run, and they fit the compute units that the chunks' products leave free.
+struct CopyStreams { hipStream_t stream[2]; int64_t users; unsigned turn; bool long_rows; };
 constexpr int MAX_DEVICES = 64;
-CopyStream g_copy[MAX_DEVICES];
+CopyStreams g_copy[MAX_DEVICES];
 std::mutex g_copy_mutex;
 
-hipError_t copy_stream_get(int device, hipStream_t* out) {
+hipError_t copy_streams_get(int device, hipStream_t* first) {
   if (device < 0 || device >= MAX_DEVICES) return hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(g_copy_mutex);
-  CopyStream& q = g_copy[device];
-  if (!q.stream) {
-    hipError_t e = hipStreamCreateWithFlags(&q.stream, hipStreamNonBlocking);
-    if (e != hipSuccess) { q.stream = nullptr; return e; }
+  CopyStreams& q = g_copy[device];
+  for (hipStream_t& s : q.stream) {
+    if (s) continue;
+    const hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e != hipSuccess) { s = nullptr; return e; }
   }
   ++q.users;
-  *out = q.stream;
+  *first = q.stream[0];
   return hipSuccess;
 }
 
-void copy_stream_put(int device) {   // the device is current and idle
+void copy_streams_put(int device) {   // the device is current and idle
   std::lock_guard<std::mutex> lock(g_copy_mutex);
-  CopyStream& q = g_copy[device];
+  CopyStreams& q = g_copy[device];
   if (--q.users > 0) return;
-  (void)hipStreamDestroy(q.stream);
-  q.stream = nullptr;
+  for (hipStream_t& s : q.stream) {
+    (void)hipStreamDestroy(s);
+    s = nullptr;
+  }
+}
+
+// In front of a call's first copy: the stream for all of them.
+void copies_begin(stem_ctx* c, int64_t rows) {
+  std::lock_guard<std::mutex> lock(g_copy_mutex);
+  CopyStreams& q = g_copy[c->device];
+  const bool is_long = stem_route_copy_streams(rows, (int64_t)c->desc.d_ff * esize(c)) == 1;
+  if (!is_long && q.long_rows) q.long_rows = hipStreamQuery(q.stream[0]) == hipErrorNotReady;
+  c->side = q.stream[is_long ? 0 : q.long_rows ? 1 : q.turn++ & 1];
+  q.long_rows |= is_long;
+  c->copies_open = 1;
 }
 
 // Waits for the copies of this context's last prefetch, before its pinned arrays are written again.  A call that ended with an error
@@ -96,7 +110,7 @@ hipError_t copies_done(stem_ctx* c) {
   return e;
 }
 
-// Clears device memory before it returns, on a stream of its own: on the copy stream it would wait for all other contexts' rows.
+// Clears device memory before it returns, on a stream of its own: on a copy stream it would wait for other contexts' rows.
 hipError_t zero_now(void* p, size_t bytes) {
   hipStream_t s;
   hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
@@ -138,7 +152,7 @@ void release(stem_ctx* c) {
   (void)hipFree(c->edit_idx_dev); (void)hipFree(c->edit_rep_dev);
   if (c->inst_pinned) (void)hipHostFree(c->inst_pinned);
   (void)hipFree(c->inst_dev);
-  if (c->side) copy_stream_put(c->device);
+  if (c->side) copy_streams_put(c->device);
   if (c->ready) (void)hipEventDestroy(c->ready);
   if (c->copied) (void)hipEventDestroy(c->copied);
   for (int i = 0; i < 2; ++i) if (c->pack_done[i]) (void)hipEventDestroy(c->pack_done[i]);
@@ -195,6 +209,8 @@ void stem_route_forward(int d, int F, int64_t T, int32_t* route) {
     }
   }
 }
+
+int stem_route_copy_streams(int64_t rows, int64_t row_bytes) { return rows * row_bytes >= STEM_PF_LONG ? 1 : 2; }
 
 void stem_exchange_polls(stem_ctx* c, int polls) { c->polls = polls; }
 
@@ -283,7 +299,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->flag), 64, hipHostMallocDefault));
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->uniq_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->remap_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
-  ok(copy_stream_get(device, &c->side));
+  ok(copy_streams_get(device, &c->side));
   if (e == hipSuccess && c->tickets) ok(zero_now(c->rounds, STEM_TICKETS * 12));
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
   ok(hipEventCreateWithFlags(&c->copied, hipEventDisableTiming));
@@ -827,7 +843,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
     return fail(c, STEM_ERR_WORKSPACE, "stem_prefetch_rows: %lld distinct ids but E_compact holds %lld rows",
                 (long long)U, (long long)cap);
 
-  c->copies_open = 1;
+  copies_begin(c, U);
   if (c->prefetch_mode == STEM_PREFETCH_MEMCPY) {
     if (T > 0) HIP_TRY(c, hipMemcpyAsync(remap, c->remap_pinned, (size_t)T * 4, hipMemcpyHostToDevice, c->side));
     // Pack the rows into pinned staging with a few host threads and copy chunk by chunk,
@@ -967,7 +983,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
                 (long long)n_miss, (long long)cap);
   }
 
-  c->copies_open = 1;
+  copies_begin(c, n_miss);
   HIP_TRY(c, stem_copy_lists_kernel(c, c->remap_pinned, remap, T, c->order_pinned, c->order_dev, n_miss, c->max_tokens, c->side));
   {
     int64_t k0 = 0;

@@ -13,14 +13,10 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 // its compute unit with a copy waits for the link with every K tile, and a round of tiles for the slowest of them: the
 // workgroups therefore claim LDS that no tile of the large bf16 products can do without (two of them fit a compute unit), and
 // the products of a chunk leave 32 compute units free (STEM_PF_CHUNK_TILES).  The fp32 products' tiles (32 and 64 KB) still share
-// with a copy.  The copies of a device's contexts run one after another on one stream (api.hip), so 16 compute units at most are held.
-// Zipf ids, ms, calls in turn on three contexts / two / by itself: copies of all contexts at once, on a stream each / one after
-// another: 2048 x 8192, 65536 tokens 5.22 / 4.83 / 4.61 and 4.13 / 4.14 / 4.62, 24576 tokens 2.20 / 2.01 / 2.23 and 1.96 / 1.95 /
-// 2.23, 16384 tokens 1.47 / 1.40 / 1.69 and 1.41 / 1.42 / 1.69, 4096 tokens 0.504 / 0.468 / 0.645 and 0.477 / 0.475 / 0.645; 1024 x
-// 4096, 8192 tokens 0.394 / 0.405 / 0.498 and 0.382 / 0.384 / 0.504, 1000 tokens 0.088 / 0.082 / 0.130 and 0.086 / 0.086 / 0.131.
-// What it costs: the link is idle for some 10 us between two calls' rows, 0.632 / 0.635 / 0.830 and 0.646 / 0.648 / 0.836 at 1024 x 4096,
-// 16384 tokens (the lists on a stream of their own do not shorten that).
-// A copy that shares the compute units with the GEMM tiles, 32 workgroups, 65536 tokens: 6.40 / 5.80 / 4.85.
+// with a copy.  The contexts of a device share two copy streams (api.hip, STEM_PF_LONG), so 32 compute units at most are held.
+// A copy that shares the compute units with the GEMM tiles, 32 workgroups, 65536 tokens of 2048 x 8192, calls in turn on three contexts /
+// two / by itself: 6.40 / 5.80 / 4.85 ms; with compute units to itself and a copy stream per context 5.22 / 4.83 / 4.61, with one for all
+// 4.13 / 4.14 / 4.62.
 constexpr int COPY_WGS = 16, FLIGHT = 4;
 constexpr int COPY_LDS = 65 * 1024;   // two fit 160 KB, one and the smallest tile of gemm_bf16.hip (96 KB) do not
 constexpr int BATCH = 64;             // pieces whose rows a wavefront looks up at a time, one per lane

@@ -44,6 +44,18 @@ enum StemKernelId {
 // with a copy stream per context, 240 tiles 4.97 / 4.69 and 4.13 / 4.59 with one for all, 224 tiles 4.60 / 4.70 and 4.11 / 4.64; 16384
 // tokens 240 tiles 1.42 / 1.74, 224 tiles 1.42 / 1.69; 1024 x 4096, 16384 tokens 0.652 / 0.870 and 0.648 / 0.843.
 #define STEM_PF_CHUNK_TILES 224
+// Bytes of rows from which host-table calls follow each other on one copy stream instead of two in turn.  ms, calls in turn on three
+// contexts / two / by itself, one stream / two: 512 x 1536, 4096 tokens (4 MB) 0.096 / 0.096 / 0.124 and 0.080 / 0.081 / 0.124, 65536
+// tokens (33 MB) 0.647 / 0.645 / 0.805 and 0.615 / 0.635 / 0.809; 1024 x 4096, 4096 tokens (12 MB) 0.227 / 0.227 / 0.261 and 0.209 /
+// 0.228 / 0.261, 8192 tokens 0.381 / 0.381 / 0.442 and 0.364 / 0.393 / 0.443, 16384 tokens 0.647 / 0.643 / 0.695 and 0.612 / 0.631 /
+// 0.702, 65536 tokens (89 MB) 1.717 / 1.713 / 1.839 and 1.682 / 1.685 / 1.853; 2048 x 8192, 1000 tokens 0.163 / 0.163 / 0.199 and 0.173 /
+// 0.170 / 0.198, 4096 tokens (25 MB) 0.476 / 0.470 / 0.571 and 0.459 / 0.506 / 0.568, 24576 tokens (104 MB) 1.942 / 1.932 / 2.060 and
+// 1.915 / 1.933 / 2.055, 40000 tokens (151 MB) 2.836 / 2.822 / 2.975 and 3.013 / 2.925 / 2.967, 65536 tokens (216 MB) 4.138 / 4.121 /
+// 4.365 and 4.862 / 4.820 / 4.362.  A stream for each context: 512 x 1536, 4096 tokens 0.081 / 0.081 / 0.121, 65536 tokens 0.621 / 0.633 /
+// 0.805; 1024 x 4096, 4096 tokens 0.218 / 0.228 / 0.260, 8192 tokens 0.382 / 0.392 / 0.440, 16384 tokens 0.626 / 0.630 / 0.693, 65536 tokens
+// 1.753 / 1.688 / 1.833; 2048 x 8192, 1000 tokens 0.183 / 0.170 / 0.198, 4096 tokens 0.492 / 0.502 / 0.563, 24576 tokens 2.113 / 1.932 / 2.056,
+// 40000 tokens 3.320 / 2.939 / 2.964, 65536 tokens 5.234 / 4.786 / 4.367.
+#define STEM_PF_LONG ((int64_t)128 << 20)
 
 struct stem_ctx {
   stem_layer_desc desc;
@@ -69,7 +81,7 @@ struct stem_ctx {
   int32_t* flag;         // pinned host int, device-visible: sticky id-range flag
 
   // host-resident table mode
-  hipStream_t side;      // the device's copy stream, shared by its contexts
+  hipStream_t side;      // the one of the device's two copy streams that the last prefetch took
   hipEvent_t ready;      // rows and remap of the last prefetch are there
   hipEvent_t copied;     // and everything else the call has put on the side stream is done
   int copies_open;       // a prefetch has put copies on the side stream and not recorded `copied`
@@ -216,6 +228,7 @@ void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* 
 void stem_route_forward(int d_model, int d_ff, int64_t T, int32_t* route);
 int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   // a context's room for K slices
 int stem_route_sort(int64_t T, int V);   // SortRoute
+int stem_route_copy_streams(int64_t rows, int64_t row_bytes);   // how many copy streams host-table calls of this many rows take in turn
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
 }
 // SORT_ONE_*: one launch, ranks by counting or, for vocabularies beyond 2^18, the passes of one workgroup; SORT_RANKS_8192: ranks by counting

@@ -1,5 +1,6 @@
 """Contexts whose host-resident rows cross the link at the same time: what a call on one waits for, and what it leaves to the other."""
 import ctypes
+import threading
 
 import pytest
 import torch
@@ -100,3 +101,85 @@ def test_a_refused_call_leaves_the_next_one_nothing_to_wait_for(copy, cached):
     assert copy.under_way()
     copy.end()
     q.ctx.close()
+
+
+def test_short_calls_beside_a_long_one_and_beside_each_other(copy):
+    """Rows of a few MB do not wait for another context's 2 GiB, and the rows of two such calls do not all wait for one another."""
+    layers = [Layer(k) for k in range(2, 5)]
+    copy.begin()
+    for q in layers:
+        q.prefetch()
+    for q in layers:
+        L.lib().hipEventSynchronize(ctypes.c_void_p(q.ready))
+    assert copy.under_way()
+    copy.end()
+    for _ in range(3):   # the long call's are done: both streams in turn
+        for q in layers:
+            q.E.zero_()
+        torch.cuda.synchronize()
+        for q in layers:
+            q.prefetch()
+        for q in layers:
+            q.check()
+    for q in layers:
+        q.ctx.close()
+
+
+def test_a_context_is_closed_while_another_ones_rows_are_under_way(copy):
+    gone, stays = Layer(5), Layer(6)
+    copy.begin()
+    for q in (gone, stays):
+        q.prefetch()
+    gone.ctx.close()
+    stays.check()
+    copy.end()
+    copy.begin()
+    stays.prefetch()
+    stays.check()
+    copy.end()
+    stays.ctx.close()
+
+
+def test_the_row_cache_beside_another_ones_rows(copy):
+    """Promoted rows are copied behind a call's own: hits, misses and promotions of three batches, each beside a long copy."""
+    q = Layer(7)
+    L.stem_cache_init(q.ctx, 100)
+    for k in range(3):
+        copy.begin()
+        ids = torch.from_numpy(inputs.zipf_ids(q.T, q.V, seed=70 + k))
+        _, _, ready = L.stem_prefetch_rows_cached(q.ctx, q.E_host, ids, q.E, 100, q.remap)
+        L.stem_ffn_forward(q.ctx, q.inp["x"], q.remap, q.inp["W_gate"], q.inp["W_down"], q.E, q.y, wait_event=ready)
+        torch.cuda.current_stream().synchronize()
+        assert copy.under_way()
+        copy.end()
+        assert torch.equal(q.E[q.remap.long()].cpu(), q.E_host[ids.long()])
+        state = L.stem_cache_state(q.ctx, 100).long()
+        assert torch.equal(q.E[:100][(state >= 0).to(DEV)].cpu(), q.E_host[state[state >= 0]])
+    q.ctx.close()
+
+
+def test_calls_from_two_threads():
+    layers = [Layer(8), Layer(9)]
+    wrong = []
+
+    def work(q):
+        try:
+            s = torch.cuda.Stream()
+            for _ in range(20):
+                q.prefetch()
+                L.stem_ffn_forward(q.ctx, q.inp["x"], q.remap, q.inp["W_gate"], q.inp["W_down"], q.E, q.y, wait_event=q.ready,
+                                   E_rows=q.n, stream=s)
+                s.synchronize()
+                if Hn.max_rel(q.y.float().cpu(), q.want.float().cpu()) > Hn.TOL["bf16"]:
+                    wrong.append(q)
+        except Exception as e:
+            wrong.append(e)
+
+    threads = [threading.Thread(target=work, args=(q,)) for q in layers]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    for q in layers:
+        q.ctx.close()

@@ -1,8 +1,10 @@
 """CPU-only: the rules that choose a call's kernels, asked through the library itself."""
+import ctypes
 import random
 
 import pytest
 
+from paper_2601_10639_amd import stemlib as L
 from tests.harness import EPI_BF16, EPI_F32, EPI_GATE, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
 
 
@@ -74,3 +76,16 @@ def test_weight_gradients_over_buffers_that_are_read_before_them_do_not_share_a_
                     for at, shares in ((lie[over] - size[grad], True), (lie[over] - size[grad] + 16, not refused),
                                        (lie[over] + size[over] - 16, not refused), (lie[over] + size[over], True)):
                         assert route_weight_grads_apart(T, d, F, **{**q, grad: at}) == shares, (up, grad, over, with_dx, at)
+
+
+@pytest.mark.parametrize("rows,F,streams", [
+    # three contexts in turn, one copy stream / two in turn, ms
+    (1433, 1536, 2),        # 4096 tokens: 0.096 / 0.080
+    (1416, 4096, 2),        # 4096 tokens: 0.227 / 0.209
+    (4138, 4096, 2),        # 16384 tokens: 0.647 / 0.612
+    (6332, 8192, 2),        # 24576 tokens: 1.942 / 1.915
+    (9189, 8192, 1),        # 40000 tokens: 2.836 / 3.013
+    (13209, 8192, 1),       # 65536 tokens: 4.138 / 4.862
+])
+def test_host_table_calls_that_share_the_link_where_that_was_measured_shorter(rows, F, streams):
+    assert L.lib().stem_route_copy_streams(ctypes.c_int64(rows), ctypes.c_int64(2 * F)) == streams
