@@ -171,6 +171,9 @@ StemRoute forward_route(int64_t T, int N, int K, int d_ff) {
   return T <= 512 && stem_gemm_skinny_fits((int)T, d_ff) ? ROUTE_FEW_ROW : ROUTE_TILES;
 }
 
+// What the gate product of a forward call touches of W_down: the tile kernel has no such loads, and other arguments in their place.
+int touch_bytes(StemRoute gate, int64_t T, int d, int F) { return gate == ROUTE_TILES ? 0 : stem_touch_bytes((int)T, d, F); }
+
 EmbedScratch embed_scratch(const stem_ctx* c) {
   EmbedScratch w;
   w.sort_keys[0] = c->sort_keys[0]; w.sort_keys[1] = c->sort_keys[1];
@@ -209,6 +212,8 @@ void stem_route_forward(int d, int F, int64_t T, int32_t* route) {
     }
   }
 }
+
+int stem_route_touch_bytes(int d, int F, int64_t T) { return touch_bytes(forward_route(T, F, d, F), T, d, F); }
 
 int stem_route_copy_streams(int64_t rows, int64_t row_bytes) { return rows * row_bytes >= STEM_PF_LONG ? 1 : 2; }
 
@@ -396,7 +401,7 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     const int down_epi = residual ? EPI_BF16_RES : EPI_BF16;
     if (!wait_event) {
       a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);
-      a.next = static_cast<const bf16_t*>(W_down); a.next_bytes = stem_touch_bytes((int)T, d, F);
+      if (const int bytes = touch_bytes(gate, T, d, F)) { a.next = static_cast<const bf16_t*>(W_down); a.next_bytes = bytes; }
       if (gate == ROUTE_DECODE) HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
       else if (gate == ROUTE_FEW_ROW) HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_GATE, EPI_GATE, a, s));
       else HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_GATE, OP_KC, OP_KC, EPI_GATE, a, s));

@@ -228,6 +228,7 @@ void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* 
 void stem_route_forward(int d_model, int d_ff, int64_t T, int32_t* route);
 int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   // a context's room for K slices
 int stem_route_sort(int64_t T, int V);   // SortRoute
+int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, touched by the gate product of that call
 int stem_route_copy_streams(int64_t rows, int64_t row_bytes);   // how many copy streams host-table calls of this many rows take in turn
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
 }
@@ -240,7 +241,7 @@ enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_409
 // 112 tokens (below, the gate product waits for them itself) and 8 MB of weights (below, the launches are latency) to 16 MB, or 34
 // up to 128 tokens, where the down product is the decode kernel's (above, the gate product is bound by L2).  Layer forward, us,
 // without / with: 1024 x 4096, 112 tokens 16.9 / 16.7, 192 tokens 22.4 / 20.7, 384 tokens 27.7 / 26.0; 1280 x 5120, 128 tokens 28.0 /
-// 25.3, 450 tokens 39.6 / 39.4; 1536 x 5120, 384 tokens 41.2 / 37.4; 2048 x 8192, 128 tokens 35.3 / 34.3; against 1024 x 4096, 24
+// 25.3; 1536 x 5120, 384 tokens 41.2 / 37.4; 2048 x 8192, 128 tokens 35.3 / 34.3; against 1024 x 4096, 24
 // tokens 12.4 / 13.4; 896 x 3584, 128 tokens 15.0 / 15.6; 2048 x 8192, 192 tokens 37.7 / 40.0; 1792 x 7168, 192 tokens 34.4 / 36.0.
 inline int stem_touch_bytes(int M, int d, int F) {
   const int64_t w = (int64_t)d * F * 2;

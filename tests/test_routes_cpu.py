@@ -5,7 +5,7 @@ import random
 import pytest
 
 from paper_2601_10639_amd import stemlib as L
-from tests.harness import EPI_BF16, EPI_F32, EPI_GATE, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
+from tests.harness import DECODE, EPI_BF16, EPI_F32, EPI_GATE, FEW_ROW, TILES, route_forward, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
 
 
 def test_no_k_slice_is_empty():
@@ -89,3 +89,18 @@ def test_weight_gradients_over_buffers_that_are_read_before_them_do_not_share_a_
 ])
 def test_host_table_calls_that_share_the_link_where_that_was_measured_shorter(rows, F, streams):
     assert L.lib().stem_route_copy_streams(ctypes.c_int64(rows), ctypes.c_int64(2 * F)) == streams
+
+
+@pytest.mark.parametrize("T,d,F,gate,touched", [
+    (111, 1024, 4096, DECODE, False),
+    (112, 1024, 4096, DECODE, True),
+    (128, 2048, 8192, DECODE, True),
+    (192, 2048, 8192, FEW_ROW, False),
+    (384, 1536, 5120, FEW_ROW, True),
+    (450, 1280, 5120, TILES, False),      # other kernels' arguments stand there for the tile kernel
+    (512, 1536, 5120, TILES, False),
+    (513, 1024, 4096, TILES, False),
+])
+def test_gate_products_that_touch_the_down_products_weights(T, d, F, gate, touched):
+    assert route_forward(T, d, F)[0][0] == gate
+    assert L.lib().stem_route_touch_bytes(d, F, ctypes.c_int64(T)) == (2 * d * F if touched else 0)
