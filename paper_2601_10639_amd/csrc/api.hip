@@ -434,7 +434,17 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     if (down == ROUTE_DECODE) {
       HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_DOWN, EPI_BF16, b, s));
     } else if (down == ROUTE_FEW_ROW) {
+      // K slices finish y while others still read H and W_down: where y lies over one of these it is put together behind the slices'
+      // partial tiles and copied.  (Room is there: slices take 8 MB and 8 KB * d at most, y 1 KB * d, of the smaller of 64 MB and 32 KB * d.)
+      const size_t Td = (size_t)T * d * 2;
+      const bool over = stem_gemm_skinny_ksplit((int)T, d, F, c->splitk_bytes) > 1 &&
+                        (overlap(y, Td, H, (size_t)T * F * 2) || overlap(y, Td, W_down, (size_t)F * d * 2));
+      if (over) {
+        b.ws_bytes -= Td;
+        b.C = reinterpret_cast<char*>(b.ws) + b.ws_bytes;
+      }
       HIP_TRY(c, stem_gemm_skinny_bf16(c, K_GEMM_DOWN, EPI_BF16, b, s));
+      if (over) HIP_TRY(c, hipMemcpyAsync(y, b.C, Td, hipMemcpyDeviceToDevice, s));
     } else {
       HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_DOWN, OP_KC, OP_KC, down_epi, b, s));
     }

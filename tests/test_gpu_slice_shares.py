@@ -78,6 +78,44 @@ def test_slices_of_products_of_several_sizes_count_on_one_word():
     ctx.close()
 
 
+@pytest.mark.parametrize("T,d,F,slices", [(129, 1408, 2112, 4), (256, 2048, 8192, 4), (385, 1344, 2112, 2)])
+def test_output_over_what_the_slices_read(T, d, F, slices):
+    """y inside the buffer that H is saved to, or over W_down: as if every slice had read all of it before y is written."""
+    assert Hn.route_forward(T, d, F)[1] == (Hn.FEW_ROW, 128, 64, slices)
+    s = inputs.StemShape("slice-over", d, F, 300, 1, T, "bf16")
+    inp = inputs.layer_inputs(s, seed=84, device=DEV, tokens=T)
+    ctx = Hn.make_ctx(s, T)
+    want, H = torch.empty_like(inp["x"]), torch.empty(T, F, dtype=torch.bfloat16, device=DEV)
+    L.stem_ffn_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"], want, None, H)
+    n = T * d
+    for at in (0, n // 16 * 8, T * F - n):                     # y in H: its beginning, its middle, its end
+        room = torch.zeros(T * F, dtype=torch.bfloat16, device=DEV)
+        y = room[at:at + n].view(T, d)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            L.stem_ffn_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"], y, None, room.view(T, F),
+                               stream=torch.cuda.current_stream())
+        for replay in (False, True, True):
+            room.zero_()
+            if replay:
+                graph.replay()
+            else:
+                L.stem_ffn_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"], y, None, room.view(T, F))
+            torch.cuda.synchronize()
+            assert torch.equal(y, want)
+            left = torch.ones(T * F, dtype=torch.bool, device=DEV)
+            left[at:at + n] = False
+            assert torch.equal(room[left], H.view(-1)[left])   # what y does not cover of H
+    for at in (0, F * d - 8):                                  # y over W_down's beginning, and over its last 16 bytes
+        room = torch.zeros(F * d + n, dtype=torch.bfloat16, device=DEV)
+        room[:F * d].copy_(inp["W_down"].view(-1))
+        y = room[at:at + n].view(T, d)
+        L.stem_ffn_forward(ctx, inp["x"], inp["ids"], inp["W_gate"], room[:F * d].view(d, F), inp["E"], y)
+        assert torch.equal(y, want)
+    L.stem_sync_status(ctx)
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,d,F", [
     (112, 1024, 3904),        # the fewest tokens, 7.99 MB of weights
     (128, 2048, 8192),        # all lines of the largest, four by each thread
