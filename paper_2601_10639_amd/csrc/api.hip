@@ -231,6 +231,16 @@ int stem_route_weight_grads_apart(int d, int F, int64_t T, const void* dy, const
   return !overlap(dW_gate, Fd, dV, TF);
 }
 
+int stem_route_gate_up_together(int d, int F, int64_t T, const void* W_up, const void* E, int64_t E_rows, const void* ids, const void* G,
+                                const void* Up, const void* H) {
+  // One after the other, the up product reads W_up and stores Up, then the gate product reads E, ids and Up and stores G and H.  Together
+  // all is stored while W_up, E and the ids are read.  (G or H in Up's place is fine: a lane stores Up first.)
+  const size_t TF = (size_t)T * F * 2, Fd = (size_t)F * d * 2;
+  for (const void* out : {G, Up, H})
+    if (overlap(out, TF, W_up, Fd) || (out != Up && overlap(out, TF, Up, TF))) return 0;
+  return !(E && (overlap(Up, TF, E, (size_t)E_rows * F * 2) || overlap(Up, TF, ids, (size_t)T * 4)));
+}
+
 const char* stem_status_string(stem_status s) {
   switch (s) {
     case STEM_OK: return "STEM_OK";
@@ -617,12 +627,7 @@ stem_status stem_ffn_up_forward(stem_ctx* c, const void* x, const int32_t* ids, 
   u.A = static_cast<const bf16_t*>(x); u.lda = d;
   u.B = static_cast<const bf16_t*>(W_up); u.ldb = d;
   u.M = (int)T; u.N = F; u.K = d; u.C = Up; u.flag = c->flag; u.ws = c->splitk_ws; u.ws_bytes = c->splitk_bytes;
-  // One launch for both products, unless the buffers lie so that it matters which is first: G and H are stored while W_up is read and
-  // beside Up, and Up while E and the ids are read.  (G or H in Up's place is fine: a lane stores Up first.)
-  const size_t TF = (size_t)T * F * 2, Fd = (size_t)F * d * 2;
-  auto over = [&](const void* p, const void* q) { return p != q && overlap(p, TF, q, TF); };
-  const bool together = !overlap(save_G, TF, W_up, Fd) && !overlap(H, TF, W_up, Fd) &&
-                        !over(save_G, Up) && !over(H, Up) && !(E && (overlap(Up, TF, E, (size_t)E_rows * F * 2) || overlap(Up, TF, ids, (size_t)T * 4)));
+  const bool together = stem_route_gate_up_together(d, F, T, W_up, E, E_rows, ids, save_G, Up, H);
   if (!together) HIP_TRY(c, stem_gemm_bf16(c, K_GEMM_UP, OP_KC, OP_KC, EPI_BF16, u, s));
   GemmArgs a = u;    // G = x W_gate^T;  H = SiLU(G) * (Up [+ E[ids]])
   a.B = static_cast<const bf16_t*>(W_gate); a.C = nullptr;

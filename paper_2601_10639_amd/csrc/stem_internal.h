@@ -223,6 +223,9 @@ int stem_route_tile(const int32_t* M, const int32_t* N, int n, int tile_rows, in
 // whether the weight gradients may share a launch before dx (null: not wanted) as their buffers lie; W_up, dV, dW_up: null without an up projection
 int stem_route_weight_grads_apart(int d_model, int d_ff, int64_t T, const void* dy, const void* H, const void* dx, const void* W_gate,
                                   const void* W_up, const void* dV, const float* dW_gate, const float* dW_up);
+// whether stem_ffn_up_forward's gate and up product may share a launch as the buffers lie (E, ids, G may be null)
+int stem_route_gate_up_together(int d_model, int d_ff, int64_t T, const void* W_up, const void* E, int64_t E_rows, const void* ids,
+                                const void* G, const void* Up, const void* H);
 void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* route);
 // the gate (route[0..3]) and down (route[4..7]) products of a bf16 stem_ffn_forward call of T tokens, in a context made for as many
 void stem_route_forward(int d_model, int d_ff, int64_t T, int32_t* route);

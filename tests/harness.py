@@ -69,6 +69,15 @@ def route_weight_grads_apart(T, d, F, **at):
     return bool(L.lib().stem_route_weight_grads_apart(d, F, ctypes.c_int64(T), *[ctypes.c_void_p(at.get(k)) for k in names]))
 
 
+def route_gate_up_together(T, d, F, E_rows, **at):
+    """Whether the gate and up product may share a launch, as the buffers lie that are given by name: byte addresses, None for one not there."""
+    names = ("W_up", "E", "ids", "G", "Up", "H")
+    assert set(at) <= set(names)
+    p = {k: ctypes.c_void_p(at.get(k)) for k in names}
+    return bool(L.lib().stem_route_gate_up_together(d, F, ctypes.c_int64(T), p["W_up"], p["E"], ctypes.c_int64(E_rows), p["ids"], p["G"],
+                                                    p["Up"], p["H"]))
+
+
 def route_sort(T, V):
     return L.lib().stem_route_sort(ctypes.c_int64(T), V)
 

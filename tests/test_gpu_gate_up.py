@@ -68,3 +68,37 @@ def test_gate_and_up_product_over_each_other_and_over_what_they_read():
         assert torch.equal(_forward(ctx, inp, E, out if at == 0 else None, Up, out if at else None, w), y)
         assert torch.equal(out, H if at else G)
     ctx.close()
+
+
+@pytest.mark.parametrize("T,d,F,tile,split", [
+    (390, 3072, 2112, (128, 128), True),      # the up product in two K slices, whose sum is stored when all have read W_up
+    (1345, 576, 4096, (192, 128), False),
+    (1500, 320, 4160, (256, 128), False),
+    (1990, 320, 4160, (256, 256), False),
+])
+@pytest.mark.parametrize("table", [True, False])
+def test_outputs_over_w_up_take_two_launches_on_every_tiling(T, d, F, tile, split, table):
+    assert Hn.route_tiles(T, F, d, 1, Hn.EPI_GATE)[1:3] == tile
+    assert (Hn.route_tiles(T, F, d, 1, Hn.EPI_BF16, L.lib().stem_route_splitk_bytes(d, F, T))[3] > 1) == split
+    inp, ctx = _layer(T, d, F, 97)
+    f64 = {k: inputs.to_f64(v) for k, v in inp.items() if k != "ids"}
+    yo, fw = O.up_forward(f64["x"], inp["ids"].cpu().numpy(), f64["W_gate"], f64["W_up"], f64["W_down"], f64["E"] if table else None)
+    ref = {"G": fw["g"], "Up": fw["up"], "H": fw["h"]}
+    E = inp["E"] if table else None
+    for over in [None, "G", "H"] + (["Up"] if split else []):
+        out = {k: torch.empty(T, F, dtype=torch.bfloat16, device=DEV) for k in ref}
+        w = inp["W_up"]
+        if over:
+            room = torch.empty(T * F + F * d, dtype=torch.bfloat16, device=DEV)
+            w = room[T * F // 2 // 8 * 8:][:F * d].view(F, d)
+            w.copy_(inp["W_up"])
+            out[over] = room[:T * F].view(T, F)
+        at = {k: v.data_ptr() for k, v in out.items()}
+        if table:
+            at.update(E=E.data_ptr(), ids=inp["ids"].data_ptr())
+        assert Hn.route_gate_up_together(T, d, F, E.shape[0] if table else 0, W_up=w.data_ptr(), **at) == (over is None)
+        y = _forward(ctx, inp, E, out["G"], out["Up"], out["H"], w)
+        errs = {k: Hn.max_rel(out[k].float().cpu(), v) for k, v in ref.items()}
+        errs["y"] = Hn.max_rel(y.float().cpu(), yo)
+        assert all(v <= Hn.TOL["bf16"] for v in errs.values()), (over, errs)
+    ctx.close()

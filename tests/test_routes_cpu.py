@@ -5,7 +5,7 @@ import random
 import pytest
 
 from paper_2601_10639_amd import stemlib as L
-from tests.harness import DECODE, EPI_BF16, EPI_F32, EPI_GATE, FEW_ROW, TILES, route_forward, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
+from tests.harness import DECODE, EPI_BF16, EPI_F32, EPI_GATE, FEW_ROW, TILES, route_forward, route_gate_up_together, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
 
 
 def test_no_k_slice_is_empty():
@@ -104,3 +104,26 @@ def test_host_table_calls_that_share_the_link_where_that_was_measured_shorter(ro
 def test_gate_products_that_touch_the_down_products_weights(T, d, F, gate, touched):
     assert route_forward(T, d, F)[0][0] == gate
     assert L.lib().stem_route_touch_bytes(d, F, ctypes.c_int64(T)) == (2 * d * F if touched else 0)
+
+
+@pytest.mark.parametrize("table", [False, True])
+def test_gate_and_up_product_over_buffers_that_the_other_reads_do_not_share_a_launch(table):
+    T, d, F, V = 300, 256, 832, 500
+    TF = T * F * 2
+    size = dict(W_up=F * d * 2, E=V * F * 2, ids=T * 4, G=TF, Up=TF, H=TF)
+    lie = {k: (i + 1) << 24 for i, k in enumerate(size) if table or k not in ("E", "ids")}
+
+    def share(**at):
+        return route_gate_up_together(T, d, F, V if table else 0, **{**lie, **at})
+
+    assert share() and share(G=None) and share(G=lie["Up"]) and share(H=lie["Up"]) and share(G=lie["H"])
+    for out, over in [(o, i) for o in ("G", "Up", "H") for i in lie if i != o and (o == "Up" or i in ("W_up", "Up"))]:
+        if out == "Up" and over in ("G", "H"):
+            continue                                       # asked as G and H over Up
+        at = lie[over]
+        assert share(**{out: at - TF}) and share(**{out: at + size[over]}), (out, over)
+        for p in (at - TF + 16, at + size[over] - 16, *([at] if over != "Up" else [])):
+            assert not share(**{out: p}), (out, over, p - at)
+    # what one after the other did not keep either: G and H over the table, the ids and each other
+    if table:
+        assert share(G=lie["E"]) and share(H=lie["ids"])
