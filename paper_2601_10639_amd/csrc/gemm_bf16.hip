@@ -298,13 +298,14 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   const int wave = load_wave ? wave_id - C::WAVES : wave_id;
   const int wm = wave / C::WN, wn = wave % C::WN;
   // Gate and up product in one: half of a wavefront's columns are C's, the other half Up's, so that the tile's B rows are, 32 * NJ / 2 at
-  // a time, of W_gate and of W_up in turn: what loader w brings (LOADERS is 4, WN 2) is of one of them.  As two launches the second
+  // a time, of W_gate and of W_up in turn: what a loader brings is of one of them.  As two launches the second
   // read Up back in an epilogue under which nothing else runs, all tiles at once, and small batches paid a launch, a prologue and a
   // split product's sum more.  Forward call, us, two launches / one, additive and dense layer: 1024 x 4096, 300 tokens 36.1 / 26.2 and
   // 34.6 / 25.9, 4096 tokens 123.2 / 116.5 and 107.8 / 102.2, 16384 tokens 425 / 398 and 401 / 378; 1216 x 3328, 5000 tokens 167 / 144 and
   // 161 / 141; 2048 x 8192, 700 tokens 95.2 / 91.3 and 93.5 / 89.3, 16384 tokens 1352 / 1319 and 1308 / 1286.  The tiling is choose_plan's
   // for a product of twice the width, and the best of the four or within 3 % of it at 16 layers.
   constexpr bool DUAL = EPI == EPI_GATE_DUAL || EPI == EPI_GATE_DUALE;
+  static_assert(!DUAL || LOADERS == 2 * C::WN, "a loader's B rows are one half of a wavefront's columns");
   constexpr int OUT_TN = DUAL ? C::TN / 2 : C::TN;   // columns of the output per tile
   int ntm = (p.M + C::TM - 1) / C::TM, ntn = (p.N + OUT_TN - 1) / OUT_TN;
   constexpr int BAND = (EPI == EPI_DH || EPI == EPI_DH_UP || EPI == EPI_DH_UPE) ? 7 : 4;   // see tile_at

@@ -11,6 +11,11 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+# the joint gate and up product of the layers with an up projection
+GATE_UP_TILE = {(1000, 512, 4160): (256, 256), (1300, 1152, 6016): (256, 128), (520, 64, 8192): (128, 128), (385, 128, 128): (128, 128),
+                (600, 512, 2112): (128, 128), (1535, 1088, 4032): (256, 256), (1345, 576, 4096): (256, 256)}
+
+
 # tile and K slices of dH (and the gate product beyond 512 tokens), dx, dx of two operand pairs, the weight gradients
 @pytest.mark.parametrize("T,d,F,routes", [
     # ragged last tiles; the last of 8 slices of 9 K tiles has two
@@ -32,6 +37,8 @@ def test_bf16_products_on_every_tiling(T, d, F, routes, up, table=True):
                             Hn.route_tiles(F, d, T, 1, Hn.EPI_F32))] == routes
     if T > 512:
         assert Hn.route_forward(T, d, F) == ((Hn.TILES, *routes[0]), (Hn.TILES, *routes[1]))
+    if up:
+        assert Hn.route_tiles(T, 2 * F, d, 1, Hn.EPI_GATE)[1:3] == GATE_UP_TILE[T, d, F]
     V = 300
     s = inputs.StemShape("tilings", d, F, V, 1, T, "bf16")
     inp = inputs.layer_inputs(s, seed=61, device=DEV, tokens=T)
