@@ -822,43 +822,44 @@ int64_t stem_sort_count_entries(int64_t max_tokens) {
 }
 
 // One launch up to 8192 ids, of workgroups that count ranks, while the vocabulary's bitmap is at most 32 KB (2^18 ids); beyond that
-// vocabulary, or with an output that lies over the ids, which those workgroups read while others write, one workgroup up to
-// 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 22 in a graph).  Counting is quadratic: 8192 ids
+// vocabulary, or where buffers of the call lie over each other (those workgroups read the ids and store all outputs at the same time), one
+// workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 22 in a graph).  Counting is quadratic: 8192 ids
 // 15.7 us against 22.3 on merged runs, 16384 ids 45 against 24.  Then runs of
 // 1024, while their number is one group of the merge's searches, and runs of 4096, us in a graph: 6000 ids 22 / 29, 16384
 // ids 25 / 32 (one workgroup 43, the digit passes below 140), 32768 ids 36 / 34, 65536 ids 58 / 38 (digit passes 182).
 // The digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
 // (262144 ids: 126 us against 640).
+static bool ranks_fit(int64_t T, int V) { return T <= RANK_MAX && V <= RANK_WORDS * 32; }
+
 int stem_route_sort(int64_t T, int V) {
   const int vbits = bits_for(V);
   if (T <= 4096 && vbits + bits_for((int)T) <= 32) return T <= 1024 ? SORT_ONE_1024 : SORT_ONE_4096;
-  if (T <= RANK_MAX && V <= RANK_WORDS * 32) return SORT_RANKS_8192;
+  if (ranks_fit(T, V)) return SORT_RANKS_8192;
   const bool short_runs = T <= MERGE_WAYS * 1024;
   if (T <= 262144 && vbits + (short_runs ? 10 : 12) <= 32) return short_runs ? SORT_RUNS_1024 : SORT_RUNS_4096;
   return SORT_DIGITS;
 }
 
-// whether no output of the sort lies over the ids
-static bool ids_apart(const int32_t* ids, int64_t T, int V, const void* sorted_ids, const void* perm, const void* uniq_ids,
-                      const void* seg_offsets, const void* n_uniq, const void* seg_of) {
+int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
+                          const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of) {
+  if (!ranks_fit(T, V)) return 0;
   const int64_t cap = std::min<int64_t>(T, V);
-  const struct { const void* at; int64_t n; } out[] = {{sorted_ids, T}, {perm, T}, {uniq_ids, cap}, {seg_offsets, cap + 1}, {n_uniq, 1}, {seg_of, T}};
-  const uintptr_t a = reinterpret_cast<uintptr_t>(ids);
-  for (const auto& o : out) {
-    const uintptr_t b = reinterpret_cast<uintptr_t>(o.at);
-    if (a < b + (size_t)o.n * 4 && b < a + (size_t)T * 4) return false;
-  }
-  return true;
+  const struct { const int32_t* at; int64_t n; } buf[] = {{ids, T}, {sorted_ids, T}, {perm, T}, {uniq_ids, cap}, {seg_offsets, cap + 1}, {n_uniq, 1}, {seg_of, T}};
+  for (const auto& p : buf)
+    for (const auto* q = buf; q < &p; ++q)
+      if (reinterpret_cast<uintptr_t>(p.at) < reinterpret_cast<uintptr_t>(q->at + q->n) &&
+          reinterpret_cast<uintptr_t>(q->at) < reinterpret_cast<uintptr_t>(p.at + p.n))
+        return 0;
+  return 1;
 }
 
 hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t* ids, int64_t T, int V,
                             int32_t* sorted_ids, int32_t* perm, int32_t* uniq_ids, int32_t* seg_offsets,
                             int32_t* n_uniq, hipStream_t s) {
   const int passes = (bits_for(V) + RADIX_BITS - 1) / RADIX_BITS;
-  const bool ranked = T <= RANK_MAX && V <= RANK_WORDS * 32;
   const int route = stem_route_sort(T, V);
   const int pos_bits = bits_for((int)std::min<int64_t>(T, 1 << 30));
-  if (ranked && ids_apart(ids, T, V, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of)) {
+  if (stem_route_sort_ranks(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of)) {
     ProfScope ps(ctx, K_SORT_FUSED, s);
     const int own = T <= 2048 ? 8 : 16;
     auto* const kernel = T <= 1024 ? sort_ranks_kernel<1, 8> : T <= 2048 ? sort_ranks_kernel<2, 8> : T <= 4096 ? sort_ranks_kernel<4, 16> : sort_ranks_kernel<8, 16>;
@@ -876,7 +877,7 @@ hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t
                          sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
     return hipGetLastError();
   }
-  if (route == SORT_RUNS_1024 || route == SORT_RUNS_4096 || route == SORT_RANKS_8192) {   // (the last: outputs over the ids)
+  if (route == SORT_RUNS_1024 || route == SORT_RUNS_4096 || route == SORT_RANKS_8192) {   // (the last: buffers over each other)
     const int items = route == SORT_RUNS_4096 ? 4 : 1, run_bits = items == 1 ? 10 : 12;
     const int R = items * 1024, runs = (int)((T + R - 1) / R);
     {

@@ -231,11 +231,15 @@ void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* 
 void stem_route_forward(int d_model, int d_ff, int64_t T, int32_t* route);
 int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   // a context's room for K slices
 int stem_route_sort(int64_t T, int V);   // SortRoute
+// whether the kernel that counts ranks sorts them, which it does where the size allows and no two of the call's buffers overlap
+int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
+                          const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of);
 int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, touched by the gate product of that call
 int stem_route_copy_streams(int64_t rows, int64_t row_bytes);   // how many copy streams host-table calls of this many rows take in turn
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
 }
-// SORT_ONE_*: one launch, ranks by counting or, for vocabularies beyond 2^18, the passes of one workgroup; SORT_RANKS_8192: ranks by counting
+// By size.  SORT_ONE_* and SORT_RANKS_8192: ranks by counting where stem_route_sort_ranks says so, else the passes of one workgroup up to
+// 4096 ids and merged runs of 1024 beyond.
 enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS, SORT_RANKS_8192 };
 
 // Bytes of W_down that the gate product of a decode-sized call touches, a dword per 128-byte line behind its first K tiles, so that

@@ -82,6 +82,13 @@ def route_sort(T, V):
     return L.lib().stem_route_sort(ctypes.c_int64(T), V)
 
 
+def route_sort_ranks(T, V, **at):
+    """Whether the kernel that counts ranks sorts a call whose buffers lie at these byte addresses."""
+    names = ("ids", "sorted_ids", "perm", "uniq_ids", "seg_offsets", "n_uniq", "seg_of")
+    assert set(at) <= set(names)
+    return bool(L.lib().stem_route_sort_ranks(ctypes.c_int64(T), V, *[ctypes.c_void_p(at.get(k)) for k in names]))
+
+
 def hip_forward_backward(ctx, inp, save_H=True, want_dx=True, after_forward=None):
     """forward + backward through libstem; returns device tensors.  `after_forward()` runs between the two calls."""
     dev = inp["x"].device

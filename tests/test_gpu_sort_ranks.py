@@ -60,3 +60,39 @@ def test_ids_outside_the_table_count_as_the_clamped_ones(T):
     assert e.value.status == L.STEM_ERR_ID_RANGE
     Hn.check_integers(eg, np.clip(ids.astype(np.int64), 0, V - 1).astype(np.int32))
     ctx.close()
+
+
+@pytest.mark.parametrize("T,V", [(7, 40), (1000, 300), (1000, 5000), (4096, 1 << 18), (4097, 1 << 18), (8192, 128256)])
+def test_outputs_over_the_ids_and_over_each_other(T, V):
+    """Every output over the ids, whole and by one element, and the sorted ids where the distinct ones go (up to 4096 ids: beyond, the
+    runs' kernels number the distinct ids while others still read the sorted ones).  What a call does not write stays as it was."""
+    ids = inputs.zipf_ids(T, V, seed=93).astype(np.int32)
+    ctx = L.stem_create(64, 64, V, L.STEM_BF16, T, 0)
+    cap = min(T, V)
+    size = dict(sorted_ids=T, perm=T, uniq_ids=cap, seg_offsets=cap + 1, n_uniq=1)
+    U = len(np.unique(ids))
+
+    def call(over):
+        out = {k: torch.full((n,), -9, dtype=torch.int32, device=DEV) for k, n in size.items()}
+        room = torch.full((2 * T + 2,), -9, dtype=torch.int32, device=DEV)
+        room[:T] = torch.from_numpy(ids).to(DEV)
+        for name, at in over.items():
+            out[name] = out[at] if isinstance(at, str) else room[at:at + size[name]]
+        lie = {k: v.data_ptr() for k, v in out.items()}
+        assert Hn.route_sort_ranks(T, V, ids=room.data_ptr(), **lie) == (not over)
+        L.stem_embed_grad(ctx, room[:T], None, out["sorted_ids"], out["perm"], out["uniq_ids"], out["seg_offsets"], out["n_uniq"], None, T=T)
+        return out
+
+    whole = call({})
+    Hn.check_integers(whole, ids)
+    assert bool((whole["uniq_ids"][U:] == -9).all()) and bool((whole["seg_offsets"][U + 1:] == -9).all())
+    for name in size:
+        for at in (0, T - 1):
+            Hn.check_integers(call({name: at}), ids)
+    if T <= 4096 and T <= V:
+        out = call({"sorted_ids": "uniq_ids"})
+        assert int(out["n_uniq"].item()) == U
+        for name, n in (("uniq_ids", U), ("seg_offsets", U + 1), ("perm", T)):
+            assert torch.equal(out[name][:n], whole[name][:n])
+    L.stem_sync_status(ctx)
+    ctx.close()
