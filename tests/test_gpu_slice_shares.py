@@ -1,4 +1,6 @@
 """The few-row kernel's K slices: each workgroup of a tile finishes a share of its rows, or leaves it to the last to arrive."""
+import ctypes
+
 import pytest
 import torch
 
@@ -120,9 +122,12 @@ def test_output_over_what_the_slices_read(T, d, F, slices):
     (112, 1024, 3904),        # the fewest tokens, 7.99 MB of weights
     (128, 2048, 8192),        # all lines of the largest, four by each thread
     (129, 1536, 5184),        # just below the most from 129 tokens on
-    (384, 1536, 5120),        # few-row gate product, whose grid does not come to all lines
+    (384, 1536, 5120),        # few-row gate product
+    (128, 16000, 1024),       # the decode kernel's grid comes to 16.8 of 32.8 MB
+    (300, 6144, 1216),        # the few-row kernel's to 11.2 of 14.9 MB
 ])
 def test_gate_product_that_touches_the_down_products_weights(T, d, F):
+    assert L.lib().stem_route_touch_bytes(d, F, ctypes.c_int64(T)) == 2 * d * F
     V = 300
     s = inputs.StemShape("touch", d, F, V, 1, T, "bf16")
     inp = inputs.layer_inputs(s, seed=83, device=DEV, tokens=T)
