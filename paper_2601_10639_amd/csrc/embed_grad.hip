@@ -1,5 +1,5 @@
 // Gradient of the per-layer table, restricted to the rows a batch touches:
-// stable sort of (token id, position) by radix passes (in LDS, as merged runs, or digit by digit), distinct ids with run offsets, and a
+// stable sort of (token id, position) by counting ranks or by radix passes (in LDS, as merged runs, or digit by digit), distinct ids with run offsets, and a
 // fixed-order segmented sum of the per-token row gradients.  Integer results are unique,
 // floating sums use one fixed association, so every run gives the same bits.
 #include <algorithm>
@@ -357,12 +357,12 @@ __global__ __launch_bounds__(1024) void sort_lds_kernel(const int32_t* __restric
   }
 }
 
-// ---- up to 4096 ids: ranks by counting ----------------------------------------------------------------
+// ---- up to 8192 ids: ranks by counting ----------------------------------------------------------------
 // One workgroup's passes are a chain of barriers, and it has one compute unit of the chip.  Here each workgroup places 8 or 16 ids and
 // looks at all of them: an id's place is the number of smaller (id, position) keys, counted by ballots, 64 keys a compare; where its run
 // begins, the number of keys below (id, 0); the number of its run, the distinct ids below it, from a bitmap of the ids in LDS and its
 // prefix sums.  Nothing passes between workgroups, so one launch does it all.  What bounds it is the launch, the id loads and
-// five barriers, from some 2000 ids on the scalar unit, which counts each compare's bits.  us in a graph, before (one workgroup's passes,
+// four barriers, from some 2000 ids on the scalar unit, which counts each compare's bits.  us in a graph, before (one workgroup's passes,
 // beyond 4096 ids runs and their merge) / this, Zipf ids: 128 ids 5.8 / 4.1, 1000 7.5 / 4.4, 1999 12.6 / 5.3, 4096 13.4 / 7.6, 8192
 // 22.4 / 15.7; one id for all: 4096 13.2 / 7.8.  (16 ids a workgroup up to 2048: 1000 ids 4.9, 1999 6.1; 32: 6.0 and 7.7.)
 constexpr int RANK_WORDS = 8192;                 // 32 KB of bitmap: vocabularies up to 2^18
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(1024) void sort_ranks_kernel(const int32_t* __restr
       below += __popcll(__ballot(key[c] < k));
       start += __popcll(__ballot(key[c] < k_id));
     }
-    mine = lane == q ? below | start << 16 : mine;   // sums up to 4096 each
+    mine = lane == q ? below | start << 16 : mine;   // sums over the wavefronts up to 8192 each
   }
   if (lane < OWN) counts[wave][lane] = mine;
   __syncthreads();                               // counts, and all ids are in the bitmap

@@ -189,7 +189,9 @@ struct GemmArgs {
   bf16_t* outdU;   // EPI_DH
   bf16_t* outdG;   // EPI_DH
   int32_t* flag;
-  float* ws;       // room for split-K launches: [ksplit][M][N] fp32 partial products; null = never split
+  // room for split-K launches, null = never split.  fp32 partial products: [ksplit][M][N] of the large kernel; whole tiles,
+  // [ksplit][tiles][...], of the decode and the few-row kernel (128x64), which is more where M or N is ragged
+  float* ws;
   size_t ws_bytes; // capacity of ws
   union {
     int32_t* tickets;           // decode kernel: the context's tickets; null = never split
