@@ -36,7 +36,8 @@
  *     stem_profile_enable.  No call that enqueues work allocates or frees.
  *     Calls on one context must not overlap in time (they share that scratch).
  *   - The contexts of a device share two side streams, on which rows of host-resident
- *     tables are copied; they live as long as there is a context on the device.
+ *     tables are copied; they live as long as there is a context on the device.  (The
+ *     second is created by the first prefetch call that takes it.)
  */
 #ifndef STEM_H
 #define STEM_H

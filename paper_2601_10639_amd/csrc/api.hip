@@ -57,24 +57,28 @@ stem_status enter(stem_ctx* c, int64_t T) {
   return STEM_OK;
 }
 
-// The streams on which the contexts of a device copy rows from host memory: two for all of them, made with the first context and
-// destroyed with the last.  Calls of STEM_PF_LONG bytes of rows and more all go on the first: their rows cross the link one call's
-// after another's, in the order in which the forward passes wait for them.  Shorter calls take both in turn, so that one call's rows
-// are on the link while it would stand still between the rows of two others, and only the second
-// while a long call's are under way on the first.  Never more than two copies run, and they fit the compute units that the chunks' products leave free.
+// The streams on which the contexts of a device copy rows from host memory: one that is made with the first context, and a second that the
+// first call makes which needs it; both go with the last context.  Calls of STEM_PF_LONG bytes of rows and more all take the first: their
+// rows cross the link one call's after another's, in the order in which the forward passes wait for them.  Shorter calls take both in
+// turn where there are several contexts, so that one call's rows are on the link while it would stand still between those of two
+// others, and only the second while a long call's are under way on the first.  No more than two copies run, and they fit the compute
+// units that the chunks' products leave free.
+// (The second not before it is needed: a third hardware queue in the process, even an idle one, costs a decode step up to 1.3 %, 256
+// tokens through 16 layers of 2048 x 8192 650 / 660 us.)
 struct CopyStreams { hipStream_t stream[2]; int64_t users; unsigned turn; bool long_rows; };
 constexpr int MAX_DEVICES = 64;
 CopyStreams g_copy[MAX_DEVICES];
 std::mutex g_copy_mutex;
 
+bool busy(hipStream_t s) { return s && hipStreamQuery(s) == hipErrorNotReady; }
+
 hipError_t copy_streams_get(int device, hipStream_t* first) {
   if (device < 0 || device >= MAX_DEVICES) return hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(g_copy_mutex);
   CopyStreams& q = g_copy[device];
-  for (hipStream_t& s : q.stream) {
-    if (s) continue;
-    const hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
-    if (e != hipSuccess) { s = nullptr; return e; }
+  if (!q.stream[0]) {
+    const hipError_t e = hipStreamCreateWithFlags(&q.stream[0], hipStreamNonBlocking);
+    if (e != hipSuccess) { q.stream[0] = nullptr; return e; }
   }
   ++q.users;
   *first = q.stream[0];
@@ -85,21 +89,26 @@ void copy_streams_put(int device) {   // the device is current and idle
   std::lock_guard<std::mutex> lock(g_copy_mutex);
   CopyStreams& q = g_copy[device];
   if (--q.users > 0) return;
-  for (hipStream_t& s : q.stream) {
-    (void)hipStreamDestroy(s);
-    s = nullptr;
-  }
+  for (hipStream_t s : q.stream)
+    if (s) (void)hipStreamDestroy(s);
+  q = {};
 }
 
 // In front of a call's first copy: the stream for all of them.
-void copies_begin(stem_ctx* c, int64_t rows) {
+hipError_t copies_begin(stem_ctx* c, int64_t rows) {
   std::lock_guard<std::mutex> lock(g_copy_mutex);
   CopyStreams& q = g_copy[c->device];
   const bool is_long = stem_route_copy_streams(rows, (int64_t)c->desc.d_ff * esize(c)) == 1;
-  if (!is_long && q.long_rows) q.long_rows = hipStreamQuery(q.stream[0]) == hipErrorNotReady;
-  c->side = q.stream[is_long ? 0 : q.long_rows ? 1 : q.turn++ & 1];
+  if (!is_long && q.long_rows) q.long_rows = busy(q.stream[0]);
+  const int i = is_long ? 0 : q.long_rows ? 1 : q.users > 1 ? q.turn++ & 1 : 0;
   q.long_rows |= is_long;
+  if (!q.stream[i]) {
+    const hipError_t e = hipStreamCreateWithFlags(&q.stream[i], hipStreamNonBlocking);
+    if (e != hipSuccess) { q.stream[i] = nullptr; return e; }
+  }
+  c->side = q.stream[i];
   c->copies_open = 1;
+  return hipSuccess;
 }
 
 // Waits for the copies of this context's last prefetch, before its pinned arrays are written again.  A call that ended with an error
@@ -110,14 +119,17 @@ hipError_t copies_done(stem_ctx* c) {
   return e;
 }
 
-// Clears device memory before it returns, on a stream of its own: on a copy stream it would wait for other contexts' rows.
-hipError_t zero_now(void* p, size_t bytes) {
-  hipStream_t s;
-  hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
-  if (e != hipSuccess) return e;
-  e = stem_fill_zero(p, bytes, s);
-  const hipError_t done = hipStreamSynchronize(s);
-  (void)hipStreamDestroy(s);
+// Clears device memory before it returns: on the copy stream, or while other contexts' rows are under way there, which it would wait for,
+// on a stream of its own.
+hipError_t zero_now(void* p, size_t bytes, hipStream_t copies) {
+  hipStream_t s = copies;
+  const bool own = busy(copies);
+  if (own) {
+    const hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e != hipSuccess) return e;
+  }
+  const hipError_t e = stem_fill_zero(p, bytes, s), done = hipStreamSynchronize(s);
+  if (own) (void)hipStreamDestroy(s);
   return e != hipSuccess ? e : done;
 }
 
@@ -315,7 +327,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->uniq_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->remap_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(copy_streams_get(device, &c->side));
-  if (e == hipSuccess && c->tickets) ok(zero_now(c->rounds, STEM_TICKETS * 12));
+  if (e == hipSuccess && c->tickets) ok(zero_now(c->rounds, STEM_TICKETS * 12, c->side));
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
   ok(hipEventCreateWithFlags(&c->copied, hipEventDisableTiming));
   for (int i = 0; i < 2; ++i) ok(hipEventCreateWithFlags(&c->pack_done[i], hipEventDisableTiming));
@@ -863,7 +875,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
     return fail(c, STEM_ERR_WORKSPACE, "stem_prefetch_rows: %lld distinct ids but E_compact holds %lld rows",
                 (long long)U, (long long)cap);
 
-  copies_begin(c, U);
+  HIP_TRY(c, copies_begin(c, U));
   if (c->prefetch_mode == STEM_PREFETCH_MEMCPY) {
     if (T > 0) HIP_TRY(c, hipMemcpyAsync(remap, c->remap_pinned, (size_t)T * 4, hipMemcpyHostToDevice, c->side));
     // Pack the rows into pinned staging with a few host threads and copy chunk by chunk,
@@ -1003,7 +1015,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
                 (long long)n_miss, (long long)cap);
   }
 
-  copies_begin(c, n_miss);
+  HIP_TRY(c, copies_begin(c, n_miss));
   HIP_TRY(c, stem_copy_lists_kernel(c, c->remap_pinned, remap, T, c->order_pinned, c->order_dev, n_miss, c->max_tokens, c->side));
   {
     int64_t k0 = 0;

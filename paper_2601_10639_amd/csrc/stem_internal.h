@@ -237,7 +237,7 @@ int stem_route_sort(int64_t T, int V);   // SortRoute
 int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
                           const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of);
 int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, touched by the gate product of that call
-int stem_route_copy_streams(int64_t rows, int64_t row_bytes);   // how many copy streams host-table calls of this many rows take in turn
+int stem_route_copy_streams(int64_t rows, int64_t row_bytes);   // how many copy streams host-table calls of this many rows take
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
 }
 // By size.  SORT_ONE_* and SORT_RANKS_8192: ranks by counting where stem_route_sort_ranks says so, else the passes of one workgroup up to
