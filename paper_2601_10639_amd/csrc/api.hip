@@ -114,7 +114,7 @@ hipError_t copies_begin(stem_ctx* c, int64_t rows) {
 // Waits for the copies of this context's last prefetch, before its pinned arrays are written again.  A call that ended with an error
 // between its first copy and their event has left copies that no event stands for: then the whole stream is waited for.
 hipError_t copies_done(stem_ctx* c) {
-  const hipError_t e = c->copies_open ? hipStreamSynchronize(c->side) : hipEventSynchronize(c->copied);
+  const hipError_t e = c->copies_open ? hipStreamSynchronize(c->side) : hipEventSynchronize(c->done);
   if (e == hipSuccess) c->copies_open = 0;
   return e;
 }
@@ -166,7 +166,7 @@ void release(stem_ctx* c) {
   (void)hipFree(c->inst_dev);
   if (c->side) copy_streams_put(c->device);
   if (c->ready) (void)hipEventDestroy(c->ready);
-  if (c->copied) (void)hipEventDestroy(c->copied);
+  if (c->promoted) (void)hipEventDestroy(c->promoted);
   for (int i = 0; i < 2; ++i) if (c->pack_done[i]) (void)hipEventDestroy(c->pack_done[i]);
   if (c->prof_ev) {
     for (int i = 0; i < 2 * STEM_MAX_PROF_EVENTS; ++i) if (c->prof_ev[i]) (void)hipEventDestroy(c->prof_ev[i]);
@@ -329,7 +329,8 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(copy_streams_get(device, &c->side));
   if (e == hipSuccess && c->tickets) ok(zero_now(c->rounds, STEM_TICKETS * 12, c->side));
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
-  ok(hipEventCreateWithFlags(&c->copied, hipEventDisableTiming));
+  ok(hipEventCreateWithFlags(&c->promoted, hipEventDisableTiming));
+  c->done = c->ready;
   for (int i = 0; i < 2; ++i) ok(hipEventCreateWithFlags(&c->pack_done[i], hipEventDisableTiming));
   c->slot = static_cast<int32_t*>(malloc((size_t)desc->vocab * 4));
   if (e != hipSuccess || !c->slot) {
@@ -913,7 +914,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
     if (nchunks > 1) { c->pf_chunks = nchunks; c->pf_T = T; c->pf_chunk_tokens = chunk_tokens; }
   }
   HIP_TRY(c, hipEventRecord(c->ready, c->side));
-  HIP_TRY(c, hipEventRecord(c->copied, c->side));
+  c->done = c->ready;
   c->copies_open = 0;
   *ready_event = c->ready;
   return STEM_OK;
@@ -1082,14 +1083,16 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
     ++n_inst;
   }
   for (int64_t j = 0; j < U; ++j) c->slot[c->uniq_pinned[j]] = -1;
+  c->done = c->ready;
   if (n_inst > 0) {
     HIP_TRY(c, hipMemcpyAsync(c->inst_dev, c->inst_pinned, (size_t)n_inst * 4, hipMemcpyHostToDevice, c->side));
     HIP_TRY(c, hipMemcpyAsync(c->inst_dev + c->max_tokens, c->inst_pinned + c->max_tokens, (size_t)n_inst * 4,
                               hipMemcpyHostToDevice, c->side));
     HIP_TRY(c, stem_copy_rows_kernel(c, E_dev, c->inst_dev, c->inst_dev + c->max_tokens, n_inst, (int64_t)row_bytes,
                                      E_dev, c->side));
+    HIP_TRY(c, hipEventRecord(c->promoted, c->side));
+    c->done = c->promoted;
   }
-  HIP_TRY(c, hipEventRecord(c->copied, c->side));
   c->copies_open = 0;
   return STEM_OK;
 }

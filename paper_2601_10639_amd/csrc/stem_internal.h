@@ -83,8 +83,9 @@ struct stem_ctx {
   // host-resident table mode
   hipStream_t side;      // the one of the device's two copy streams that the last prefetch took
   hipEvent_t ready;      // rows and remap of the last prefetch are there
-  hipEvent_t copied;     // and everything else the call has put on the side stream is done
-  int copies_open;       // a prefetch has put copies on the side stream and not recorded `copied`
+  hipEvent_t promoted;   // and the rows it has put into the cache are copied too
+  hipEvent_t done;       // the one of these two that is behind all copies of the last prefetch
+  int copies_open;       // a prefetch has put copies on the side stream and not recorded that event
   int32_t* slot;         // host [V], -1 = absent
   int32_t* uniq_pinned;  // pinned host [max_tokens]
   int32_t* remap_pinned; // pinned host [max_tokens]
