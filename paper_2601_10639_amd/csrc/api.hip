@@ -58,11 +58,11 @@ stem_status enter(stem_ctx* c, int64_t T) {
 }
 
 // The streams on which the contexts of a device copy rows from host memory: one that is made with the first context, and a second that the
-// first call makes which needs it; both go with the last context.  Calls of STEM_PF_LONG bytes of rows and more all take the first: their
-// rows cross the link one call's after another's, in the order in which the forward passes wait for them.  Shorter calls take both in
+// first call makes which needs it; both go with the last context.  What stem_route_copy_streams answers 1 for takes the first: such calls'
+// rows cross the link one call's after another's, in the order in which the forward passes wait for them.  Other calls take both in
 // turn where there are several contexts, so that one call's rows are on the link while it would stand still between those of two
-// others, and only the second while a long call's are under way on the first.  No more than two copies run, and they fit the compute
-// units that the chunks' products leave free.
+// others.  While rows of STEM_PF_LONG bytes and more are under way on the first, all shorter calls take the second.  No more than two
+// copies run, and they fit the compute units that the chunks' products leave free.
 // (The second not before it is needed: a third hardware queue in the process, even an idle one, costs a decode step up to 1.3 %, 256
 // tokens through 16 layers of 2048 x 8192 650 / 660 us.)
 struct CopyStreams { hipStream_t stream[2]; int64_t users; unsigned turn; bool long_rows; };
@@ -95,12 +95,13 @@ void copy_streams_put(int device) {   // the device is current and idle
 }
 
 // In front of a call's first copy: the stream for all of them.
-hipError_t copies_begin(stem_ctx* c, int64_t rows) {
+hipError_t copies_begin(stem_ctx* c, int64_t T, int64_t rows) {
   std::lock_guard<std::mutex> lock(g_copy_mutex);
   CopyStreams& q = g_copy[c->device];
-  const bool is_long = stem_route_copy_streams(rows, (int64_t)c->desc.d_ff * esize(c)) == 1;
+  const bool is_long = rows * (int64_t)(c->desc.d_ff * esize(c)) >= STEM_PF_LONG;
   if (!is_long && q.long_rows) q.long_rows = busy(q.stream[0]);
-  const int i = is_long ? 0 : q.long_rows ? 1 : q.users > 1 ? q.turn++ & 1 : 0;
+  const bool in_turn = q.users > 1 && stem_route_copy_streams(c->desc.d_model, c->desc.d_ff, c->desc.dtype, T, rows) == 2;
+  const int i = is_long ? 0 : q.long_rows ? 1 : in_turn ? q.turn++ & 1 : 0;
   q.long_rows |= is_long;
   if (!q.stream[i]) {
     const hipError_t e = hipStreamCreateWithFlags(&q.stream[i], hipStreamNonBlocking);
@@ -227,7 +228,11 @@ void stem_route_forward(int d, int F, int64_t T, int32_t* route) {
 
 int stem_route_touch_bytes(int d, int F, int64_t T) { return touch_bytes(forward_route(T, F, d, F), T, d, F); }
 
-int stem_route_copy_streams(int64_t rows, int64_t row_bytes) { return rows * row_bytes >= STEM_PF_LONG ? 1 : 2; }
+int stem_route_copy_streams(int d, int F, int dtype, int64_t T, int64_t rows) {
+  const int64_t bytes = rows * F * (dtype == STEM_BF16 ? 2 : 4);
+  const bool one = bytes >= STEM_PF_LONG || T * d >= rows * (dtype == STEM_BF16 ? 7500 : 1250) || (T <= 1024 && (int64_t)d * F >= 12 << 20);
+  return one ? 1 : 2;
+}
 
 void stem_exchange_polls(stem_ctx* c, int polls) { c->polls = polls; }
 
@@ -876,7 +881,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
     return fail(c, STEM_ERR_WORKSPACE, "stem_prefetch_rows: %lld distinct ids but E_compact holds %lld rows",
                 (long long)U, (long long)cap);
 
-  HIP_TRY(c, copies_begin(c, U));
+  HIP_TRY(c, copies_begin(c, T, U));
   if (c->prefetch_mode == STEM_PREFETCH_MEMCPY) {
     if (T > 0) HIP_TRY(c, hipMemcpyAsync(remap, c->remap_pinned, (size_t)T * 4, hipMemcpyHostToDevice, c->side));
     // Pack the rows into pinned staging with a few host threads and copy chunk by chunk,
@@ -1016,7 +1021,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
                 (long long)n_miss, (long long)cap);
   }
 
-  HIP_TRY(c, copies_begin(c, n_miss));
+  HIP_TRY(c, copies_begin(c, T, n_miss));
   HIP_TRY(c, stem_copy_lists_kernel(c, c->remap_pinned, remap, T, c->order_pinned, c->order_dev, n_miss, c->max_tokens, c->side));
   {
     int64_t k0 = 0;

@@ -44,17 +44,7 @@ enum StemKernelId {
 // with a copy stream per context, 240 tiles 4.97 / 4.69 and 4.13 / 4.59 with one for all, 224 tiles 4.60 / 4.70 and 4.11 / 4.64; 16384
 // tokens 240 tiles 1.42 / 1.74, 224 tiles 1.42 / 1.69; 1024 x 4096, 16384 tokens 0.652 / 0.870 and 0.648 / 0.843.
 #define STEM_PF_CHUNK_TILES 224
-// Bytes of rows from which host-table calls follow each other on one copy stream instead of two in turn.  ms, calls in turn on three
-// contexts / two / by itself, one stream / two: 512 x 1536, 4096 tokens (4 MB) 0.096 / 0.096 / 0.124 and 0.080 / 0.081 / 0.124, 65536
-// tokens (33 MB) 0.647 / 0.645 / 0.805 and 0.615 / 0.635 / 0.809; 1024 x 4096, 4096 tokens (12 MB) 0.227 / 0.227 / 0.261 and 0.209 /
-// 0.228 / 0.261, 8192 tokens 0.381 / 0.381 / 0.442 and 0.364 / 0.393 / 0.443, 16384 tokens 0.647 / 0.643 / 0.695 and 0.612 / 0.631 /
-// 0.702, 65536 tokens (89 MB) 1.717 / 1.713 / 1.839 and 1.682 / 1.685 / 1.853; 2048 x 8192, 1000 tokens 0.163 / 0.163 / 0.199 and 0.173 /
-// 0.170 / 0.198, 4096 tokens (25 MB) 0.476 / 0.470 / 0.571 and 0.459 / 0.506 / 0.568, 24576 tokens (104 MB) 1.942 / 1.932 / 2.060 and
-// 1.915 / 1.933 / 2.055, 40000 tokens (151 MB) 2.836 / 2.822 / 2.975 and 3.013 / 2.925 / 2.967, 65536 tokens (216 MB) 4.138 / 4.121 /
-// 4.365 and 4.862 / 4.820 / 4.362.  A stream for each context: 512 x 1536, 4096 tokens 0.081 / 0.081 / 0.121, 65536 tokens 0.621 / 0.633 /
-// 0.805; 1024 x 4096, 4096 tokens 0.218 / 0.228 / 0.260, 8192 tokens 0.382 / 0.392 / 0.440, 16384 tokens 0.626 / 0.630 / 0.693, 65536 tokens
-// 1.753 / 1.688 / 1.833; 2048 x 8192, 1000 tokens 0.183 / 0.170 / 0.198, 4096 tokens 0.492 / 0.502 / 0.563, 24576 tokens 2.113 / 1.932 / 2.056,
-// 40000 tokens 3.320 / 2.939 / 2.964, 65536 tokens 5.234 / 4.786 / 4.367.
+// Bytes of rows from which a host-table call is long (api.hip): it takes the first copy stream, and the others the second meanwhile
 #define STEM_PF_LONG ((int64_t)128 << 20)
 
 struct stem_ctx {
@@ -238,7 +228,18 @@ int stem_route_sort(int64_t T, int V);   // SortRoute
 int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
                           const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of);
 int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, touched by the gate product of that call
-int stem_route_copy_streams(int64_t rows, int64_t row_bytes);   // how many copy streams host-table calls of this many rows take
+// How many copy streams host-table calls of T tokens and this many distinct rows take in turn.  With one the link stands still between two
+// calls' rows, and a copy that waits for compute units finds them taken by tiles (15 to 60 us a call); two hold 32 compute units
+// instead of 16, and where products weigh as much as the rows, that and the later first rows cost more.  The line: 15 kFLOP of products
+// per byte of rows (bf16 products of 1 PFLOP/s then take three quarters of the rows' time; the fp32 ones run at a thirteenth of that), and up
+// to 1024 tokens layers of 12 M weights a matrix, whose products are one round on all compute units.  Calls in turn on three contexts, us, a
+// stream for each / one / two in turn: 512 x 1536, 2000 tokens 52 / 65 / 55; 1024 x 4096, 2000 tokens 144 / 144 / 136, 8192 tokens 386 /
+// 374 / 354, 65536 tokens (12 kFLOP a byte) 1727 / 1691 / 1643; 1536 x 5120, 2000 tokens 175 / 175 / 157, 49152 tokens (14.7) 2154 / 1978 / 1954;
+// 2048 x 8192, 4096 tokens 495 / 470 / 453, 16384 tokens (14.4) 1462 / 1404 / 1357; against 1472 x 5248, vocabulary 8499, 12668 tokens (15.4)
+// 591 / 495 / 515; 2048 x 8192, vocabulary 30000, 16384 tokens (17.6) 1360 / 1170 / 1240, 65536 tokens (20.3) 5234 / 4138 / 4862, 700 tokens 147 /
+// 124 / 146; fp32, 256 x 1024, 8192 tokens (0.9) 212 / 203 / 197, 512 x 2048, vocabulary 8000, 2000 tokens (1.5) 156 / 131 / 149.  On two contexts two in
+// turn are within 1 % of a stream for each, and of one but at 8192 tokens of 1024 x 4096 (381 / 393) and 4096 of 2048 x 8192 (470 / 510).
+int stem_route_copy_streams(int d_model, int d_ff, int dtype, int64_t T, int64_t rows);
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
 }
 // By size.  SORT_ONE_* and SORT_RANKS_8192: ranks by counting where stem_route_sort_ranks says so, else the passes of one workgroup up to

@@ -78,17 +78,24 @@ def test_weight_gradients_over_buffers_that_are_read_before_them_do_not_share_a_
                         assert route_weight_grads_apart(T, d, F, **{**q, grad: at}) == shares, (up, grad, over, with_dx, at)
 
 
-@pytest.mark.parametrize("rows,F,streams", [
-    # three contexts in turn, one copy stream / two in turn, ms
-    (1433, 1536, 2),        # 4096 tokens: 0.096 / 0.080
-    (1416, 4096, 2),        # 4096 tokens: 0.227 / 0.209
-    (4138, 4096, 2),        # 16384 tokens: 0.647 / 0.612
-    (6332, 8192, 2),        # 24576 tokens: 1.942 / 1.915
-    (9189, 8192, 1),        # 40000 tokens: 2.836 / 3.013
-    (13209, 8192, 1),       # 65536 tokens: 4.138 / 4.862
+@pytest.mark.parametrize("T,d,F,dtype,rows,streams", [
+    # three contexts in turn, one copy stream / two in turn, us
+    (2000, 512, 1536, L.STEM_BF16, 845, 2),         # 65 / 55
+    (4096, 1024, 4096, L.STEM_BF16, 1421, 2),       # 227 / 209
+    (65536, 1024, 4096, L.STEM_BF16, 10913, 2),     # 1691 / 1643
+    (16384, 2048, 8192, L.STEM_BF16, 4677, 2),      # 1404 / 1357
+    (12668, 1472, 5248, L.STEM_BF16, 2421, 1),      # 495 / 515: the products weigh as much as the rows
+    (16384, 2048, 8192, L.STEM_BF16, 3804, 1),      # 1170 / 1240
+    (40000, 2048, 8192, L.STEM_BF16, 9189, 1),      # 2836 / 3013
+    (65536, 2048, 8192, L.STEM_BF16, 51237, 1),     # long
+    (700, 2048, 8192, L.STEM_BF16, 390, 1),         # 124 / 146
+    (850, 2048, 6144, L.STEM_BF16, 450, 1),         # 110 / 119
+    (850, 1728, 5824, L.STEM_BF16, 450, 2),         # 107 / 106
+    (1000, 256, 1024, L.STEM_F32, 407, 2),          # 55 / 45
+    (2000, 512, 2048, L.STEM_F32, 670, 1),          # 131 / 149
 ])
-def test_host_table_calls_that_share_the_link_where_that_was_measured_shorter(rows, F, streams):
-    assert L.lib().stem_route_copy_streams(ctypes.c_int64(rows), ctypes.c_int64(2 * F)) == streams
+def test_host_table_calls_that_share_the_link_where_that_was_measured_shorter(T, d, F, dtype, rows, streams):
+    assert L.lib().stem_route_copy_streams(d, F, dtype, ctypes.c_int64(T), ctypes.c_int64(rows)) == streams
 
 
 @pytest.mark.parametrize("T,d,F,gate,touched", [
