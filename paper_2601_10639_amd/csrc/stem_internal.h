@@ -253,7 +253,8 @@ enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_409
 // up to 128 tokens, where the down product is the decode kernel's (above, the gate product is bound by L2).  Layer forward, us,
 // without / with: 1024 x 4096, 112 tokens 16.9 / 16.7, 192 tokens 22.4 / 20.7, 384 tokens 27.7 / 26.0; 1280 x 5120, 128 tokens 28.0 /
 // 25.3; 1536 x 5120, 384 tokens 41.2 / 37.4; 2048 x 8192, 128 tokens 35.3 / 34.3; against 1024 x 4096, 24
-// tokens 12.4 / 13.4; 896 x 3584, 128 tokens 15.0 / 15.6; 2048 x 8192, 192 tokens 37.7 / 40.0; 1792 x 7168, 192 tokens 34.4 / 36.0.
+// tokens 12.4 / 13.4; 896 x 3584, 128 tokens 15.0 / 15.6; 2048 x 8192, 192 tokens 37.7 / 40.0; 1792 x 7168, 192 tokens 34.4 / 36.0; 128
+// tokens of 2304 x 8192 42.6 / 45.7, of 2048 x 10240 47.7 / 51.5.
 inline int stem_touch_bytes(int M, int d, int F) {
   const int64_t w = (int64_t)d * F * 2;
   return M >= 112 && M <= 512 && w >= 7900000 && w <= (M <= 128 ? 34 : 16) * 1000000ll ? (int)w : 0;
