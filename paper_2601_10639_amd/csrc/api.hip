@@ -424,8 +424,6 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
     b.M = (int)T; b.N = d; b.K = F; b.C = y; b.flag = c->flag;
     b.residual = static_cast<const bf16_t*>(residual);
     b.ws = c->splitk_ws; b.ws_bytes = c->splitk_bytes;
-    if (down == ROUTE_DECODE) b.tickets = c->tickets;
-    else if (down == ROUTE_FEW_ROW) { b.rounds = c->rounds; b.polls = c->polls; }
     const int down_epi = residual ? EPI_BF16_RES : EPI_BF16;
     if (!wait_event) {
       a.outG = static_cast<bf16_t*>(save_G); a.outH = static_cast<bf16_t*>(H);
@@ -460,8 +458,10 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
       HIP_TRY(c, stem_silu_gather(c, 1, G, ids, E, (int)E_rows, H, T, F, s));
     }
     if (down == ROUTE_DECODE) {
+      b.tickets = c->tickets;
       HIP_TRY(c, stem_gemm_decode_bf16(c, K_GEMM_DOWN, EPI_BF16, b, s));
     } else if (down == ROUTE_FEW_ROW) {
+      b.rounds = c->rounds; b.polls = c->polls;
       // K slices finish y while others still read H and W_down: where y lies over one of these it is put together behind the slices'
       // partial tiles and copied.  (Room is there: slices take 8 MB and 8 KB * d at most, y 1 KB * d, of the smaller of 64 MB and 32 KB * d.)
       const size_t Td = (size_t)T * d * 2;
