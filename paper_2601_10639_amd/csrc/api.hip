@@ -95,21 +95,21 @@ void copy_streams_put(int device) {   // the device is current and idle
 }
 
 // In front of a call's first copy: the stream for all of them.
-hipError_t copies_begin(stem_ctx* c, int64_t T, int64_t rows) {
+void copies_begin(stem_ctx* c, int64_t T, int64_t rows) {
   std::lock_guard<std::mutex> lock(g_copy_mutex);
   CopyStreams& q = g_copy[c->device];
   const bool is_long = rows * (int64_t)(c->desc.d_ff * esize(c)) >= STEM_PF_LONG;
   if (!is_long && q.long_rows) q.long_rows = busy(q.stream[0]);
   const bool in_turn = q.users > 1 && stem_route_copy_streams(c->desc.d_model, c->desc.d_ff, c->desc.dtype, T, rows) == 2;
-  const int i = is_long ? 0 : q.long_rows ? 1 : in_turn ? q.turn++ & 1 : 0;
+  int i = is_long ? 0 : q.long_rows ? 1 : in_turn ? q.turn++ & 1 : 0;
   q.long_rows |= is_long;
-  if (!q.stream[i]) {
-    const hipError_t e = hipStreamCreateWithFlags(&q.stream[i], hipStreamNonBlocking);
-    if (e != hipSuccess) { q.stream[i] = nullptr; return e; }
+  if (!q.stream[i] && hipStreamCreateWithFlags(&q.stream[i], hipStreamNonBlocking) != hipSuccess) {   // then the first does
+    q.stream[i] = nullptr;
+    i = 0;
+    (void)hipGetLastError();
   }
   c->side = q.stream[i];
   c->copies_open = 1;
-  return hipSuccess;
 }
 
 // Waits for the copies of this context's last prefetch, before its pinned arrays are written again.  A call that ended with an error
@@ -881,7 +881,7 @@ stem_status stem_prefetch_rows(stem_ctx* c, const void* E_host, const int32_t* i
     return fail(c, STEM_ERR_WORKSPACE, "stem_prefetch_rows: %lld distinct ids but E_compact holds %lld rows",
                 (long long)U, (long long)cap);
 
-  HIP_TRY(c, copies_begin(c, T, U));
+  copies_begin(c, T, U);
   if (c->prefetch_mode == STEM_PREFETCH_MEMCPY) {
     if (T > 0) HIP_TRY(c, hipMemcpyAsync(remap, c->remap_pinned, (size_t)T * 4, hipMemcpyHostToDevice, c->side));
     // Pack the rows into pinned staging with a few host threads and copy chunk by chunk,
@@ -1021,7 +1021,7 @@ stem_status stem_prefetch_rows_cached(stem_ctx* c, const void* E_host, const int
                 (long long)n_miss, (long long)cap);
   }
 
-  HIP_TRY(c, copies_begin(c, T, n_miss));
+  copies_begin(c, T, n_miss);
   HIP_TRY(c, stem_copy_lists_kernel(c, c->remap_pinned, remap, T, c->order_pinned, c->order_dev, n_miss, c->max_tokens, c->side));
   {
     int64_t k0 = 0;

@@ -15,10 +15,10 @@ pytestmark = pytest.mark.gpu
 
 
 class LongCopy:
-    """A context of 128 KB rows and a call whose rows, 2 GiB, take some 38 ms over the link."""
+    """A context of 256 KB rows and a call whose rows, 4 GiB, take some 75 ms over the link."""
 
     def __init__(self):
-        T, F = 16384, 32768
+        T, F = 16384, 65536
         self.E_host = torch.empty(T, F, dtype=torch.float32, pin_memory=True)
         self.E_host[:, 0] = torch.arange(T, dtype=torch.float32)
         self.ids = torch.arange(T, dtype=torch.int32)
@@ -104,7 +104,7 @@ def test_a_refused_call_leaves_the_next_one_nothing_to_wait_for(copy, cached):
 
 
 def test_short_calls_beside_a_long_one_and_beside_each_other(copy):
-    """Rows of a few MB do not wait for another context's 2 GiB, and the rows of two such calls do not all wait for one another."""
+    """Rows of a few MB do not wait for another context's 4 GiB, and the rows of two such calls do not all wait for one another."""
     layers = [Layer(k) for k in range(2, 5)]
     copy.begin()
     for q in layers:

@@ -102,3 +102,20 @@ def test_outputs_over_w_up_take_two_launches_on_every_tiling(T, d, F, tile, spli
         errs["y"] = Hn.max_rel(y.float().cpu(), yo)
         assert all(v <= Hn.TOL["bf16"] for v in errs.values()), (over, errs)
     ctx.close()
+
+
+@pytest.mark.parametrize("T,d,F,tile", [(130, 704, 2368, (128, 128)), (1990, 1024, 4032, (256, 256))])
+def test_ids_outside_the_table_in_the_joint_launch(T, d, F, tile):
+    assert Hn.route_tiles(T, 2 * F, d, 1, Hn.EPI_GATE)[1:3] == tile
+    inp, ctx = _layer(T, d, F, 98)
+    E_rows = inp["E"].shape[0]
+    bad = inp["ids"].clone()
+    bad[0], bad[T // 2], bad[-1] = -1, 2 ** 31 - 1, E_rows
+    y = torch.empty_like(inp["x"])
+    L.stem_ffn_up_forward(ctx, inp["x"], bad, inp["W_gate"], inp["W_up"], inp["W_down"], inp["E"], y)
+    with pytest.raises(L.StemError) as e:
+        L.stem_sync_status(ctx)
+    assert e.value.status == L.STEM_ERR_ID_RANGE
+    inp["ids"] = bad.clamp(0, E_rows - 1)
+    assert torch.equal(_forward(ctx, inp, inp["E"], None, None, None), y)
+    ctx.close()
