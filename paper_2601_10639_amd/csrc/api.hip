@@ -758,10 +758,9 @@ stem_status stem_embed_grad(stem_ctx* c, const int32_t* ids, const void* dU, int
   if (misaligned(dU) || misaligned(dE_rows))
     return fail(c, STEM_ERR_INVALID_ARG, "stem_embed_grad: dU and dE_rows must be 16-byte aligned");
   const EmbedScratch ws = embed_scratch(c);
-  HIP_TRY(c, stem_sort_unique(c, ws, ids, T, c->desc.vocab, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, s));
+  HIP_TRY(c, stem_table_grad(c, ws, c->desc.dtype == STEM_BF16, ids, dU, T, c->desc.vocab, c->desc.d_ff, sorted_ids, perm, uniq_ids,
+                             seg_offsets, n_uniq, dE_rows, s));
   c->seg_T = T;
-  if (dU)
-    HIP_TRY(c, stem_seg_reduce(c, ws, c->desc.dtype == STEM_BF16, dU, perm, seg_offsets, T, c->desc.d_ff, dE_rows, s));
   return STEM_OK;
 }
 

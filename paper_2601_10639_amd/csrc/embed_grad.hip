@@ -688,23 +688,25 @@ __global__ __launch_bounds__(256) void seg_combine_kernel(const int32_t* __restr
   }
 }
 
-// Small batches, where a chunk's row loads and the second launch are all latency: one launch, a workgroup for every sorted
-// position and slab of 64 * COLS columns.  A run is summed by the workgroups of its first positions, the others end at once.
+// Small batches, where a chunk's row loads and the second launch are all latency: whole runs are summed in one launch, with a
+// workgroup for every position and band of up to 16 slabs of 64 * COLS columns.  A run is summed by the workgroups of its first
+// positions, the others end at once.
 //
-// A run of up to 16 rows is one round of loads of one wavefront.  Longer ones are dealt to 4 * PARTS row groups, PARTS = 1, 2, 4,
-// 8 up to 64, 128, 256 rows and beyond, in which PARTS workgroups take 1 / PARTS of the slab's columns each: a lane then has 16
-// rows at most (32 of 1024), and a long run is read by as many more compute units.  Rows are added in ascending position, four
+// A run of up to 16 rows is one round of loads of one wavefront for each slab, which the wavefronts of the run's first workgroup share out.
+// Longer ones are dealt to 4 * PARTS row groups, PARTS = 1, 2, 4, 8 up to 64, 128, 256 rows and beyond, in which PARTS teams of four
+// wavefronts take 1 / PARTS of a slab's columns each: a lane then has 16 rows at most (32 of 1024, 64 of 2048), and a long run is read
+// by as many more compute units: the run's workgroups take its (slab, part) pairs in turn.  Rows are added in ascending position, four
 // at a time, then the groups of a wavefront in order, then the wavefronts: no term of 1024 meets more than 20 additions.
-// us in a graph, two launches / four wavefronts of one workgroup for the whole run / now:
-//                    bf16 1024 x 4096     bf16 256 x 8192      fp32 1024 x 2048     fp32 256 x 1024
-//   Zipf ids         11.6 / 11.7 / 7.6    11.3 / 5.0 / 4.8     12.6 / 7.5 / 6.5     12.0 / 3.4 / 3.0
-//   one id for half  12.0 / 25.1 / 6.9    11.2 / 15.5 / 5.8    12.7 / 15.7 / 5.9    12.1 / 6.1 / 4.0
-//   one id for all   10.6 / 58.5 / 8.2    10.4 / 27.8 / 6.4     8.7 / 40.3 / 9.1     8.0 / 10.0 / 5.1
-// (9.1: 1024 rows of 8 KB, of which the row groups read every 32nd, in the same memory channels; 900 rows 8.4 / - / 5.9.)
-// The relative error of fp32 unit normals, all of one id, 1024 rows: 1.20e-7 / 2.92e-7 / 1.04e-7.
-// (Row loads that bypass the caches, as the large batches' do: one id for all, bf16 1024 x 4096 15.5.)
+// us in a graph, sums of a sorted batch: two launches of 32-row chunks / a workgroup for every position and slab / now:
+//                    bf16 1024 x 4096     bf16 256 x 8192      fp32 1024 x 2048     fp32 256 x 1024     bf16 1999 x 8192
+//   Zipf ids         11.6 / 8.0 / 6.7     11.3 / 5.1 / 5.1     12.6 / 6.9 / 5.0     12.0 / 3.0 / 3.0    17.7 / 18.0 / 14.3
+//   one id for half  12.0 / 7.2 / 6.1     11.2 / 5.9 / 6.2     12.7 / 6.0 / 4.9     12.1 / 4.0 / 4.0    17.3 / - / 12.6
+//   one id for all   10.6 / 8.3 / 7.4     10.4 / 6.4 / 6.3      8.7 / 9.2 / 5.8      8.0 / 5.1 / 5.1    13.8 / 19.7 / 14.0
+// (a workgroup of four wavefronts for a long run's whole slab: 58.5 at 1024 x 4096, one id for all.)
+// The relative error of fp32 unit normals, all of one id, 1024 rows: 1.20e-7 in two launches, 2.92e-7 with four wavefronts for the
+// whole run, 1.04e-7 so.
+// (Row loads that bypass the caches, as the large batches' do: one id for all, bf16 1024 x 4096 15.5 us instead of 8.2.)
 constexpr int ROUND = 16;        // rows a lane requests together
-constexpr int MAX_PARTS = 8;     // a part of a slab is no narrower than 8 lanes: 128 bytes of a row
 
 template <bool BF16>
 __device__ __forceinline__ void add_quad(const typename RowVec<BF16>::raw_t* rows, int n, float (&acc)[RowVec<BF16>::COLS]) {
@@ -722,8 +724,8 @@ __device__ __forceinline__ void add_quad(const typename RowVec<BF16>::raw_t* row
 
 // Adds `rows` (at most R) rows of a run of n, from its r-th on.  Loads carry no conditions, or the compiler waits for those it
 // cannot count; what lies beyond the rows is read for nothing, within the run.
-template <bool BF16, int R>
-__device__ __forceinline__ void add_rows(const void* dU, const int32_t* perm, int r, int rows, int n, int F, int col,
+template <bool BF16, int R, class Rows>
+__device__ __forceinline__ void add_rows(const void* dU, Rows perm, int r, int rows, int n, int F, int col,
                                          float (&acc)[RowVec<BF16>::COLS]) {
   int row[R];
   typename RowVec<BF16>::raw_t data[R];
@@ -735,67 +737,108 @@ __device__ __forceinline__ void add_rows(const void* dU, const int32_t* perm, in
   for (int u = 0; u < R; u += 4) add_quad<BF16>(data + u, rows - u, acc);
 }
 
-template <bool BF16>
-__global__ __launch_bounds__(256) void seg_runs_kernel(const void* __restrict__ dU, const int32_t* __restrict__ perm,
-                                                       const int32_t* __restrict__ seg_of,
-                                                       const int32_t* __restrict__ seg_offsets, int F,
-                                                       float* __restrict__ dE_rows) {
+// Slabs of a band at most: a run of more than 64, 128, 256 rows then has as many workgroups as (slab, part) pairs, one each.
+constexpr int MAX_BAND = 16;
+
+// a run of n rows is summed in 1 << run_shift(n) parts of a slab's columns
+__device__ __forceinline__ int run_shift(int n) { return n <= 4 * ROUND ? 0 : n <= 8 * ROUND ? 1 : n <= 16 * ROUND ? 2 : 3; }
+
+// Up to ROUND rows of a run, from its r-th on, in the columns of a wavefront's lane.
+template <bool BF16, class Rows>
+__device__ __forceinline__ void add_round(const void* dU, Rows rows_of, int r, int rows, int F, int col, float (&acc)[RowVec<BF16>::COLS]) {
+  typename RowVec<BF16>::raw_t data[ROUND];
+#pragma unroll
+  for (int u = 0; u < ROUND; ++u)
+    if (u < rows) data[u] = RowVec<BF16>::load_plain(dU, rows_of[r + u], F, col);
+#pragma unroll
+  for (int u = 0; u < ROUND; ++u) asm("" : "+v"(data[u]));   // or additions move to the loads, and wait there for each by itself
+#pragma unroll
+  for (int u = 0; u < ROUND; u += 4) add_quad<BF16>(data + u, rows - u, acc);
+}
+
+// A run of up to ROUND rows, in a slab's columns, by one wavefront
+template <bool BF16, class Rows>
+__device__ __forceinline__ void sum_short(const void* dU, Rows rows_of, int n, int slab, int lane, int F, float* out) {
   constexpr int COLS = RowVec<BF16>::COLS;
-  __shared__ float red[256 * (COLS + 1)];   // a thread's sums, one float apart
-  const int k = blockIdx.x;
-  const int j = seg_of[k], far = seg_of[max(k - MAX_PARTS, 0)];
-  if (k >= MAX_PARTS && far == j) return;
-  const int start = seg_offsets[j], n = seg_offsets[j + 1] - start;
-  const int shift = n <= 4 * ROUND ? 0 : n <= 8 * ROUND ? 1 : n <= 16 * ROUND ? 2 : 3;
-  // which part: another one in each slab, or the workgroups of all slabs would be on the XCDs of the first positions
-  const int part = n <= ROUND ? k - start : (k - start - (int)blockIdx.y) & (MAX_PARTS - 1);
-  if (part >= 1 << shift) return;
-  const int tid = threadIdx.x;
+  const int col = (slab * 64 + lane) * COLS;
   float acc[COLS];
 #pragma unroll
   for (int x = 0; x < COLS; ++x) acc[x] = 0.f;
+  add_round<BF16>(dU, rows_of, 0, n, F, col < F ? col : 0, acc);
+  if (col < F) store_cols<COLS>(out + col, acc);
+}
 
-  if (shift == 0) {   // rows of whole wavefronts: their numbers come through scalar loads
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (n <= ROUND && wave > 0) return;
-    const int q = n <= ROUND ? n : (n + 3) >> 2, r = wave * q, rows = min(q, n - r);
-    const int col = (blockIdx.y * 64 + lane) * COLS, colc = col < F ? col : 0;
-    typename RowVec<BF16>::raw_t data[ROUND];
+// The same for up to 4 rows and 4 slabs, `step` apart, all requested together
+template <bool BF16, class Rows>
+__device__ __forceinline__ void sum_shortest(const void* dU, Rows rows_of, int n, int slab, int step, int slabs, int lane, int F, float* out) {
+  constexpr int COLS = RowVec<BF16>::COLS, STEPS = ROUND / 4;
+  typename RowVec<BF16>::raw_t data[STEPS][4];
 #pragma unroll
-    for (int u = 0; u < ROUND; ++u)
-      if (u < rows) data[u] = RowVec<BF16>::load_plain(dU, perm[start + r + u], F, colc);
+  for (int s = 0; s < STEPS; ++s)
+    if (slab + s * step < slabs) {
+      const int col = ((slab + s * step) * 64 + lane) * COLS, colc = col < F ? col : 0;
 #pragma unroll
-    for (int u = 0; u < ROUND; ++u) asm("" : "+v"(data[u]));   // or additions move to the loads, and wait there for each by itself
-#pragma unroll
-    for (int u = 0; u < ROUND; u += 4) add_quad<BF16>(data + u, rows - u, acc);
-    if (n > ROUND) {
-      if (wave > 0) {
-#pragma unroll
-        for (int x = 0; x < COLS; ++x) red[tid * (COLS + 1) + x] = acc[x];
-      }
-      __syncthreads();
-      if (wave == 0)
-        for (int w = 1; w < 4; ++w)
-#pragma unroll
-          for (int x = 0; x < COLS; ++x) acc[x] += red[(w * 64 + lane) * (COLS + 1) + x];
+      for (int u = 0; u < 4; ++u)
+        if (u < n) data[s][u] = RowVec<BF16>::load_plain(dU, rows_of[u], F, colc);
     }
-    if (wave == 0 && col < F) store_cols<COLS>(dE_rows + (int64_t)j * F + col, acc);
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) asm("" : "+v"(data[s][u]));
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) {
+    const int col = ((slab + s * step) * 64 + lane) * COLS;
+    float acc[COLS];
+#pragma unroll
+    for (int x = 0; x < COLS; ++x) acc[x] = 0.f;
+    add_quad<BF16>(data[s], n, acc);
+    if (slab + s * step < slabs && col < F) store_cols<COLS>(out + col, acc);
+  }
+}
+
+// A part of a longer run's slab by four wavefronts, t their thread, red 256 * (COLS + 1) floats: first the row groups' sums, then, behind
+// a barrier, all of them.
+template <bool BF16, class Rows>
+__device__ __forceinline__ void sum_groups(const void* dU, Rows rows_of, int n, int part, int slab, int t, int F, float* red,
+                                           float (&acc)[RowVec<BF16>::COLS]) {
+  constexpr int COLS = RowVec<BF16>::COLS;
+  const int shift = run_shift(n);
+#pragma unroll
+  for (int x = 0; x < COLS; ++x) acc[x] = 0.f;
+  if (shift == 0) {   // rows of whole wavefronts: their numbers come through scalar loads
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int q = (n + 3) >> 2, r = wave * q, rows = min(q, n - r);
+    const int col = (slab * 64 + (t & 63)) * COLS;
+    add_round<BF16>(dU, rows_of, r, rows, F, col < F ? col : 0, acc);
+  } else {
+    const int width = 64 >> shift, groups = 4 << shift;    // lanes of a part, row groups
+    const int col = (slab * 64 + part * width + (t & (width - 1))) * COLS, colc = col < F ? col : 0;
+    const int q = (n + groups - 1) >> (2 + shift);         // rows of a group (the last ones may have fewer, or none)
+    const int r = (t >> (6 - shift)) * q, rows = min(q, n - r);
+    if (q <= ROUND / 2) add_rows<BF16, ROUND / 2>(dU, rows_of, r, rows, n, F, colc, acc);
+    else
+      for (int rb = 0; rb < q; rb += ROUND) add_rows<BF16, ROUND>(dU, rows_of, r + rb, rows - rb, n, F, colc, acc);
+  }
+#pragma unroll
+  for (int x = 0; x < COLS; ++x) red[t * (COLS + 1) + x] = acc[x];
+}
+template <bool BF16>
+__device__ __forceinline__ void sum_join(int n, int part, int slab, int t, int F, const float* red, float (&acc)[RowVec<BF16>::COLS],
+                                         float* out) {
+  constexpr int COLS = RowVec<BF16>::COLS;
+  const int shift = run_shift(n);
+  if (shift == 0) {
+    const int col = (slab * 64 + t) * COLS;
+    if (t >= 64 || col >= F) return;
+    for (int w = 1; w < 4; ++w)
+#pragma unroll
+      for (int x = 0; x < COLS; ++x) acc[x] += red[(w * 64 + t) * (COLS + 1) + x];
+    store_cols<COLS>(out + col, acc);
     return;
   }
-
-  const int width = 64 >> shift, groups = 4 << shift;      // lanes of a part, row groups
-  const int first_col = (blockIdx.y * 64 + part * width) * COLS;
-  const int col = first_col + (tid & (width - 1)) * COLS, colc = col < F ? col : 0;
-  const int q = (n + groups - 1) >> (2 + shift);           // rows of a group (the last ones may have fewer, or none)
-  const int r = (tid >> (6 - shift)) * q, rows = min(q, n - r);
-  if (q <= ROUND / 2) add_rows<BF16, ROUND / 2>(dU, perm + start, r, rows, n, F, colc, acc);
-  else
-    for (int rb = 0; rb < q; rb += ROUND) add_rows<BF16, ROUND>(dU, perm + start, r + rb, rows - rb, n, F, colc, acc);
-#pragma unroll
-  for (int x = 0; x < COLS; ++x) red[tid * (COLS + 1) + x] = acc[x];
-  __syncthreads();
   // a column: the groups of each wavefront in order, then the wavefronts
-  for (int c = tid; c < width * COLS && first_col + c < F; c += 256) {
+  const int width = 64 >> shift, first_col = (slab * 64 + part * width) * COLS;
+  for (int c = t; c < width * COLS && first_col + c < F; c += 256) {
     const float* from = red + (c / COLS) * (COLS + 1) + c % COLS;
     float sum = 0.f;
     for (int w = 0; w < 4; ++w) {
@@ -803,7 +846,161 @@ __global__ __launch_bounds__(256) void seg_runs_kernel(const void* __restrict__ 
       for (int g = 0; g < 1 << shift; ++g) s += from[(w * 64 + g * width) * (COLS + 1)];
       sum += s;
     }
-    dE_rows[(int64_t)j * F + first_col + c] = sum;
+    out[first_col + c] = sum;
+  }
+}
+
+// The slabs of the workgroup's band, and whether the rank-th workgroup of a run of n rows has any of its sums.
+template <bool BF16>
+__device__ __forceinline__ int band_slabs(int F, int band) {
+  constexpr int COLS = RowVec<BF16>::COLS;
+  return min((F + 64 * COLS - 1) / (64 * COLS) - (int)blockIdx.y * band, band);
+}
+template <int GROUPS>
+__device__ __forceinline__ bool sums_some(int n, int rank, int slabs) {
+  return rank == 0 || (n > ROUND && rank * GROUPS < slabs << run_shift(n));
+}
+
+// That workgroup's sums: GROUPS teams of four wavefronts.  rows_of: the run's positions in the batch; out: its row.
+template <bool BF16, int GROUPS, class Rows>
+__device__ __forceinline__ void sum_run(const void* dU, Rows rows_of, int n, int rank, int slabs, int slab0, int F, float* out,
+                                        float* red) {
+  constexpr int COLS = RowVec<BF16>::COLS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (n <= 4) {   // (slabs counted from the row's start)
+    for (int slab = slab0 + wave; slab < slab0 + slabs; slab += 4 * GROUPS * (ROUND / 4))
+      sum_shortest<BF16>(dU, rows_of, n, slab, 4 * GROUPS, slab0 + slabs, lane, F, out);
+    return;
+  }
+  if (n <= ROUND) {
+    for (int slab = wave; slab < slabs; slab += 4 * GROUPS) sum_short<BF16>(dU, rows_of, n, slab0 + slab, lane, F, out);
+    return;
+  }
+  const int team = wave >> 2, t = tid & 255, shift = run_shift(n), item = rank * GROUPS + team;
+  const int slab = item >> shift, part = item & ((1 << shift) - 1);
+  const bool mine = slab < slabs;
+  float acc[COLS];
+  red += team * 256 * (COLS + 1);
+  if (mine) sum_groups<BF16>(dU, rows_of, n, part, slab0 + slab, t, F, red, acc);
+  __syncthreads();
+  if (mine) sum_join<BF16>(n, part, slab0 + slab, t, F, red, acc, out);
+}
+
+template <bool BF16, int GROUPS>
+__global__ __launch_bounds__(256 * GROUPS) void seg_runs_kernel(const void* __restrict__ dU, const int32_t* __restrict__ perm,
+                                                                const int32_t* __restrict__ seg_of,
+                                                                const int32_t* __restrict__ seg_offsets, int F, int band,
+                                                                float* __restrict__ dE_rows) {
+  __shared__ float red[GROUPS * 256 * (RowVec<BF16>::COLS + 1)];   // a thread's sums, one float apart
+  const int k = blockIdx.x, slabs = band_slabs<BF16>(F, band), most = (slabs * 8 + GROUPS - 1) / GROUPS;   // workgroups of a run
+  const int j = seg_of[k], far = seg_of[max(k - most, 0)];
+  if (k >= most && far == j) return;
+  const int start = seg_offsets[j], n = seg_offsets[j + 1] - start;
+  if (sums_some<GROUPS>(n, k - start, slabs))
+    sum_run<BF16, GROUPS>(dU, perm + start, n, k - start, slabs, blockIdx.y * band, F, dE_rows + (int64_t)j * F, red);
+}
+
+// The same for a batch that is not sorted yet, with the sort: every workgroup looks at all ids.  The tokens with its token's id are the
+// run, the number of smaller ids is where the run begins, and the number of distinct smaller ids, from a bitmap of the ids in LDS, the run's
+// number.  The workgroup of a run's first token writes the sort's outputs for the run besides.  Nothing passes between
+// workgroups.
+// What bounds it is the launch, the ids' loads and three barriers, beyond some 1500 tokens the looks at all ids by every workgroup.  us in
+// a graph, rank sort and sums as two launches / this, Zipf ids: fp32 128 x 256 7.0 / 4.2, 1000 x 1024 9.5 / 6.8, 2048 x 2048 16.5 / 11.9; bf16
+// 128 x 8192 8.8 / 5.5, 512 x 8192 12.7 / 7.3, 1024 x 4096 13.1 / 9.0, 1999 x 8192 23.2 / 19.4, 2048 x 4096 19.7 / 13.8; one id for all:
+// fp32 1000 x 1024 9.6 / 8.5, 2048 x 256 13.9 / 13.1, bf16 2000 x 1536 16.1 / 15.5.  (One slab of a short run after another 1999 x 8192
+// 20.7, 2048 x 4096 14.9; counting with the ballots of every 64 ids for rank
+// and run, not only of those that hold the id: 1000 x 1024 7.8, 1999 x 8192 22.1; a workgroup for every token and slab: 1000 x 1024 11.3.)
+constexpr int SMALL_MAX = 2048;                  // tokens
+constexpr int SMALL_WORDS = 4096;                // 16 KB of bitmap: vocabularies up to 2^17
+template <bool BF16, int GROUPS, int MOST>       // GROUPS of four wavefronts; up to MOST tokens
+__global__ __launch_bounds__(256 * GROUPS) void sort_sum_kernel(const int32_t* __restrict__ ids, int T, int V,
+                                                                const void* __restrict__ dU, int F, int band, int32_t* __restrict__ sorted_ids,
+                                                                int32_t* __restrict__ perm, int32_t* __restrict__ uniq_ids,
+                                                                int32_t* __restrict__ seg_offsets, int32_t* __restrict__ n_uniq,
+                                                                int32_t* __restrict__ seg_of, float* __restrict__ dE_rows, int32_t* flag) {
+  constexpr int COLS = RowVec<BF16>::COLS, THREADS = 256 * GROUPS, WAVES = 4 * GROUPS, CHUNKS = MOST / THREADS;
+  __shared__ float red[GROUPS * 256 * (COLS + 1)];
+  __shared__ uint32_t bitmap[SMALL_WORDS];
+  __shared__ uint64_t same_s[MOST / 64];         // which of 64 tokens have the id
+  __shared__ int rows[MOST];                     // the run's tokens
+  __shared__ uint64_t counts[WAVES];             // smaller ids | earlier tokens of the run << 16 | its tokens << 32
+  __shared__ int set_s[WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = blockIdx.x;
+  const bool total = i == 0;                     // also looks for ids outside the table, and counts all distinct ones
+  auto clamped = [&](int id) { return min(max(id, 0), V - 1); };
+  int kv[CHUNKS];
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) kv[c] = ids[min(tid + THREADS * c, T - 1)];
+  const int own = clamped(ids[i]);
+  int less = 0, early = 0, n = 0;
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    const int id = clamped(kv[c]), at = (c * WAVES + wave) * 64;
+    if (total && id != kv[c]) *flag = 1;
+    kv[c] = at + lane < T ? id : 0x7fffffff;     // beyond the batch: no id
+    less += __popcll(__ballot(kv[c] < own));
+    const uint64_t same = __ballot(kv[c] == own);
+    if (same) {                                  // (few of the wavefronts' chunks: the scalar unit is what counting waits for)
+      n += __popcll(same);
+      early += __popcll(i >= at + 64 ? same : i > at ? same & ((1ull << (i - at)) - 1ull) : 0ull);
+    }
+  }
+  if (lane == 0) counts[wave] = (uint32_t)(less + (early << 16)) + ((uint64_t)n << 32);
+  __syncthreads();
+  uint64_t count = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) count += counts[w];
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)count);
+  n = __builtin_amdgcn_readfirstlane((uint32_t)(count >> 32));
+  const int rank = lo >> 16, start = lo & 0xffff, slabs = band_slabs<BF16>(F, band);
+  if (!sums_some<GROUPS>(n, rank, slabs)) return;
+
+  const int words = total ? (V + 31) >> 5 : (own >> 5) + 1;
+  for (int w = tid; w < words; w += THREADS) bitmap[w] = 0;
+  uint64_t same[CHUNKS];
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    same[c] = __ballot(kv[c] == own);
+    if (lane == 0) same_s[c * WAVES + wave] = same[c];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    const int id = kv[c];
+    // (a look first: a frequent id would queue all its lanes at one word)
+    if ((total ? id != 0x7fffffff : id < own) && !(bitmap[id >> 5] >> (id & 31) & 1u)) atomicOr(&bitmap[id >> 5], 1u << (id & 31));
+    if (same[c] >> lane & 1ull) {
+      int before = __popcll(same[c] & ((1ull << lane) - 1ull));
+      for (int x = 0; x < c * WAVES + wave; ++x) before += __popcll(same_s[x]);
+      rows[before] = tid + THREADS * c;
+    }
+  }
+  __syncthreads();
+  int set = 0;                                   // distinct ids below the own one, and all << 16
+  for (int w = tid; w < words; w += THREADS) {
+    const uint32_t bits = bitmap[w], low = w < own >> 5 ? ~0u : w == own >> 5 ? (1u << (own & 31)) - 1u : 0u;
+    set += __popc(bits & low) | __popc(bits) << 16;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) set += __shfl_xor(set, o);
+  if (lane == 0) set_s[wave] = set;
+  __syncthreads();
+  set = 0;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) set += set_s[w];
+  const int j = __builtin_amdgcn_readfirstlane(set & 0xffff);
+  sum_run<BF16, GROUPS>(dU, rows, n, rank, slabs, blockIdx.y * band, F, dE_rows + (int64_t)j * F, red);
+  if (rank > 0 || blockIdx.y > 0) return;
+  for (int k = tid; k < n; k += THREADS) {
+    sorted_ids[start + k] = own;
+    perm[start + k] = rows[k];
+    seg_of[start + k] = j;
+  }
+  if (tid == 0) {
+    uniq_ids[j] = own;
+    seg_offsets[j] = start;
+    if (total) { seg_offsets[set >> 16] = T; *n_uniq = set >> 16; }
   }
 }
 
@@ -932,21 +1129,63 @@ hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t
   return hipGetLastError();
 }
 
+// Where one launch sums whole runs, and of how many teams of four wavefronts its workgroups are.
+// Up to 2048 tokens (the looks at all ids are quadratic) and 8192 workgroups, most of which end at once.  Two teams while the tokens alone
+// don't fill the chip and a row has slabs for them, and up to 256 tokens two workgroups for a row of 16 slabs: us, one team / two / two
+// and bands of 8 slabs: bf16, 8192 columns, 128 tokens 9.4 / 6.9 / 5.6, 256 9.9 / 7.3 / 7.0, 512 9.3 / 7.5 / 10.0; fp32 1024 x 2048 7.5 / 8.6.
+static int run_slabs(int is_bf16, int F) { return (F + (is_bf16 ? 511 : 255)) / (is_bf16 ? 512 : 256); }
+static bool runs_wide(int64_t T, int slabs) { return T <= 512 && slabs > 4; }
+static int run_band(int64_t T, int slabs) { return T <= 256 && slabs > 4 ? 8 : MAX_BAND; }
+static int run_bands(int64_t T, int slabs) { return (slabs + run_band(T, slabs) - 1) / run_band(T, slabs); }
+static bool runs_fit(int is_bf16, int64_t T, int F) { return T <= SMALL_MAX && T * run_bands(T, run_slabs(is_bf16, F)) <= 8192; }
+
+int stem_route_sort_sum(int is_bf16, int64_t T, int V, int F, const int32_t* ids, const void* dU, const int32_t* sorted_ids,
+                        const int32_t* perm, const int32_t* uniq_ids, const int32_t* seg_offsets, const int32_t* n_uniq,
+                        const int32_t* seg_of, const float* dE_rows) {
+  if (!dU || !runs_fit(is_bf16, T, F) || V > SMALL_WORDS * 32 ||
+      !stem_route_sort_ranks(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, seg_of))
+    return 0;
+  const int64_t cap = std::min<int64_t>(T, V);
+  const struct { const void* at; int64_t n; } buf[] = {{dU, T * F * (is_bf16 ? 2 : 4)}, {dE_rows, cap * F * 4}, {ids, T * 4},
+      {sorted_ids, T * 4}, {perm, T * 4}, {uniq_ids, cap * 4}, {seg_offsets, cap * 4 + 4}, {n_uniq, 4}, {seg_of, T * 4}};
+  for (const auto& p : buf)
+    for (const auto* q = buf; q < buf + 2 && q < &p; ++q) {
+      const uintptr_t a = reinterpret_cast<uintptr_t>(p.at), b = reinterpret_cast<uintptr_t>(q->at);
+      if (a < b + q->n && b < a + p.n) return 0;
+    }
+  return 1;
+}
+
+hipError_t stem_table_grad(stem_ctx* ctx, const EmbedScratch& ws, int is_bf16, const int32_t* ids, const void* dU, int64_t T, int V, int F,
+                           int32_t* sorted_ids, int32_t* perm, int32_t* uniq_ids, int32_t* seg_offsets, int32_t* n_uniq, float* dE_rows,
+                           hipStream_t s) {
+  if (stem_route_sort_sum(is_bf16, T, V, F, ids, dU, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, dE_rows)) {
+    ProfScope ps(ctx, K_SEG_REDUCE, s);
+    const int slabs = run_slabs(is_bf16, F);
+    const bool wide = runs_wide(T, slabs);
+    auto* const kernel = T > 1024 ? (is_bf16 ? sort_sum_kernel<true, 1, 2048> : sort_sum_kernel<false, 1, 2048>)
+                         : wide   ? (is_bf16 ? sort_sum_kernel<true, 2, 1024> : sort_sum_kernel<false, 2, 1024>)
+                                  : (is_bf16 ? sort_sum_kernel<true, 1, 1024> : sort_sum_kernel<false, 1, 1024>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)T, (unsigned)run_bands(T, slabs)), dim3(wide ? 512 : 256), 0, s, ids, (int)T, V, dU, F,
+                       run_band(T, slabs), sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, dE_rows, ws.flag);
+    return hipGetLastError();
+  }
+  const hipError_t e = stem_sort_unique(ctx, ws, ids, T, V, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, s);
+  return e != hipSuccess || !dU ? e : stem_seg_reduce(ctx, ws, is_bf16, dU, perm, seg_offsets, T, F, dE_rows, s);
+}
+
 hipError_t stem_seg_reduce(stem_ctx* ctx, const EmbedScratch& ws, int is_bf16, const void* dU, const int32_t* perm,
                            const int32_t* seg_offsets, int64_t T, int F, float* dE_rows, hipStream_t s) {
   const int chunks = (int)((T + SEG_ROWS - 1) / SEG_ROWS);
   const int cols = is_bf16 ? 8 : 4;
-  // One launch up to 1024 positions, where it is as fast even with one id for all of them; what that costs beyond depends on the
-  // ids.  us in a graph, two launches / one, Zipf ids: fp32 128 x 256 11.2 / 2.5, 1000 x 1024 12.3 / 4.8, 2048 x 2048 13.4 / 10.1;
-  // bf16 130 x 8192 11.4 / 3.6, 500 x 8192 11.9 / 7.5, 1024 x 8192 13.6 / 11.9, 1999 x 8192 16.6 / 18.0.  One id for all: fp32
-  // 1024 x 2048 8.7 / 9.1, 2048 x 2048 9.8 / 14.7; bf16 1024 x 4096 10.6 / 8.2, 1999 x 8192 13.2 / 19.7.  Most workgroups end at
-  // once: 8192 of them at most.
-  const int64_t run_slabs = (F + 64 * cols - 1) / (64 * cols);
-  if (T <= 1024 && T * run_slabs <= 8192) {
+  if (runs_fit(is_bf16, T, F)) {
     ProfScope ps(ctx, K_SEG_REDUCE, s);
-    const dim3 grid((unsigned)T, (unsigned)run_slabs);
-    if (is_bf16) hipLaunchKernelGGL(seg_runs_kernel<true>, grid, dim3(256), 0, s, dU, perm, ws.seg_of, seg_offsets, F, dE_rows);
-    else hipLaunchKernelGGL(seg_runs_kernel<false>, grid, dim3(256), 0, s, dU, perm, ws.seg_of, seg_offsets, F, dE_rows);
+    const int slabs = run_slabs(is_bf16, F);
+    const bool wide = runs_wide(T, slabs);
+    auto* const kernel = wide ? (is_bf16 ? seg_runs_kernel<true, 2> : seg_runs_kernel<false, 2>)
+                              : (is_bf16 ? seg_runs_kernel<true, 1> : seg_runs_kernel<false, 1>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)T, (unsigned)run_bands(T, slabs)), dim3(wide ? 512 : 256), 0, s, dU, perm, ws.seg_of,
+                       seg_offsets, F, run_band(T, slabs), dE_rows);
     return hipGetLastError();
   }
   const int slabs = (F + 256 * cols - 1) / (256 * cols);

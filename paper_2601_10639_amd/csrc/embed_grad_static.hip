@@ -105,9 +105,8 @@ extern "C" stem_status stem_embed_grad_noalloc(int32_t dtype, int32_t vocab, int
   // Nothing else of the scratch has to start at zero: every word the kernels read was written earlier
   // in the same call (digit counts by the counting pass, run indices by the sort, partial sums by the
   // chunk that owns them), so what the previous call left behind is never seen.
-  if ((e = stem_sort_unique(nullptr, ws, ids, T, vocab, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, s)) != hipSuccess)
-    return stem_fail(nullptr, STEM_ERR_HIP, "stem_embed_grad_noalloc: sort launch: %s", hipGetErrorString(e));
-  if (dU && (e = stem_seg_reduce(nullptr, ws, dtype == STEM_BF16, dU, perm, seg_offsets, T, d_ff, dE_rows, s)) != hipSuccess)
-    return stem_fail(nullptr, STEM_ERR_HIP, "stem_embed_grad_noalloc: reduce launch: %s", hipGetErrorString(e));
+  if ((e = stem_table_grad(nullptr, ws, dtype == STEM_BF16, ids, dU, T, vocab, d_ff, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq,
+                           dE_rows, s)) != hipSuccess)
+    return stem_fail(nullptr, STEM_ERR_HIP, "stem_embed_grad_noalloc: launch: %s", hipGetErrorString(e));
   return STEM_OK;
 }

@@ -227,6 +227,10 @@ int stem_route_sort(int64_t T, int V);   // SortRoute
 // whether the kernel that counts ranks sorts them, which it does where the size allows and no two of the call's buffers overlap
 int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
                           const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of);
+// whether the sort and the sums of a call with these buffers (dU may be null: no sums) are one launch
+int stem_route_sort_sum(int is_bf16, int64_t T, int V, int F, const int32_t* ids, const void* dU, const int32_t* sorted_ids,
+                        const int32_t* perm, const int32_t* uniq_ids, const int32_t* seg_offsets, const int32_t* n_uniq,
+                        const int32_t* seg_of, const float* dE_rows);
 int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, touched by the gate product of that call
 // How many copy streams host-table calls of T tokens and this many distinct rows take in turn.  With one the link stands still between two
 // calls' rows, and a copy that waits for compute units finds them taken by tiles (15 to 60 us a call); two hold 32 compute units
@@ -324,6 +328,10 @@ hipError_t stem_sort_unique(stem_ctx* prof, const EmbedScratch& ws, const int32_
                             int32_t* n_uniq, hipStream_t s);
 hipError_t stem_seg_reduce(stem_ctx* prof, const EmbedScratch& ws, int is_bf16, const void* dU, const int32_t* perm,
                            const int32_t* seg_offsets, int64_t T, int F, float* dE_rows, hipStream_t s);
+// both, or without dU the sort alone
+hipError_t stem_table_grad(stem_ctx* prof, const EmbedScratch& ws, int is_bf16, const int32_t* ids, const void* dU, int64_t T, int V, int F,
+                           int32_t* sorted_ids, int32_t* perm, int32_t* uniq_ids, int32_t* seg_offsets, int32_t* n_uniq, float* dE_rows,
+                           hipStream_t s);
 int64_t stem_seg_chunks(int64_t max_tokens);
 int64_t stem_sort_count_entries(int64_t max_tokens);
 // error text for calls that have no context (stem_last_error(NULL) returns it)

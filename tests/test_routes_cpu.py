@@ -5,7 +5,7 @@ import random
 import pytest
 
 from paper_2601_10639_amd import stemlib as L
-from tests.harness import DECODE, EPI_BF16, EPI_F32, EPI_GATE, FEW_ROW, TILES, route_forward, route_gate_up_together, route_sort_ranks, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
+from tests.harness import DECODE, EPI_BF16, EPI_F32, EPI_GATE, FEW_ROW, TILES, route_forward, route_gate_up_together, route_sort_ranks, route_sort_sum, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
 
 
 def test_no_k_slice_is_empty():
@@ -150,3 +150,22 @@ def test_ranks_are_counted_where_no_two_buffers_of_the_sort_overlap(T, V):
             for at, ranks in ((lie[b] - 4 * size[a], True), (lie[b] - 4 * size[a] + 4, False), (lie[b], False),
                               (lie[b] + 4 * size[b] - 4, False), (lie[b] + 4 * size[b], True)):
                 assert route_sort_ranks(T, V, **{**lie, a: at}) == ranks, (a, b, at - lie[b])
+
+
+@pytest.mark.parametrize("bf16,T,V,F", [(True, 7, 40, 64), (False, 1000, 300, 1024), (True, 512, 1 << 17, 8192), (True, 2048, 128256, 8192)])
+def test_sort_and_sums_share_a_launch_where_no_two_of_their_buffers_overlap(bf16, T, V, F):
+    cap, es = min(T, V), 2 if bf16 else 4
+    ints = dict(ids=T, sorted_ids=T, perm=T, uniq_ids=cap, seg_offsets=cap + 1, n_uniq=1, seg_of=T)
+    size = dict(dU=T * F * es, dE_rows=cap * F * 4, **{k: 4 * n for k, n in ints.items()})
+    lie = {k: (i + 1) << 28 for i, k in enumerate(size)}
+    share = lambda **over: route_sort_sum(bf16, T, V, F, **{**lie, **over})
+    assert share() and not share(dU=0)
+    assert not route_sort_sum(bf16, T, (1 << 17) + 1, F, **lie) and not route_sort_sum(bf16, 2049, V, F, **lie)
+    assert not route_sort_sum(bf16, T, V, 1 << 23, **lie)
+    for a in size:
+        for b in size:
+            if a == b:
+                continue
+            for at, one in ((lie[b] - size[a], True), (lie[b] - size[a] + 4, False), (lie[b], False), (lie[b] + size[b] - 4, False),
+                            (lie[b] + size[b], True)):
+                assert share(**{a: at}) == one, (a, b, at - lie[b])
