@@ -9,6 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstem.so")
+BIND = os.path.join(HERE, "_bind.so")   # the hot calls' binding, a Python module
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "gemm_bf16.hip", "gemm_skinny_bf16.hip", "gemm_decode_bf16.hip", "kernels_f32.hip", "embed_grad.hip", "embed_grad_static.hip", "adamw.hip", "prefetch.hip", "edit.hip", "calibrate.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
@@ -31,6 +32,23 @@ def _run(cmd):
     return err
 
 
+def _build_bind() -> str:
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    inc = [f"-I{p}" for p in (*cpp_extension.include_paths(), sysconfig.get_paths()["include"])]
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    obj = os.path.join(OBJ_DIR, "bind.o")
+    msg = _run(["g++", "-O2", "-fPIC", "-std=c++17", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+                "-c", os.path.join(CSRC, "bind.cpp"), "-o", obj])
+    # (libstem.so is found beside it; torch's libraries are loaded by then)
+    _run(["g++", "-shared", "-o", BIND, obj, f"-L{HERE}", "-l:libstem.so", "-Wl,-rpath,$ORIGIN", f"-L{torch_lib}", "-lc10", "-ltorch_cpu",
+          "-ltorch_python"])
+    return msg
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     hipcc = _hipcc()
@@ -41,6 +59,9 @@ def build(verbose: bool = False) -> str:
             if verbose and msg.strip():
                 print(msg, file=sys.stderr)
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    msg = _build_bind()
+    if verbose and msg.strip():
+        print(msg, file=sys.stderr)
     return LIB
 
 

@@ -1,4 +1,5 @@
-"""ctypes binding of libstem's C ABI (include/stem.h): same names, argument marshalling only.
+"""ctypes binding of libstem's C ABI (include/stem.h): same names, argument marshalling only.  The ordinary call of a
+training or decode step is marshalled natively instead (csrc/bind.cpp), where the interpreter would take as long as the GPU.
 
 Every function takes torch tensors (device memory unless the C header says host),
 checks dtype / contiguity, and passes raw pointers plus the current torch stream.
@@ -46,6 +47,7 @@ class StemError(RuntimeError):
 
 
 _lib = None
+_bind = None
 
 
 def lib() -> ctypes.CDLL:
@@ -117,6 +119,16 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+def _load_bind():
+    global _bind
+    lib()
+    from . import _bind as native
+    native.setup(StemCtx, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    os.register_at_fork(after_in_child=native.off)   # torch refuses the device there
+    _bind = native
+    return native
+
+
 def status_string(status: int) -> str:
     return lib().stem_status_string(status).decode()
 
@@ -151,9 +163,7 @@ def _check(ctx, status: int, where: str):
         raise StemError(status, where, lib().stem_last_error(h).decode())
 
 
-# Pointers and streams go to the library as plain integers, which its argument types convert; a small layer's call
-# spends as long here as on the GPU (24 tokens, d_model 1024: 14 us a call with a c_void_p object per argument and a
-# torch Stream per call).
+# Pointers and streams go to the library as plain integers, which its argument types convert.
 def _stream(stream) -> int:
     if stream is None:
         return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
@@ -214,95 +224,121 @@ def stem_sync_status(ctx: StemCtx, stream=None):
 
 def stem_ffn_forward(ctx: StemCtx, x, ids, W_gate, W_down, E, y, save_G=None, save_H=None, wait_event=None,
                      stream=None, E_rows=None, T=None):
-    dt = ctx.torch_dtype
-    T = x.shape[0] if T is None else T
-    E_rows = E.shape[0] if E_rows is None else E_rows
-    st = lib().stem_ffn_forward(ctx.handle, _ptr(x, dt, name="x"), _ptr(ids, torch.int32, name="ids"),
-                                _ptr(W_gate, dt, name="W_gate"), _ptr(W_down, dt, name="W_down"),
-                                _ptr(E, dt, name="E"), E_rows, T, _ptr(y, dt, name="y"),
-                                _ptr(save_G, dt, name="save_G"), _ptr(save_H, dt, name="save_H"),
-                                wait_event, _stream(stream))
-    _check(ctx, st, "stem_ffn_forward")
+    st = (_bind or _load_bind()).ffn_forward(ctx, x, ids, W_gate, W_down, E, y, save_G, save_H, wait_event, stream,
+                                             E_rows, T)
+    if st is None:   # not the ordinary call
+        dt = ctx.torch_dtype
+        T = x.shape[0] if T is None else T
+        E_rows = E.shape[0] if E_rows is None else E_rows
+        st = lib().stem_ffn_forward(ctx.handle, _ptr(x, dt, name="x"), _ptr(ids, torch.int32, name="ids"),
+                                    _ptr(W_gate, dt, name="W_gate"), _ptr(W_down, dt, name="W_down"),
+                                    _ptr(E, dt, name="E"), E_rows, T, _ptr(y, dt, name="y"),
+                                    _ptr(save_G, dt, name="save_G"), _ptr(save_H, dt, name="save_H"),
+                                    wait_event, _stream(stream))
+    if st != STEM_OK:
+        _check(ctx, st, "stem_ffn_forward")
 
 
 def stem_ffn_forward_residual(ctx: StemCtx, x, ids, W_gate, W_down, E, residual, y, stream=None, E_rows=None, T=None):
     """y = residual + layer(x); y may be residual (and x) itself."""
-    dt = ctx.torch_dtype
-    T = x.shape[0] if T is None else T
-    E_rows = E.shape[0] if E_rows is None else E_rows
-    st = lib().stem_ffn_forward_residual(ctx.handle, _ptr(x, dt, name="x"), _ptr(ids, torch.int32, name="ids"),
-                                         _ptr(W_gate, dt, name="W_gate"), _ptr(W_down, dt, name="W_down"),
-                                         _ptr(E, dt, name="E"), E_rows, T, _ptr(residual, dt, name="residual"),
-                                         _ptr(y, dt, name="y"), _stream(stream))
-    _check(ctx, st, "stem_ffn_forward_residual")
+    st = (_bind or _load_bind()).ffn_forward_residual(ctx, x, ids, W_gate, W_down, E, residual, y, stream, E_rows, T)
+    if st is None:   # not the ordinary call
+        dt = ctx.torch_dtype
+        T = x.shape[0] if T is None else T
+        E_rows = E.shape[0] if E_rows is None else E_rows
+        st = lib().stem_ffn_forward_residual(ctx.handle, _ptr(x, dt, name="x"), _ptr(ids, torch.int32, name="ids"),
+                                             _ptr(W_gate, dt, name="W_gate"), _ptr(W_down, dt, name="W_down"),
+                                             _ptr(E, dt, name="E"), E_rows, T, _ptr(residual, dt, name="residual"),
+                                             _ptr(y, dt, name="y"), _stream(stream))
+    if st != STEM_OK:
+        _check(ctx, st, "stem_ffn_forward_residual")
 
 
 def stem_ffn_backward(ctx: StemCtx, dy, x, ids, W_gate, W_down, E, saved_G, saved_H, dx, dW_gate, dW_down, dU,
                       accumulate: bool = False, stream=None, E_rows=None, T=None):
-    dt = ctx.torch_dtype
-    T = dy.shape[0] if T is None else T
-    E_rows = E.shape[0] if E_rows is None else E_rows
-    st = lib().stem_ffn_backward(ctx.handle, _ptr(dy, dt, name="dy"), _ptr(x, dt, name="x"),
-                                 _ptr(ids, torch.int32, name="ids"), _ptr(W_gate, dt, name="W_gate"),
-                                 _ptr(W_down, dt, name="W_down"), _ptr(E, dt, name="E"), E_rows,
-                                 _ptr(saved_G, dt, name="saved_G"), _ptr(saved_H, dt, name="saved_H"), T,
-                                 _ptr(dx, dt, name="dx"), _ptr(dW_gate, torch.float32, name="dW_gate"),
-                                 _ptr(dW_down, torch.float32, name="dW_down"), _ptr(dU, dt, name="dU"),
-                                 1 if accumulate else 0, _stream(stream))
-    _check(ctx, st, "stem_ffn_backward")
+    st = (_bind or _load_bind()).ffn_backward(ctx, dy, x, ids, W_gate, W_down, E, saved_G, saved_H, dx, dW_gate,
+                                              dW_down, dU, accumulate, stream, E_rows, T)
+    if st is None:   # not the ordinary call
+        dt = ctx.torch_dtype
+        T = dy.shape[0] if T is None else T
+        E_rows = E.shape[0] if E_rows is None else E_rows
+        st = lib().stem_ffn_backward(ctx.handle, _ptr(dy, dt, name="dy"), _ptr(x, dt, name="x"),
+                                     _ptr(ids, torch.int32, name="ids"), _ptr(W_gate, dt, name="W_gate"),
+                                     _ptr(W_down, dt, name="W_down"), _ptr(E, dt, name="E"), E_rows,
+                                     _ptr(saved_G, dt, name="saved_G"), _ptr(saved_H, dt, name="saved_H"), T,
+                                     _ptr(dx, dt, name="dx"), _ptr(dW_gate, torch.float32, name="dW_gate"),
+                                     _ptr(dW_down, torch.float32, name="dW_down"), _ptr(dU, dt, name="dU"),
+                                     1 if accumulate else 0, _stream(stream))
+    if st != STEM_OK:
+        _check(ctx, st, "stem_ffn_backward")
 
 
 def stem_ffn_up_forward(ctx: StemCtx, x, ids, W_gate, W_up, W_down, E, y, save_G=None, save_Up=None, save_H=None,
                         stream=None, E_rows=None, T=None):
     """E (and ids) may be None: the dense SwiGLU FFN."""
-    dt = ctx.torch_dtype
-    T = x.shape[0] if T is None else T
-    E_rows = (E.shape[0] if E is not None else 0) if E_rows is None else E_rows
-    st = lib().stem_ffn_up_forward(ctx.handle, _ptr(x, dt, name="x"), _ptr(ids, torch.int32, name="ids"),
-                                   _ptr(W_gate, dt, name="W_gate"), _ptr(W_up, dt, name="W_up"),
-                                   _ptr(W_down, dt, name="W_down"), _ptr(E, dt, name="E"), E_rows, T,
-                                   _ptr(y, dt, name="y"), _ptr(save_G, dt, name="save_G"),
-                                   _ptr(save_Up, dt, name="save_Up"), _ptr(save_H, dt, name="save_H"), _stream(stream))
-    _check(ctx, st, "stem_ffn_up_forward")
+    st = (_bind or _load_bind()).ffn_up_forward(ctx, x, ids, W_gate, W_up, W_down, E, y, save_G, save_Up, save_H,
+                                                stream, E_rows, T)
+    if st is None:   # not the ordinary call
+        dt = ctx.torch_dtype
+        T = x.shape[0] if T is None else T
+        E_rows = (E.shape[0] if E is not None else 0) if E_rows is None else E_rows
+        st = lib().stem_ffn_up_forward(ctx.handle, _ptr(x, dt, name="x"), _ptr(ids, torch.int32, name="ids"),
+                                       _ptr(W_gate, dt, name="W_gate"), _ptr(W_up, dt, name="W_up"),
+                                       _ptr(W_down, dt, name="W_down"), _ptr(E, dt, name="E"), E_rows, T,
+                                       _ptr(y, dt, name="y"), _ptr(save_G, dt, name="save_G"),
+                                       _ptr(save_Up, dt, name="save_Up"), _ptr(save_H, dt, name="save_H"), _stream(stream))
+    if st != STEM_OK:
+        _check(ctx, st, "stem_ffn_up_forward")
 
 
 def stem_ffn_up_backward(ctx: StemCtx, dy, x, ids, W_gate, W_up, W_down, E, saved_G, saved_Up, saved_H, dx, dW_gate,
                          dW_up, dW_down, dV, accumulate: bool = False, stream=None, E_rows=None, T=None):
-    dt = ctx.torch_dtype
-    f32 = torch.float32
-    T = dy.shape[0] if T is None else T
-    E_rows = (E.shape[0] if E is not None else 0) if E_rows is None else E_rows
-    st = lib().stem_ffn_up_backward(ctx.handle, _ptr(dy, dt, name="dy"), _ptr(x, dt, name="x"),
-                                    _ptr(ids, torch.int32, name="ids"), _ptr(W_gate, dt, name="W_gate"),
-                                    _ptr(W_up, dt, name="W_up"), _ptr(W_down, dt, name="W_down"),
-                                    _ptr(E, dt, name="E"), E_rows, _ptr(saved_G, dt, name="saved_G"),
-                                    _ptr(saved_Up, dt, name="saved_Up"), _ptr(saved_H, dt, name="saved_H"), T,
-                                    _ptr(dx, dt, name="dx"), _ptr(dW_gate, f32, name="dW_gate"),
-                                    _ptr(dW_up, f32, name="dW_up"), _ptr(dW_down, f32, name="dW_down"),
-                                    _ptr(dV, dt, name="dV"), 1 if accumulate else 0, _stream(stream))
-    _check(ctx, st, "stem_ffn_up_backward")
+    st = (_bind or _load_bind()).ffn_up_backward(ctx, dy, x, ids, W_gate, W_up, W_down, E, saved_G, saved_Up, saved_H,
+                                                 dx, dW_gate, dW_up, dW_down, dV, accumulate, stream, E_rows, T)
+    if st is None:   # not the ordinary call
+        dt = ctx.torch_dtype
+        f32 = torch.float32
+        T = dy.shape[0] if T is None else T
+        E_rows = (E.shape[0] if E is not None else 0) if E_rows is None else E_rows
+        st = lib().stem_ffn_up_backward(ctx.handle, _ptr(dy, dt, name="dy"), _ptr(x, dt, name="x"),
+                                        _ptr(ids, torch.int32, name="ids"), _ptr(W_gate, dt, name="W_gate"),
+                                        _ptr(W_up, dt, name="W_up"), _ptr(W_down, dt, name="W_down"),
+                                        _ptr(E, dt, name="E"), E_rows, _ptr(saved_G, dt, name="saved_G"),
+                                        _ptr(saved_Up, dt, name="saved_Up"), _ptr(saved_H, dt, name="saved_H"), T,
+                                        _ptr(dx, dt, name="dx"), _ptr(dW_gate, f32, name="dW_gate"),
+                                        _ptr(dW_up, f32, name="dW_up"), _ptr(dW_down, f32, name="dW_down"),
+                                        _ptr(dV, dt, name="dV"), 1 if accumulate else 0, _stream(stream))
+    if st != STEM_OK:
+        _check(ctx, st, "stem_ffn_up_backward")
 
 
 def stem_embed_grad(ctx: StemCtx, ids, dU, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, dE_rows, stream=None,
                     T=None):
-    i32 = torch.int32
-    T = ids.shape[0] if T is None else T
-    st = lib().stem_embed_grad(ctx.handle, _ptr(ids, i32, name="ids"), _ptr(dU, ctx.torch_dtype, name="dU"), T,
-                               _ptr(sorted_ids, i32, name="sorted_ids"), _ptr(perm, i32, name="perm"),
-                               _ptr(uniq_ids, i32, name="uniq_ids"), _ptr(seg_offsets, i32, name="seg_offsets"),
-                               _ptr(n_uniq, i32, name="n_uniq"), _ptr(dE_rows, torch.float32, name="dE_rows"),
-                               _stream(stream))
-    _check(ctx, st, "stem_embed_grad")
+    st = (_bind or _load_bind()).embed_grad(ctx, ids, dU, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, dE_rows,
+                                            stream, T)
+    if st is None:   # not the ordinary call
+        i32 = torch.int32
+        T = ids.shape[0] if T is None else T
+        st = lib().stem_embed_grad(ctx.handle, _ptr(ids, i32, name="ids"), _ptr(dU, ctx.torch_dtype, name="dU"), T,
+                                   _ptr(sorted_ids, i32, name="sorted_ids"), _ptr(perm, i32, name="perm"),
+                                   _ptr(uniq_ids, i32, name="uniq_ids"), _ptr(seg_offsets, i32, name="seg_offsets"),
+                                   _ptr(n_uniq, i32, name="n_uniq"), _ptr(dE_rows, torch.float32, name="dE_rows"),
+                                   _stream(stream))
+    if st != STEM_OK:
+        _check(ctx, st, "stem_embed_grad")
 
 
 def stem_embed_grad_presorted(ctx: StemCtx, dU, perm, seg_offsets, dE_rows, stream=None, T=None):
     """The row sums alone, after a stem_embed_grad(dU=None) call on the same context and T."""
-    T = dU.shape[0] if T is None else T
-    st = lib().stem_embed_grad_presorted(ctx.handle, _ptr(dU, ctx.torch_dtype, name="dU"), T,
-                                         _ptr(perm, torch.int32, name="perm"),
-                                         _ptr(seg_offsets, torch.int32, name="seg_offsets"),
-                                         _ptr(dE_rows, torch.float32, name="dE_rows"), _stream(stream))
-    _check(ctx, st, "stem_embed_grad_presorted")
+    st = (_bind or _load_bind()).embed_grad_presorted(ctx, dU, perm, seg_offsets, dE_rows, stream, T)
+    if st is None:   # not the ordinary call
+        T = dU.shape[0] if T is None else T
+        st = lib().stem_embed_grad_presorted(ctx.handle, _ptr(dU, ctx.torch_dtype, name="dU"), T,
+                                             _ptr(perm, torch.int32, name="perm"),
+                                             _ptr(seg_offsets, torch.int32, name="seg_offsets"),
+                                             _ptr(dE_rows, torch.float32, name="dE_rows"), _stream(stream))
+    if st != STEM_OK:
+        _check(ctx, st, "stem_embed_grad_presorted")
 
 
 def stem_embed_grad_noalloc(dtype: int, vocab: int, d_ff: int, ids, dU, sorted_ids, perm, uniq_ids, seg_offsets,
@@ -322,17 +358,21 @@ def stem_embed_grad_noalloc(dtype: int, vocab: int, d_ff: int, ids, dU, sorted_i
 def stem_embed_sparse_adamw(ctx: StemCtx, uniq_ids, n_uniq, dE_rows, E, master, m, v, lr, beta1, beta2, eps,
                             weight_decay, step, stream=None, max_rows=None):
     """E, master, m, v may be pinned host tensors (table and optimiser state resident in host memory)."""
-    hp = stem_adamw_hparams(lr, beta1, beta2, eps, weight_decay, step)
-    f32 = torch.float32
-    max_rows = dE_rows.shape[0] if max_rows is None else max_rows
-    st = lib().stem_embed_sparse_adamw(ctx.handle, _ptr(uniq_ids, torch.int32, name="uniq_ids"),
-                                       _ptr(n_uniq, torch.int32, name="n_uniq"), max_rows,
-                                       _ptr(dE_rows, f32, name="dE_rows"),
-                                       _ptr(E, ctx.torch_dtype, cuda="or_pinned", name="E"),
-                                       _ptr(master, f32, cuda="or_pinned", name="master"),
-                                       _ptr(m, f32, cuda="or_pinned", name="m"),
-                                       _ptr(v, f32, cuda="or_pinned", name="v"), ctypes.byref(hp), _stream(stream))
-    _check(ctx, st, "stem_embed_sparse_adamw")
+    st = (_bind or _load_bind()).embed_sparse_adamw(ctx, uniq_ids, n_uniq, dE_rows, E, master, m, v, lr, beta1, beta2,
+                                                    eps, weight_decay, step, stream, max_rows)
+    if st is None:   # not the ordinary call
+        hp = stem_adamw_hparams(lr, beta1, beta2, eps, weight_decay, step)
+        f32 = torch.float32
+        max_rows = dE_rows.shape[0] if max_rows is None else max_rows
+        st = lib().stem_embed_sparse_adamw(ctx.handle, _ptr(uniq_ids, torch.int32, name="uniq_ids"),
+                                           _ptr(n_uniq, torch.int32, name="n_uniq"), max_rows,
+                                           _ptr(dE_rows, f32, name="dE_rows"),
+                                           _ptr(E, ctx.torch_dtype, cuda="or_pinned", name="E"),
+                                           _ptr(master, f32, cuda="or_pinned", name="master"),
+                                           _ptr(m, f32, cuda="or_pinned", name="m"),
+                                           _ptr(v, f32, cuda="or_pinned", name="v"), ctypes.byref(hp), _stream(stream))
+    if st != STEM_OK:
+        _check(ctx, st, "stem_embed_sparse_adamw")
 
 
 def stem_prefetch_rows(ctx: StemCtx, E_host, ids_host, E_compact, remap, uniq_ids_host=None, T=None):
