@@ -22,7 +22,7 @@ const char* const kKernelNames[K_COUNT_] = {
     "gemm_dw_gate",    "silu_gather",      "sort_count",    "sort_scan",    "sort_scatter",
     "sort_fused",      "unique",          "seg_reduce",   "seg_combine",   "sparse_adamw", "row_copy",
     "splitk_reduce",   "gemm_up",      "gemm_dw_up",   "sort_merge",
-    "grads_f32", "gemm_dw", "list_copy"};
+    "grads_f32", "gemm_dw", "list_copy", "ffn_decode"};
 
 #define fail stem_fail
 
@@ -313,8 +313,11 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   if (desc->dtype == STEM_BF16) {
     c->splitk_bytes = (size_t)stem_route_splitk_bytes(desc->d_model, desc->d_ff, max_tokens);
     ok(hipMalloc(reinterpret_cast<void**>(&c->splitk_ws), c->splitk_bytes));
-    ok(dmalloc(&c->rounds, STEM_TICKETS * 3 / 2));   // the tickets behind them
-    if (c->rounds) c->tickets = reinterpret_cast<int32_t*>(c->rounds + STEM_TICKETS);
+    ok(dmalloc(&c->rounds, STEM_COUNTERS / 8));   // the tickets behind them, and then flags and claims
+    if (c->rounds) {
+      c->tickets = reinterpret_cast<int32_t*>(c->rounds + STEM_TICKETS);
+      c->sync = reinterpret_cast<uint32_t*>(c->tickets + STEM_TICKETS);
+    }
     c->polls = STEM_POLLS;
   }
   for (int i = 0; i < 2; ++i) {
@@ -332,7 +335,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->uniq_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(hipHostMalloc(reinterpret_cast<void**>(&c->remap_pinned), std::max<size_t>(max_tokens, 1) * 4, hipHostMallocDefault));
   ok(copy_streams_get(device, &c->side));
-  if (e == hipSuccess && c->tickets) ok(zero_now(c->rounds, STEM_TICKETS * 12, c->side));
+  if (e == hipSuccess && c->tickets) ok(zero_now(c->rounds, STEM_COUNTERS, c->side));
   ok(hipEventCreateWithFlags(&c->ready, hipEventDisableTiming));
   ok(hipEventCreateWithFlags(&c->promoted, hipEventDisableTiming));
   c->done = c->ready;
@@ -411,7 +414,13 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
   const int d = c->desc.d_model, F = c->desc.d_ff;
   void* H = save_H ? save_H : c->H_ws;
 
-  if (c->desc.dtype == STEM_BF16) {
+  if (c->desc.dtype == STEM_BF16 && !wait_event && stem_route_one_launch(d, F, T) &&
+      stem_route_one_launch_apart(d, F, T, save_G, save_H, W_down, residual, y)) {
+    const StemDecodeArgs a = {static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(W_gate), static_cast<const bf16_t*>(W_down),
+                              static_cast<const bf16_t*>(E), static_cast<const bf16_t*>(residual), ids, static_cast<bf16_t*>(y),
+                              static_cast<bf16_t*>(save_G), static_cast<bf16_t*>(save_H), (int)T, d, F, (int)E_rows};
+    HIP_TRY(c, stem_ffn_decode_bf16(c, a, s));
+  } else if (c->desc.dtype == STEM_BF16) {
     GemmArgs a = {};
     a.A = static_cast<const bf16_t*>(x); a.lda = d;
     a.B = static_cast<const bf16_t*>(W_gate); a.ldb = d;

@@ -33,6 +33,7 @@ enum StemKernelId {
   K_GRADS_F32,       // dx, dWd and dWg of a small fp32 layer in one launch
   K_GEMM_DW,         // two or three weight gradients in one launch
   K_LIST_COPY,       // host-resident table: remap and the row copy's lists
+  K_FFN_DECODE,      // a decode step's layer in one launch
   K_COUNT_
 };
 
@@ -61,7 +62,8 @@ struct stem_ctx {
   size_t splitk_bytes;   // its size; no launch splits beyond it
   int32_t* tickets;      // [STEM_TICKETS] counters of finished K slices per output tile, zero between launches
   unsigned long long* rounds; // [STEM_TICKETS] the same for the few-row kernel, which counts on from launch to launch
-  int polls;             // how often a workgroup of it looks for the other slices of its tile
+  uint32_t* sync;        // [33 * 256] flags, 32 times, and claims of the layer in one launch (ffn_decode_bf16.hip)
+  int polls;             // how often a workgroup of these two looks for the others
   int32_t* sort_keys[2]; // [max_tokens]
   int32_t* sort_vals[2]; // [max_tokens]
   int32_t* sort_counts;  // [64 * waves]
@@ -220,8 +222,13 @@ int stem_route_weight_grads_apart(int d_model, int d_ff, int64_t T, const void* 
 int stem_route_gate_up_together(int d_model, int d_ff, int64_t T, const void* W_up, const void* E, int64_t E_rows, const void* ids,
                                 const void* G, const void* Up, const void* H);
 void stem_route_decode(int M, int N, int K, int epi, int64_t ws_bytes, int32_t* route);
-// the gate (route[0..3]) and down (route[4..7]) products of a bf16 stem_ffn_forward call of T tokens, in a context made for as many
+// the gate (route[0..3]) and down (route[4..7]) products of a bf16 stem_ffn_forward call of T tokens that is not one launch, in a context made for
+// as many
 void stem_route_forward(int d_model, int d_ff, int64_t T, int32_t* route);
+// whether a forward call with the table on the device is one launch (ffn_decode_bf16.hip): by size, and as its buffers lie (null: not there)
+int stem_route_one_launch(int d_model, int d_ff, int64_t T);
+int stem_route_one_launch_apart(int d_model, int d_ff, int64_t T, const void* G, const void* H, const void* W_down, const void* residual,
+                                const void* y);
 int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   // a context's room for K slices
 int stem_route_sort(int64_t T, int V);   // SortRoute
 // whether the kernel that counts ranks sorts them, which it does where the size allows and no two of the call's buffers overlap
@@ -244,7 +251,7 @@ int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, to
 // 124 / 146; fp32, 256 x 1024, 8192 tokens (0.9) 212 / 203 / 197, 512 x 2048, vocabulary 8000, 2000 tokens (1.5) 156 / 131 / 149.  On two contexts two in
 // turn are within 1 % of a stream for each, and of one but at 8192 tokens of 1024 x 4096 (381 / 393) and 4096 of 2048 x 8192 (470 / 510).
 int stem_route_copy_streams(int d_model, int d_ff, int dtype, int64_t T, int64_t rows);
-void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices waits for another
+void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices or of the layer in one launch waits for another
 }
 // By size.  SORT_ONE_* and SORT_RANKS_8192: ranks by counting where stem_route_sort_ranks says so, else the passes of one workgroup up to
 // 4096 ids and merged runs of 1024 beyond.
@@ -281,10 +288,20 @@ hipError_t stem_gemm_skinny_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs
 
 // ---- decode-sized bf16 GEMM (gemm_decode_bf16.hip): both operands K-contiguous --------------------
 #define STEM_TICKETS 256
+#define STEM_COUNTERS (STEM_TICKETS * (8 + 4) + 33 * 256 * 4)   // bytes of a context's rounds, tickets, flags and claims
 #define STEM_POLLS 2000   // 1 to 2 ms: the slices of a tile are some us apart unless other streams hold the compute units
 bool stem_gemm_decode_fits(int M, int N, int K);
 // epi: EPI_BF16 (+ residual; split along K through a.ws and a.tickets where that pays) or EPI_GATE
 hipError_t stem_gemm_decode_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs& a, hipStream_t s);
+
+// ---- a decode step's layer in one launch (ffn_decode_bf16.hip): the table on the device ----
+struct StemDecodeArgs {
+  const bf16_t *x, *Wg, *Wd, *E, *residual;   // residual may be null
+  const int32_t* ids;
+  bf16_t *y, *save_G, *save_H;                // the saved ones may be null
+  int T, d, F, E_rows;
+};
+hipError_t stem_ffn_decode_bf16(stem_ctx* ctx, const StemDecodeArgs& a, hipStream_t s);
 
 // ---- fp32 path and element-wise kernels (kernels_f32.hip) -------------------------
 struct GemmF32Args {

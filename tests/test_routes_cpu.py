@@ -169,3 +169,24 @@ def test_sort_and_sums_share_a_launch_where_no_two_of_their_buffers_overlap(bf16
             for at, one in ((lie[b] - size[a], True), (lie[b] - size[a] + 4, False), (lie[b], False), (lie[b] + size[b] - 4, False),
                             (lie[b] + size[b], True)):
                 assert share(**{a: at}) == one, (a, b, at - lie[b])
+
+
+@pytest.mark.parametrize("T,d,F", [(1, 64, 64), (24, 1024, 4096)])
+def test_saved_activations_beside_the_layer_in_one_launch(T, d, F):
+    size = dict(G=T * F * 2, H=T * F * 2, W_down=F * d * 2, residual=T * d * 2, y=T * d * 2)
+    lie = {k: (i + 1) << 28 for i, k in enumerate(size)}
+    apart = lambda **over: bool(L.lib().stem_route_one_launch_apart(d, F, ctypes.c_int64(T), *[ctypes.c_void_p({**lie, **over}[k]) for k in size]))
+    assert apart() and apart(G=None, H=None) and apart(G=lie["H"]) and apart(residual=lie["y"]) and apart(residual=lie["W_down"])
+    for a in ("G", "H"):
+        for b in ("W_down", "residual", "y"):
+            for at, ok in ((lie[b] - size[a], True), (lie[b] - size[a] + 2, False), (lie[b], False), (lie[b] + size[b] - 2, False),
+                           (lie[b] + size[b], True)):
+                assert apart(**{a: at}) == ok, (a, b, at - lie[b])
+
+
+def test_sizes_of_the_layer_in_one_launch():
+    one = lambda T, d, F: bool(L.lib().stem_route_one_launch(d, F, ctypes.c_int64(T)))
+    assert one(1, 64, 64) and one(32, 2048, 8192) and not one(0, 64, 64) and not one(33, 2048, 8192)
+    assert not one(1, 2112, 64) and not one(1, 64, 8256)
+    assert one(64, 512, 2048) and not one(65, 512, 2048) and not one(33, 576, 2048) and one(48, 1024, 4096) and not one(49, 1024, 4096)
+    assert not one(33, 1024, 3584) and not one(33, 1088, 4096)
