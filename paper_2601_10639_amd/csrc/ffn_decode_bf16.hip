@@ -17,7 +17,7 @@
 // The exchange.  H is stored and loaded with the device scope bit (sc1), past the L2s of the eight XCDs, which do not see each
 // other's lines; a workgroup waits until its stores are complete and then raises its flag to the launch's number, and one wavefront looks at
 // all flags at once.  There are 32 copies of the flags, each looked at by 8 workgroups: 256 that read the same 8 lines wait
-// for each other (1.0 us a look; 7.9 -> 7.1 us a layer of 512 x 1536 with 1 and 32 copies).  The grid is the context's, not the
+// for each other (1.0 us a look; a layer of 512 x 1536, one token, with 1 / 8 copies 6.9 / 6.1 us, with 16 / 32 5.7 / 5.5).  The grid is the context's, not the
 // call's, so every launch raises the same flags by one: nothing is reset, and a graph replays it.
 //
 // Nobody waits for good, as workgroups may not all be on the chip, where other streams fill it: one that has looked `polls` times
@@ -58,7 +58,7 @@ struct Args {
   const bf16_t *x, *Wg, *Wd, *E, *residual;
   const int32_t* ids;
   bf16_t *y, *H, *save_G, *save_H;      // H: the exchange's; the saved ones may be null
-  uint32_t* sync;                       // 256 flags, 256 claims
+  uint32_t* sync;                       // 32 x 256 flags, 256 claims
   int32_t* bad_id;
   int T, d, F, E_rows, polls;
 };
@@ -255,7 +255,8 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
 
   // ---- the exchange
   u32x4_t claims = {};
-  if (wave == 0) {
+  constexpr int LOOKS = WAVES - 1;   // the wavefront that looks: the first ones have H to store and wait for (0.1 to 0.3 us)
+  if (wave == LOOKS) {
     if (lane < REPLICAS) __builtin_amdgcn_raw_buffer_store_b32(epoch, rflags, (lane * MAX_WGS + b) * 4, 0, SC1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // complete before it looks at the others'
     auto all_there = [&]() __attribute__((always_inline)) {
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
       __syncthreads();   // all have read next_share
     }
     // a share that was given up, if there is one: the claims that were there, one after another
-    if (wave == 0) {
+    if (wave == LOOKS) {
       int found = -1;
       for (;;) {
         const uint64_t any = __ballot(claims[0] == epoch || claims[1] == epoch || claims[2] == epoch || claims[3] == epoch);
