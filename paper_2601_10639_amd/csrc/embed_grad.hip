@@ -1,5 +1,5 @@
 // Gradient of the per-layer table, restricted to the rows a batch touches:
-// stable sort of (token id, position) by counting ranks or by radix passes (in LDS, as merged runs, or digit by digit), distinct ids with run offsets, and a
+// stable sort of (token id, position) by counting ranks, by buckets of the vocabulary or by radix passes (in LDS, as merged runs, or digit by digit), distinct ids with run offsets, and a
 // fixed-order segmented sum of the per-token row gradients.  Integer results are unique,
 // floating sums use one fixed association, so every run gives the same bits.
 #include <algorithm>
@@ -357,16 +357,15 @@ __global__ __launch_bounds__(1024) void sort_lds_kernel(const int32_t* __restric
   }
 }
 
-// ---- up to 8192 ids: ranks by counting ----------------------------------------------------------------
-// One workgroup's passes are a chain of barriers, and it has one compute unit of the chip.  Here each workgroup places 8 or 16 ids and
+// ---- up to 2048 ids: ranks by counting ----------------------------------------------------------------
+// One workgroup's passes are a chain of barriers, and it has one compute unit of the chip.  Here each workgroup places 8 ids and
 // looks at all of them: an id's place is the number of smaller (id, position) keys, counted by ballots, 64 keys a compare; where its run
 // begins, the number of keys below (id, 0); the number of its run, the distinct ids below it, from a bitmap of the ids in LDS and its
 // prefix sums.  Nothing passes between workgroups, so one launch does it all.  What bounds it is the launch, the id loads and
-// four barriers, from some 2000 ids on the scalar unit, which counts each compare's bits.  us in a graph, before (one workgroup's passes,
-// beyond 4096 ids runs and their merge) / this, Zipf ids: 128 ids 5.8 / 4.1, 1000 7.5 / 4.4, 1999 12.6 / 5.3, 4096 13.4 / 7.6, 8192
-// 22.4 / 15.7; one id for all: 4096 13.2 / 7.8.  (16 ids a workgroup up to 2048: 1000 ids 4.9, 1999 6.1; 32: 6.0 and 7.7.)
+// four barriers.  us in a graph, before (one workgroup's passes) / this, Zipf ids: 128 ids 5.8 / 4.1, 1000 7.5 / 4.4, 1999 12.6 / 5.3.
+// (16 ids a workgroup: 1000 ids 4.9, 1999 6.1; 32: 6.0 and 7.7.)  Counting is quadratic: 4096 ids 7.6, 8192 15.7.
 constexpr int RANK_WORDS = 8192;                 // 32 KB of bitmap: vocabularies up to 2^18
-constexpr int RANK_MAX = 8192;                   // ids
+constexpr int RANK_MAX = 2048;                   // ids
 template <int CHUNKS, int OWN>                   // T <= CHUNKS * 1024; ids a workgroup places, at most a wavefront's lanes
 __global__ __launch_bounds__(1024) void sort_ranks_kernel(const int32_t* __restrict__ ids, int T, int V, int pos_bits,
                                                           int32_t* __restrict__ sorted_ids, int32_t* __restrict__ perm,
@@ -411,7 +410,7 @@ __global__ __launch_bounds__(1024) void sort_ranks_kernel(const int32_t* __restr
       below += __popcll(__ballot(key[c] < k));
       start += __popcll(__ballot(key[c] < k_id));
     }
-    mine = lane == q ? below | start << 16 : mine;   // sums over the wavefronts up to 8192 each
+    mine = lane == q ? below | start << 16 : mine;   // sums over the wavefronts up to 2048 each
   }
   if (lane < OWN) counts[wave][lane] = mine;
   __syncthreads();                               // counts, and all ids are in the bitmap
@@ -438,6 +437,128 @@ __global__ __launch_bounds__(1024) void sort_ranks_kernel(const int32_t* __restr
   perm[place] = own_i;
   seg_of[place] = run;
   if (place == start) { uniq_ids[run] = own_id; seg_offsets[run] = start; }
+}
+
+// ---- more ids, up to 16384: a workgroup for every bucket of the vocabulary -------------------------------------------
+// Merged runs are three launches.  Here each of up to 256 workgroups owns the ids of a stretch of the vocabulary: it looks at all ids, keeps
+// its own in order in LDS and sorts them by one stable counting pass (a wavefront's rounds of 64 by ballots, a table of counts per wavefront
+// and id, its scan, the rounds again).  Where its ids begin is the number of smaller ids, the number of its first run the distinct smaller
+// ids, from a bitmap in LDS.  Nothing passes between workgroups, and one frequent id makes one workgroup's pass longer, not the others'.
+// What bounds it are the looks at all ids and their bits in the bitmap.  us in a graph, before (ranks up to 8192 ids, then merged runs) / this,
+// Zipf ids and one id for all: 3000 ids 7.6 / 7.1 and 7.8 / 7.4, 4096 7.8 / 7.3 and 7.9 / 7.9, 5000 14.9 / 8.2 and 15.2 / 9.6, 8192 15.9 /
+// 9.2 and 16.0 / 11.4, 16384 24.6 / 13.5 and 22.0 / 19.7; 2048 ids 5.5 / 7.6 and 5.7 / 7.1.  (Rounds by bits alone, and twice: 16384 ids 15.0
+// and 35.1.)  16384 ids are what its LDS holds.
+constexpr int BUCKET_MIN = 2048, BUCKET_MAX = 16384;   // ids: more than the one, up to the other
+constexpr int BUCKET_IDS = 1024;                 // vocabulary entries of a bucket at most
+template <int CHUNKS>                            // T <= CHUNKS * 1024
+__global__ __launch_bounds__(1024) void sort_buckets_kernel(const int32_t* __restrict__ ids, int T, int V, int R, int bits,
+                                                            int32_t* __restrict__ sorted_ids, int32_t* __restrict__ perm,
+                                                            int32_t* __restrict__ uniq_ids, int32_t* __restrict__ seg_offsets,
+                                                            int32_t* __restrict__ n_uniq, int32_t* __restrict__ seg_of, int32_t* flag) {
+  constexpr int POS = 14;                        // bits of a position
+  __shared__ __attribute__((aligned(16))) uint32_t bitmap[RANK_WORDS];
+  __shared__ uint32_t list[CHUNKS * 1024];       // id in the bucket << POS | position
+  __shared__ uint16_t table[SORT_WAVES][BUCKET_IDS];
+  __shared__ int bin_start[BUCKET_IDS], bin_run[BUCKET_IDS];
+  __shared__ int own_s[CHUNKS * SORT_WAVES], less_s[SORT_WAVES], wsum[4][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lo = blockIdx.x * R, hi = min(lo + R, V);            // R: a multiple of 32
+  const uint64_t below = (1ull << lane) - 1ull;
+  int kv[CHUNKS];
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) kv[c] = ids[min(tid + 1024 * c, T - 1)];
+  for (int w = tid; w < lo >> 5; w += 1024) bitmap[w] = 0;
+  for (int w = 0; w < SORT_WAVES; ++w)
+    if (tid < R) table[w][tid] = 0;
+  int less = 0;
+  uint64_t own[CHUNKS];
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    const int id = min(max(kv[c], 0), V - 1);
+    if (blockIdx.x == 0 && id != kv[c]) *flag = 1;
+    kv[c] = tid + 1024 * c < T ? id : 0x7fffffff;                // beyond the batch: in no bucket
+    less += __popcll(__ballot(kv[c] < lo));
+    own[c] = __ballot(kv[c] >= lo && kv[c] < hi);
+    if (lane == 0) own_s[c * SORT_WAVES + wave] = __popcll(own[c]);
+  }
+  if (lane == 0) less_s[wave] = less;
+  __syncthreads();
+  int n;
+  {
+    const int v = tid < CHUNKS * SORT_WAVES ? own_s[tid] : 0, before = block_exclusive(v, wsum[0], lane, wave, &n);
+    if (tid < CHUNKS * SORT_WAVES) own_s[tid] = before;
+  }
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c)               // (a look first: a frequent id would queue all its lanes at one word)
+    if (kv[c] < lo && !(bitmap[kv[c] >> 5] >> (kv[c] & 31) & 1u)) atomicOr(&bitmap[kv[c] >> 5], 1u << (kv[c] & 31));
+  int base = 0;
+#pragma unroll
+  for (int w = 0; w < SORT_WAVES; ++w) base += less_s[w];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c)
+    if (own[c] >> lane & 1ull) list[own_s[c * SORT_WAVES + wave] + __popcll(own[c] & below)] = (uint32_t)(kv[c] - lo) << POS | (uint32_t)(tid + 1024 * c);
+  int set = 0, distinct;
+  for (int w = tid; w < lo >> 5; w += 1024) set += __popc(bitmap[w]);
+  block_exclusive(set, wsum[1], lane, wave, &distinct);          // its barrier is the list's too
+
+  // Every wavefront counts a stretch of the list by rounds of 64, and notes of each entry how many with its id are before it there.
+  // Lanes with one id find each other by comparing with the first one's, a few times over (a frequent id fills whole rounds), then bit by bit.
+  uint16_t* const nth = reinterpret_cast<uint16_t*>(bitmap);     // the bitmap has been counted
+  static_assert(CHUNKS * 1024 * 2 <= sizeof(bitmap), "an entry each");
+  const int stretch = ((n + 1023) >> 10) * 64;
+  for (int i0 = wave * stretch; i0 < min((wave + 1) * stretch, n); i0 += 64) {
+    const int i = i0 + lane;
+    const bool valid = i < n;
+    const int id = (int)(list[min(i, n - 1)] >> POS);
+    uint64_t left = __ballot(valid), same = 0;
+    for (int peel = 0; peel < 3 && left; ++peel) {
+      const uint64_t m = __ballot(id == __builtin_amdgcn_readlane(id, __builtin_ctzll(left))) & left;
+      if (m >> lane & 1ull) same = m;
+      left &= ~m;
+    }
+    if (left) {
+      uint64_t rest = left;
+      for (int x = 0; x < bits; ++x) {
+        const bool bit = (id >> x) & 1;
+        const uint64_t bb = __ballot(bit);
+        rest &= bit ? bb : ~bb;
+      }
+      if (left >> lane & 1ull) same = rest;
+    }
+    if (valid) {
+      const int before = table[wave][id];
+      nth[i] = (uint16_t)(before + __popcll(same & below));
+      if (!(same & below)) table[wave][id] = (uint16_t)(before + __popcll(same));
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  int count = 0;                                 // of id lo + tid; the table becomes what earlier wavefronts have of it
+  if (tid < R)
+    for (int w = 0; w < SORT_WAVES; ++w) {
+      const int t = table[w][tid];
+      table[w][tid] = (uint16_t)count;
+      count += t;
+    }
+  int here;
+  const int start = block_exclusive(count, wsum[2], lane, wave), run = distinct + block_exclusive(count > 0, wsum[3], lane, wave, &here);
+  if (tid < R) {
+    bin_start[tid] = base + start;
+    bin_run[tid] = run;
+    if (count > 0) { uniq_ids[run] = lo + tid; seg_offsets[run] = base + start; }
+  }
+  if (hi == V && tid == 0) {
+    seg_offsets[distinct + here] = T;
+    *n_uniq = distinct + here;
+  }
+  __syncthreads();
+  for (int i = tid; i < n; i += 1024) {
+    const int id = (int)(list[i] >> POS), place = bin_start[id] + table[i / stretch][id] + nth[i];
+    sorted_ids[place] = lo + id;
+    perm[place] = (int)(list[i] & ((1u << POS) - 1u));
+    seg_of[place] = bin_run[id];
+  }
 }
 
 // ---- larger batches: merge of the sorted runs by rank, then distinct ids and run index ---------------
@@ -1018,15 +1139,15 @@ int64_t stem_sort_count_entries(int64_t max_tokens) {
   return tiles * SORT_WAVES * RADIX;
 }
 
-// One launch up to 8192 ids, of workgroups that count ranks, while the vocabulary's bitmap is at most 32 KB (2^18 ids); beyond that
-// vocabulary, or where buffers of the call lie over each other (those workgroups read the ids and store all outputs at the same time), one
-// workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three launches take 22 in a graph).  Counting is quadratic: 8192 ids
-// 15.7 us against 22.3 on merged runs, 16384 ids 45 against 24.  Then runs of
+// One launch up to 16384 ids, of workgroups that count ranks up to 2048 and take a bucket of the vocabulary each beyond, while the
+// vocabulary's bitmap is at most 32 KB (2^18 ids); beyond that vocabulary, or where buffers of the call lie over each other (those
+// workgroups read the ids and store all outputs at the same time), one workgroup up to 4096 ids (8 us up to 1024, 14 us beyond, where three
+// launches take 22 in a graph).  Then runs of
 // 1024, while their number is one group of the merge's searches, and runs of 4096, us in a graph: 6000 ids 22 / 29, 16384
 // ids 25 / 32 (one workgroup 43, the digit passes below 140), 32768 ids 36 / 34, 65536 ids 58 / 38 (digit passes 182).
 // The digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
 // (262144 ids: 126 us against 640).
-static bool ranks_fit(int64_t T, int V) { return T <= RANK_MAX && V <= RANK_WORDS * 32; }
+static bool ranks_fit(int64_t T, int V) { return T <= 8192 && V <= RANK_WORDS * 32; }   // (4097 to 8192: SORT_RANKS_8192)
 
 int stem_route_sort(int64_t T, int V) {
   const int vbits = bits_for(V);
@@ -1037,17 +1158,27 @@ int stem_route_sort(int64_t T, int V) {
   return SORT_DIGITS;
 }
 
-int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
-                          const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of) {
-  if (!ranks_fit(T, V)) return 0;
+// Whether no two buffers of a sort overlap: workgroups that read the ids store all outputs at the same time.
+static bool sort_apart(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
+                       const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of) {
   const int64_t cap = std::min<int64_t>(T, V);
   const struct { const int32_t* at; int64_t n; } buf[] = {{ids, T}, {sorted_ids, T}, {perm, T}, {uniq_ids, cap}, {seg_offsets, cap + 1}, {n_uniq, 1}, {seg_of, T}};
   for (const auto& p : buf)
     for (const auto* q = buf; q < &p; ++q)
       if (reinterpret_cast<uintptr_t>(p.at) < reinterpret_cast<uintptr_t>(q->at + q->n) &&
           reinterpret_cast<uintptr_t>(q->at) < reinterpret_cast<uintptr_t>(p.at + p.n))
-        return 0;
-  return 1;
+        return false;
+  return true;
+}
+
+int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
+                          const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of) {
+  return ranks_fit(T, V) && sort_apart(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, seg_of);
+}
+
+int stem_route_sort_buckets(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
+                            const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of) {
+  return T > BUCKET_MIN && T <= BUCKET_MAX && V <= 256 * BUCKET_IDS && sort_apart(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, seg_of);
 }
 
 hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t* ids, int64_t T, int V,
@@ -1056,11 +1187,18 @@ hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t
   const int passes = (bits_for(V) + RADIX_BITS - 1) / RADIX_BITS;
   const int route = stem_route_sort(T, V);
   const int pos_bits = bits_for((int)std::min<int64_t>(T, 1 << 30));
-  if (stem_route_sort_ranks(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of)) {
+  if (stem_route_sort_buckets(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of)) {
     ProfScope ps(ctx, K_SORT_FUSED, s);
-    const int own = T <= 2048 ? 8 : 16;
-    auto* const kernel = T <= 1024 ? sort_ranks_kernel<1, 8> : T <= 2048 ? sort_ranks_kernel<2, 8> : T <= 4096 ? sort_ranks_kernel<4, 16> : sort_ranks_kernel<8, 16>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((T + own - 1) / own)), dim3(1024), 0, s, ids, (int)T, V, pos_bits, sorted_ids, perm,
+    const int R = std::max(32, ((V + 255) / 256 + 31) / 32 * 32), buckets = (V + R - 1) / R;
+    auto* const kernel = T <= 4096 ? sort_buckets_kernel<4> : T <= 8192 ? sort_buckets_kernel<8> : sort_buckets_kernel<16>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)buckets), dim3(1024), 0, s, ids, (int)T, V, R, bits_for(R), sorted_ids, perm, uniq_ids,
+                       seg_offsets, n_uniq, ws.seg_of, ws.flag);
+    return hipGetLastError();
+  }
+  if (T <= RANK_MAX && stem_route_sort_ranks(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of)) {
+    ProfScope ps(ctx, K_SORT_FUSED, s);
+    auto* const kernel = T <= 1024 ? sort_ranks_kernel<1, 8> : sort_ranks_kernel<2, 8>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((T + 7) / 8)), dim3(1024), 0, s, ids, (int)T, V, pos_bits, sorted_ids, perm,
                        uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
     return hipGetLastError();
   }

@@ -231,9 +231,13 @@ int stem_route_one_launch_apart(int d_model, int d_ff, int64_t T, const void* G,
                                 const void* y);
 int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   // a context's room for K slices
 int stem_route_sort(int64_t T, int V);   // SortRoute
-// whether the kernel that counts ranks sorts them, which it does where the size allows and no two of the call's buffers overlap
+// whether, up to 8192 ids, many workgroups that look at all ids sort them (ranks up to 2048, buckets beyond): where the vocabulary allows it and no
+// two of the call's buffers overlap
 int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
                           const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of);
+// whether buckets of the vocabulary do (2049 to 16384 ids)
+int stem_route_sort_buckets(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
+                            const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of);
 // whether the sort and the sums of a call with these buffers (dU may be null: no sums) are one launch
 int stem_route_sort_sum(int is_bf16, int64_t T, int V, int F, const int32_t* ids, const void* dU, const int32_t* sorted_ids,
                         const int32_t* perm, const int32_t* uniq_ids, const int32_t* seg_offsets, const int32_t* n_uniq,
@@ -253,8 +257,7 @@ int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, to
 int stem_route_copy_streams(int d_model, int d_ff, int dtype, int64_t T, int64_t rows);
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices or of the layer in one launch waits for another
 }
-// By size.  SORT_ONE_* and SORT_RANKS_8192: ranks by counting where stem_route_sort_ranks says so, else the passes of one workgroup up to
-// 4096 ids and merged runs of 1024 beyond.
+// By size, where stem_route_sort_buckets and, up to 2048 ids, stem_route_sort_ranks say no.  SORT_RANKS_8192: merged runs of 1024 too.
 enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS, SORT_RANKS_8192 };
 
 // Bytes of W_down that the gate product of a decode-sized call touches, a dword per 128-byte line behind its first K tiles, so that

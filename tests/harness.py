@@ -89,6 +89,13 @@ def route_sort_ranks(T, V, **at):
     return bool(L.lib().stem_route_sort_ranks(ctypes.c_int64(T), V, *[ctypes.c_void_p(at.get(k)) for k in names]))
 
 
+def route_sort_buckets(T, V, **at):
+    """Whether buckets of the vocabulary do."""
+    names = ("ids", "sorted_ids", "perm", "uniq_ids", "seg_offsets", "n_uniq", "seg_of")
+    assert set(at) <= set(names)
+    return bool(L.lib().stem_route_sort_buckets(ctypes.c_int64(T), V, *[ctypes.c_void_p(at.get(k)) for k in names]))
+
+
 def route_sort_sum(bf16, T, V, F, **at):
     """Whether one launch sorts and sums a call whose buffers lie at these byte addresses (seg_of: the context's)."""
     names = ("ids", "dU", "sorted_ids", "perm", "uniq_ids", "seg_offsets", "n_uniq", "seg_of", "dE_rows")
