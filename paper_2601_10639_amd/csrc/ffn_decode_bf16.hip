@@ -27,9 +27,9 @@
 // flags the last time, where that last flag was missing, so the claim is there when the last workgroup reads it.  (Each takes a claim back to
 // 0 by compare and swap, so a share is done once.)
 //
-// Layer forward, us, two launches of the decode kernel / this, 1, 8, 24, 32 tokens: 512 x 1536 8.0 / 5.5, 8.1 / 5.7, 8.2 / 6.4, 8.3 / 6.8 (two
-// launches there are what the host takes for them); 1024 x 4096 8.8 / 7.8, 9.6 / 7.9, 11.6 / 9.6, 11.9 / 10.5; 1536 x 5120 12.3 / 9.6,
-// 14.2 / 9.9, 17.6 / 12.8, 17.9 / 13.9; 2048 x 8192 16.8 / 15.2, 17.7 / 15.7, 20.8 / 19.0, 22.3 / 20.4.  What bounds it, from stamps, 24 tokens
+// Layer forward, us, two launches of the decode kernel / this, 1, 8, 24, 32 tokens: 512 x 1536 8.0 / 5.4, 8.1 / 5.6, 8.2 / 6.3, 8.3 / 6.7 (two
+// launches there are what the host takes for them); 1024 x 4096 8.8 / 7.7, 9.6 / 7.8, 11.6 / 9.4, 11.9 / 10.3; 1536 x 5120 12.3 / 9.5,
+// 14.2 / 9.7, 17.6 / 12.3, 17.9 / 13.5; 2048 x 8192 16.8 / 15.1, 17.7 / 15.5, 20.8 / 18.8, 22.3 / 20.2.  What bounds it, from stamps, 24 tokens
 // at 1024 x 4096: first W_gate bytes 1.0 us after the start, all of them 2.7, H complete 3.7 (the last workgroup's 4.7), everybody through
 // 5.6, H read 7.5 (196 KB a compute unit from L2), end 8.3; one token at 2048 x 8192: the weights, 12.4 of 14 us.  (Without W_down before the
 // exchange 1536 x 5120 and above 0.5 to 0.7 us more; all of it before, 0.1 to 0.9.  H loaded without the scope bit: the same.)
