@@ -50,7 +50,6 @@ namespace {
 constexpr int WAVES = 8, THREADS = 64 * WAVES, MAX_WGS = 256;
 constexpr uint32_t OOB = 0x80000000u;   // a buffer offset beyond any operand: reads as zero
 constexpr int SC1 = 16;                 // cache policy bit of the buffer instructions: device scope
-constexpr int NT = 2;                   // and: not to be kept
 constexpr int REPLICAS = 32;            // of the flags
 constexpr int FLIGHT = 8;               // fragments of H a wavefront has in flight at least
 
@@ -125,6 +124,11 @@ __device__ __forceinline__ f32x4_t sum_partials(const float* from, int s) {
 template <int RG, int KG, int TQ, int RD>
 __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
   constexpr int TM = 8 * TQ;
+  // Cache policy of the weights.  The last level holds 256 MB: weights of a stack that fits are best kept there, others best read past it
+  // (policy 2).  A call doesn't know the stack: of layers up to 8.4 MB (RG * KG up to 2) twenty or thirty fit, of larger ones they don't.
+  // us a layer, kept / past it, one token: 512 x 1536 (3.1 MB) 8 to 48 layers 4.9 / 5.4; 1024 x 4096 (16.8 MB) 16 layers 7.1 / 7.7, 24 and 48
+  // 7.9 / 7.7; 1536 x 5120 8 layers 8.9 / 9.5, 16 to 48 9.9 / 9.5; 2048 x 8192 4 layers 14.4 / 14.8, 8 to 48 16.5 / 15.1.
+  constexpr int KEEP = RG * KG <= 2 ? 0 : 2;
   constexpr int LD = RD == 8 ? 1 : 2;                                        // lines of 64 k in a piece of W_down
   constexpr int KD = 4 * RG / LD, EARLY = KD / 2;                           // pieces a wavefront; requested at the start
   constexpr int GP = 8 * RG + 4, DP = RD == 8 ? 12 : 4;                      // floats between two tokens' sums in LDS
@@ -172,7 +176,7 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
     for (int i = 0; i < KG; ++i) {
       const int kl = wave + WAVES * i;
 #pragma unroll
-      for (int r = 0; r < RG; ++r) w[i][r] = load16<NT>(rw, (ow + (uint32_t)(r * 8 * p.d * 2 + kl * 128)) | (kl * 64 < p.d && gate ? 0 : OOB));
+      for (int r = 0; r < RG; ++r) w[i][r] = load16<KEEP>(rw, (ow + (uint32_t)(r * 8 * p.d * 2 + kl * 128)) | (kl * 64 < p.d && gate ? 0 : OOB));
     }
   }
   keep_order();
@@ -194,7 +198,7 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
 #pragma unroll
     for (int i = 0; i < KD; ++i) {
       const int k = (wave + WAVES * i) * 64 * LD;
-      if (i >= from && i < to) wd[i] = load16<NT>(rwd, (at + k * 2) | (k + chunk * 8 < p.F ? 0 : OOB));
+      if (i >= from && i < to) wd[i] = load16<KEEP>(rwd, (at + k * 2) | (k + chunk * 8 < p.F ? 0 : OOB));
     }
     if (to == KD)
       rv = *reinterpret_cast<const u32x2_t*>(residual + (size_t)(y_tok < p.T ? y_tok : p.T - 1) * p.d + (mine ? share : 0) * RD + y_row);
