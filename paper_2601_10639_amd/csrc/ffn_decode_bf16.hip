@@ -18,7 +18,8 @@
 // other's lines; a workgroup waits until its stores are complete and then raises its flag to the launch's number, and one wavefront looks at
 // all flags at once.  There are 32 copies of the flags, each looked at by 8 workgroups: 256 that read the same 8 lines wait
 // for each other (1.0 us a look; a layer of 512 x 1536, one token, with 1 / 8 copies 6.9 / 6.1 us, with 16 / 32 5.7 / 5.5).  The grid is the context's, not the
-// call's, so every launch raises the same flags by one: nothing is reset, and a graph replays it.
+// call's, so every launch raises the same flags to the next number, which is never 0 (a claim nobody has made): nothing is reset, and a
+// graph replays it.
 //
 // Nobody waits for good, as workgroups may not all be on the chip, where other streams fill it: one that has looked `polls` times
 // gives its rows up by writing the launch's number into its claim, looks at the flags once more, and unless all are there, or it cannot
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
   const rsrc_t rflags = rsrc(p.sync, REPLICAS * MAX_WGS * 4), rclaims = rsrc(p.sync + REPLICAS * MAX_WGS, MAX_WGS * 4);
   const rsrc_t rH = rsrc(p.H, (p.F + 64 * LD - 1) / (64 * LD) * LD * p.T * 128);
 
-  const uint32_t epoch = 1 + __builtin_amdgcn_raw_buffer_load_b32(rflags, b * 4, 0, SC1);
+  const uint32_t epoch = stem_launch_after(__builtin_amdgcn_raw_buffer_load_b32(rflags, b * 4, 0, SC1));
 
   // ---- all loads: ids, W_gate and x, the table rows, W_down, the residual.  None is conditional, or the compiler waits for all of those it
   // cannot count: what a workgroup has no part in is read out of range or for nothing.
@@ -414,6 +415,14 @@ int stem_route_one_launch_apart(int d, int F, int64_t T, const void* G, const vo
       if (x && z && x < z + b.n && z < x + a.n) return 0;
     }
   return 1;
+}
+
+uint32_t stem_next_launch(uint32_t last) { return stem_launch_after(last); }
+
+int stem_exchange_launch(stem_ctx* c, uint32_t last) {
+  hipError_t e = hipDeviceSynchronize();
+  if (e == hipSuccess) e = hipMemsetD32(reinterpret_cast<hipDeviceptr_t>(c->sync), (int)last, REPLICAS * MAX_WGS);
+  return e != hipSuccess ? e : hipDeviceSynchronize();
 }
 
 hipError_t stem_ffn_decode_bf16(stem_ctx* ctx, const StemDecodeArgs& a, hipStream_t s) {

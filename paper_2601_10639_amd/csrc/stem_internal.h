@@ -255,6 +255,8 @@ int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, to
 // 124 / 146; fp32, 256 x 1024, 8192 tokens (0.9) 212 / 203 / 197, 512 x 2048, vocabulary 8000, 2000 tokens (1.5) 156 / 131 / 149.  On two contexts two in
 // turn are within 1 % of a stream for each, and of one but at 8192 tokens of 1024 x 4096 (381 / 393) and 4096 of 2048 x 8192 (470 / 510).
 int stem_route_copy_streams(int d_model, int d_ff, int dtype, int64_t T, int64_t rows);
+uint32_t stem_next_launch(uint32_t last);           // stem_launch_after, and
+int stem_exchange_launch(stem_ctx* c, uint32_t last);   // all flags of the layer in one launch as launch `last` left them (waits for the device)
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices or of the layer in one launch waits for another
 }
 // By size, where stem_route_sort_buckets and, up to 2048 ids, stem_route_sort_ranks say no.  SORT_RANKS_8192: merged runs of 1024 too.
@@ -305,6 +307,9 @@ struct StemDecodeArgs {
   int T, d, F, E_rows;
 };
 hipError_t stem_ffn_decode_bf16(stem_ctx* ctx, const StemDecodeArgs& a, hipStream_t s);
+// The number of the launch that finds its flags at `last`: never 0, which in a claim says that nothing was given up, and which would come
+// again with every 2^32-th launch (6 to 18 hours of decoding on one context).  Numbers are compared for equality only.
+__host__ __device__ inline uint32_t stem_launch_after(uint32_t last) { return last == 0xffffffffu ? 1u : last + 1u; }
 
 // ---- fp32 path and element-wise kernels (kernels_f32.hip) -------------------------
 struct GemmF32Args {

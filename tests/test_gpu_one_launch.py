@@ -113,6 +113,31 @@ def test_calls_of_other_sizes_between_and_graph_replays():
     ctx.close()
 
 
+@pytest.mark.parametrize("T,d,F", [(3, 512, 1536), (24, 2048, 8192)])
+def test_launch_numbers_wrap(T, d, F):
+    """The calls about the 2^32-th of a context, eager and from a graph, waited for and given up."""
+    s = _layer(T, d, F, 300, 40)
+    ctx = L.stem_create(d, F, 300, L.STEM_BF16, T, 0)
+    want = s["x"].clone()
+    _call(ctx, dict(s, x=want, r=want), want)
+    x = s["x"].clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        _call(ctx, dict(s, x=x, r=x), x)
+    for polls, replay in ((2000, False), (2000, True), (0, False)):
+        L.lib().stem_exchange_polls(ctx.handle, polls)
+        assert L.lib().stem_exchange_launch(ctx.handle, ctypes.c_uint32(2 ** 32 - 3)) == 0
+        for n in range(5):
+            x.copy_(s["x"])
+            if replay:
+                graph.replay()
+            else:
+                _call(ctx, dict(s, x=x, r=x), x)
+            assert torch.equal(x, want), (polls, replay, n)
+    L.stem_sync_status(ctx)
+    ctx.close()
+
+
 def test_two_contexts_on_two_streams_at_once():
     d, F, V, T = 1024, 4096, 500, 24
     ss = [_layer(T, d, F, V, 50 + i) for i in range(2)]

@@ -190,3 +190,22 @@ def test_sizes_of_the_layer_in_one_launch():
     assert not one(1, 2112, 64) and not one(1, 64, 8256)
     assert one(64, 512, 2048) and not one(65, 512, 2048) and not one(33, 576, 2048) and one(48, 1024, 4096) and not one(49, 1024, 4096)
     assert not one(33, 1024, 3584) and not one(33, 1088, 4096)
+
+
+def test_launch_numbers_of_the_layer_in_one_launch_are_never_what_an_idle_claim_holds():
+    """A workgroup looks for shares that were given up until no claim holds the launch's number, and idle claims hold 0."""
+    after = L.lib().stem_next_launch
+    after.restype = ctypes.c_uint32
+    number = lambda last: after(ctypes.c_uint32(last))
+    most = 2 ** 32 - 1
+    assert [number(n) for n in (0, 1, 2 ** 31 - 1, 2 ** 31, most - 1)] == [1, 2, 2 ** 31, 2 ** 31 + 1, most] and number(most) == 1
+    for last in (0, most - 4):
+        seen = [last]
+        for _ in range(8):
+            seen.append(number(seen[-1]))
+            claims, looks = [0] * 256, 0
+            while seen[-1] in claims and looks < 300:      # (taken: back to 0)
+                claims[claims.index(seen[-1])] = 0
+                looks += 1
+            assert looks == 0 and seen[-1] != 0
+        assert len(set(seen)) == len(seen)                 # no number is left of a launch before
