@@ -45,7 +45,9 @@ struct Args {
     const at::ScalarType want = kind == I32 ? at::kInt : kind == ACT && dtype == STEM_BF16 ? at::kBFloat16 : at::kFloat;
     if (t.layout() != at::kStrided || t.scalar_type() != want || !t.is_cuda() || !t.is_contiguous()) throw Unusual();
     device_seen = true;
-    return static_cast<T*>(const_cast<void*>(t.const_data_ptr()));
+    // (as data_ptr() in Python: a tensor that shares its storage with another until one is written gets its own first.  Inputs too, as a
+    // call may write to the same tensor)
+    return static_cast<T*>(t.mutable_data_ptr());
   }
 
   static int64_t as_integer(PyObject* o) {

@@ -65,6 +65,29 @@ def test_both_bindings_make_the_same_calls(dtype, monkeypatch):
             assert torch.equal(t, b[k]), k
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_lazily_cloned_tensors_are_written_apart_from_their_source(dtype):
+    native = L._bind or L._load_bind()
+    a, b = _state(dtype), _state(dtype)
+    source = {k: t for k, t in b.items() if isinstance(t, torch.Tensor)}
+    before = {k: t.clone() for k, t in source.items()}
+    b.update({k: torch._lazy_clone(t) for k, t in source.items()})
+    for (name, args, _), (_, lazy, _) in zip(_step(a), _step(b)):
+        assert getattr(native, name)(*args) == getattr(native, name)(*lazy) == L.STEM_OK, name
+    if dtype == "bf16":   # in place
+        x = a["x"].clone()
+        shared = torch._lazy_clone(x)
+        L.stem_ffn_forward_residual(b["ctx"], shared, *[b[k] for k in ("ids", "W_gate", "W_down", "E")], shared, shared)
+        want = torch.empty_like(x)
+        L.stem_ffn_forward_residual(b["ctx"], x, *[b[k] for k in ("ids", "W_gate", "W_down", "E")], x, want)
+        assert torch.equal(shared, want) and torch.equal(x, a["x"])
+    L.stem_sync_status(a["ctx"])
+    L.stem_sync_status(b["ctx"])
+    for k, t in source.items():
+        assert torch.equal(t, before[k]), k          # nothing was written through it
+        assert torch.equal(a[k], b[k]), k
+
+
 def test_what_is_not_ordinary_is_left_to_the_other_binding():
     native = L._bind or L._load_bind()
     s = _state("bf16")
