@@ -234,7 +234,7 @@ int stem_route_copy_streams(int d, int F, int dtype, int64_t T, int64_t rows) {
   return one ? 1 : 2;
 }
 
-void stem_exchange_polls(stem_ctx* c, int polls) { c->polls = polls; }
+void stem_exchange_polls(stem_ctx* c, int polls) { c->polls = c->looks = polls; }
 
 int stem_route_weight_grads_apart(int d, int F, int64_t T, const void* dy, const void* H, const void* dx, const void* W_gate,
                                   const void* W_up, const void* dV, const float* dW_gate, const float* dW_up) {
@@ -319,6 +319,7 @@ stem_status stem_create(stem_ctx** out, const stem_layer_desc* desc, int64_t max
       c->sync = reinterpret_cast<uint32_t*>(c->tickets + STEM_TICKETS);
     }
     c->polls = STEM_POLLS;
+    c->looks = STEM_LOOKS;
   }
   for (int i = 0; i < 2; ++i) {
     ok(dmalloc(&c->sort_keys[i], (size_t)max_tokens));

@@ -1,5 +1,4 @@
-// A decode step's whole layer in one launch: y = (SiLU(x W_gate^T) * E[ids]) W_down^T [+ residual], up to 32 tokens (64 of small layers),
-// bf16, gfx950.
+// A decode step's whole layer in one launch: y = (SiLU(x W_gate^T) * E[ids]) W_down^T [+ residual], up to 32 tokens, bf16, gfx950.
 //
 // Two launches of so few tokens are latency and weight bytes: each pays for its start (1.5 us), for the first bytes from HBM (1), for a
 // reduction and for its end.  A workgroup here has 1 / 256 of either weight matrix in registers: W_gate's loads and half of W_down's are
@@ -21,16 +20,29 @@
 // call's, so every launch raises the same flags to the next number, which is never 0 (a claim nobody has made): nothing is reset, and a
 // graph replays it.
 //
-// Nobody waits for good, as workgroups may not all be on the chip, where other streams fill it: one that has looked `polls` times
+// Workgroups wait for workgroups, so what a launch shares the chip with matters: a compute unit is held until the launch is resident as a
+// whole.  Therefore two workgroups fit a compute unit (registers: 128, which takes recomputed indices, scalar offsets and, for the widest
+// layers, fewer early loads; LDS: up to 80 KB, which bounds d_model times tokens; see FIT).  Two launches side by side are then resident
+// together, a third gets in when one of them ends.  With one a compute unit, three launches at a time kept each other off the chip until
+// somebody gave up: eight layers of 2048 x 8192, one token, us a step of each stream, two launches a layer / this, one a compute unit / this,
+// two: 2 at a time 210 / 222 / 196, 4 streams 315 / 7760 / 266; beside a prefill of 4096 tokens 1064 / 1107 / 700 to 780, whose own call took
+// 265 / 415 / 305 (257 alone).  1024 x 4096, 32 tokens, 4 streams 212 / 7860 / 192.
+//
+// Nobody waits for good, as other streams may fill the chip all the same: one that has looked `looks` times
 // gives its rows up by writing the launch's number into its claim, looks at the flags once more, and unless all are there, or it cannot
 // take the claim back, ends.  Whoever sees all flags does its own rows and then those of every claim it can take.  No row is left: the
 // workgroup whose flag was complete last sees all of them; who gave up before that has its claim complete before it looked at the
 // flags the last time, where that last flag was missing, so the claim is there when the last workgroup reads it.  (Each takes a claim back to
-// 0 by compare and swap, so a share is done once.)
+// 0 by compare and swap, so a share is done once.)  Workgroups begin their search for claims at different ones, and load them anew where
+// another was faster.  us a round of 8 streams (six decode steps of 2048 x 8192 and 1024 x 4096, 1 to 32 tokens, one of 512 x 1536, all at
+// once; two launches a layer 990) by the number of looks, searches in one order / in different ones: 2000 3700 / 3380, 400 2300 / 1420, 200 1700 / 1190, 100 1310 /
+// 1190, 50 - / 1300, 20 - / 2330; of three decode steps and two prefills among 8 streams (770) at 400 looks 1020 / 995, 200 985 / 935, 100 970 / 905.
+// (Workgroups that give up one after another, over nine times as many looks: 1600 and 1080 at 50.)  On four streams of such a mix 360 and 345,
+// where two launches a layer take 385 and 365.
 //
-// Layer forward, us, two launches of the decode kernel / this, 1, 8, 24, 32 tokens: 512 x 1536 8.0 / 5.4, 8.1 / 5.6, 8.2 / 6.3, 8.3 / 6.7 (two
-// launches there are what the host takes for them); 1024 x 4096 8.8 / 7.7, 9.6 / 7.8, 11.6 / 9.4, 11.9 / 10.3; 1536 x 5120 12.3 / 9.5,
-// 14.2 / 9.7, 17.6 / 12.3, 17.9 / 13.5; 2048 x 8192 16.8 / 15.1, 17.7 / 15.5, 20.8 / 18.8, 22.3 / 20.2.  What bounds it, from stamps, 24 tokens
+// Layer forward, us, two launches of the decode kernel / this, 1, 8, 16, 24, 32 tokens, 16 or 24 layers in a graph: 512 x 1536 7.0 / 5.4, 7.3 / 5.6, 7.7 / 5.8,
+// 8.3 / 6.3, 8.6 / 6.8; 1024 x 4096 9.4 / 8.0, 9.9 / 8.1, 11.3 / 8.7, 12.0 / 9.7, 12.3 / 10.6; 1536 x 5120 12.4 / 9.9, 13.4 / 9.8, 15.2 / 11.1,
+// 16.4 / 12.3; 2048 x 8192 17.2 / 16.0, 17.3 / 15.9, 18.8 / 18.2.  What bounds it, from stamps of one workgroup a compute unit, 24 tokens
 // at 1024 x 4096: first W_gate bytes 1.0 us after the start, all of them 2.7, H complete 3.7 (the last workgroup's 4.7), everybody through
 // 5.6, H read 7.5 (196 KB a compute unit from L2), end 8.3; one token at 2048 x 8192: the weights, 12.4 of 14 us.  (Without W_down before the
 // exchange 1536 x 5120 and above 0.5 to 0.7 us more; all of it before, 0.1 to 0.9.  H loaded without the scope bit: the same.)
@@ -60,7 +72,7 @@ struct Args {
   bf16_t *y, *H, *save_G, *save_H;      // H: the exchange's; the saved ones may be null
   uint32_t* sync;                       // 32 x 256 flags, 256 claims
   int32_t* bad_id;
-  int T, d, F, E_rows, polls;
+  int T, d, F, E_rows, looks;
 };
 
 __device__ __forceinline__ float sigmoidf_fast(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
@@ -79,12 +91,17 @@ __device__ __forceinline__ rsrc_t rsrc(P* p, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(static_cast<const void*>(p)), 0, bytes, 0x00020000);
 }
 template <int AUX>
-__device__ __forceinline__ bf16x8_t load16(rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX));
+__device__ __forceinline__ bf16x8_t load16(rsrc_t r, uint32_t off, int scalar_off = 0) {
+  return __builtin_bit_cast(bf16x8_t, __builtin_amdgcn_raw_buffer_load_b128(r, off, scalar_off, AUX));
 }
 __device__ __forceinline__ void keep_order() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
+}
+// v for uses from here on: what they compute from it is not kept in registers from earlier ones
+__device__ __forceinline__ int afresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
 }
 __device__ __forceinline__ f32x4_t mfma(bf16x8_t w, bf16x8_t t, f32x4_t acc) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, t, acc, 0, 0, 0);
@@ -121,9 +138,10 @@ __device__ __forceinline__ f32x4_t sum_partials(const float* from, int s) {
 }
 
 // RG x 8 columns of H a workgroup (d_ff up to RG * 2048), KG lines of 64 k a wavefront (d_model up to KG * 512), up to 8 TQ tokens,
-// RD = 8 or 4 rows of W_down a workgroup
+// RD = 8 or 4 rows of W_down a workgroup.  LDS is 8 KB * KG * TQ: two workgroups fit a compute unit up to 9 of these.
+constexpr int FIT = 9;
 template <int RG, int KG, int TQ, int RD>
-__global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
+__global__ __launch_bounds__(THREADS, 4) void ffn_decode_kernel(Args p) {
   constexpr int TM = 8 * TQ;
   // Cache policy of the weights.  The last level holds 256 MB: weights of a stack that fits are best kept there, others best read past it
   // (policy 2).  A call doesn't know the stack: of layers up to 8.4 MB (RG * KG up to 2) twenty or thirty fit, of larger ones they don't.
@@ -131,7 +149,8 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
   // 7.9 / 7.7; 1536 x 5120 8 layers 8.9 / 9.5, 16 to 48 9.9 / 9.5; 2048 x 8192 4 layers 14.4 / 14.8, 8 to 48 16.5 / 15.1.
   constexpr int KEEP = RG * KG <= 2 ? 0 : 2;
   constexpr int LD = RD == 8 ? 1 : 2;                                        // lines of 64 k in a piece of W_down
-  constexpr int KD = 4 * RG / LD, EARLY = KD / 2;                           // pieces a wavefront; requested at the start
+  constexpr int KD = 4 * RG / LD;                                            // pieces a wavefront
+  constexpr int EARLY = RG * KG >= 12 && TQ >= 2 ? 2 : KD / 2;               // requested at the start (where registers are short: few)
   constexpr int GP = 8 * RG + 4, DP = RD == 8 ? 12 : 4;                      // floats between two tokens' sums in LDS
   // LDS, a region for each wavefront: its part of x, then its partial sums
   constexpr int XB = KG * TQ * 1024, GB = TM * GP * 4, DB = TM * DP * 4, REGION = XB > GB ? (XB > DB ? XB : DB) : (GB > DB ? GB : DB);
@@ -187,22 +206,25 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
   const u32x2_t ev = *reinterpret_cast<const u32x2_t*>(p.E + (size_t)id * p.F + h_col);
   keep_order();
   const rsrc_t rwd = rsrc(p.Wd, p.d * p.F * 2);
-  // y by 4 rows of a token, YS lanes each
+  // y by 4 rows of a token, YS lanes each: thread t's
   constexpr int YQ = TM * RD / 4, YS = THREADS / YQ < 8 ? THREADS / YQ < 4 ? 2 : 4 : 8;
-  const int y_s = tid % YS, y_row = RD == 8 ? (tid / YS & 1) * 4 : 0, y_tok = tid / (YS * (RD / 4));
+  auto y_row = [](int t) { return RD == 8 ? (t / YS & 1) * 4 : 0; };
+  auto y_tok = [](int t) { return t / (YS * (RD / 4)); };
   const bf16_t* const residual = p.residual ? p.residual : p.x;
   bf16x8_t wd[KD];
   u32x2_t rv;
   auto load_share = [&](int share, bool mine, int from, int to) __attribute__((always_inline)) {
-    const int row = RD == 8 ? o : lane >> 2 & 3, chunk = RD == 8 ? 2 * g + c : 4 * g + (lane & 3);
+    const int t = afresh(tid), lane = t & 63;
+    const int row = RD == 8 ? lane >> 1 & 7 : lane >> 2 & 3, chunk = RD == 8 ? 2 * (lane >> 4) + (lane & 1) : 4 * (lane >> 4) + (lane & 3);
     const uint32_t at = (uint32_t)((share * RD + row) * p.F + chunk * 8) * 2 | (mine ? 0 : OOB);
 #pragma unroll
     for (int i = 0; i < KD; ++i) {
       const int k = (wave + WAVES * i) * 64 * LD;
-      if (i >= from && i < to) wd[i] = load16<KEEP>(rwd, (at + k * 2) | (k + chunk * 8 < p.F ? 0 : OOB));
+      if (i >= from && i < to)                                // (d_ff is whole lines: a piece of one is in range or not)
+        wd[i] = LD == 1 ? load16<KEEP>(rwd, k < p.F ? at : OOB, k * 2) : load16<KEEP>(rwd, (at + k * 2) | (k + chunk * 8 < p.F ? 0 : OOB));
     }
     if (to == KD)
-      rv = *reinterpret_cast<const u32x2_t*>(residual + (size_t)(y_tok < p.T ? y_tok : p.T - 1) * p.d + (mine ? share : 0) * RD + y_row);
+      rv = *reinterpret_cast<const u32x2_t*>(residual + (size_t)(y_tok(t) < p.T ? y_tok(t) : p.T - 1) * p.d + (mine ? share : 0) * RD + y_row(t));
   };
   if (EARLY) load_share(b, down, 0, EARLY);
   keep_order();
@@ -271,7 +293,7 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
       return __ballot((n > 0 && f[0] != epoch) || (n > 1 && f[1] != epoch) || (n > 2 && f[2] != epoch) || (n > 3 && f[3] != epoch)) == 0;
     };
     bool there = all_there();
-    for (int n = down ? p.polls : 0; !there && n > 0; --n) there = all_there();
+    for (int n = down ? p.looks : 0; !there && n > 0; --n) there = all_there();
     bool mine = there && down;
     if (!there && down) {            // give the share up
       uint32_t* const claim = p.sync + REPLICAS * MAX_WGS + b;
@@ -299,6 +321,7 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
     if (share >= 0) {
       constexpr int FD = LD * TQ;                                   // fragments, and accumulators, of a piece
       constexpr int BATCH = FLIGHT / FD > KD ? KD : FLIGHT / FD > 0 ? FLIGHT / FD : 1;    // pieces whose fragments are in flight together
+      const int l = afresh(lane), c = l & 1, o = l >> 1 & 7, g = l >> 4;
       f32x4_t acc[FD];
 #pragma unroll
       for (int f = 0; f < FD; ++f) acc[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -317,7 +340,8 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
           for (int f = 0; f < FD; ++f)                              // beyond d_ff: reads as zero
             if (i0 + i < KD) {
               const int piece = wave + WAVES * (i0 + i), k = piece * 64 * LD + (4 * g + f / TQ * 2 + c) * 8;
-              v[i][f] = load16<SC1>(rH, (oh[f % TQ] + (piece * LD + f / TQ) * p.T * 128) | (RD == 8 || k < p.F ? 0 : OOB));
+              v[i][f] = LD == 1 ? load16<SC1>(rH, piece * 64 < p.F ? oh[f] : OOB, piece * p.T * 128)
+                                : load16<SC1>(rH, (oh[f % TQ] + (piece * LD + f / TQ) * p.T * 128) | (k < p.F ? 0 : OOB));
             }
         keep_order();
 #pragma unroll
@@ -340,8 +364,9 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
         }
       }
       __syncthreads();
-      if (y_tok < p.T) {
-        const f32x4_t s = sum_partials<YS, REGION / 4>(red + y_tok * DP + y_row, y_s);
+      const int t = afresh(tid), tok = y_tok(t), row = y_row(t), y_s = t % YS;
+      if (tok < p.T) {
+        const f32x4_t s = sum_partials<YS, REGION / 4>(red + tok * DP + row, y_s);
         float out[4] = {s[0], s[1], s[2], s[3]};
         if (p.residual) {   // the layer's output joins the residual stream: added in fp32, rounded once
           float r[4];
@@ -349,7 +374,7 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) out[q] += r[q];
         }
-        if (y_s == 0) *reinterpret_cast<u32x2_t*>(p.y + (size_t)y_tok * p.d + share * RD + y_row) = pack4(out);
+        if (y_s == 0) *reinterpret_cast<u32x2_t*>(p.y + (size_t)tok * p.d + share * RD + row) = pack4(out);
       }
     } else {
       __syncthreads();   // all have read next_share
@@ -357,10 +382,12 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
     // a share that was given up, if there is one: the claims that were there, one after another
     if (wave == LOOKS) {
       int found = -1;
+      const int turn = b * 37 >> 2 & 63;                   // where this workgroup begins to look
       for (;;) {
-        const uint64_t any = __ballot(claims[0] == epoch || claims[1] == epoch || claims[2] == epoch || claims[3] == epoch);
+        uint64_t any = __ballot(claims[0] == epoch || claims[1] == epoch || claims[2] == epoch || claims[3] == epoch);
         if (!any) break;
-        const int from = __builtin_ctzll(any);
+        any = any >> turn | any << (63 - turn) << 1;
+        const int from = (__builtin_ctzll(any) + turn) & 63;
         bool got = false;
         int which = 0;
         if (lane == from) {
@@ -372,6 +399,8 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
         }
         which = __builtin_amdgcn_readlane(which, from);
         if (__ballot(got)) { found = from * 4 + which; break; }
+        asm volatile("" ::: "memory");                     // another workgroup was faster: what is there now
+        claims = __builtin_amdgcn_raw_buffer_load_b128(rclaims, lane * 16, 0, SC1);
       }
       if (lane == 0) *next_share = found;
     }
@@ -384,23 +413,22 @@ __global__ __launch_bounds__(THREADS) void ffn_decode_kernel(Args p) {
 
 template <int RG, int KG, int RD>
 void launch(const Args& p, int wgs, hipStream_t s) {
-  auto* kernel = p.T <= 8    ? ffn_decode_kernel<RG, KG, 1, RD>
-                 : p.T <= 16 ? ffn_decode_kernel<RG, KG, 2, RD>
-                 : p.T <= 24 ? ffn_decode_kernel<RG, KG, 3, RD>
-                             : ffn_decode_kernel<RG, KG, 4, RD>;
-  if constexpr (RG <= 2 && KG <= 2)
-    if (p.T > 32) kernel = p.T <= 48 ? ffn_decode_kernel<RG, KG, 6, RD> : ffn_decode_kernel<RG, KG, 8, RD>;
+  auto* kernel = p.T <= 8 ? ffn_decode_kernel<RG, KG, 1, RD> : ffn_decode_kernel<RG, KG, 2, RD>;
+  if constexpr (KG * 3 <= FIT)
+    if (p.T > 16) kernel = ffn_decode_kernel<RG, KG, 3, RD>;
+  if constexpr (KG * 4 <= FIT)
+    if (p.T > 24) kernel = ffn_decode_kernel<RG, KG, 4, RD>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(THREADS), 0, s, p);
 }
 
 }  // namespace
 
-// Every workgroup reads all tokens' H, so its time grows with the tokens where two launches' tiles share them: layer forward, us, two
-// launches / this, 33, 48, 64 tokens: 512 x 2048 10.5 / 7.9, 10.5 / 8.1, 10.7 / 9.2; 1024 x 4096 12.6 / 11.9, 13.4 / 12.2, 13.6 / 14.0; 768 x 2496
-// 11.0 / 11.2, 11.1 / 11.3, 11.3 / 12.6; 1024 x 3072 11.5 / 11.8, 12.0 / 12.0, 12.2 / 13.5.  Wider layers do not fit a workgroup's registers.
+// Up to 32 tokens: every workgroup reads all tokens' H, and a lane's sums of more don't fit its registers.  And while two workgroups fit a
+// compute unit: up to 32 tokens of d_model up to 1024, 24 up to 1536, 16 up to 2048.  (One a compute unit, by itself, two launches /
+// this: 1536 x 5120, 32 tokens 17.3 / 13.7; 2048 x 8192, 24 and 32 20.2 / 18.9, 21.5 / 20.9; 48 tokens of 512 x 2048 10.5 / 7.9, of
+// 1024 x 4096 13.2 / 12.4.  Three of them at a time take ten times as long as two launches a layer do.)  Wider layers do not fit a workgroup's registers.
 int stem_route_one_launch(int d, int F, int64_t T) {
-  if (T < 1 || d % 64 || F % 64 || d > 2048 || F > 8192) return 0;
-  return T <= 32 || (d <= 512 && F <= 2048 && T <= 64) || (d <= 1024 && F > 3584 && F <= 4096 && T <= 48);
+  return T >= 1 && T <= 32 && d % 64 == 0 && F % 64 == 0 && d <= 2048 && F <= 8192 && (d + 511) / 512 * ((T + 7) / 8) <= FIT;
 }
 
 // Two launches store G and H before W_down and the residual are read and y is stored; here other workgroups do the one while some do the
@@ -430,7 +458,7 @@ hipError_t stem_ffn_decode_bf16(stem_ctx* ctx, const StemDecodeArgs& a, hipStrea
   Args p;
   p.x = a.x; p.Wg = a.Wg; p.Wd = a.Wd; p.E = a.E; p.residual = a.residual; p.ids = a.ids; p.y = a.y; p.save_G = a.save_G; p.save_H = a.save_H;
   p.H = reinterpret_cast<bf16_t*>(ctx->splitk_ws); p.sync = ctx->sync; p.bad_id = ctx->flag;
-  p.T = a.T; p.d = a.d; p.F = a.F; p.E_rows = a.E_rows; p.polls = ctx->polls;
+  p.T = a.T; p.d = a.d; p.F = a.F; p.E_rows = a.E_rows; p.looks = ctx->looks;
   const int rg = (a.F + 2047) / 2048, rd = a.d <= 1024 ? 4 : 8;
   const int gates = (a.F + 8 * rg - 1) / (8 * rg), downs = a.d / rd, wgs = gates > downs ? gates : downs;
   ProfScope ps(ctx, K_FFN_DECODE, s);

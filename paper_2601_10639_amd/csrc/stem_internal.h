@@ -63,7 +63,8 @@ struct stem_ctx {
   int32_t* tickets;      // [STEM_TICKETS] counters of finished K slices per output tile, zero between launches
   unsigned long long* rounds; // [STEM_TICKETS] the same for the few-row kernel, which counts on from launch to launch
   uint32_t* sync;        // [33 * 256] flags, 32 times, and claims of the layer in one launch (ffn_decode_bf16.hip)
-  int polls;             // how often a workgroup of these two looks for the others
+  int polls;             // how often a workgroup of the few-row kernel looks for the others
+  int looks;             // and of the layer in one launch
   int32_t* sort_keys[2]; // [max_tokens]
   int32_t* sort_vals[2]; // [max_tokens]
   int32_t* sort_counts;  // [64 * waves]
@@ -294,6 +295,7 @@ hipError_t stem_gemm_skinny_bf16(stem_ctx* ctx, int kid, int epi, const GemmArgs
 // ---- decode-sized bf16 GEMM (gemm_decode_bf16.hip): both operands K-contiguous --------------------
 #define STEM_TICKETS 256
 #define STEM_COUNTERS (STEM_TICKETS * (8 + 4) + 33 * 256 * 4)   // bytes of a context's rounds, tickets, flags and claims
+#define STEM_LOOKS 200    // some 100 us: the workgroups of a layer in one launch are some us apart unless other streams hold the compute units
 #define STEM_POLLS 2000   // 1 to 2 ms: the slices of a tile are some us apart unless other streams hold the compute units
 bool stem_gemm_decode_fits(int M, int N, int K);
 // epi: EPI_BF16 (+ residual; split along K through a.ws and a.tickets where that pays) or EPI_GATE

@@ -186,10 +186,10 @@ def test_saved_activations_beside_the_layer_in_one_launch(T, d, F):
 
 def test_sizes_of_the_layer_in_one_launch():
     one = lambda T, d, F: bool(L.lib().stem_route_one_launch(d, F, ctypes.c_int64(T)))
-    assert one(1, 64, 64) and one(32, 2048, 8192) and not one(0, 64, 64) and not one(33, 2048, 8192)
-    assert not one(1, 2112, 64) and not one(1, 64, 8256)
-    assert one(64, 512, 2048) and not one(65, 512, 2048) and not one(33, 576, 2048) and one(48, 1024, 4096) and not one(49, 1024, 4096)
-    assert not one(33, 1024, 3584) and not one(33, 1088, 4096)
+    assert one(1, 64, 64) and not one(0, 64, 64) and not one(1, 2112, 64) and not one(1, 64, 8256)
+    for d, most in ((64, 32), (512, 32), (576, 32), (1024, 32), (1088, 24), (1536, 24), (1600, 16), (2048, 16)):
+        for F in (64, 3648, 4096, 8192):
+            assert all(one(T, d, F) == (T <= most) for T in range(1, 66)), (d, F)
 
 
 def test_launch_numbers_of_the_layer_in_one_launch_are_never_what_an_idle_claim_holds():
