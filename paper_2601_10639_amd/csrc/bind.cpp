@@ -6,10 +6,12 @@
 //
 // Only the ordinary call is made here: plain torch tensors of the right type in contiguous device memory, ints, floats and bools.
 // Every function returns None, having done nothing, where anything else is among the arguments, and stemlib.py then makes the call as it
-// does without this module: its checks say what is wrong, or take what this one does not know.
+// does without this module: its checks say what is wrong, or take what this one does not know.  It looks into torch's and Python's objects,
+// so stemlib.py uses it only with the versions it was built for.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include "../../include/stem.h"
 
@@ -218,4 +220,13 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_bind", nullptr, -1, methods, null
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__bind() { return PyModule_Create(&module); }
+#define STR_(x) #x
+#define STR(x) STR_(x)
+PyMODINIT_FUNC PyInit__bind() {
+  PyObject* const m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "BUILT_FOR", "torch " TORCH_VERSION ", Python " STR(PY_MAJOR_VERSION) "." STR(PY_MINOR_VERSION)) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -4,12 +4,15 @@ training or decode step is marshalled natively instead (csrc/bind.cpp), where th
 Every function takes torch tensors (device memory unless the C header says host),
 checks dtype / contiguity, and passes raw pointers plus the current torch stream.
 Nothing is computed here; if the shared library is missing the import of any entry
-point fails loudly — there is no fallback path.
+point fails loudly — there is no fallback path.  Without the native binding (not built, or
+for another torch or Python) the same calls are made from here, with a warning.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 
 import torch
 
@@ -119,10 +122,26 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _NoBind:
+    """In the native binding's place where that cannot be used: every call is made from here."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_bind():
     global _bind
     lib()
-    from . import _bind as native
+    here = f"torch {torch.__version__.split('+')[0]}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+    try:
+        from . import _bind as native
+        if native.BUILT_FOR != here:
+            raise ImportError(f"built for {native.BUILT_FOR}")
+    except ImportError as e:
+        warnings.warn(f"the native binding of the hot calls is not used, which costs each some us on the host ({e}; here: {here}); "
+                      "`python -m paper_2601_10639_amd.build` builds it", RuntimeWarning, stacklevel=3)
+        _bind = _NoBind()
+        return _bind
     native.setup(StemCtx, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
     os.register_at_fork(after_in_child=native.off)   # torch refuses the device there
     _bind = native

@@ -3,6 +3,7 @@ declares, and rejects bad arguments on the host before touching a device."""
 import ctypes
 import os
 import re
+import sys
 
 import pytest
 
@@ -95,6 +96,38 @@ def test_binding_refuses_wrong_dtypes_before_calling():
     x = torch.zeros(4, 64, dtype=torch.float32)
     with pytest.raises(TypeError):
         L.stem_ffn_forward(Fake(), x, torch.zeros(4, dtype=torch.int32), x, x, x, x)
+
+
+@pytest.mark.parametrize("native", [None, "another torch"])
+def test_hot_calls_without_the_native_binding(lib, native, monkeypatch):
+    """Not built, or built for another torch: the calls are made from Python, as all others are."""
+    import torch
+
+    import paper_2601_10639_amd as package
+
+    class Fake:
+        handle = ctypes.c_void_p(None)
+        torch_dtype = torch.bfloat16
+
+    class Other:
+        BUILT_FOR = "torch 1.0.0, Python 3.10"
+
+    name = package.__name__ + "._bind"
+    monkeypatch.setitem(sys.modules, name, Other() if native else None)
+    monkeypatch.delattr(package, "_bind", raising=False)
+    monkeypatch.setattr(L, "_bind", None)
+    x, f, ids = torch.zeros(4, 64, dtype=torch.bfloat16), torch.zeros(4, 64), torch.zeros(4, dtype=torch.int32)
+    calls = [lambda c: L.stem_ffn_forward(c, x, ids, x, x, x, x), lambda c: L.stem_ffn_forward_residual(c, x, ids, x, x, x, x, x),
+             lambda c: L.stem_ffn_backward(c, x, x, ids, x, x, x, x, x, x, f, f, x), lambda c: L.stem_ffn_up_forward(c, x, ids, x, x, x, x, x),
+             lambda c: L.stem_ffn_up_backward(c, x, x, ids, x, x, x, x, x, x, x, x, f, f, f, x),
+             lambda c: L.stem_embed_grad(c, ids, x, ids, ids, ids, ids, ids, f), lambda c: L.stem_embed_grad_presorted(c, x, ids, ids, f),
+             lambda c: L.stem_embed_sparse_adamw(c, ids, ids, f, x, f, f, f, 1e-3, 0.9, 0.95, 1e-8, 0.1, 1)]
+    with pytest.warns(RuntimeWarning, match="native binding"):
+        with pytest.raises(ValueError, match="x"):       # the Python binding's check: x is not on the device
+            calls[0](Fake())
+    for call in calls[1:]:
+        with pytest.raises(ValueError):
+            call(Fake())
 
 
 def test_early_touch_of_gathered_rows_stays_inside_the_table():
