@@ -1147,12 +1147,10 @@ int64_t stem_sort_count_entries(int64_t max_tokens) {
 // ids 25 / 32 (one workgroup 43, the digit passes below 140), 32768 ids 36 / 34, 65536 ids 58 / 38 (digit passes 182).
 // The digit passes are left to ids or batches that the packed keys or the unique kernel's quadratic reads do not suit
 // (262144 ids: 126 us against 640).
-static bool ranks_fit(int64_t T, int V) { return T <= 8192 && V <= RANK_WORDS * 32; }   // (4097 to 8192: SORT_RANKS_8192)
-
+// The rule by size for calls that neither ranks nor buckets sort.
 int stem_route_sort(int64_t T, int V) {
   const int vbits = bits_for(V);
   if (T <= 4096 && vbits + bits_for((int)T) <= 32) return T <= 1024 ? SORT_ONE_1024 : SORT_ONE_4096;
-  if (ranks_fit(T, V)) return SORT_RANKS_8192;
   const bool short_runs = T <= MERGE_WAYS * 1024;
   if (T <= 262144 && vbits + (short_runs ? 10 : 12) <= 32) return short_runs ? SORT_RUNS_1024 : SORT_RUNS_4096;
   return SORT_DIGITS;
@@ -1173,7 +1171,7 @@ static bool sort_apart(int64_t T, int V, const int32_t* ids, const int32_t* sort
 
 int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
                           const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of) {
-  return ranks_fit(T, V) && sort_apart(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, seg_of);
+  return T <= RANK_MAX && V <= RANK_WORDS * 32 && sort_apart(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, seg_of);
 }
 
 int stem_route_sort_buckets(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
@@ -1195,7 +1193,7 @@ hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t
                        seg_offsets, n_uniq, ws.seg_of, ws.flag);
     return hipGetLastError();
   }
-  if (T <= RANK_MAX && stem_route_sort_ranks(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of)) {
+  if (stem_route_sort_ranks(T, V, ids, sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of)) {
     ProfScope ps(ctx, K_SORT_FUSED, s);
     auto* const kernel = T <= 1024 ? sort_ranks_kernel<1, 8> : sort_ranks_kernel<2, 8>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)((T + 7) / 8)), dim3(1024), 0, s, ids, (int)T, V, pos_bits, sorted_ids, perm,
@@ -1212,7 +1210,7 @@ hipError_t stem_sort_unique(stem_ctx* ctx, const EmbedScratch& ws, const int32_t
                          sorted_ids, perm, uniq_ids, seg_offsets, n_uniq, ws.seg_of, ws.flag);
     return hipGetLastError();
   }
-  if (route == SORT_RUNS_1024 || route == SORT_RUNS_4096 || route == SORT_RANKS_8192) {   // (the last: buffers over each other)
+  if (route == SORT_RUNS_1024 || route == SORT_RUNS_4096) {
     const int items = route == SORT_RUNS_4096 ? 4 : 1, run_bits = items == 1 ? 10 : 12;
     const int R = items * 1024, runs = (int)((T + R - 1) / R);
     {

@@ -232,11 +232,10 @@ int stem_route_one_launch_apart(int d_model, int d_ff, int64_t T, const void* G,
                                 const void* y);
 int64_t stem_route_splitk_bytes(int d_model, int d_ff, int64_t max_tokens);   // a context's room for K slices
 int stem_route_sort(int64_t T, int V);   // SortRoute
-// whether, up to 8192 ids, many workgroups that look at all ids sort them (ranks up to 2048, buckets beyond): where the vocabulary allows it and no
-// two of the call's buffers overlap
+// whether ranks by counting sort them: up to 2048 ids, where the vocabulary allows it and no two of the call's buffers overlap
 int stem_route_sort_ranks(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
                           const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of);
-// whether buckets of the vocabulary do (2049 to 16384 ids)
+// whether buckets of the vocabulary do: 2049 to 16384 ids, likewise
 int stem_route_sort_buckets(int64_t T, int V, const int32_t* ids, const int32_t* sorted_ids, const int32_t* perm, const int32_t* uniq_ids,
                             const int32_t* seg_offsets, const int32_t* n_uniq, const int32_t* seg_of);
 // whether the sort and the sums of a call with these buffers (dU may be null: no sums) are one launch
@@ -260,8 +259,8 @@ uint32_t stem_next_launch(uint32_t last);           // stem_launch_after, and
 int stem_exchange_launch(stem_ctx* c, uint32_t last);   // all flags of the layer in one launch as launch `last` left them (waits for the device)
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices or of the layer in one launch waits for another
 }
-// By size, where stem_route_sort_buckets and, up to 2048 ids, stem_route_sort_ranks say no.  SORT_RANKS_8192: merged runs of 1024 too.
-enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS, SORT_RANKS_8192 };
+// By size, where stem_route_sort_ranks and stem_route_sort_buckets say no.
+enum SortRoute { SORT_ONE_1024 = 0, SORT_ONE_4096, SORT_RUNS_1024, SORT_RUNS_4096, SORT_DIGITS };
 
 // Bytes of W_down that the gate product of a decode-sized call touches, a dword per 128-byte line behind its first K tiles, so that
 // the down product finds them in the memory-side cache: all or none.  L2 serves hits and misses in turn, so what the touches cost

@@ -1,5 +1,5 @@
-"""The sort of up to 8192 ids by counting ranks, against the oracle: sizes about its workgroups and its keys per thread, vocabularies about
-its bitmap's size, and outputs that lie over the ids."""
+"""The sort of up to 8192 ids by counting ranks, or beyond 2048 by buckets of the vocabulary, against the oracle: sizes about their workgroups
+and keys per thread, vocabularies about the bitmap's size, and outputs that lie over the ids."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +8,6 @@ from paper_2601_10639_amd import inputs, stemlib as L
 from tests import harness as Hn
 
 DEV = "cuda:0"
-RANKS_8192 = 5
 
 pytestmark = pytest.mark.gpu
 
@@ -16,13 +15,14 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,V,route", [
     (7, 40, Hn.SORT_ONE_1024), (8, 33, Hn.SORT_ONE_1024), (9, 32, Hn.SORT_ONE_1024), (1023, 1 << 18, Hn.SORT_ONE_1024),
     (1024, 65, Hn.SORT_ONE_1024), (1025, 1 << 18, Hn.SORT_ONE_4096), (2047, 257, Hn.SORT_ONE_4096), (2048, 128256, Hn.SORT_ONE_4096),
-    (2049, 31, Hn.SORT_ONE_4096), (4096, 1 << 18, Hn.SORT_ONE_4096), (4097, 1 << 18, RANKS_8192), (8191, 8193, RANKS_8192),
-    (8192, 1 << 18, RANKS_8192),
+    (2049, 31, Hn.SORT_ONE_4096), (4096, 1 << 18, Hn.SORT_ONE_4096), (4097, 1 << 18, Hn.SORT_RUNS_1024), (8191, 8193, Hn.SORT_RUNS_1024),
+    (8192, 1 << 18, Hn.SORT_RUNS_1024),
     # one id more than the bitmap holds: the kernels for larger vocabularies
     (1000, (1 << 18) + 1, Hn.SORT_ONE_1024), (3000, (1 << 18) + 1, Hn.SORT_ONE_4096), (8192, (1 << 18) + 1, Hn.SORT_RUNS_1024),
     (8193, 1 << 18, Hn.SORT_RUNS_1024),
 ])
 def test_ranks_by_counting(T, V, route):
+    """`route`: what sorts where an output lies over the ids, or beyond the bitmap's vocabularies."""
     assert Hn.route_sort(T, V) == route
     rng = np.random.default_rng(91)
     mixed = inputs.zipf_ids(T, V, seed=91)
@@ -32,8 +32,12 @@ def test_ranks_by_counting(T, V, route):
     ctx = L.stem_create(64, 64, V, L.STEM_BF16, T, 0)
     for ids in batches:
         ids = ids.astype(np.int32)
-        eg = Hn.hip_embed_grad(ctx, torch.from_numpy(ids).to(DEV), None, V, with_rows=False)
+        dev = torch.from_numpy(ids).to(DEV)
+        eg = Hn.hip_embed_grad(ctx, dev, None, V, with_rows=False)
         Hn.check_integers(eg, ids)
+        lie = {k: eg[k].data_ptr() for k in ("sorted_ids", "perm", "uniq_ids", "seg_offsets", "n_uniq")}
+        assert Hn.route_sort_ranks(T, V, ids=dev.data_ptr(), **lie) == (T <= 2048 and V <= 1 << 18)
+        assert Hn.route_sort_buckets(T, V, ids=dev.data_ptr(), **lie) == (T > 2048 and V <= 1 << 18)
         # an output over the ids, and one that begins at their last
         for name in ("sorted_ids", "perm", "uniq_ids"):
             room = torch.zeros(2 * T, dtype=torch.int32, device=DEV)
@@ -79,7 +83,8 @@ def test_outputs_over_the_ids_and_over_each_other(T, V):
         for name, at in over.items():
             out[name] = out[at] if isinstance(at, str) else room[at:at + size[name]]
         lie = {k: v.data_ptr() for k, v in out.items()}
-        assert Hn.route_sort_ranks(T, V, ids=room.data_ptr(), **lie) == (not over)
+        ranks, buckets = (f(T, V, ids=room.data_ptr(), **lie) for f in (Hn.route_sort_ranks, Hn.route_sort_buckets))
+        assert (ranks, buckets) == (not over and T <= 2048, not over and T > 2048)
         L.stem_embed_grad(ctx, room[:T], None, out["sorted_ids"], out["perm"], out["uniq_ids"], out["seg_offsets"], out["n_uniq"], None, T=T)
         return out
 

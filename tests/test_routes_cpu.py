@@ -5,7 +5,7 @@ import random
 import pytest
 
 from paper_2601_10639_amd import stemlib as L
-from tests.harness import DECODE, EPI_BF16, EPI_F32, EPI_GATE, FEW_ROW, TILES, route_forward, route_gate_up_together, route_sort_ranks, route_sort_sum, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
+from tests.harness import DECODE, EPI_BF16, EPI_F32, EPI_GATE, FEW_ROW, TILES, route_forward, route_gate_up_together, route_sort_buckets, route_sort_ranks, route_sort_sum, route_tiles as tiles, route_weight_grads, route_weight_grads_apart
 
 
 def test_no_k_slice_is_empty():
@@ -136,20 +136,23 @@ def test_gate_and_up_product_over_buffers_that_the_other_reads_do_not_share_a_la
         assert share(G=lie["E"]) and share(H=lie["ids"])
 
 
-@pytest.mark.parametrize("T,V", [(7, 40), (1000, 300), (4096, 1 << 18), (8192, 128256)])
-def test_ranks_are_counted_where_no_two_buffers_of_the_sort_overlap(T, V):
+@pytest.mark.parametrize("T,V,route", [(7, 40, route_sort_ranks), (1000, 300, route_sort_ranks), (2048, 1 << 18, route_sort_ranks),
+                                       (2049, 300, route_sort_buckets), (4096, 1 << 18, route_sort_buckets), (16384, 128256, route_sort_buckets)])
+def test_ranks_are_counted_and_buckets_sorted_where_no_two_buffers_of_the_sort_overlap(T, V, route):
     cap = min(T, V)
     size = dict(ids=T, sorted_ids=T, perm=T, uniq_ids=cap, seg_offsets=cap + 1, n_uniq=1, seg_of=T)
     lie = {k: (i + 1) << 24 for i, k in enumerate(size)}
-    assert route_sort_ranks(T, V, **lie)
-    assert not route_sort_ranks(8193, V, **lie) and not route_sort_ranks(T, (1 << 18) + 1, **lie)
+    assert route(T, V, **lie) and not route(T, (1 << 18) + 1, **lie)
+    assert route_sort_ranks(2048, V, **lie) and not route_sort_ranks(2049, V, **lie)
+    assert not route_sort_buckets(2048, V, **lie) and route_sort_buckets(2049, V, **lie)
+    assert route_sort_buckets(16384, V, **lie) and not route_sort_buckets(16385, V, **lie)
     for a in size:
         for b in size:
             if a == b:
                 continue
             for at, ranks in ((lie[b] - 4 * size[a], True), (lie[b] - 4 * size[a] + 4, False), (lie[b], False),
                               (lie[b] + 4 * size[b] - 4, False), (lie[b] + 4 * size[b], True)):
-                assert route_sort_ranks(T, V, **{**lie, a: at}) == ranks, (a, b, at - lie[b])
+                assert route(T, V, **{**lie, a: at}) == ranks, (a, b, at - lie[b])
 
 
 @pytest.mark.parametrize("bf16,T,V,F", [(True, 7, 40, 64), (False, 1000, 300, 1024), (True, 512, 1 << 17, 8192), (True, 2048, 128256, 8192)])
