@@ -235,6 +235,7 @@ int stem_route_copy_streams(int d, int F, int dtype, int64_t T, int64_t rows) {
 }
 
 void stem_exchange_polls(stem_ctx* c, int polls) { c->polls = c->looks = polls; }
+void stem_exchange_two_launches(stem_ctx* c, int on) { c->two_launches = on; }
 
 int stem_route_weight_grads_apart(int d, int F, int64_t T, const void* dy, const void* H, const void* dx, const void* W_gate,
                                   const void* W_up, const void* dV, const float* dW_gate, const float* dW_up) {
@@ -415,7 +416,7 @@ static stem_status forward_impl(stem_ctx* c, const void* x, const int32_t* ids, 
   const int d = c->desc.d_model, F = c->desc.d_ff;
   void* H = save_H ? save_H : c->H_ws;
 
-  if (c->desc.dtype == STEM_BF16 && !wait_event && stem_route_one_launch(d, F, T) &&
+  if (c->desc.dtype == STEM_BF16 && !wait_event && !c->two_launches && stem_route_one_launch(d, F, T) &&
       stem_route_one_launch_apart(d, F, T, save_G, save_H, W_down, residual, y)) {
     const StemDecodeArgs a = {static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(W_gate), static_cast<const bf16_t*>(W_down),
                               static_cast<const bf16_t*>(E), static_cast<const bf16_t*>(residual), ids, static_cast<bf16_t*>(y),

@@ -65,6 +65,7 @@ struct stem_ctx {
   uint32_t* sync;        // [33 * 256] flags, 32 times, and claims of the layer in one launch (ffn_decode_bf16.hip)
   int polls;             // how often a workgroup of the few-row kernel looks for the others
   int looks;             // and of the layer in one launch
+  int two_launches;      // a layer that one launch would do takes two (tests)
   int32_t* sort_keys[2]; // [max_tokens]
   int32_t* sort_vals[2]; // [max_tokens]
   int32_t* sort_counts;  // [64 * waves]
@@ -255,6 +256,7 @@ int stem_route_touch_bytes(int d_model, int d_ff, int64_t T);   // of W_down, to
 // 124 / 146; fp32, 256 x 1024, 8192 tokens (0.9) 212 / 203 / 197, 512 x 2048, vocabulary 8000, 2000 tokens (1.5) 156 / 131 / 149.  On two contexts two in
 // turn are within 1 % of a stream for each, and of one but at 8192 tokens of 1024 x 4096 (381 / 393) and 4096 of 2048 x 8192 (470 / 510).
 int stem_route_copy_streams(int d_model, int d_ff, int dtype, int64_t T, int64_t rows);
+void stem_exchange_two_launches(stem_ctx* c, int on);   // no layer in one launch on this context
 uint32_t stem_next_launch(uint32_t last);           // stem_launch_after, and
 int stem_exchange_launch(stem_ctx* c, uint32_t last);   // all flags of the layer in one launch as launch `last` left them (waits for the device)
 void stem_exchange_polls(stem_ctx* c, int polls);   // 0: no workgroup of the few-row kernel's K slices or of the layer in one launch waits for another

@@ -103,6 +103,16 @@ def route_sort_sum(bf16, T, V, F, **at):
     return bool(L.lib().stem_route_sort_sum(int(bf16), ctypes.c_int64(T), V, F, *[ctypes.c_void_p(at.get(k, 0)) for k in names]))
 
 
+def kernels(ctx, call):
+    """{kernel name: launches} of a call on the context."""
+    L.stem_profile_enable(ctx, True)
+    L.stem_profile_reset(ctx)
+    call()
+    seen = {k: n for k, (_, n) in L.stem_profile_read(ctx).items()}
+    L.stem_profile_enable(ctx, False)
+    return seen
+
+
 def hip_forward_backward(ctx, inp, save_H=True, want_dx=True, after_forward=None):
     """forward + backward through libstem; returns device tensors.  `after_forward()` runs between the two calls."""
     dev = inp["x"].device

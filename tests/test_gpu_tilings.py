@@ -157,10 +157,11 @@ def test_decode_products_on_every_tile(T, d, F, gate, down):
     s = inputs.StemShape("decode-tiles", d, F, V, 1, T, "bf16")
     inp = inputs.layer_inputs(s, seed=65, device=DEV, tokens=T)
     ctx = Hn.make_ctx(s, T)
+    L.lib().stem_exchange_two_launches(ctx.handle, 1)   # (up to 32 tokens: what serves calls that are not one launch)
     a = (ctx, inp["x"], inp["ids"], inp["W_gate"], inp["W_down"], inp["E"])
     e = lambda n: torch.empty(T, n, dtype=torch.bfloat16, device=DEV)  # noqa: E731
     y, G, H, yr, xr = e(d), e(F), e(F), e(d), inp["x"].clone()
-    L.stem_ffn_forward(*a, y, G, H)
+    assert Hn.kernels(ctx, lambda: L.stem_ffn_forward(*a, y, G, H)) == {"gemm_gate_fused": 1, "gemm_down": 1}
     L.stem_ffn_forward_residual(*a, inp["x"], yr)
     L.stem_ffn_forward_residual(ctx, xr, *a[2:], xr, xr)                # in place
     reps = [torch.empty_like(y) for _ in range(3)]
@@ -193,22 +194,42 @@ def test_down_product_of_up_to_eight_tokens(T, d, F, gate, down):
     test_decode_products_on_every_tile(T, d, F, gate, down)
 
 
+SORT_KERNELS = [{"sort_fused"}, {"sort_fused"}, {"sort_fused", "sort_merge", "unique"}, {"sort_fused", "sort_merge", "unique"},
+                {"sort_count", "sort_scan", "sort_scatter", "unique"}]
+
+
+def _sort(ctx, ids, route, dU=None):
+    """The names of the kernels of a table gradient whose sorted ids take the ids' place (not in the digit passes, which may read them
+    meanwhile), and its outputs."""
+    dev = torch.from_numpy(ids).to(DEV)
+    e = lambda n: torch.empty(n, dtype=torch.int32, device=DEV)  # noqa: E731
+    T, cap = len(ids), min(len(ids), ctx.vocab)
+    out = dict(sorted_ids=dev if route != Hn.SORT_DIGITS else e(T), perm=e(T), uniq_ids=e(cap), seg_offsets=e(cap + 1), n_uniq=e(1))
+    lie = {k: v.data_ptr() for k, v in out.items()}
+    assert not Hn.route_sort_ranks(T, ctx.vocab, ids=dev.data_ptr(), **lie) and not Hn.route_sort_buckets(T, ctx.vocab, ids=dev.data_ptr(), **lie)
+    out["dE_rows"] = None if dU is None else torch.empty(cap, ctx.d_ff, dtype=torch.float32, device=DEV)
+    seen = Hn.kernels(ctx, lambda: L.stem_embed_grad(ctx, dev, dU, *out.values()))
+    return {k for k in seen if not k.startswith("seg")}, out
+
+
 @pytest.mark.parametrize("T,V,route", [
     (1, 1, Hn.SORT_ONE_1024), (63, 2, Hn.SORT_ONE_1024), (1024, 128256, Hn.SORT_ONE_1024), (1025, 128256, Hn.SORT_ONE_4096),
     (4096, 1 << 20, Hn.SORT_ONE_4096), (4097, 1 << 20, Hn.SORT_RUNS_1024),
     (4096, (1 << 20) + 1, Hn.SORT_RUNS_1024),            # an id that leaves no room for 12 position bits
-    (16384, 50304, Hn.SORT_RUNS_1024), (16385, 50304, Hn.SORT_RUNS_4096),   # the most runs of 1024; a last run with one key
+    (16384, (1 << 18) + 1, Hn.SORT_RUNS_1024), (16384, 50304, Hn.SORT_RUNS_1024), (16385, 50304, Hn.SORT_RUNS_4096),   # the most runs of 1024; a last run with one key
     (65537, 128256, Hn.SORT_RUNS_4096), (262144, 7, Hn.SORT_RUNS_4096),   # more runs than searches in flight; long runs of equal ids
     (5000, 5_000_000, Hn.SORT_DIGITS), (262145, 3, Hn.SORT_DIGITS),       # ids, then a batch, beyond the merge's
 ])
 def test_sort_on_every_path(T, V, route):
+    """(Ranks and buckets of up to 16384 ids aside: the sorted ids go over the ids, which they leave to these kernels.)"""
     assert Hn.route_sort(T, V) == route
     ids = inputs.zipf_ids(T, V, seed=67)
     ids[T // 2:] = np.random.default_rng(68).integers(0, V, T - T // 2)
     ctx = L.stem_create(64, 64, V, L.STEM_BF16, T, 0)
     for turn in range(2):                                # the second call finds the first one's scratch
-        eg = Hn.hip_embed_grad(ctx, torch.from_numpy(ids).to(DEV), None, V, with_rows=False)
+        seen, eg = _sort(ctx, ids, route)
         L.stem_sync_status(ctx)
+        assert seen == SORT_KERNELS[route]
         Hn.check_integers(eg, ids)
         ids = ids[::-1].copy()
     ctx.close()
@@ -358,8 +379,9 @@ def test_out_of_range_ids_on_every_sort(T, V, route):
     ids, clamped = _with_bad_ids(inputs.zipf_ids(T, V, seed=76), [0, 7, 63, 64, 255, 256, T // 2, T - 1], V)
     ctx = L.stem_create(64, 64, V, L.STEM_BF16, T, 0)
     dU = inputs.normal((T, 64), 1.0, 77, torch.bfloat16, DEV)
-    eg = Hn.hip_embed_grad(ctx, torch.from_numpy(ids).to(DEV), dU, V)
+    seen, eg = _sort(ctx, ids, route, dU)
     _expect_id_range(ctx)
+    assert seen == SORT_KERNELS[route]
     clamped = clamped.astype(np.int32)
     U = Hn.check_integers(eg, clamped)
     assert Hn.max_rel(eg["dE_rows"][:U].cpu(), O.embed_grad(clamped, inputs.to_f64(dU))["dE_rows"]) <= 1e-5
