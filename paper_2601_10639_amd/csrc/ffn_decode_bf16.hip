@@ -145,8 +145,9 @@ __global__ __launch_bounds__(THREADS, 4) void ffn_decode_kernel(Args p) {
   constexpr int TM = 8 * TQ;
   // Cache policy of the weights.  The last level holds 256 MB: weights of a stack that fits are best kept there, others best read past it
   // (policy 2).  A call doesn't know the stack: of layers up to 8.4 MB (RG * KG up to 2) twenty or thirty fit, of larger ones they don't.
-  // us a layer, kept / past it, one token: 512 x 1536 (3.1 MB) 8 to 48 layers 4.9 / 5.4; 1024 x 4096 (16.8 MB) 16 layers 7.1 / 7.7, 24 and 48
-  // 7.9 / 7.7; 1536 x 5120 8 layers 8.9 / 9.5, 16 to 48 9.9 / 9.5; 2048 x 8192 4 layers 14.4 / 14.8, 8 to 48 16.5 / 15.1.
+  // us a layer, kept / past it, one token: 512 x 1536 (3.1 MB) 8 layers 5.6 / 5.7, 24 5.4 / 5.6, 48 5.3 / 5.5; 1024 x 4096 (16.8 MB) 8 layers 7.8 / 8.3,
+  // 16 7.8 / 8.0, 24 8.2 / 8.0, 48 8.1 / 7.9; 1536 x 5120 8 layers 9.7 / 10.2, 16 10.3 / 9.9, 48 9.9 / 9.5; 2048 x 8192 4 layers 17.0 / 16.5, 8 17.6 /
+  // 16.1, 16 17.2 / 15.9, 48 16.6 / 15.7.
   constexpr int KEEP = RG * KG <= 2 ? 0 : 2;
   constexpr int LD = RD == 8 ? 1 : 2;                                        // lines of 64 k in a piece of W_down
   constexpr int KD = 4 * RG / LD;                                            // pieces a wavefront

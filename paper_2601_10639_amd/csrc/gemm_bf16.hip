@@ -713,9 +713,9 @@ __global__ __launch_bounds__((C::WAVES + C::LW) * 64) void gemm_bf16_kernel(Gemm
   // ev: gathered table row, uv: up-projection row (dense and additive variants), gv: saved G row
   uint4 ev[2][PASSES], gv[2][PASSES], uv[2][PASSES];
   // The backward pass reads the saved G and Up once, so there they are read past the caches and leave the room to dU, dG and the operand
-  // panels (whole training steps, us, kept / past: 3000 tokens of a dense 1536 x 5120 layer 450 / 435, 4096 of an additive 1024 x 4096
-  // layer 379 / 374, 1999 of 2048 x 8192 463 / 459; 600 of 1536 x 5120 and 5000 of 640 x 2048 the same.  G stored past them as well: 1999
-  // 457, but 640 x 2048 174 against 172; dU too: 600 of 1536 x 5120 132.5 against 130.3).
+  // panels (whole training steps, us, kept / past: 3000 tokens of a dense 1536 x 5120 layer 450 / 435; 4096 of an additive 1024 x 4096
+  // layer, 1999 of 2048 x 8192, 600 of 1536 x 5120 and 5000 of 640 x 2048 the same within what runs differ by, 1 to 2 %.  G stored past them as well: 1999
+  // tokens 457 against 459, but 640 x 2048 174 against 172; dU too: 600 of 1536 x 5120 132.5 against 130.3).
   auto load_once = [](const bf16_t* at) __attribute__((always_inline)) {
     if (!DH_LIKE) return *reinterpret_cast<const uint4*>(at);
     return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(at)));
