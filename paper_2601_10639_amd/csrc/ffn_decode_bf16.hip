@@ -34,11 +34,11 @@
 // workgroup whose flag was complete last sees all of them; who gave up before that has its claim complete before it looked at the
 // flags the last time, where that last flag was missing, so the claim is there when the last workgroup reads it.  (Each takes a claim back to
 // 0 by compare and swap, so a share is done once.)  Workgroups begin their search for claims at different ones, and load them anew where
-// another was faster.  us a round of 8 streams (six decode steps of 2048 x 8192 and 1024 x 4096, 1 to 32 tokens, one of 512 x 1536, all at
+// another was faster.  us a round of 8 streams (seven decode steps of 2048 x 8192 and 1024 x 4096, 1 to 32 tokens, one of 512 x 1536, all at
 // once; two launches a layer 990) by the number of looks, searches in one order / in different ones: 2000 3700 / 3380, 400 2300 / 1420, 200 1700 / 1190, 100 1310 /
-// 1190, 50 - / 1300, 20 - / 2330; of three decode steps and two prefills among 8 streams (770) at 400 looks 1020 / 995, 200 985 / 935, 100 970 / 905.
-// (Workgroups that give up one after another, over nine times as many looks: 1600 and 1080 at 50.)  On four streams of such a mix 360 and 345,
-// where two launches a layer take 385 and 365.
+// 1190, 50 - / 1300, 20 - / 2330; of five decode steps and three prefills on 8 streams (770) at 400 looks 1020 / 995, 200 985 / 935, 100 970 / 905.
+// (Workgroups that give up one after another, over nine times as many looks: 1600 and 1080 at 50.)  On four streams two decode
+// steps and two prefills take 358, four decode steps 345, where two launches a layer take 385 and 365.
 //
 // Layer forward, us, two launches of the decode kernel / this, 1, 8, 16, 24, 32 tokens, 16 or 24 layers in a graph: 512 x 1536 7.0 / 5.4, 7.3 / 5.6, 7.7 / 5.8,
 // 8.3 / 6.3, 8.6 / 6.8; 1024 x 4096 9.4 / 8.0, 9.9 / 8.1, 11.3 / 8.7, 12.0 / 9.7, 12.3 / 10.6; 1536 x 5120 12.4 / 9.9, 13.4 / 9.8, 15.2 / 11.1,
